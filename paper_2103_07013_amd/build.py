@@ -12,8 +12,12 @@ HEADERS = ["raster_kernels.h", "raster_device.h", "clusters.h", os.path.join("..
 # -ffp-contract=off: the numeric rule fixes where fused multiply-adds happen.
 # packed FP32 instructions are switched off on purpose (hipcc's host pass does not know the
 # feature and says so; that message is harmless).
+# -amdgpu-atomic-optimizer-strategy=None: the kernels add up over a wavefront themselves and let one lane
+# do the atomic; the compiler's own combining would wrap that lane in a second reduction (a dozen
+# instructions around every work counter in LDS).
 HIPCC_FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-ffp-contract=off", "-fPIC", "-shared",
-               "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
+               "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+               "-mllvm", "-amdgpu-atomic-optimizer-strategy=None"]
 
 
 def stale() -> bool:

@@ -84,6 +84,80 @@ __device__ __forceinline__ Setup make_setup(uint32_t xy0, uint32_t xy1, uint32_t
     return s;
 }
 
+// Correctly rounded 1 / w from the hardware approximation and one correction step: equal to the IEEE
+// quotient whenever the result is a normal number (compared for all 2^32 arguments on gfx950).  Zeros,
+// denormals, infinities and arguments whose reciprocal is not normal come out as something that is
+// not normal either.  3 instructions instead of the 11 of a division.
+__device__ __forceinline__ float recip_normal(float w) {
+    const float r = __builtin_amdgcn_rcpf(w);
+    return fmaf(fmaf(-w, r, 1.0f), r, r);
+}
+constexpr int kClassNormal = 0x108;      // v_cmp_class: +normal | -normal
+__device__ __forceinline__ float recip(float w) {
+    float r = recip_normal(w);
+    if (!__builtin_amdgcn_classf(r, kClassNormal)) r = 1.0f / w;
+    return r;
+}
+
+// Correctly rounded a / b for operands and quotients far from the ends of the exponent range.  With
+// y = RN(1/b) the product q0 = RN(a y) lies within half a unit of every midpoint that a / b can come
+// within 2^-47 of, the remainder a - b q0 is exact, and RN(q0 + remainder y) is then the IEEE quotient
+// (Markstein's correction).  6 instructions instead of 11 and no use of VCC.
+__device__ __forceinline__ float div_in_range(float a, float b) {
+    const float y = recip_normal(b);
+    const float q = a * y;
+    return fmaf(fmaf(-b, q, a), y, q);
+}
+// Vertices whose 1/w lies in [2^-60, 2^60] keep every depth of their triangles in that range: the
+// interpolated 1/w times A2 < 2^31 then stays within [2^-60, 2^91], which div_in_range is made for.
+__device__ __forceinline__ bool iw_in_range(float iw) {      // one subtraction, one compare; false for NaN and negatives
+    return __float_as_uint(iw) - 0x21800000u <= 0x5D800000u - 0x21800000u;
+}
+
+typedef short short2v __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ short2v as_s2(uint32_t v) { return __builtin_bit_cast(short2v, v); }
+__device__ __forceinline__ uint32_t as_u32(short2v v) { return __builtin_bit_cast(uint32_t, v); }
+
+// Set-up of a triangle on packed 16-bit coordinates: half the instructions of make_setup.  Only for
+// triangles whose coordinate differences fit 16 bits (a whole 64-pixel frame does; on larger frames the
+// callers check the box).  E2 follows from E0 + E1 + E2 = A2.
+struct PackedSetup {
+    uint32_t v1, v2;          // reference vertices of edges 0 and 1
+    uint32_t e0, e1;          // edge vectors v2 - v1 and v0 - v2
+    float iw0, iw1, iw2;
+    int A2;
+    int t0, t1, t2;           // smallest value of E that is inside: 0 on a top-left edge, 1 otherwise
+};
+// Top-left: dy < 0, or dy = 0 and dx > 0, with dy in the high half; dx = dy = 0 only if A2 = 0.
+__device__ __forceinline__ int packed_threshold(uint32_t e) { return (int)e < 0x8000 ? 0 : 1; }
+__device__ __forceinline__ int cross16(uint32_t a, uint32_t b) {
+    return __mul24(unpack_x(a), unpack_y(b)) - __mul24(unpack_x(b), unpack_y(a));
+}
+__device__ __forceinline__ PackedSetup make_packed_setup(uint32_t xy0, uint32_t xy1, uint32_t xy2, float iw0, float iw1,
+                                                         float iw2) {
+    PackedSetup s;
+    const int a2 = cross16(as_u32(as_s2(xy1) - as_s2(xy0)), as_u32(as_s2(xy2) - as_s2(xy0)));
+    const bool swap = a2 < 0;      // two-sided: exchange vertices 1 and 2
+    s.A2 = swap ? -a2 : a2;
+    s.v1 = swap ? xy2 : xy1;
+    s.v2 = swap ? xy1 : xy2;
+    s.iw0 = iw0;
+    s.iw1 = swap ? iw2 : iw1;
+    s.iw2 = swap ? iw1 : iw2;
+    s.e0 = as_u32(as_s2(s.v2) - as_s2(s.v1));
+    s.e1 = as_u32(as_s2(xy0) - as_s2(s.v2));
+    s.t0 = packed_threshold(s.e0);
+    s.t1 = packed_threshold(s.e1);
+    s.t2 = packed_threshold(as_u32(as_s2(s.v1) - as_s2(xy0)));
+    return s;
+}
+// Edge functions at pixel centre p (packed like the vertices): dx (py - Y) - dy (px - X).
+__device__ __forceinline__ void packed_edges(const PackedSetup& s, uint32_t p, int& E0, int& E1, int& E2) {
+    E0 = cross16(s.e0, as_u32(as_s2(p) - as_s2(s.v1)));
+    E1 = cross16(s.e1, as_u32(as_s2(p) - as_s2(s.v2)));
+    E2 = s.A2 - E0 - E1;
+}
+
 // The part of the frame one work-group owns: pixels [x0, x0 + w) x [y0, y0 + h), and the same
 // rectangle in normalised device coordinates (aL <= x/w <= aR, aT <= y/w <= aB).
 struct Window {
@@ -150,20 +224,29 @@ __device__ __forceinline__ uint32_t outcode(const Clip4& c) {
     return oc;
 }
 
+// Round to the nearest 1/256 pixel (ties to even) and pack.  Adding 1.5 * 2^23 - kOrigin rounds to an
+// integer in the addition itself and leaves X - kOrigin in the low 16 bits of the sum, for every
+// coordinate that can be packed: 2 additions and a byte permute instead of the 8 instructions of two
+// conversions, subtractions and a merge.
+__device__ __forceinline__ uint32_t snap_xy(float fx, float fy) {
+    constexpr float magic = 12582912.0f - (float)kOrigin;
+    static_assert(kOrigin % 2 == 0, "ties go to even coordinates");
+    return __builtin_amdgcn_perm(__float_as_uint(fy + magic), __float_as_uint(fx + magic), 0x05040100u);
+}
+
 // Perspective divide + snap.  Returns false when the vertex cannot be placed on the sub-pixel grid
 // of the frame (the numeric rule then drops its triangle).  can_project tells whether the vertex is
 // in front of the eye with finite screen coordinates; such a vertex outside the frame is packed
 // with its coordinates clamped to the 16-bit range, which keeps it on its side of the frame.
 __device__ __forceinline__ bool project(const Clip4& c, const FrameParams& fp, uint32_t& xy, float& iw,
                                         bool& can_project) {
-    iw = 1.0f / c.w;
+    iw = recip(c.w);
     float xn = c.x * iw, yn = c.y * iw;
     float fx = fmaf(xn, fp.sx, fp.sx), fy = fmaf(yn, fp.sy, fp.sy);
     bool ok = (c.w > 0.0f) && fx >= -64.0f && fx <= fp.xmax && fy >= -64.0f && fy <= fp.ymax;
     can_project = (c.w > 0.0f) && fabsf(fx) < 3.0e38f && fabsf(fy) < 3.0e38f;
-    int X = min(max(__float2int_rn(fx), kOrigin - 32768), kOrigin + 32767);
-    int Y = min(max(__float2int_rn(fy), kOrigin - 32768), kOrigin + 32767);
-    xy = pack_xy(X, Y);
+    const float lowest = (float)(kOrigin - 32768), highest = (float)(kOrigin + 32767);
+    xy = snap_xy(__builtin_amdgcn_fmed3f(fx, lowest, highest), __builtin_amdgcn_fmed3f(fy, lowest, highest));
     return ok;
 }
 
