@@ -280,7 +280,7 @@ constexpr uint32_t kNoPixel = 0xFFFFFFFFu;   // box_footprint: the box cannot co
 // box.  So if the smallest w over the box (minus a rounding margin) is larger than the depth
 // already stored at every pixel whose centre the projected box can reach, nothing in the box can
 // win the z-test.  Returns the packed test record, or 0 when no bound can be given (the box
-// may reach the eye plane, or is more than 32 pixels wide or high):
+// may reach the eye plane, clip w is far from 1, or the box is more than 32 pixels wide or high):
 //   bit 0 testable | x0 6 bits | y0 6 bits (both relative to the window) | width-1 5 bits |
 //   height-1 5 bits, and in wbits18 the exponent and top ten mantissa bits of the w bound
 //   (truncated, i.e. rounded towards the eye)
@@ -293,7 +293,9 @@ __device__ __forceinline__ uint32_t box_footprint(const float (&M)[16], const Fr
     float wmin = M[15] + fminf(M[12] * lx, M[12] * hx) + fminf(M[13] * ly, M[13] * hy) + fminf(M[14] * lz, M[14] * hz);
     float wmag = fmaf(fabsf(M[12]), ax, fmaf(fabsf(M[13]), ay, fmaf(fabsf(M[14]), az, fabsf(M[15]))));
     float wcons = wmin - eps * wmag;
-    if (!(wcons > 0.0f)) return 0u;
+    // (outside this range A2 / (e0/w0 + e1/w1 + e2/w2) can overflow or lose its precision, and a depth need no longer
+    // be a mean of clip w values)
+    if (!(wcons > 0x1p-60f && wmag < 0x1p100f)) return 0u;
     float x0 = 3.0e38f, x1 = -3.0e38f, y0 = 3.0e38f, y1 = -3.0e38f;
 #pragma unroll
     for (int k = 0; k < 8; ++k) {
