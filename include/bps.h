@@ -69,7 +69,7 @@ typedef struct {
     int32_t height, width;   /* output frame size; multiples of 8, 8..128 */
     int32_t mode;            /* BPS_MODE_DEPTH or BPS_MODE_RGBD */
     float background_depth;  /* written where no triangle covers the pixel centre */
-    int32_t splits;          /* work-groups per environment; 0 = choose from B and the device */
+    int32_t splits;          /* work-groups on shares of the scene per window of the frame; 0 = choose from B and the device */
     int32_t threads;         /* work-group size: 0 = default, else 256, 384, 512 or 1024 */
     uint32_t flags;          /* BPS_FLAG_* bits, 0 = defaults */
     int32_t supersample;     /* 0 or 1 = off; 2 = render at 2 height x 2 width and average 2x2 blocks into the
@@ -81,7 +81,7 @@ typedef struct {
  * request per simulation step; its frame size is the policy's input resolution, Sec. 4.1).  *out
  * receives the handle.  Allocates the device scene table, the events of the request staging ring
  * and (lazily, in the first requests that need them) the staging buffers, the global visibility
- * buffer used when an environment is split over several work-groups, and the colour pass's buffers. */
+ * buffer used when a scene's clusters are split over several work-groups, and the colour pass's buffers. */
 bps_status bps_create(const bps_config *cfg, bps_renderer **out);
 
 /* Waits for the device, frees every scene and buffer.  NULL is ignored. */
@@ -171,8 +171,7 @@ bps_status bps_render(bps_renderer *r, const bps_scene *scene_ids, const float *
  * Limits: depth renderers without supersampling, forced splits or diagnostics; view_proj must be
  * DEVICE memory; B x (64x64-pixel tiles per frame) <= 16384 work-groups (e.g. 16384 environments at
  * 64x64, 4096 at 128x128), otherwise BPS_ERR_INVALID_ARG / BPS_ERR_UNSUPPORTED and nothing is enqueued.
- * One environment is never split over several work-groups here, so very small batches run slower
- * than through bps_render.  scene_ids is host memory as in bps_render.
+ * Small batches are cut into smaller windows as in bps_render.  scene_ids is host memory as in bps_render.
  * Every call on a GPU, from any renderer and stream, uses that GPU's one array: calls on one stream
  * are ordered and safe; calls that overlap on one GPU (different streams or renderers) race.  Nothing
  * in the array needs clearing: each call overwrites what it reads. */

@@ -123,9 +123,11 @@ struct bps_renderer {
     size_t ev_used = 0;
     bool profiling = false;
     uint32_t profile_every = 1, profile_count = 0;   // every n-th request is timed
-    // cached plan: valid while the scene ids and split count repeat
+    // cached plan: valid while the scene ids, the split count and the window size repeat
     std::vector<bps_scene> plan_ids;
     int plan_splits = 0;
+    int plan_windows = 0;
+    bool fixed_layout = false;        // the raster kernel's instances with a constant LDS layout fit this device
     uint64_t plan_version = 0;        // counts the plans made; ring slots remember which one they hold
     std::vector<bps::WorkItem> plan_items;
     std::vector<bps_scene> call_slots;    // table slots of the current request's scene handles (keeps its capacity)
@@ -220,35 +222,72 @@ bool slot_busy(const bps_renderer* r, int slot) {
 
 bool fp_cull_enabled(const bps_renderer* r) { return !(r->cfg.flags & BPS_FLAG_NO_CLUSTER_CULL); }
 
-// Choose how many work-groups share one environment: enough groups to fill the device a few
-// times over when the batch is small, one group per environment when the batch is large.
-int plan_splits(const bps_renderer* r, uint32_t B, uint32_t min_clusters) {
-    if (r->cfg.splits > 0) return r->cfg.splits;
+// How one request is cut into work-groups: nx x ny windows of w x h pixels per frame, and S interleaved
+// shares of the scene's clusters per window.
+struct Cut {
+    int w, h, nx, ny, S;
+    int windows() const { return nx * ny; }
+};
+
+Cut choose_cut(const bps_renderer* r, uint32_t B, uint32_t min_clusters, uint32_t max_clusters) {
+    auto parts = [](int n, int size) { return (n + size - 1) / size; };
+    Cut c{r->tile_w, r->tile_h, parts(r->rw, r->tile_w), parts(r->rh, r->tile_h), 1};
+    if (r->cfg.splits > 0) {
+        c.S = r->cfg.splits;
+        return c;
+    }
+    if (fp_cull_enabled(r) && (max_clusters + 63u) / 64u <= (uint32_t)bps::kOrderCap) {
+        // Windows are halved along their longer side while the device has room for the groups: a launch then
+        // lasts as long as its costliest group, and half a window costs about two thirds of a whole one.  Room
+        // is two groups per compute unit (all of them resident at once), and more the larger a window's part of
+        // the scene is, because large scenes hold the costliest groups: up to 2 + clusters per window / 2048
+        // groups per compute unit (at most 4.6) were worth it, on scenes of 10 k to 1 M triangles.  Measured
+        // against undivided windows (1 M triangles, 64x64, us per request): B = 100: 271 -> 108, 300: 276 ->
+        // 176, 600: 282 -> 260, past the rule 768: 307 -> 320; 200 k: B = 8: 81 -> 41, 128: 109 -> 79,
+        // 256: 111 -> 106, past the rule 512: 129 -> 154.
+        const double room_per_cu_max = 4.6;
+        while (c.w > 8 || c.h > 8) {
+            const double per_window = (double)max_clusters / c.windows();
+            const double room = r->num_cu * std::min(2.0 + per_window / 2048.0, room_per_cu_max);
+            Cut f = c;
+            if (f.w >= f.h) {
+                f.nx = parts(r->rw, std::max(8, (f.w + 1) / 2));
+                f.w = parts(r->rw, f.nx);
+            } else {
+                f.ny = parts(r->rh, std::max(8, (f.h + 1) / 2));
+                f.h = parts(r->rh, f.ny);
+            }
+            if (f.windows() == c.windows() || f.windows() > 64 || (double)B * f.windows() > room) break;
+            c = f;
+        }
+        return c;
+    }
+    // without culling every window would stream the whole scene, and scenes whose blocks cannot be ordered
+    // in LDS are better cut into shares that can: several groups on interleaved shares of the clusters
     int waves = r->threads / 64;
-    int want_groups = 4 * r->num_cu;
-    int s = 1;
-    int groups = (int)B * r->tiles;
-    if (groups < 2 * r->num_cu) s = (want_groups + groups - 1) / groups;
+    int want_groups = 4 * r->num_cu, groups = (int)B * r->tiles;
+    if (groups < 2 * r->num_cu) c.S = (want_groups + groups - 1) / groups;
     int max_s = std::max(1, (int)(min_clusters / (uint32_t)(8 * waves)));   // >= 8 clusters per wave
-    return std::max(1, std::min(s, max_s));
+    c.S = std::max(1, std::min(c.S, max_s));
+    return c;
 }
 
-// The launch plan: one work item per (environment, tile, slice of its scene's clusters);
+// The launch plan: one work item per (environment, window, share of its scene's clusters);
 // environments of one scene are kept on one accelerator die so its L2 serves every re-read of that
-// scene.  Cached while the scene ids and the split count repeat.
-void make_plan(bps_renderer* r, const bps_scene* scene_ids, uint32_t B, int S) {
-    bool replan = r->plan_splits != S || r->plan_ids.size() != B || std::memcmp(r->plan_ids.data(), scene_ids, B * sizeof(bps_scene)) != 0;
+// scene.  Cached while the scene ids and the cut repeat.
+void make_plan(bps_renderer* r, const bps_scene* scene_ids, uint32_t B, const Cut& cut) {
+    const int S = cut.S, windows = cut.windows();
+    bool replan = r->plan_splits != S || r->plan_windows != windows || r->plan_ids.size() != B ||
+                  std::memcmp(r->plan_ids.data(), scene_ids, B * sizeof(bps_scene)) != 0;
     if (replan) {
         std::vector<uint32_t> order(B);
         for (uint32_t b = 0; b < B; ++b) order[b] = b;
         std::stable_sort(order.begin(), order.end(), [&](uint32_t a, uint32_t b) { return scene_ids[a] < scene_ids[b]; });
         std::vector<bps::WorkItem> sorted;
-        sorted.reserve((size_t)B * S * r->tiles);
+        sorted.reserve((size_t)B * S * windows);
         for (uint32_t k = 0; k < B; ++k) {
             uint32_t b = order[k];
-            uint32_t C = r->scenes[scene_ids[b]].dev.n_clusters;
-            (void)C;
-            for (int tile = 0; tile < r->tiles; ++tile)
+            for (int tile = 0; tile < windows; ++tile)
                 for (int s = 0; s < S; ++s) {
                     bps::WorkItem it;
                     it.env = b;
@@ -269,22 +308,23 @@ void make_plan(bps_renderer* r, const bps_scene* scene_ids, uint32_t B, int S) {
         }
         r->plan_ids.assign(scene_ids, scene_ids + B);
         r->plan_splits = S;
+        r->plan_windows = windows;
         ++r->plan_version;
     }
 }
 
-bps::FrameParams frame_params(const bps_renderer* r, int S) {
+bps::FrameParams frame_params(const bps_renderer* r, const Cut& cut) {
     bps::FrameParams fp;
     fp.H = r->rh;
     fp.W = r->rw;
-    fp.tile_w = r->tile_w;
-    fp.tile_h = r->tile_h;
+    fp.tile_w = cut.w;
+    fp.tile_h = cut.h;
     fp.sx = 128.0f * (float)fp.W;
     fp.sy = 128.0f * (float)fp.H;
     fp.xmax = 2.0f * fp.sx + 64.0f;
     fp.ymax = 2.0f * fp.sy + 64.0f;
     fp.background = r->cfg.background_depth;
-    fp.merge = S > 1 ? 1 : 0;
+    fp.merge = cut.S > 1 ? 1 : 0;
     fp.cull = (r->cfg.flags & BPS_FLAG_NO_CLUSTER_CULL) ? 0 : (r->cfg.flags & BPS_FLAG_NO_OCCLUSION_CULL) ? 1 : 2;
     fp.list_cap = r->list_cap;
     fp.round_target = r->round_target;
@@ -394,7 +434,8 @@ bps_status bps_create(const bps_config* cfg, bps_renderer** out) {
         if (const char* e = std::getenv("BPS_FIRST_ROUND")) r->first_round = std::max(1, std::atoi(e));
 #endif
         r->lds = bps::lds_bytes(r->tile_h, r->tile_w, r->threads, r->list_cap);
-        BPS_HIP(r, bps::prepare_raster(r->threads, r->lds));
+        r->fixed_layout = bps::lds_bytes(64, 64, 512, (int)bps::kListCap64) <= r->max_lds;
+        BPS_HIP(r, bps::prepare_raster(r->threads, r->lds, r->fixed_layout));
         BPS_HIP(r, hipMalloc((void**)&r->d_scenes, sizeof(bps::SceneDev) * kMaxScenes));
         BPS_HIP(r, hipMemset(r->d_scenes, 0, sizeof(bps::SceneDev) * kMaxScenes));
         for (RingSlot& s : r->ring) {
@@ -791,7 +832,7 @@ bps_status bps_render(bps_renderer* r, const bps_scene* scene_ids, const float* 
     const bool rgbd = r->cfg.mode == BPS_MODE_RGBD;
     if (rgbd && !out_rgb) return fail(r, BPS_ERR_INVALID_ARG, "bps_render: out_rgb is required in RGB-D mode");
     hipStream_t stream = (hipStream_t)stream_;
-    uint32_t min_clusters = 0xFFFFFFFFu;
+    uint32_t min_clusters = 0xFFFFFFFFu, max_clusters = 0u;
     r->call_slots.resize(B);
     for (uint32_t b = 0; b < B; ++b) {
         const int s = slot_of(r, scene_ids[b]);
@@ -799,6 +840,7 @@ bps_status bps_render(bps_renderer* r, const bps_scene* scene_ids, const float* 
         if (rgbd && !r->scenes[s].has_colors)
             return fail(r, BPS_ERR_INVALID_ARG, "bps_render: scene %d (scene_ids[%u]) was loaded without colours", scene_ids[b], b);
         min_clusters = std::min(min_clusters, r->scenes[s].dev.n_clusters);
+        max_clusters = std::max(max_clusters, r->scenes[s].dev.n_clusters);
         r->call_slots[b] = s;
     }
     scene_ids = r->call_slots.data();      // table slots from here on
@@ -831,9 +873,9 @@ bps_status bps_render(bps_renderer* r, const bps_scene* scene_ids, const float* 
         out_depth = r->ss_depth;
         out_rgb = r->ss_rgb;
     }
-    const int S = plan_splits(r, B, min_clusters);
-
-    make_plan(r, scene_ids, B, S);
+    const Cut cut = choose_cut(r, B, min_clusters, max_clusters);
+    const int S = cut.S;
+    make_plan(r, scene_ids, B, cut);
     const size_t n_items = r->plan_items.size();
 
     // ---- stage the request (work items + matrices unless they already live on the device)
@@ -929,7 +971,7 @@ bps_status bps_render(bps_renderer* r, const bps_scene* scene_ids, const float* 
     const bool uses_shared = rgbd || S > 1 || r->ss > 1 || r->want_stats;
     if (uses_shared && r->shared_done && r->shared_stream != stream) BPS_HIP(r, hipStreamWaitEvent(stream, r->shared_done, 0));
 
-    const bps::FrameParams fp = frame_params(r, S);
+    const bps::FrameParams fp = frame_params(r, cut);
 
     unsigned long long* d_stats = nullptr;
     if (r->want_stats) {
@@ -964,7 +1006,7 @@ bps_status bps_render(bps_renderer* r, const bps_scene* scene_ids, const float* 
         r->ev_used += 2;
     }
     bps::launch_raster(r->threads, dim3((unsigned)n_items), r->lds, stream, r->d_scenes, planned ? d_ordered : d_items, d_vp, fp,
-                       r->gvis, out_depth, out_tri_id, d_stats);
+                       r->fixed_layout, r->gvis, out_depth, out_tri_id, d_stats);
     BPS_HIP(r, hipGetLastError());
     if (ev_stop) BPS_HIP(r, hipEventRecord(ev_stop, stream));
     if (S > 1) {
@@ -1008,7 +1050,7 @@ bps_status bps_render_static(bps_renderer* r, const bps_scene* scene_ids, const 
     if (r->cfg.mode != BPS_MODE_DEPTH || r->ss > 1 || r->want_stats || r->cfg.splits > 1)
         return fail(r, BPS_ERR_UNSUPPORTED,
                     "bps_render_static: depth renderers only, without supersampling, forced splits or diagnostics");
-    const size_t n_items = (size_t)B * (size_t)r->tiles;
+    size_t n_items = (size_t)B * (size_t)r->tiles;
     if (n_items > kStaticMaxItems || B > 0xFFFFu)
         return fail(r, BPS_ERR_INVALID_ARG, "bps_render_static: %zu work-groups (B x tiles of the frame) exceed the static scratch (%u)",
                     n_items, kStaticMaxItems);
@@ -1019,11 +1061,13 @@ bps_status bps_render_static(bps_renderer* r, const bps_scene* scene_ids, const 
     (void)hipGetLastError();
     if (!vp_on_device) return fail(r, BPS_ERR_INVALID_ARG, "bps_render_static: view_proj must be device memory");
     hipStream_t stream = (hipStream_t)stream_;
+    uint32_t max_clusters = 0u;
     r->call_slots.resize(B);
     for (uint32_t b = 0; b < B; ++b) {
         const int s = slot_of(r, scene_ids[b]);
         if (s < 0) return fail(r, BPS_ERR_BAD_HANDLE, "bps_render_static: scene_ids[%u]=%d is not a loaded scene", b, scene_ids[b]);
         r->call_slots[b] = s;
+        max_clusters = std::max(max_clusters, r->scenes[s].dev.n_clusters);
     }
     scene_ids = r->call_slots.data();      // table slots from here on
     BPS_HIP(r, hipSetDevice(r->device));
@@ -1042,7 +1086,10 @@ bps_status bps_render_static(bps_renderer* r, const bps_scene* scene_ids, const 
             }
         }
     }
-    make_plan(r, scene_ids, B, 1);      // (host containers only; they keep their capacity between calls)
+    Cut cut = choose_cut(r, B, 1u, max_clusters);
+    cut.S = 1;                          // (no merge buffer here)
+    make_plan(r, scene_ids, B, cut);    // (host containers only; they keep their capacity between calls)
+    n_items = r->plan_items.size();     // (small batches are cut finer, never past the number the device holds at once)
     // a ring slot is taken for its completion event only: scene retirement tracks requests through them
     RingSlot& slot = r->ring[r->ring_next];
     r->ring_next = (r->ring_next + 1) % kRing;
@@ -1062,7 +1109,7 @@ bps_status bps_render_static(bps_renderer* r, const bps_scene* scene_ids, const 
                 const uint32_t count = (uint32_t)std::min<size_t>(bps::kPackedItemsPerLaunch, n_items - first);
                 for (uint32_t k = 0; k < count; ++k) {
                     const bps::WorkItem& it = r->plan_items[first + k];
-                    packed.word[k] = it.env | (it.scene << 16) | (it.tile << 28);
+                    packed.word[k] = it.env | (it.scene << bps::kPackedEnvBits) | (it.tile << (bps::kPackedEnvBits + kSlotBits));
                 }
                 bps::launch_unpack_items(stream, packed, (uint32_t)first, count, d_items);
                 BPS_HIP(r, hipGetLastError());
@@ -1071,14 +1118,14 @@ bps_status bps_render_static(bps_renderer* r, const bps_scene* scene_ids, const 
             g_scratch_plan[r->device] = r->plan_version;
         }
     }
-    const bps::FrameParams fp = frame_params(r, 1);
+    const bps::FrameParams fp = frame_params(r, cut);
     const bool planned = fp_cull_enabled(r) && n_items > (size_t)2 * r->num_cu && !(r->cfg.flags & BPS_FLAG_NO_DISPATCH_ORDER);
     if (planned) {
         bps::launch_plan(stream, r->d_scenes, d_items, view_proj, fp, (uint32_t)n_items, d_cost, d_ordered);
         BPS_HIP(r, hipGetLastError());
     }
     bps::launch_raster(r->threads, dim3((unsigned)n_items), r->lds, stream, r->d_scenes, planned ? d_ordered : d_items, view_proj,
-                       fp, nullptr, out_depth, out_tri_id, nullptr);
+                       fp, r->fixed_layout, nullptr, out_depth, out_tri_id, nullptr);
     BPS_HIP(r, hipGetLastError());
     BPS_HIP(r, hipEventRecord(slot.done, stream));
     slot.pending = true;
@@ -1166,7 +1213,11 @@ bps_status bps_query(bps_renderer* r, bps_scene scene, int32_t what, uint64_t* v
     case 4: *value = r->last_splits; return BPS_OK;
     case 5: *value = r->last_groups; return BPS_OK;
     case 6: *value = (uint64_t)r->threads; return BPS_OK;
-    case 7: *value = (uint64_t)r->lds; return BPS_OK;
+    case 7:
+        *value = r->fixed_layout && r->threads == 512 && !(r->cfg.flags & (BPS_FLAG_NO_CLUSTER_CULL | BPS_FLAG_NO_OCCLUSION_CULL))
+                     ? (uint64_t)bps::lds_bytes(64, 64, 512, (int)bps::kListCap64)
+                     : (uint64_t)r->lds;
+        return BPS_OK;
     case 8: *value = r->arena_allocs; return BPS_OK;
     case 9: *value = (uint64_t)r->arena_pool.size() + (uint64_t)r->retired.size(); return BPS_OK;
     default: return fail(r, BPS_ERR_INVALID_ARG, "bps_query: unknown item %d", what);

@@ -67,7 +67,7 @@ constexpr uint32_t kInvalid = 0x40u;   // outcode bit: vertex unusable, drop its
 constexpr uint32_t kNoProject = 0x80u; // outcode bit: vertex has no finite screen position (w <= 0 or overflow)
 
 // per-wave LDS block: 64 staged vertices (8 B + 4 B outcode each), small queue 8 x 64 words
-constexpr uint32_t kListCap64 = 1216;   // survivor-list capacity of the 64x64 instance (two groups per compute unit)
+constexpr uint32_t kListCap64 = 1216;   // survivor-list capacity of the fixed-layout instances (two groups per compute unit)
 constexpr uint32_t kWaveLdsBytes = 64 * 12 + 8 * 64 * 4;
 
 // The work-group's ring of triangles waiting for the clipper.  A wavefront adds at most 128 entries
@@ -93,7 +93,9 @@ __host__ __device__ inline size_t lds_bytes(int tile_h, int tile_w, int threads,
 
 // DIAG = true is the instance launched while diagnostics are on; it alone keeps counters and timers.
 // CULL = FrameParams::cull of the launch (0 none, 1 frustum, 2 frustum + occlusion).
-// FRAME = 64 or 128: the frame is square of that size and drawn as 64x64 windows; 0 = any frame.
+// FRAME = 64 or 128: the frame is square of that size and drawn as 64x64 windows; 1 = any frame and window,
+// with the LDS layout of those two (a 64x64 key buffer and kListCap64 survivors, whatever the window's size);
+// 0 = any frame, window, layout.
 template <int NT, bool DIAG, int CULL, int FRAME>
 __global__ void k_raster(const SceneDev* __restrict__ scenes, const WorkItem* __restrict__ items,
                          const float* __restrict__ view_proj, FrameParams fp, unsigned long long* __restrict__ gvis,
@@ -107,17 +109,19 @@ __global__ void k_fill_keys(unsigned long long* __restrict__ gvis, size_t n);
 __global__ void k_zero_words(unsigned long long* __restrict__ p, size_t n);
 
 void launch_raster(int threads, dim3 grid, size_t lds, hipStream_t stream, const SceneDev* scenes, const WorkItem* items,
-                   const float* view_proj, const FrameParams& fp, unsigned long long* gvis, float* out_depth,
-                   uint32_t* out_id, unsigned long long* stats);
+                   const float* view_proj, const FrameParams& fp, bool fixed_layout, unsigned long long* gvis,
+                   float* out_depth, uint32_t* out_id, unsigned long long* stats);
 // Fills ordered[n_items] with the items in launch order, costliest first; cost is scratch, one word
 // per item.
 constexpr uint32_t kMaxPlannedItems = 16384;
 void launch_plan(hipStream_t stream, const SceneDev* scenes, const WorkItem* items, const float* view_proj,
                  const FrameParams& fp, uint32_t n_items, uint32_t* cost, WorkItem* ordered);
-hipError_t prepare_raster(int threads, size_t lds);
+hipError_t prepare_raster(int threads, size_t lds, bool fixed_layout);
 // Work items handed over as kernel arguments (no host-to-device copy, no staging memory): up to
-// kPackedItemsPerLaunch items per launch, each packed as env | scene << 16 | tile << 28 (one
-// work-group per environment and tile, i.e. split_of = 1 << 16).
+// kPackedItemsPerLaunch items per launch, each packed as env (14 bits: at most kMaxPlannedItems items) |
+// scene (12 bits) | tile (6 bits); one work-group per environment and tile, i.e. split_of = 1 << 16.
+constexpr uint32_t kPackedEnvBits = 14, kPackedSceneBits = 12;
+static_assert(kMaxPlannedItems <= 1u << kPackedEnvBits, "every environment of a request has an item");
 constexpr uint32_t kPackedItemsPerLaunch = 960;
 struct PackedItems {
     uint32_t word[kPackedItemsPerLaunch];

@@ -52,8 +52,8 @@ __device__ __forceinline__ void drain_small(const WaveLds& L, int n, int lane, u
     const int dy0 = unpack_y(s.e0), dy1 = unpack_y(s.e1);
     const int right0 = -(dy0 << 8), right1 = -(dy1 << 8);
     const int wrap0 = (unpack_x(s.e0) + __mul24(nx - 1, dy0)) << 8, wrap1 = (unpack_x(s.e1) + __mul24(nx - 1, dy1)) << 8;
-    int at = __mul24(j_lo - win.y0, win.w) + (i_lo - win.x0), col = 0;
-    const int at_wrap = win.w - nx + 1;
+    int at = __mul24(j_lo - win.y0, win.pitch) + (i_lo - win.x0), col = 0;
+    const int at_wrap = win.pitch - nx + 1;
     const float a2f = (float)s.A2;
     ++L.tally[kTDrains];
     for (int k = 0; k < kSmallMax; ++k) {
@@ -216,7 +216,7 @@ __device__ __forceinline__ void emit(const WaveLds& L, int& small_count, bool va
                 if (act & (st.A2 != 0) & (E0 >= st.t0) & (E1 >= st.t1) & (E2 >= st.t2)) {
                     const float num = fmaf((float)E2, st.iw2, fmaf((float)E1, st.iw1, (float)E0 * st.iw0));
                     const u64 key = ((u64)__float_as_uint(div_in_range(a2f, num)) << 32) | (u64)mid;
-                    atomicMin(&vis[__mul24(mj + dj - win.y0, win.w) + (mi + di - win.x0)], key);
+                    atomicMin(&vis[__mul24(mj + dj - win.y0, win.pitch) + (mi + di - win.x0)], key);
                 }
             }
     }
@@ -565,8 +565,9 @@ __global__ __launch_bounds__(NT, 4) void k_raster(const SceneDev* __restrict__ s
     // capacity of the survivor list, so that every LDS address below is a compile-time constant.
     // FRAME = 64 or 128: an instance for square frames of that size, drawn as 64x64 windows (the
     // paper's two resolutions).  The frame parameters the loops use are constants there.
+    // FRAME = 1: any frame and any window of at most 64x64 pixels, with the same constant LDS layout.
     FrameParams fq = fp;
-    if (FRAME) {
+    if (FRAME > 1) {
         fq.H = FRAME; fq.W = FRAME; fq.tile_w = 64; fq.tile_h = 64;
         fq.sx = 128.0f * FRAME; fq.sy = 128.0f * FRAME; fq.xmax = 256.0f * FRAME + 64.0f; fq.ymax = 256.0f * FRAME + 64.0f;
     }
@@ -610,6 +611,7 @@ __global__ __launch_bounds__(NT, 4) void k_raster(const SceneDev* __restrict__ s
     // this work-group's window of the frame
     const int tiles_x = (fp.W + fp.tile_w - 1) / fp.tile_w;
     Window win;
+    win.pitch = 64;
     if (FRAME == 64) {
         // the instance for 64x64 frames (the paper's main resolution): the window is the frame, and
         // with its origin and size known to the compiler the pixel arithmetic of every loop shrinks
@@ -629,9 +631,10 @@ __global__ __launch_bounds__(NT, 4) void k_raster(const SceneDev* __restrict__ s
         win.aR = 2.0f * (float)(win.x0 + win.w) / (float)fp.W - 1.0f;
         win.aT = 2.0f * (float)win.y0 / (float)fp.H - 1.0f;
         win.aB = 2.0f * (float)(win.y0 + win.h) / (float)fp.H - 1.0f;
+        if (FRAME == 0) win.pitch = win.w;
     }
-    const int npix = win.w * win.h;
-    for (int p = tid; p < npix; p += NT) vis[p] = kEmptyKey;
+    const int nslots = win.h * win.pitch;      // (columns beyond the window's width are never looked at)
+    for (int p = tid; p < nslots; p += NT) vis[p] = kEmptyKey;
 
     int small_count = 0;
     uint32_t clip_tail_seen = 0u, clip_head_seen = 0u;    // this wavefront's last view of the clip ring
@@ -728,7 +731,7 @@ __global__ __launch_bounds__(NT, 4) void k_raster(const SceneDev* __restrict__ s
     // the first round is kept short: what it draws (the nearest blocks) lets later rounds reject
     // hidden clusters before they are queued
     uint32_t round_target = occlusion ? min((uint32_t)fp.round_target, (uint32_t)fp.first_round) : (uint32_t)fp.round_target;
-    const int htx = (win.w + 7) >> 3;     // Hi-Z tiles per row of the window
+    const int htx = FRAME ? 8 : (win.w + 7) >> 3;     // Hi-Z tiles per row of the window
     bool later_round = false;             // something has been drawn: the depth buffer can reject
     for (;;) {
         for (;;) {
@@ -783,7 +786,7 @@ __global__ __launch_bounds__(NT, 4) void k_raster(const SceneDev* __restrict__ s
                         if (ballot64(fine) != 0ull) {
                             // one footprint row per step: its up to four depth words are read together
                             const uint32_t bound = wb18 << 13;
-                            int at = __mul24(fy, win.w) + fx;
+                            int at = __mul24(fy, win.pitch) + fx;
                             uint32_t farthest = 0u;
                             for (int row = 0; row < 4; ++row) {
                                 const bool act = fine && row <= bh;
@@ -793,7 +796,7 @@ __global__ __launch_bounds__(NT, 4) void k_raster(const SceneDev* __restrict__ s
                                 const uint32_t d2 = act && bw >= 2 ? vis_hi[2 * (at + 2)] : 0u;
                                 const uint32_t d3 = act && bw >= 3 ? vis_hi[2 * (at + 3)] : 0u;
                                 farthest = max(farthest, max(max(d0, d1), max(d2, d3)));
-                                at += win.w;
+                                at += win.pitch;
                             }
                             if (fine && farthest < bound) visible = false;
                         }
@@ -896,11 +899,11 @@ __global__ __launch_bounds__(NT, 4) void k_raster(const SceneDev* __restrict__ s
                     const int cols_log2 = bw == 0 ? 0 : 32 - __builtin_clz((uint32_t)bw);
                     const int qx = min(lane & ((1 << cols_log2) - 1), bw), qy = lane >> cols_log2;
                     const int rows_per_pass = 64 >> cols_log2;
-                    const uint32_t* const corner = vis_hi + 2 * (__mul24(fy, win.w) + fx);
+                    const uint32_t* const corner = vis_hi + 2 * (__mul24(fy, win.pitch) + fx);
                     bool shows = false;
                     for (int row0 = 0; row0 <= bh && !shows; row0 += rows_per_pass) {
                         ++tally[kTPopPasses];
-                        const uint32_t d = corner[2 * (__mul24(min(row0 + qy, bh), win.w) + qx)];
+                        const uint32_t d = corner[2 * (__mul24(min(row0 + qy, bh), win.pitch) + qx)];
                         shows = ballot64(d >= wbits) != 0ull;
                     }
                     if (!shows) { ++st_hidden; continue; }
@@ -1050,7 +1053,7 @@ __global__ __launch_bounds__(NT, 4) void k_raster(const SceneDev* __restrict__ s
                 const int t = u >> 3, py = ((t / htx) << 3) + (u & 7), px0 = (t % htx) << 3;
                 uint32_t dbits = 0u;
                 if (py < win.h) {
-                    const uint32_t* row = vis_hi + 2 * (__mul24(py, win.w) + px0);
+                    const uint32_t* row = vis_hi + 2 * (__mul24(py, win.pitch) + px0);
 #pragma unroll
                     for (int k = 0; k < 8; ++k) dbits = max(dbits, px0 + k < win.w ? row[2 * k] : 0u);
                 }
@@ -1132,8 +1135,9 @@ __global__ __launch_bounds__(NT, 4) void k_raster(const SceneDev* __restrict__ s
 
     // ---- resolve this work-group's frame
     const size_t base = (size_t)item.env * fq.H * fq.W;
-    for (int p = tid; p < npix; p += NT) {
-        const int y = p / win.w, x = p - y * win.w;
+    for (int p = tid; p < nslots; p += NT) {
+        const int y = FRAME ? p >> 6 : p / win.w, x = FRAME ? p & 63 : p - y * win.w;
+        if (FRAME == 1 && x >= win.w) continue;
         const size_t o = base + (size_t)(win.y0 + y) * fq.W + (size_t)(win.x0 + x);
         const u64 key = vis[p];
         const bool hit = key != kEmptyKey;
@@ -1321,10 +1325,10 @@ __global__ __launch_bounds__(64) void k_unpack_items(PackedItems packed, uint32_
     if (k >= count) return;
     const uint32_t w = packed.word[k];
     WorkItem it;
-    it.env = w & 0xFFFFu;
-    it.scene = (w >> 16) & 0xFFFu;
+    it.env = w & ((1u << kPackedEnvBits) - 1u);
+    it.scene = (w >> kPackedEnvBits) & ((1u << kPackedSceneBits) - 1u);
     it.split_of = 1u << 16;
-    it.tile = w >> 28;
+    it.tile = w >> (kPackedEnvBits + kPackedSceneBits);
     items[first + k] = it;
 }
 
@@ -1352,35 +1356,40 @@ const void* raster_entry(int threads) {
 }
 }  // namespace
 
-hipError_t prepare_raster(int threads, size_t lds) {
+hipError_t prepare_raster(int threads, size_t lds, bool fixed_layout) {
     const void* entries[6] = {raster_entry<false, 0>(threads), raster_entry<false, 1>(threads), raster_entry<false, 2>(threads),
                               raster_entry<true, 0>(threads),  raster_entry<true, 1>(threads),  raster_entry<true, 2>(threads)};
     for (const void* f : entries) {
         hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return e;
     }
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_raster<512, false, 2, 64>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) return e;
-    return hipFuncSetAttribute(reinterpret_cast<const void*>(&k_raster<512, false, 2, 128>),
-                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (!fixed_layout) return hipSuccess;
+    const void* fixed[3] = {reinterpret_cast<const void*>(&k_raster<512, false, 2, 64>),
+                            reinterpret_cast<const void*>(&k_raster<512, false, 2, 128>),
+                            reinterpret_cast<const void*>(&k_raster<512, false, 2, 1>)};
+    for (const void* f : fixed) {
+        hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes(64, 64, 512, (int)kListCap64));
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 void launch_raster(int threads, dim3 grid, size_t lds, hipStream_t stream, const SceneDev* scenes, const WorkItem* items,
-                   const float* view_proj, const FrameParams& fp, unsigned long long* gvis, float* out_depth,
-                   uint32_t* out_id, unsigned long long* stats) {
-    // 64x64 and 128x128 frames in the default configuration have instances of their own
-    if (threads == 512 && !stats && fp.cull == 2 && fp.tile_w == 64 && fp.tile_h == 64 && fp.list_cap == (int)kListCap64) {
-        if (fp.W == 64 && fp.H == 64) {
-            hipLaunchKernelGGL((k_raster<512, false, 2, 64>), grid, dim3(512), lds, stream, scenes, items, view_proj, fp, gvis,
-                               out_depth, out_id, stats);
-            return;
-        }
-        if (fp.W == 128 && fp.H == 128) {
-            hipLaunchKernelGGL((k_raster<512, false, 2, 128>), grid, dim3(512), lds, stream, scenes, items, view_proj, fp, gvis,
-                               out_depth, out_id, stats);
-            return;
-        }
+                   const float* view_proj, const FrameParams& fp, bool fixed_layout, unsigned long long* gvis,
+                   float* out_depth, uint32_t* out_id, unsigned long long* stats) {
+    // The default configuration runs on instances whose LDS layout is a compile-time constant: one each for
+    // 64x64 and 128x128 frames drawn as 64x64 windows, and one for every other frame and window size.
+    if (threads == 512 && !stats && fp.cull == 2 && fixed_layout) {
+        const size_t lds64 = lds_bytes(64, 64, 512, (int)kListCap64);
+        const bool full = fp.tile_w == 64 && fp.tile_h == 64;
+#define BPS_LAUNCH_FIXED(FRAME)                                                                                        \
+    hipLaunchKernelGGL((k_raster<512, false, 2, FRAME>), grid, dim3(512), lds64, stream, scenes, items, view_proj, fp, gvis, \
+                       out_depth, out_id, stats)
+        if (full && fp.W == 64 && fp.H == 64) BPS_LAUNCH_FIXED(64);
+        else if (full && fp.W == 128 && fp.H == 128) BPS_LAUNCH_FIXED(128);
+        else BPS_LAUNCH_FIXED(1);
+#undef BPS_LAUNCH_FIXED
+        return;
     }
 #define BPS_LAUNCH3(NT, DIAG, CULL)                                                                                    \
     hipLaunchKernelGGL((k_raster<NT, DIAG, CULL, 0>), grid, dim3(NT), lds, stream, scenes, items, view_proj, fp, gvis,          \
