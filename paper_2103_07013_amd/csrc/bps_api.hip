@@ -113,8 +113,6 @@ struct bps_renderer {
     int ring_next = 0;
     unsigned long long* gvis = nullptr;   // [max_batch][H][W], only for split frames
     uint32_t* ids = nullptr;              // [max_batch][H][W], RGB-D requests without a caller id buffer
-    uint32_t* shade_queue = nullptr;      // queues of the pixels whose winner needs the clipper, then two counter blocks
-    uint32_t shade_parity = 0;            // which of the two counters the next RGB-D request uses
     unsigned long long* d_stats = nullptr;   // diagnostics block: 8 counters + one duration per work-group
     size_t stats_cap = 0;
     bool want_stats = false;
@@ -486,7 +484,6 @@ void bps_destroy(bps_renderer* r) {
     }
     if (r->gvis) (void)hipFree(r->gvis);
     if (r->ids) (void)hipFree(r->ids);
-    if (r->shade_queue) (void)hipFree(r->shade_queue);
     if (r->ss_depth) (void)hipFree(r->ss_depth);
     if (r->ss_rgb) (void)hipFree(r->ss_rgb);
     if (r->d_stats) (void)hipFree(r->d_stats);
@@ -962,12 +959,6 @@ bps_status bps_render(bps_renderer* r, const bps_scene* scene_ids, const float* 
 
     // Requests on one stream run in order.  A request on another stream may overlap the previous one
     // unless both use one of the renderer's own buffers: then it waits for that one.
-    // ---- RGB-D: queue of the pixels whose winning triangle crosses a clip plane, and its two counters
-    if (rgbd && !r->shade_queue) {
-        const size_t n = (size_t)bps::kShadeQueues * bps::shade_queue_cap((size_t)r->cfg.max_batch * HW);
-        BPS_HIP(r, hipMalloc((void**)&r->shade_queue, (n + 2 * 32 * bps::kShadeQueues) * sizeof(uint32_t)));
-        BPS_HIP(r, hipMemsetAsync(r->shade_queue + n, 0, 2 * 32 * bps::kShadeQueues * sizeof(uint32_t), stream));
-    }
     const bool uses_shared = rgbd || S > 1 || r->ss > 1 || r->want_stats;
     if (uses_shared && r->shared_done && r->shared_stream != stream) BPS_HIP(r, hipStreamWaitEvent(stream, r->shared_done, 0));
 
@@ -1016,11 +1007,7 @@ bps_status bps_render(bps_renderer* r, const bps_scene* scene_ids, const float* 
         BPS_HIP(r, hipGetLastError());
     }
     if (rgbd) {
-        uint32_t* counters = r->shade_queue + (size_t)bps::kShadeQueues * bps::shade_queue_cap((size_t)r->cfg.max_batch * HW);
-        bps::launch_shade(stream, r->d_scenes, d_env_scene, d_vp, fp, B, out_tri_id, out_rgb, r->shade_queue,
-                          counters + 32 * bps::kShadeQueues * r->shade_parity,
-                          counters + 32 * bps::kShadeQueues * (r->shade_parity ^ 1u));
-        r->shade_parity ^= 1u;
+        bps::launch_shade(stream, r->d_scenes, d_env_scene, d_vp, fp, B, out_tri_id, out_rgb);
         BPS_HIP(r, hipGetLastError());
     }
     if (r->ss > 1) {

@@ -126,6 +126,7 @@ struct PackedSetup {
     uint32_t e0, e1;          // edge vectors v2 - v1 and v0 - v2
     float iw0, iw1, iw2;
     int A2;
+    bool swapped;             // vertices 1 and 2 were exchanged to make A2 positive
     int t0, t1, t2;           // smallest value of E that is inside: 0 on a top-left edge, 1 otherwise
 };
 // Top-left: dy < 0, or dy = 0 and dx > 0, with dy in the high half; dx = dy = 0 only if A2 = 0.
@@ -138,6 +139,7 @@ __device__ __forceinline__ PackedSetup make_packed_setup(uint32_t xy0, uint32_t 
     PackedSetup s;
     const int a2 = cross16(as_u32(as_s2(xy1) - as_s2(xy0)), as_u32(as_s2(xy2) - as_s2(xy0)));
     const bool swap = a2 < 0;      // two-sided: exchange vertices 1 and 2
+    s.swapped = swap;
     s.A2 = swap ? -a2 : a2;
     s.v1 = swap ? xy2 : xy1;
     s.v2 = swap ? xy1 : xy2;

@@ -129,19 +129,9 @@ struct PackedItems {
 void launch_unpack_items(hipStream_t stream, const PackedItems& packed, uint32_t first, uint32_t count, WorkItem* items);
 void launch_downsample(hipStream_t stream, const float* depth, const uint8_t* rgb, uint32_t B, int H, int W,
                        float* out_depth, uint8_t* out_rgb);
-// Colour pass.  Pixels whose winning triangle needs the clipper go through kShadeQueues queues (work-group g
-// of the first kernel appends to queue g % kShadeQueues); shade_queue_cap(pixels) words per queue hold the
-// worst case.  queue: kShadeQueues * shade_queue_cap(pixels) words; count / next_count: this request's
-// counters (32 * kShadeQueues words, all zero) and the next request's (cleared by the launch).
-constexpr uint32_t kShadeQueues = 64;
-inline uint32_t shade_queue_cap(size_t pixels) {
-    const size_t groups = (pixels + 255) / 256;
-    return (uint32_t)((groups + kShadeQueues - 1) / kShadeQueues * 256);
-}
 // Fills sc.tri_rec from the scene's original arrays (once per scene, on the stream that uploads it).
 void launch_build_shade_records(hipStream_t stream, const SceneDev& sc, float* tri_rec);
 void launch_shade(hipStream_t stream, const SceneDev* scenes, const uint32_t* env_scene, const float* view_proj,
-                  const FrameParams& fp, uint32_t B, const uint32_t* tri_id, uint8_t* out_rgb, uint32_t* queue,
-                  uint32_t* count, uint32_t* next_count);
+                  const FrameParams& fp, uint32_t B, const uint32_t* tri_id, uint8_t* out_rgb);
 
 }  // namespace bps
