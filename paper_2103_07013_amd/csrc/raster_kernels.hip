@@ -74,6 +74,10 @@ __device__ __forceinline__ void drain_small(const WaveLds& L, int n, int lane, u
         at += row_end ? at_wrap : 1;
         col = row_end ? 0 : col;
     }
+    // The ids have arrived by now in all but the rarest drains (no pixel covered at all).  Without a use on every
+    // path the compiler waits for them where their register is next written, in the triangle phase, and with them
+    // for the next cluster's words, which are behind them in the order of return.
+    asm volatile("" :: "v"(id));
 }
 
 // Append small triangles to the wave's queue; whenever it reaches 64 entries, drain them.
@@ -181,7 +185,9 @@ __device__ __forceinline__ void emit(const WaveLds& L, int& small_count, bool va
     u64 med = packed_mask & ~small_mask & ballot64(within8);
     u64 big = vmask & ~small_mask & ~med;
     L.tally[kTLarge] += (uint32_t)__popcll(med | big);
-    const uint32_t id = (valid && !small) ? ctri_id[ref] : 0u;
+    if ((med | big) == 0ull) return;
+    uint32_t id = 0u;
+    if (valid && !small) id = ctri_id[ref];
     // medium triangles (box within 8x8 pixels): four per pass, sixteen lanes each, 4x4 pixels per step
     while (med) {
         ++L.tally[kTMedPasses];
@@ -229,6 +235,7 @@ __device__ __forceinline__ void emit(const WaveLds& L, int& small_count, bool va
                      bcast_f(iw0, src), bcast_f(iw1, src), bcast_f(iw2, src), (uint32_t)bcast_i((int)id, src), bi,
                      bi + (int)((bbox >> 16) & 0xFFu) - 1, bj, bj + (int)(bbox >> 24) - 1, lane, vis, win, L.tally);
     }
+    asm volatile("" :: "v"(id));      // (as at the end of drain_small)
 }
 
 // Conservative test of an axis-aligned box against the planes that bound the work-group's window
