@@ -85,10 +85,10 @@ constexpr int kHizTiles = 64;          // 8x8-pixel tiles of a window of at most
 constexpr int kDepthBins = 128;        // bins of the per-round depth sort of surviving clusters
 
 // visibility buffer, per-wave blocks, survivor list (8 B record + two 2 B sort words per cluster),
-// block order, depth histogram and its prefix, eight counters, clip ring
+// block order, depth histogram and its prefix, depth tiles, the window's planes, eight counters, clip ring
 __host__ __device__ inline size_t lds_bytes(int tile_h, int tile_w, int threads, int list_cap) {
-    return (size_t)tile_h * tile_w * 8 + (size_t)(threads / 64) * kWaveLdsBytes + (size_t)list_cap * 12 + kOrderCap * 2 +
-           2 * kDepthBins * 4 + kHizTiles * 4 + 32 + (size_t)clip_ring_entries(threads) * 4;
+    return (size_t)((tile_h * tile_w + 1) & ~1) * 8 + (size_t)(threads / 64) * kWaveLdsBytes + (size_t)list_cap * 12 + kOrderCap * 2 +
+           2 * kDepthBins * 4 + kHizTiles * 4 + 12 * 16 + 32 + (size_t)clip_ring_entries(threads) * 4;
 }
 
 // DIAG = true is the instance launched while diagnostics are on; it alone keeps counters and timers.

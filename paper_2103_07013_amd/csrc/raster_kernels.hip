@@ -246,34 +246,30 @@ __device__ __forceinline__ void emit(const WaveLds& L, int& small_count, bool va
 // in the per-vertex transform can never cull a box holding a vertex the exact rule keeps; window
 // edges lie half a pixel outside the outermost pixel centres, far more than vertex snapping moves
 // anything.  NaNs compare false and therefore never cull.
-__device__ __forceinline__ bool box_outside_frustum(const float (&M)[16], const Window& win, float lx, float ly,
-                                                    float lz, float hx, float hy, float hz) {
+//
+// The planes' coefficients and the magnitudes of the terms they are made of sit in LDS, [6][2] float4: kept in
+// registers they filled 30 of them through the whole kernel, and what that pushed out to memory came back one wait
+// at a time in this very test.
+__device__ __forceinline__ void fill_planes(float4* planes, const float* __restrict__ view_proj, const Window& win, int k) {
+    const float4* rows = reinterpret_cast<const float4*>(view_proj);
+    const float4 r3 = rows[3], r = rows[k >= 4 ? 2 : k >> 1];
+    // (row_r - a row_3) for the low side, (a row_3 - row_r) for the high side; near = row_2, far = row_3 - row_2
+    const float a = k == 0 ? win.aL : k == 1 ? win.aR : k == 2 ? win.aT : k == 3 ? win.aB : k == 4 ? 0.0f : 1.0f;
+    const float sg = (k == 1 || k == 3 || k == 5) ? -1.0f : 1.0f, aa = fabsf(a);
+    planes[2 * k] = make_float4(sg * (r.x - a * r3.x), sg * (r.y - a * r3.y), sg * (r.z - a * r3.z), sg * (r.w - a * r3.w));
+    planes[2 * k + 1] = make_float4(fabsf(r.x) + aa * fabsf(r3.x), fabsf(r.y) + aa * fabsf(r3.y),
+                                    fabsf(r.z) + aa * fabsf(r3.z), fabsf(r.w) + aa * fabsf(r3.w));
+}
+__device__ __forceinline__ bool box_outside_frustum(const float4* planes, float lx, float ly, float lz, float hx, float hy,
+                                                    float hz) {
     const float eps = 1.52587890625e-05f;   // 2^-16
     float ax = fmaxf(fabsf(lx), fabsf(hx)), ay = fmaxf(fabsf(ly), fabsf(hy)), az = fmaxf(fabsf(lz), fabsf(hz));
     bool outside = false;
 #pragma unroll
     for (int k = 0; k < 6; ++k) {
-        float px, py, pz, pw, qx, qy, qz, qw;   // plane coefficients and their magnitudes
-        if (k == 4) {
-            px = M[8]; py = M[9]; pz = M[10]; pw = M[11];
-            qx = fabsf(px); qy = fabsf(py); qz = fabsf(pz); qw = fabsf(pw);
-        } else if (k == 5) {
-            px = M[12] - M[8]; py = M[13] - M[9]; pz = M[14] - M[10]; pw = M[15] - M[11];
-            qx = fabsf(M[12]) + fabsf(M[8]); qy = fabsf(M[13]) + fabsf(M[9]);
-            qz = fabsf(M[14]) + fabsf(M[10]); qw = fabsf(M[15]) + fabsf(M[11]);
-        } else {
-            const int r = (k < 2) ? 0 : 1;
-            // (row_r - a row_3) for the low side, (a row_3 - row_r) for the high side
-            const float a = k == 0 ? win.aL : k == 1 ? win.aR : k == 2 ? win.aT : win.aB;
-            const float sg = (k == 0 || k == 2) ? 1.0f : -1.0f;
-            px = sg * (M[4 * r + 0] - a * M[12]); py = sg * (M[4 * r + 1] - a * M[13]);
-            pz = sg * (M[4 * r + 2] - a * M[14]); pw = sg * (M[4 * r + 3] - a * M[15]);
-            const float aa = fabsf(a);
-            qx = fabsf(M[4 * r + 0]) + aa * fabsf(M[12]); qy = fabsf(M[4 * r + 1]) + aa * fabsf(M[13]);
-            qz = fabsf(M[4 * r + 2]) + aa * fabsf(M[14]); qw = fabsf(M[4 * r + 3]) + aa * fabsf(M[15]);
-        }
-        float dmax = pw + fmaxf(px * lx, px * hx) + fmaxf(py * ly, py * hy) + fmaxf(pz * lz, pz * hz);
-        float mag = fmaf(qx, ax, fmaf(qy, ay, fmaf(qz, az, qw)));
+        const float4 p = planes[2 * k], q = planes[2 * k + 1];
+        float dmax = p.w + fmaxf(p.x * lx, p.x * hx) + fmaxf(p.y * ly, p.y * hy) + fmaxf(p.z * lz, p.z * hz);
+        float mag = fmaf(q.x, ax, fmaf(q.y, ay, fmaf(q.z, az, q.w)));
         outside = outside || (dmax < -eps * mag);
     }
     return outside;
@@ -578,7 +574,7 @@ __global__ __launch_bounds__(NT, 4) void k_raster(const SceneDev* __restrict__ s
         fq.H = FRAME; fq.W = FRAME; fq.tile_w = 64; fq.tile_h = 64;
         fq.sx = 128.0f * FRAME; fq.sy = 128.0f * FRAME; fq.xmax = 256.0f * FRAME + 64.0f; fq.ymax = 256.0f * FRAME + 64.0f;
     }
-    const int HW = FRAME ? 64 * 64 : fp.tile_w * fp.tile_h;
+    const int HW = FRAME ? 64 * 64 : (fp.tile_w * fp.tile_h + 1) & ~1;      // (even: what follows is 16-byte aligned)
     const int list_cap = FRAME ? (int)kListCap64 : fp.list_cap;
 
     u64* vis = reinterpret_cast<u64*>(smem);
@@ -597,7 +593,8 @@ __global__ __launch_bounds__(NT, 4) void k_raster(const SceneDev* __restrict__ s
     uint16_t* slot_in_bin = perm + list_cap;                                                       // [list_cap]
     uint32_t* hist = reinterpret_cast<uint32_t*>(slot_in_bin + list_cap);                          // [2][kDepthBins]
     uint32_t* hiz = hist + 2 * kDepthBins;                                                            // [kHizTiles]
-    uint32_t* counters = hiz + kHizTiles;
+    float4* planes = reinterpret_cast<float4*>(hiz + kHizTiles);                                       // [6][2]
+    uint32_t* counters = reinterpret_cast<uint32_t*>(planes + 12);
     uint32_t* list_count = counters;       // survivors appended in this round
     uint32_t* pop_count = counters + 1;    // survivors handed out in this round
     uint32_t* next_block = counters + 2;   // blocks handed out so far (whole item)
@@ -669,6 +666,7 @@ __global__ __launch_bounds__(NT, 4) void k_raster(const SceneDev* __restrict__ s
     // ---- prologue: counters, and the item's blocks ordered near to far
     const bool sorted = CULL != 0 && nb_item <= kOrderCap && nb_item <= 2u * (uint32_t)list_cap && nb_item > 1;
     if (tid < 8) counters[tid] = 0u;
+    if (CULL != 0 && tid < 6) fill_planes(planes, view_proj + (size_t)item.env * 16, win, tid);
     for (int t = tid; t < kHizTiles; t += NT) hiz[t] = 0xFFFFFFFFu;   // nothing drawn yet: no tile hides anything
     for (uint32_t t = tid; t <= ring.mask; t += NT) ring.slot[t] = kClipEmpty;
     // the bin counts of the two counting sorts below: zero whenever no sort is under way (the wavefront
@@ -693,7 +691,7 @@ __global__ __launch_bounds__(NT, 4) void k_raster(const SceneDev* __restrict__ s
 #pragma unroll
             for (int a = 0; a < 3; ++a) wmin += fminf(M[12 + a] * lo[a], M[12 + a] * hi[a]);
             uint32_t key = 0xFFFFFFFFu;
-            if (!box_outside_frustum(M, win, lo[0], lo[1], lo[2], hi[0], hi[1], hi[2])) {
+            if (!box_outside_frustum(planes, lo[0], lo[1], lo[2], hi[0], hi[1], hi[2])) {
                 // exponent and top three mantissa bits from 2^-7 upwards; boxes reaching the eye plane first
                 const int k = wmin > 0.0f ? (int)(__float_as_uint(wmin) >> 20) - 120 * 8 : 0;
                 const uint32_t bin = (uint32_t)min(max(k, 0), kDepthBins - 1);
@@ -771,7 +769,7 @@ __global__ __launch_bounds__(NT, 4) void k_raster(const SceneDev* __restrict__ s
                 float lx = g_bounds[cc], ly = g_bounds[sc.c_stride + cc], lz = g_bounds[2 * sc.c_stride + cc];
                 float hx = g_bounds[3 * sc.c_stride + cc], hy = g_bounds[4 * sc.c_stride + cc],
                       hz = g_bounds[5 * sc.c_stride + cc];
-                visible = visible && !box_outside_frustum(M, win, lx, ly, lz, hx, hy, hz);
+                visible = visible && !box_outside_frustum(planes, lx, ly, lz, hx, hy, hz);
                 if (occlusion && visible) {
                     foot = box_footprint(M, fq, win, lx, ly, lz, hx, hy, hz, wb18);
                     visible = foot != kNoPixel;
@@ -1181,9 +1179,6 @@ __global__ __launch_bounds__(64) void k_item_cost(const SceneDev* __restrict__ s
     if (i >= n_items) return;
     const WorkItem item = items[i];
     const SceneDev sc = scenes[item.scene];
-    float M[16];
-#pragma unroll
-    for (int k = 0; k < 16; ++k) M[k] = view_proj[(size_t)item.env * 16 + k];
     const BPS_GLOBAL float* bb = gptr(sc.bbounds);
     const uint32_t nblocks = (sc.n_clusters + 63u) / 64u;
     const uint32_t S = item.split_of >> 16, item_split = item.split_of & 0xFFFFu;
@@ -1197,11 +1192,14 @@ __global__ __launch_bounds__(64) void k_item_cost(const SceneDev* __restrict__ s
     win.aR = 2.0f * (float)(win.x0 + win.w) / (float)fp.W - 1.0f;
     win.aT = 2.0f * (float)win.y0 / (float)fp.H - 1.0f;
     win.aB = 2.0f * (float)(win.y0 + win.h) / (float)fp.H - 1.0f;
+    __shared__ float4 planes[12];
+    if (threadIdx.x < 6) fill_planes(planes, view_proj + (size_t)item.env * 16, win, (int)threadIdx.x);
+    wave_lds_sync();
     uint32_t count = 0;
     for (uint32_t gb = item_split + S * threadIdx.x; gb < nblocks; gb += S * 64u) {
         float lx = bb[gb], ly = bb[sc.b_stride + gb], lz = bb[2 * sc.b_stride + gb];
         float hx = bb[3 * sc.b_stride + gb], hy = bb[4 * sc.b_stride + gb], hz = bb[5 * sc.b_stride + gb];
-        count += box_outside_frustum(M, win, lx, ly, lz, hx, hy, hz) ? 0u : 1u;
+        count += box_outside_frustum(planes, lx, ly, lz, hx, hy, hz) ? 0u : 1u;
     }
 #pragma unroll
     for (int sh = 32; sh >= 1; sh >>= 1) count += (uint32_t)__shfl_xor((int)count, sh, 64);
