@@ -398,33 +398,161 @@ __device__ __forceinline__ int pop_clip(const ClipRing& R, uint32_t at_least, in
     return (int)n;
 }
 
-// One lane per queued straddling triangle: clip, project, fan, hand the pieces to emit().
-template <int FRAME>
-__device__ __forceinline__ void drain_clip(const WaveLds& L, uint32_t ref, int n, int& small_count, const SceneDev& sc,
-                                           const float (&M)[16], const FrameParams& fp, const Window& win, int lane,
-                                           u64* vis) {
-    bool have = lane < n && ref != kClipEmpty;
+// A straddling triangle per lane, clipped and projected: corners 0 .. cnt - 1, of which the first five are in
+// registers; a lane that needed the general clipper has all of them in xy[] / iw[] (private memory) instead.
+struct Clipped {
+    uint32_t ref;                            // cluster * 128 + slot
+    int cnt;                                 // 0: nothing to draw
+    uint32_t p0, p1, p2, p3, p4;             // packed positions
+    float w0, w1, w2, w3, w4;                // 1/w
+};
+
+// Distance of a corner from the lane's plane: z, w - z, w + x, w - x, w + y or w - y.
+struct LanePlane {
+    bool x, y, negative, no_w;
+    __device__ __forceinline__ float dist(const Clip4& q) const {
+        const float v = x ? q.x : y ? q.y : q.z;
+        return fmaf(no_w ? 0.0f : 1.0f, q.w, negative ? -v : v);
+    }
+};
+
+__device__ __forceinline__ Clip4 pick(bool first, const Clip4& p, const Clip4& q) {
+    return Clip4{first ? p.x : q.x, first ? p.y : q.y, first ? p.z : q.z, first ? p.w : q.w};
+}
+__device__ __forceinline__ Clip4 along(const Clip4& a, const Clip4& b, float t) {      // from the inside corner a to b
+    return Clip4{fmaf(t, b.x - a.x, a.x), fmaf(t, b.y - a.y, a.y), fmaf(t, b.z - a.z, a.z), fmaf(t, b.w - a.w, a.w)};
+}
+
+// One lane per queued straddling triangle: clip and project.  Triangles that cross one plane (nine in ten) or two
+// are clipped in registers; three and more, and numbers outside the range of the short divisions, by the general
+// clipper, which few wavefronts enter.  The general clipper alone kept its polygons in private memory (a trip to L2
+// per corner) and met every crossing and every corner in a branch of its own: 10 % of the kernel's vector
+// instructions, and the longest wait at the end of a round.  61 frames of 72x104: 71.5 -> 67.5 us per request, 256 of
+// 64x64: 108.5 -> 104.5, 4096 of 128x128: 2410 -> 2365; 1024 of 64x64 unchanged.
+__device__ __forceinline__ void clip_triangles(uint32_t* tally, uint32_t ref, int n, const SceneDev& sc, const float (&M)[16],
+                                               const FrameParams& fp, int lane, Clipped& out, uint32_t (&pxy)[kMaxPoly],
+                                               float (&piw)[kMaxPoly], bool& general) {
+    const bool have = lane < n && ref != kClipEmpty;
     if (!have) ref = 0u;
-    uint32_t c = ref >> 7, slot = ref & 127u;
-    uint32_t t = gptr(sc.ctris)[(size_t)c * 128 + slot] & 0x00FFFFFFu;
+    out.ref = ref;
+    const uint32_t c = ref >> 7;
+    const uint32_t t = gptr(sc.ctris)[ref] & 0x00FFFFFFu;
     const BPS_GLOBAL float* cv = gptr(sc.cverts) + (size_t)c * 192;
     Clip4 tri[3];
-    uint32_t oc_or = 0;
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
         uint32_t vi = (t >> (8 * k)) & 0xFFu;
         tri[k] = to_clip(M, cv[vi], cv[64 + vi], cv[128 + vi]);
-        oc_or |= outcode(tri[k]);
     }
+    ++tally[kTClipDrains];
+    // ---- which planes the triangle crosses, in the rule's order near, far, left, right, top, bottom
+    auto outside = [&](auto test) -> bool { return test(tri[0]) | test(tri[1]) | test(tri[2]); };
+    const bool cross[6] = {outside([](const Clip4& q) { return !(q.z >= 0.0f); }),  outside([](const Clip4& q) { return !(q.z <= q.w); }),
+                           outside([](const Clip4& q) { return !(q.x >= -q.w); }), outside([](const Clip4& q) { return !(q.x <= q.w); }),
+                           outside([](const Clip4& q) { return !(q.y >= -q.w); }), outside([](const Clip4& q) { return !(q.y <= q.w); })};
+    bool one = false, two = false, more = false;      // lanes with at least that many planes
+    bool f[6], g[6];                                  // the lane's first and second plane
+#pragma unroll
+    for (int k = 0; k < 6; ++k) {
+        f[k] = cross[k] & !one;
+        g[k] = cross[k] & one & !two;
+        more = more | (cross[k] & two);
+        two = two | (cross[k] & one);
+        one = one | cross[k];
+    }
+    auto usable = [](float num, float den) -> bool { return iw_in_range(den) & ((num == 0.0f) | iw_in_range(num)); };
+    bool fits = have & one & !more;
+    // ---- first plane: the vertex S on its own side, P before it and N after it leave the corners X1 (between P and
+    // S), X2 (between S and N) and either S or N and P.  The general clipper takes the edges c-a, a-b, b-c in turn,
+    // a crossing first and then the edge's end if that is inside: that decides where the polygon starts.
+    const LanePlane first{bool(f[2] | f[3]), bool(f[4] | f[5]), bool(f[1] | f[3] | f[5]), f[0]};
+    const float da = first.dist(tri[0]), db = first.dist(tri[1]), dc = first.dist(tri[2]);
+    const bool ia = da >= 0.0f, ib = db >= 0.0f, ic = dc >= 0.0f;
+    const bool is_a = ib == ic, is_c = !is_a & (ia == ib), is_b = !is_a & !is_c;
+    Clip4 Q0, Q1, Q2, Q3;
+    int m;
+    {
+        const Clip4 S = pick(is_a, tri[0], pick(is_b, tri[1], tri[2])), P = pick(is_a, tri[2], pick(is_b, tri[0], tri[1])),
+                    N = pick(is_a, tri[1], pick(is_b, tri[2], tri[0]));
+        const float dS = is_a ? da : is_b ? db : dc, dP = is_a ? dc : is_b ? da : db, dN = is_a ? db : is_b ? dc : da;
+        const bool s_in = is_a ? ia : is_b ? ib : ic;
+        const float n1 = s_in ? dS : dP, d1 = n1 - (s_in ? dP : dS), n2 = s_in ? dS : dN, d2 = n2 - (s_in ? dN : dS);
+        fits = fits & usable(n1, d1) & usable(n2, d2);
+        const Clip4 X1 = along(pick(s_in, S, P), pick(s_in, P, S), div_in_range(n1, d1));
+        const Clip4 X2 = along(pick(s_in, S, N), pick(s_in, N, S), div_in_range(n2, d2));
+        const Clip4 A = pick(s_in, S, N);
+        Q0 = pick(is_c, X2, pick(is_b & !s_in, P, X1));
+        Q1 = pick((is_c & s_in) | (is_b & !s_in), X1, pick(is_a & !s_in, X2, A));
+        Q2 = pick((is_c & s_in) | (is_a & !s_in), A, pick(is_c & !s_in, P, X2));
+        Q3 = pick(s_in, Q2, pick(is_a, P, pick(is_b, A, X1)));      // three corners: the last one twice
+        m = s_in ? 3 : 4;
+    }
+    auto snapped = [&](const Clip4& q, uint32_t& xy, float& iw) -> bool {
+        iw = recip_normal(q.w);
+        const float fx = fmaf(q.x * iw, fp.sx, fp.sx), fy = fmaf(q.y * iw, fp.sy, fp.sy);
+        xy = snap_xy(fx, fy);
+        // well inside what the numeric rule accepts
+        return iw_in_range(iw) & (fabsf(fx - fp.sx) <= fp.sx + 32.0f) & (fabsf(fy - fp.sy) <= fp.sy + 32.0f);
+    };
+    ++tally[kTClipPasses];
+    if (ballot64(have & two & fits) == 0ull) {
+        fits = fits & snapped(Q0, out.p0, out.w0);
+        fits = fits & snapped(Q1, out.p1, out.w1);
+        fits = fits & snapped(Q2, out.p2, out.w2);
+        fits = fits & snapped(Q3, out.p3, out.w3);
+        out.p4 = out.p3;
+        out.w4 = out.w3;
+        out.cnt = m;
+    } else {
+        // ---- second plane: the same rule over the three or four corners; lanes without one keep every corner
+        ++tally[kTClipPasses];
+        const LanePlane second{bool(g[2] | g[3]), bool(g[4] | g[5]), bool(g[1] | g[3] | g[5]), g[0]};
+        const Clip4 Q[4] = {Q0, Q1, Q2, Q3};
+        float d[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) d[k] = two ? second.dist(Q[k]) : 1.0f;
+        int at = 0, turns = 0;
+        out.p0 = out.p1 = out.p2 = out.p3 = out.p4 = 0u;
+        out.w0 = out.w1 = out.w2 = out.w3 = out.w4 = 0.0f;
+        auto put = [&](bool want, uint32_t xy, float iw) {
+            out.p0 = (want & (at == 0)) ? xy : out.p0; out.w0 = (want & (at == 0)) ? iw : out.w0;
+            out.p1 = (want & (at == 1)) ? xy : out.p1; out.w1 = (want & (at == 1)) ? iw : out.w1;
+            out.p2 = (want & (at == 2)) ? xy : out.p2; out.w2 = (want & (at == 2)) ? iw : out.w2;
+            out.p3 = (want & (at == 3)) ? xy : out.p3; out.w3 = (want & (at == 3)) ? iw : out.w3;
+            out.p4 = (want & (at == 4)) ? xy : out.p4; out.w4 = (want & (at == 4)) ? iw : out.w4;
+            at += want ? 1 : 0;
+        };
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int before = (k + 3) & 3;      // (three corners: the fourth repeats the third)
+            const bool in = d[k] >= 0.0f, in_before = d[before] >= 0.0f, turn = in != in_before, keep = in & (k < m);
+            const float num = in ? d[k] : d[before], den = num - (in ? d[before] : d[k]);
+            uint32_t xy;
+            float iw;
+            bool ok = snapped(along(pick(in, Q[k], Q[before]), pick(in, Q[before], Q[k]), div_in_range(num, den)), xy, iw);
+            fits = fits & (!turn | (ok & usable(num, den)));
+            put(turn, xy, iw);
+            ok = snapped(Q[k], xy, iw);
+            fits = fits & (!keep | ok);
+            put(keep, xy, iw);
+            turns += turn ? 1 : 0;
+        }
+        fits = fits & (turns <= 2);
+        out.cnt = at;
+    }
+    general = have & !fits;
+    if (!fits) out.cnt = 0;
+    if (ballot64(general) == 0ull) return;
+    // ---- the general clipper
+    uint32_t oc_or = 0;
+    if (general) oc_or = outcode(tri[0]) | outcode(tri[1]) | outcode(tri[2]);
     // Polygons between passes live in private memory, and a value stored there comes back only after
     // a trip to L2.  So the first pass takes the triangle from registers, and a lane's last pass
     // projects the vertices it puts out at once (one failure drops the triangle) instead of storing
     // them for a separate projection loop: a triangle that crosses one plane never reads a polygon back.
     Clip4 px[2][kMaxPoly];
-    uint32_t pxy[kMaxPoly];
-    float piw[kMaxPoly];
     bool ok = true;
-    int cnt = have ? 3 : 0;
+    int cnt = general ? 3 : 0;
     int cur = 0;
     // Planes are taken in the rule's order near, far, left, right, top, bottom, but every lane only
     // visits the planes its own triangle crosses: in pass j each lane clips against the j-th of
@@ -434,8 +562,8 @@ __device__ __forceinline__ void drain_clip(const WaveLds& L, uint32_t ref, int n
     // with 0 are exact).
     uint32_t todo = ((oc_or >> 4) & 3u) | ((oc_or & 15u) << 2);      // bit p: p-th plane of the order
     if (cnt < 3) todo = 0u;
-    if (ballot64(have && todo == 0u) != 0ull) {      // crosses no plane after all: the triangle as it is
-        if (have && todo == 0u) {
+    if (ballot64(general && todo == 0u) != 0ull) {      // crosses no plane after all: the triangle as it is
+        if (general && todo == 0u) {
 #pragma unroll
             for (int k = 0; k < 3; ++k) {
                 bool unused;
@@ -444,9 +572,8 @@ __device__ __forceinline__ void drain_clip(const WaveLds& L, uint32_t ref, int n
         }
     }
     bool first_pass = true;
-    ++L.tally[kTClipDrains];
     while (ballot64(todo != 0u) != 0ull) {
-        ++L.tally[kTClipPasses];
+        ++tally[kTClipPasses];
         const bool active = todo != 0u;
         const int p = active ? __builtin_ctz(todo) : 0;
         todo &= todo - 1u;
@@ -514,29 +641,46 @@ __device__ __forceinline__ void drain_clip(const WaveLds& L, uint32_t ref, int n
         first_pass = false;
     }
     if (cnt < 3 || !ok) cnt = 0;
+    if (general) {
+        out.cnt = cnt;
+        out.p0 = pxy[0]; out.p1 = pxy[1]; out.p2 = pxy[2];
+        out.w0 = piw[0]; out.w1 = piw[1]; out.w2 = piw[2];
+    }
+}
+
+// Clips up to 64 queued triangles and hands the pieces (0, k, k + 1) of their polygons to emit().
+template <int FRAME>
+__device__ __forceinline__ void draw_clipped(const WaveLds& L, uint32_t ref, int n, int& small_count, const SceneDev& sc,
+                                             const float (&M)[16], const FrameParams& fp, const Window& win, int lane, u64* vis) {
+    Clipped cl;
+    uint32_t pxy[kMaxPoly];      // corners of the general clipper
+    float piw[kMaxPoly];
+    bool general;
+    clip_triangles(L.tally, ref, n, sc, M, fp, lane, cl, pxy, piw, general);
     const BPS_GLOBAL uint32_t* ctri_id = gptr(sc.ctri_id);
-    const uint32_t tri_ref = c * 128u + slot;
-    // fan (0, i, i + 1): vertex i is the previous piece's last one, and the next one is fetched ahead
-    const uint32_t a = pxy[0];
-    const float wa = piw[0];
-    uint32_t b = pxy[1], d_ahead = pxy[2];
-    float wb = piw[1], wd_ahead = piw[2];
-    for (int i = 1; ; ++i) {
-        bool v = i + 1 < cnt;
-        const u64 vm = ballot64(v);
-        if (vm == 0) break;
+    const u64 general_mask = ballot64(general);
+#pragma unroll 1
+    for (int k = 0;; ++k) {
+        const bool live = k + 2 < cl.cnt;
+        if (ballot64(live) == 0ull) break;
         ++L.tally[kTFanIters];
-        const uint32_t d = d_ahead;
-        const float wd = wd_ahead;
-        d_ahead = pxy[min(i + 2, kMaxPoly - 1)];
-        wd_ahead = piw[min(i + 2, kMaxPoly - 1)];
+        const uint32_t b = cl.p1, d = cl.p2;
+        const float wb = cl.w1, wd = cl.w2;
         short2v lo, ext;
         uint32_t wide;
-        const bool has = v && centre_box(a, b, d, win, lo, ext, wide);
-        const bool tame = ballot64(has && !(iw_in_range(wa) && iw_in_range(wb) && iw_in_range(wd))) == 0ull;
-        emit<FRAME>(L, small_count, has, lo, ext, wide, tame, a, b, d, wa, wb, wd, tri_ref, ctri_id, lane, vis, win, ballot64(has));
-        b = d;
-        wb = wd;
+        const bool has = live && centre_box(cl.p0, b, d, win, lo, ext, wide);
+        bool tame = true;
+        // the next piece's corners
+        cl.p1 = cl.p2; cl.p2 = cl.p3; cl.p3 = cl.p4;
+        cl.w1 = cl.w2; cl.w2 = cl.w3; cl.w3 = cl.w4;
+        if (general_mask != 0ull) {
+            tame = ballot64(has && !(iw_in_range(cl.w0) && iw_in_range(wb) && iw_in_range(wd))) == 0ull;
+            if (general) {
+                cl.p2 = pxy[min(k + 3, kMaxPoly - 1)];
+                cl.w2 = piw[min(k + 3, kMaxPoly - 1)];
+            }
+        }
+        emit<FRAME>(L, small_count, has, lo, ext, wide, tame, cl.p0, b, d, cl.w0, wb, wd, cl.ref, ctri_id, lane, vis, win, ballot64(has));
     }
 }
 
@@ -827,7 +971,6 @@ __global__ __launch_bounds__(NT, 4) void k_raster(const SceneDev* __restrict__ s
         // every block has been handed out: this is the last round (the same for all wavefronts:
         // next_block only moves during phase A)
         const bool last_round = *next_block >= nb_visit;
-        if (n_list == 0 && last_round) break;
         st_boxed += wave == 0 ? n_list : 0u;
 
         // Order the round's survivors near to far (counting sort on a logarithmic depth key, eight
@@ -921,7 +1064,29 @@ __global__ __launch_bounds__(NT, 4) void k_raster(const SceneDev* __restrict__ s
             }
         };
         pop_visible();
-        while (pop < n_list) {
+        // Each turn takes either 64 triangles from the clip ring or the next cluster, so that the clipper and the
+        // code that draws its pieces are inlined in one place (62 -> 40 KB of code; the instruction cache holds 64 KB
+        // for two compute units).
+        for (;;) {
+            const bool streaming = pop < n_list;
+            // The ring is looked at while streaming only when this wavefront's own view says 64 may be waiting: its
+            // view of the tail dates from its last push, its view of the head is never ahead of the head, so every
+            // push that leaves 64 or more waiting is followed by a look.  When the list is used up, whatever waits is
+            // taken: what the wavefront has queued goes into the depth buffer then, so that the depth tiles and the
+            // next round's tests see everything this round drew (triangles waiting for the clipper are the ones
+            // along the window's border: until they are drawn, no footprint that touches a border pixel can be
+            // found hidden).  After the last round this overlaps the clusters that slower wavefronts still draw;
+            // whatever they add to the ring, they take when they get here.
+            if (streaming ? clip_tail_seen - clip_head_seen >= 64u : occlusion || last_round) {
+                uint32_t clip_ref;
+                const int n = pop_clip(ring, streaming ? 64u : 1u, lane, clip_ref, clip_head_seen, clip_tail_seen);
+                if (n != 0) {
+                    wave_lds_sync();
+                    draw_clipped<FRAME>(L, clip_ref, n, small_count, sc, M, fq, win, lane, vis);
+                    continue;
+                }
+            }
+            if (!streaming) break;
             const uint32_t c = c_next;
             float x = nx_, y = ny_, z = nz_;
             uint32_t t0 = nt0, t1 = nt1;
@@ -997,42 +1162,15 @@ __global__ __launch_bounds__(NT, 4) void k_raster(const SceneDev* __restrict__ s
                      __float_as_uint(d.x), a.y, b.y, d.y, c * 128u + (uint32_t)(slot * 64 + lane), g_ctri_id, lane, vis,
                      win, fast_mask & has_mask);
             }
-            // ---- clip ring: full wavefronts only while streaming.  The ring is looked at only when this
-            // wavefront's own view says 64 may be waiting: its view of the tail dates from its last push, its
-            // view of the head is never ahead of the head, so every push that leaves 64 or more waiting is
-            // followed by a look.
-            while (clip_tail_seen - clip_head_seen >= 64u) {
-                uint32_t ref;
-                const int n = pop_clip(ring, 64u, lane, ref, clip_head_seen, clip_tail_seen);
-                if (n == 0) break;
-                wave_lds_sync();
-                drain_clip<FRAME>(L, ref, n, small_count, sc, M, fq, win, lane, vis);
-            }
         }
         TICK(5);
-        // After the last round a wavefront goes straight on to flush its queues, without waiting for
-        // the others: the flush (one pass of the clipper, mostly waiting for memory) then overlaps the
-        // clusters the slower wavefronts are still drawing.
-        if (last_round) break;
-        // What the wavefront has queued goes into the depth buffer now, so that the depth tiles and the
-        // next round's tests see everything this round drew.  Triangles waiting for the clipper are the
-        // ones along the window's border: until they are drawn, no footprint that touches a border
-        // pixel can be found hidden.
-        if (occlusion) {
-            for (;;) {
-                uint32_t ref;
-                const int n = pop_clip(ring, 1u, lane, ref, clip_head_seen, clip_tail_seen);
-                if (n == 0) break;
-                wave_lds_sync();
-                drain_clip<FRAME>(L, ref, n, small_count, sc, M, fq, win, lane, vis);
-            }
-        }
-        if (occlusion && small_count > 0) {
+        if ((occlusion || last_round) && small_count > 0) {
             wave_lds_sync();
             drain_small(L, small_count, lane, vis, win, g_ctri_id);
             wave_lds_sync();
             small_count = 0;
         }
+        if (last_round) break;
         __syncthreads();
         if (tid == 0) { *list_count = 0u; *pop_count = 0u; *reserved = 0u; }
         if (occlusion) {   // (more blocks are waiting, or the loop would have ended above)
@@ -1089,18 +1227,6 @@ __global__ __launch_bounds__(NT, 4) void k_raster(const SceneDev* __restrict__ s
         later_round = true;
         __syncthreads();
         TICK(6);
-    }
-    // whatever a wavefront that is still drawing adds later, that wavefront takes when it gets here
-    for (;;) {
-        uint32_t ref;
-        const int n = pop_clip(ring, 1u, lane, ref, clip_head_seen, clip_tail_seen);
-        if (n == 0) break;
-        wave_lds_sync();
-        drain_clip<FRAME>(L, ref, n, small_count, sc, M, fq, win, lane, vis);
-    }
-    if (small_count > 0) {
-        wave_lds_sync();
-        drain_small(L, small_count, lane, vis, win, g_ctri_id);
     }
     TICK(7);
     if (stats) __syncthreads();   // the record below reuses the survivor list: every wavefront must be done with it

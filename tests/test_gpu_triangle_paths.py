@@ -58,3 +58,28 @@ def test_exponent_range_and_slivers(H, W, size):
         Ms.append(M)
     t = _check(v, idx, np.stack(Ms), H, W)
     assert (t != NOHIT).mean() > 0.02
+
+
+@pytest.mark.parametrize("H,W,B", [(64, 64, 3), (128, 128, 2), (72, 104, 40), (64, 64, 600)])
+@pytest.mark.parametrize("grid", [True, False])
+def test_clipped_triangles(grid, H, W, B):
+    """Triangles that cross one, two and more planes in every combination; on the grid many corners lie exactly on a
+    plane, and pieces and whole triangles repeat (depth ties).  Both windings, few and many work-groups."""
+    rng = np.random.default_rng(17)
+    n = 1500
+    if grid:
+        v = np.stack([rng.choice([-1.5, -1.0, -0.5, 0.0, 0.25, 1.0, 2.0], (n, 3)), rng.choice([-2.0, -1.0, 0.0, 0.5, 1.0, 1.25], (n, 3)),
+                      rng.choice([-0.25, 0.0, 0.25, 0.5, 1.0, 1.5], (n, 3))], 2)
+    else:
+        v = np.stack([rng.uniform(-1.6, 1.6, (n, 3)), rng.uniform(-1.6, 1.6, (n, 3)), rng.uniform(-0.4, 1.4, (n, 3))], 2)
+        far = rng.random((n, 3)) < 0.1
+        v[far] *= 10.0 ** rng.uniform(1, 6, (int(far.sum()), 1))
+    v = v.reshape(-1, 3).astype(np.float32)
+    idx = np.arange(3 * n, dtype=np.uint32).reshape(n, 3)
+    M = np.zeros((B, 4, 4), np.float32)
+    M[:, 0, 0], M[:, 1, 1], M[:, 2, 2], M[:, 3, 3] = 1, 1, 1, 1
+    M[1::2, 3, 2], M[1::2, 2, 3] = 1.0, -0.25            # perspective: w = z + 1, near and far cut elsewhere
+    M[2::3, 0, 0] = -1
+    M[3:, 0, 3] = rng.uniform(-0.4, 0.4, max(B - 3, 0))
+    t = _check(v, idx, M, H, W)
+    assert (t != NOHIT).mean() > 0.3
