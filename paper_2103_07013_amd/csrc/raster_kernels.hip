@@ -265,6 +265,10 @@ __device__ __forceinline__ bool box_outside_frustum(const float4* planes, float 
     const float eps = 1.52587890625e-05f;   // 2^-16
     float ax = fmaxf(fabsf(lx), fabsf(hx)), ay = fmaxf(fabsf(ly), fabsf(hy)), az = fmaxf(fabsf(lz), fabsf(hz));
     bool outside = false;
+    // (one base register and constant offsets; twelve known addresses would each be kept, and spilled, over the kernel)
+    int base = 0;
+    asm volatile("" : "+v"(base));
+    planes += base;
 #pragma unroll
     for (int k = 0; k < 6; ++k) {
         const float4 p = planes[2 * k], q = planes[2 * k + 1];
@@ -275,6 +279,7 @@ __device__ __forceinline__ bool box_outside_frustum(const float4* planes, float 
     return outside;
 }
 
+constexpr uint32_t kNoCluster = 0xFFFFFFFFu;
 constexpr uint32_t kNoPixel = 0xFFFFFFFFu;   // box_footprint: the box cannot cover any pixel centre
 
 // Screen footprint and nearest possible depth of a box, for the occlusion test made when the
@@ -1021,22 +1026,34 @@ __global__ __launch_bounds__(NT, 4) void k_raster(const SceneDev* __restrict__ s
             TICK(3);
         }
 
-        // pop one ahead so that the next cluster's words are in flight while this one is processed;
-        // a cluster whose footprint pixels all hold nearer depths by now cannot win anywhere and is
-        // dropped here (one lane per footprint pixel)
-        uint32_t pop = 0;
+        // Clusters come off the list ahead of their use, so that fewer LDS round trips wait for one another: the next
+        // place is drawn from the counter while a record is tested, and its record is read while the cluster that
+        // passed is fetched and the one before it is drawn (three trips in a row took 400 cycles per record).  A
+        // cluster whose footprint pixels all hold nearer depths by now cannot win anywhere and is dropped here (one
+        // lane per footprint pixel); the words of the first that may win are fetched while the one before it is
+        // processed.
+        uint32_t drawn = 0;      // lane 0: the place drawn last, in flight
+        auto draw_place = [&]() {
+            if (lane == 0) drawn = atomicAdd(pop_count, 1u);
+        };
+        draw_place();
+        uint32_t pop = __builtin_amdgcn_readfirstlane(drawn);      // place of the record in flight
+        auto read_record = [&]() -> u64 {
+            const uint32_t at = min(pop, (uint32_t)list_cap - 1u);      // (past the end: any record, it is not looked at)
+            return list[(by_depth && !FRAME) ? (uint32_t)perm[at] : at];
+        };
+        u64 record = read_record();
         float nx_ = 0, ny_ = 0, nz_ = 0;
-        uint32_t nt0 = 0, nt1 = 0, c_next = 0;
+        uint32_t nt0 = 0, nt1 = 0, c_next = kNoCluster;
         auto pop_visible = [&]() {
-            for (;;) {
-                if (lane == 0) pop = atomicAdd(pop_count, 1u);
-                pop = __builtin_amdgcn_readfirstlane(pop);
-                if (pop >= n_list) return;
-                const u64 e = list[(by_depth && !FRAME) ? (uint32_t)perm[pop] : pop];
-                const uint32_t lo32 = __builtin_amdgcn_readfirstlane((uint32_t)e);
-                const uint32_t hi32 = __builtin_amdgcn_readfirstlane((uint32_t)(e >> 32));
-                c_next = lo32 & 0x007FFFFFu;
+            c_next = kNoCluster;
+            while (pop < n_list) {
+                const uint32_t lo32 = __builtin_amdgcn_readfirstlane((uint32_t)record);
+                const uint32_t hi32 = __builtin_amdgcn_readfirstlane((uint32_t)(record >> 32));
+                draw_place();
+                const uint32_t c = lo32 & 0x007FFFFFu;
                 const uint32_t foot = (uint32_t)((((u64)hi32 << 32) | lo32) >> 23);
+                bool shows = true;
                 if (foot & 1u) {
                     const int fx = (int)((foot >> 1) & 63u), fy = (int)((foot >> 7) & 63u);
                     const int bw = (int)((foot >> 13) & 31u), bh = (int)((foot >> 18) & 31u);
@@ -1048,18 +1065,21 @@ __global__ __launch_bounds__(NT, 4) void k_raster(const SceneDev* __restrict__ s
                     const int qx = min(lane & ((1 << cols_log2) - 1), bw), qy = lane >> cols_log2;
                     const int rows_per_pass = 64 >> cols_log2;
                     const uint32_t* const corner = vis_hi + 2 * (__mul24(fy, win.pitch) + fx);
-                    bool shows = false;
+                    shows = false;
                     for (int row0 = 0; row0 <= bh && !shows; row0 += rows_per_pass) {
                         ++tally[kTPopPasses];
                         const uint32_t d = corner[2 * (__mul24(min(row0 + qy, bh), win.pitch) + qx)];
                         shows = ballot64(d >= wbits) != 0ull;
                     }
-                    if (!shows) { ++st_hidden; continue; }
                 }
-                const BPS_GLOBAL float* cv = g_cverts + (size_t)c_next * 192;
+                pop = __builtin_amdgcn_readfirstlane(drawn);
+                record = read_record();
+                if (!shows) { ++st_hidden; continue; }
+                const BPS_GLOBAL float* cv = g_cverts + (size_t)c * 192;
                 nx_ = cv[lane]; ny_ = cv[64 + lane]; nz_ = cv[128 + lane];
-                const BPS_GLOBAL uint32_t* ct = g_ctris + (size_t)c_next * 128;
+                const BPS_GLOBAL uint32_t* ct = g_ctris + (size_t)c * 128;
                 nt0 = ct[lane]; nt1 = ct[64 + lane];
+                c_next = c;
                 return;
             }
         };
@@ -1068,7 +1088,7 @@ __global__ __launch_bounds__(NT, 4) void k_raster(const SceneDev* __restrict__ s
         // code that draws its pieces are inlined in one place (62 -> 40 KB of code; the instruction cache holds 64 KB
         // for two compute units).
         for (;;) {
-            const bool streaming = pop < n_list;
+            const bool streaming = c_next != kNoCluster;
             // The ring is looked at while streaming only when this wavefront's own view says 64 may be waiting: its
             // view of the tail dates from its last push, its view of the head is never ahead of the head, so every
             // push that leaves 64 or more waiting is followed by a look.  When the list is used up, whatever waits is
