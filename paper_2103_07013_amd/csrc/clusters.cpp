@@ -74,6 +74,82 @@ void order_for_blocks(ClusterSet& cs) {
     cs = std::move(out);
 }
 
+// Triangles in the order of their 30-bit codes, equal codes by triangle: three counting passes of 10 bits.
+std::vector<uint32_t> sorted_by_code(const std::vector<uint32_t>& code) {
+    const size_t n = code.size();
+    std::vector<uint32_t> count(3 * 1024, 0), a(n), b(n);
+    for (size_t i = 0; i < n; ++i)
+        for (int pass = 0; pass < 3; ++pass) ++count[1024 * pass + ((code[i] >> (10 * pass)) & 1023u)];
+    for (int pass = 0; pass < 3; ++pass) {
+        uint32_t at = 0;
+        for (uint32_t d = 0; d < 1024; ++d) {
+            const uint32_t c = count[1024 * pass + d];
+            count[1024 * pass + d] = at;
+            at += c;
+        }
+    }
+    for (size_t i = 0; i < n; ++i) a[count[code[i] & 1023u]++] = (uint32_t)i;
+    for (size_t i = 0; i < n; ++i) b[count[1024 + ((code[a[i]] >> 10) & 1023u)]++] = a[i];
+    for (size_t i = 0; i < n; ++i) a[count[2048 + (code[b[i]] >> 20)]++] = b[i];
+    return a;
+}
+
+// The candidates of a growing cluster, in one list per number of vertices they would bring in (0 to 3), kept up to date
+// as vertices join.  A list holds keys: distance from the seed above, order of listing below, so that the smallest key
+// is the nearest candidate and the first listed of equals.  Choosing the cheapest reads the first list that is not
+// empty, a dozen keys, instead of nine coordinates and three marks for each of some eighty candidates.
+struct Candidates {
+    static constexpr uint32_t kNone = 0xFFFFFFFFu;
+    std::vector<uint64_t> keys[4];
+    std::vector<uint32_t> tri, at;      // by order of listing: the triangle, its place in its list
+    std::vector<uint8_t> fresh;         //                      and which list that is
+    size_t live = 0;
+
+    void clear() {
+        for (auto& k : keys) k.clear();
+        tri.clear();
+        at.clear();
+        fresh.clear();
+        live = 0;
+    }
+    void insert(uint32_t seq, uint32_t f, uint64_t key) {
+        fresh[seq] = (uint8_t)f;
+        at[seq] = (uint32_t)keys[f].size();
+        keys[f].push_back(key);
+    }
+    uint64_t remove(uint32_t seq) {
+        std::vector<uint64_t>& k = keys[fresh[seq]];
+        const uint64_t key = k[at[seq]];
+        k[at[seq]] = k.back();
+        at[(uint32_t)k.back()] = at[seq];
+        k.pop_back();
+        return key;
+    }
+    uint32_t list(uint32_t t, uint32_t f, float distance) {
+        uint32_t bits;
+        std::memcpy(&bits, &distance, 4);      // never negative or NaN: its bits order like its value
+        const uint32_t seq = (uint32_t)tri.size();
+        tri.push_back(t);
+        at.push_back(0u);
+        fresh.push_back(0);
+        insert(seq, f, ((uint64_t)bits << 32) | seq);
+        ++live;
+        return seq;
+    }
+    void move(uint32_t seq, uint32_t f) {
+        if (fresh[seq] != f) insert(seq, f, remove(seq));
+    }
+    void drop(uint32_t seq) {
+        remove(seq);
+        --live;
+    }
+    uint32_t cheapest() const {
+        for (const auto& k : keys)
+            if (!k.empty()) return (uint32_t)*std::min_element(k.begin(), k.end());
+        return kNone;
+    }
+};
+
 }  // namespace
 
 ClusterSet build_clusters(const float* vertices, uint32_t V, const uint32_t* indices, uint32_t T) {
@@ -89,18 +165,20 @@ ClusterSet build_clusters(const float* vertices, uint32_t V, const uint32_t* ind
         }
     float ext = std::max({hi[0] - lo[0], hi[1] - lo[1], hi[2] - lo[2], 1e-20f});
     float scale = 1023.0f / ext;
-    std::vector<uint64_t> keyed(T);
+    std::vector<uint32_t> codes(T);
+    std::vector<float> centroid((size_t)T * 3);
     for (uint32_t t = 0; t < T; ++t) {
         uint32_t code = 0;
         for (int a = 0; a < 3; ++a) {
             float c = (vertices[3 * (size_t)indices[3 * (size_t)t + 0] + a] + vertices[3 * (size_t)indices[3 * (size_t)t + 1] + a] +
                        vertices[3 * (size_t)indices[3 * (size_t)t + 2] + a]) * (1.0f / 3.0f);
+            centroid[3 * (size_t)t + a] = c;
             uint32_t q = (uint32_t)std::min(1023.0f, std::max(0.0f, (c - lo[a]) * scale));
             code |= spread10(q) << a;
         }
-        keyed[t] = ((uint64_t)code << 32) | t;
+        codes[t] = code;
     }
-    std::sort(keyed.begin(), keyed.end());
+    const std::vector<uint32_t> in_order = sorted_by_code(codes);
 
     // ---- region growing
     // A cluster starts at the first unassigned triangle of the spatial order and grows by the
@@ -124,14 +202,15 @@ ClusterSet build_clusters(const float* vertices, uint32_t V, const uint32_t* ind
     std::vector<uint8_t> local(V, 0);
     std::vector<uint8_t> taken(T, 0);                // by triangle
     std::vector<uint32_t> listed(T, 0xFFFFFFFFu);    // cluster whose candidate list holds the triangle
-    std::vector<uint32_t> cand;
+    std::vector<uint32_t> place(T);                  // its number there
+    Candidates cand;
     out.verts.reserve((size_t)(T / 90 + 1) * 192);
     out.tris.reserve((size_t)(T / 90 + 1) * 128);
     out.tri_id.reserve((size_t)(T / 90 + 1) * 128);
 
     uint32_t head = 0;  // first position of the spatial order not yet assigned
     while (true) {
-        while (head < T && taken[(uint32_t)keyed[head]]) ++head;
+        while (head < T && taken[in_order[head]]) ++head;
         if (head >= T) break;
         const uint32_t c = out.count++;
         size_t vbase = out.verts.size(), tbase = out.tris.size();
@@ -152,11 +231,7 @@ ClusterSet build_clusters(const float* vertices, uint32_t V, const uint32_t* ind
         float seed_c[3];
         auto growth_of = [&](uint32_t tt) {
             float g = 0.0f;
-            for (int a = 0; a < 3; ++a) {
-                float m = 0.0f;
-                for (int k = 0; k < 3; ++k) m += vertices[3 * (size_t)indices[3 * (size_t)tt + k] + a];
-                g = std::max(g, std::fabs(m * (1.0f / 3.0f) - seed_c[a]));
-            }
+            for (int a = 0; a < 3; ++a) g = std::max(g, std::fabs(centroid[3 * (size_t)tt + a] - seed_c[a]));
             return g;
         };
         auto add = [&](uint32_t tt) {
@@ -176,14 +251,25 @@ ClusterSet build_clusters(const float* vertices, uint32_t V, const uint32_t* ind
                     ++nv;
                     // triangles once taken stay taken: skip the taken head of the vertex's list for good
                     uint32_t& from = vfirst[vi];
-                    while (from < vstart[vi + 1] && taken[vtris[from]]) ++from;
-                    for (uint32_t q = from; q < vstart[vi + 1] && cand.size() < kMaxCandidates; ++q) {
+                    const uint32_t end = vstart[vi + 1];
+                    while (from < end && taken[vtris[from]]) ++from;
+                    // Candidates at this vertex now need one vertex fewer; the other triangles here become candidates
+                    // as long as there is room.  A list much longer than that is not walked to its end: every
+                    // candidate's cost is worked out anew instead.
+                    const bool walk = end - from <= 4 * kMaxCandidates;
+                    for (uint32_t q = from; q < end && (walk || cand.live < kMaxCandidates); ++q) {
                         const uint32_t o = vtris[q];
-                        if (!taken[o] && listed[o] != c) {
+                        if (taken[o] || (q > from && vtris[q - 1] == o)) continue;      // (a vertex may occur twice in a triangle)
+                        if (listed[o] == c) {
+                            if (walk) cand.move(place[o], cand.fresh[place[o]] - 1u);
+                        } else if (cand.live < kMaxCandidates) {
                             listed[o] = c;
-                            cand.push_back(o);
+                            place[o] = cand.list(o, fresh_of(o), growth_of(o));
                         }
                     }
+                    if (!walk)
+                        for (uint32_t q = 0; q < (uint32_t)cand.tri.size(); ++q)
+                            if (!taken[cand.tri[q]]) cand.move(q, fresh_of(cand.tri[q]));
                 }
                 li[k] = local[vi];
             }
@@ -192,35 +278,21 @@ ClusterSet build_clusters(const float* vertices, uint32_t V, const uint32_t* ind
             ++nt;
         };
 
-        for (int a = 0; a < 3; ++a) {
-            float m = 0.0f;
-            for (int k = 0; k < 3; ++k) m += vertices[3 * (size_t)indices[3 * (size_t)(uint32_t)keyed[head] + k] + a];
-            seed_c[a] = m * (1.0f / 3.0f);
-        }
-        add((uint32_t)keyed[head]);     // the seed keeps the clusters in spatial order
+        for (int a = 0; a < 3; ++a) seed_c[a] = centroid[3 * (size_t)in_order[head] + a];
+        add(in_order[head]);     // the seed keeps the clusters in spatial order
         while (nt < kClusterTris) {
             uint32_t best = 0xFFFFFFFFu, best_new = 4;
-            float best_grow = INFINITY;
-            size_t keep = 0;
-            for (size_t q = 0; q < cand.size(); ++q) {
-                const uint32_t tt = cand[q];
-                if (taken[tt]) continue;
-                cand[keep++] = tt;          // drop assigned triangles from the list as we go
-                const uint32_t fresh = fresh_of(tt);
-                if (fresh > best_new) continue;
-                const float grow = growth_of(tt);
-                if (fresh < best_new || grow < best_grow) {
-                    best_new = fresh;
-                    best_grow = grow;
-                    best = tt;
-                }
+            const uint32_t cheapest = cand.cheapest();
+            const bool connected = cheapest != Candidates::kNone;
+            if (connected) {
+                best = cand.tri[cheapest];
+                best_new = cand.fresh[cheapest];
             }
-            cand.resize(keep);
             if (best == 0xFFFFFFFFu) {
                 // nothing connected is left: look at the next triangles of the spatial order
                 uint32_t seen = 0;
                 for (uint32_t p = head; p < T && seen < kWindow; ++p) {
-                    const uint32_t tt = (uint32_t)keyed[p];
+                    const uint32_t tt = in_order[p];
                     if (taken[tt]) continue;
                     ++seen;
                     const uint32_t fresh = fresh_of(tt);
@@ -233,6 +305,7 @@ ClusterSet build_clusters(const float* vertices, uint32_t V, const uint32_t* ind
             }
             if (best == 0xFFFFFFFFu || nv + best_new > kClusterVerts) break;
             add(best);
+            if (connected) cand.drop(cheapest);
         }
         for (uint32_t l = nv; l < kClusterVerts; ++l)
             for (int a = 0; a < 3; ++a) out.verts[vbase + 64 * a + l] = out.verts[vbase + 64 * a];
