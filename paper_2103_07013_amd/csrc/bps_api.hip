@@ -3,6 +3,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -36,8 +37,10 @@ static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
 constexpr int kMaxDevices = 64;
 std::mutex g_scratch_mu;
 void* g_scratch_ptr[kMaxDevices] = {};
-// what the array on each device holds: the renderer and plan whose work items were unpacked last
-const void* g_scratch_owner[kMaxDevices] = {};
+// Launch plans are numbered through the whole process: a number is one plan of one renderer for good, also after
+// that renderer is gone and another one lives at its address.
+std::atomic<uint64_t> g_plans{0};
+// the plan whose work items the array on each device holds (0 = none that is whole)
 uint64_t g_scratch_plan[kMaxDevices] = {};
 
 // Device memory of one scene: a single allocation holding every array, so that loading is one
@@ -126,7 +129,7 @@ struct bps_renderer {
     int plan_splits = 0;
     int plan_windows = 0;
     bool fixed_layout = false;        // the raster kernel's instances with a constant LDS layout fit this device
-    uint64_t plan_version = 0;        // counts the plans made; ring slots remember which one they hold
+    uint64_t plan_version = 0;        // number of the current plan (0 = none yet); ring slots remember which one they hold
     std::vector<bps::WorkItem> plan_items;
     std::vector<bps_scene> call_slots;    // table slots of the current request's scene handles (keeps its capacity)
     uint64_t last_splits = 0, last_groups = 0;
@@ -307,7 +310,7 @@ void make_plan(bps_renderer* r, const bps_scene* scene_ids, uint32_t B, const Cu
         r->plan_ids.assign(scene_ids, scene_ids + B);
         r->plan_splits = S;
         r->plan_windows = windows;
-        ++r->plan_version;
+        r->plan_version = ++g_plans;
     }
 }
 
@@ -1090,7 +1093,8 @@ bps_status bps_render_static(bps_renderer* r, const bps_scene* scene_ids, const 
     uint32_t* d_cost = reinterpret_cast<uint32_t*>(d_ordered + kStaticMaxItems);
     {   // the items reach the device as kernel arguments, unless the array still holds this very plan
         std::lock_guard<std::mutex> g(g_scratch_mu);
-        if (g_scratch_owner[r->device] != r || g_scratch_plan[r->device] != r->plan_version) {
+        if (g_scratch_plan[r->device] != r->plan_version) {
+            g_scratch_plan[r->device] = 0;      // until all of it is on its way
             bps::PackedItems packed;
             for (size_t first = 0; first < n_items; first += bps::kPackedItemsPerLaunch) {
                 const uint32_t count = (uint32_t)std::min<size_t>(bps::kPackedItemsPerLaunch, n_items - first);
@@ -1101,7 +1105,6 @@ bps_status bps_render_static(bps_renderer* r, const bps_scene* scene_ids, const 
                 bps::launch_unpack_items(stream, packed, (uint32_t)first, count, d_items);
                 BPS_HIP(r, hipGetLastError());
             }
-            g_scratch_owner[r->device] = r;
             g_scratch_plan[r->device] = r->plan_version;
         }
     }

@@ -1,0 +1,77 @@
+"""The host side's launch plans, without a GPU: libbps.so runs on a stand-in for the HIP runtime (fake_hip.c), which
+tells for every raster launch what the kernel would find in its work-item array."""
+import os
+import re
+import subprocess
+import sys
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+PRELUDE = """
+import ctypes, sys
+import numpy as np
+fake = ctypes.CDLL(sys.argv[1], mode=ctypes.RTLD_GLOBAL)      # found before the real runtime
+fake.fake_log.restype = ctypes.c_char_p
+import paper_2103_07013_amd as bps
+import synth
+lib = bps.load_library()
+small = synth.make_multiroom_scene(10_000, seed=1)
+large = synth.make_multiroom_scene(100_000, seed=2)
+pool = np.zeros(1 << 16, np.float32)      # "device" matrices
+fake.fake_device_range(ctypes.c_void_p(pool.ctypes.data), ctypes.c_size_t(pool.nbytes))
+out = np.zeros(8, np.float32)             # never written: no kernel draws
+
+def load(r, s):
+    return bps.bps_load_scene(r, s.vertices, s.indices)
+
+def static(r, h, B, offset=0):
+    fake.fake_clear_log()
+    ids = np.full(B, h, np.int32)
+    assert lib.bps_render_static(r, ids.ctypes.data, pool[offset:].ctypes.data, B, out.ctypes.data, None, None) == 0, bps.bps_last_error(r)
+    print(fake.fake_log().decode(), end="")
+"""
+
+
+@pytest.fixture(scope="module")
+def fake(tmp_path_factory):
+    so = str(tmp_path_factory.mktemp("fake") / "fake_hip.so")
+    subprocess.run(["gcc", "-O1", "-shared", "-fPIC", "-I/opt/rocm/include", os.path.join(ROOT, "tests", "fake_hip.c"), "-o", so],
+                   check=True)
+    return so
+
+
+def _launches(fake, code):
+    """The raster launches of the calls in `code`, as dicts."""
+    p = subprocess.run([sys.executable, "-c", PRELUDE + code, fake], cwd=ROOT, capture_output=True, text=True, timeout=300)
+    assert p.returncode == 0, p.stdout + p.stderr
+    return [{k: int(v, 0) for k, v in re.findall(r"(\w+)=(\w+)", line)} for line in p.stdout.splitlines() if line.startswith("k_raster")]
+
+
+@pytest.mark.parametrize("first,second", [("small", "large"), ("large", "small")])
+def test_static_plan_of_a_renderer_that_is_gone(fake, first, second):
+    """300 environments are drawn whole in the small scene and as halves in the large one.  The second renderer's
+    handle may well be the address the first one had; its items must be its own all the same."""
+    got = _launches(fake, f"""
+for s in ({first}, {second}, {first}):
+    r = bps.bps_create(max_batch=300)
+    h = load(r, s)
+    static(r, h, 300)
+    static(r, h, 300)      # the same plan again
+    bps.bps_destroy(r)
+""")
+    tiles = {"small": 1, "large": 2}
+    assert [g["tiles"] for g in got] == [tiles[s] for s in (first, first, second, second, first, first)]
+    assert all(g["wrong"] == 0 and g["envs"] == 300 and g["groups"] == 300 * g["tiles"] for g in got)
+
+
+def test_static_plans_of_renderers_in_turn(fake):
+    got = _launches(fake, """
+a, b = bps.bps_create(max_batch=300), bps.bps_create(max_batch=300)
+ha, hb = load(a, small), load(b, large)
+for r, h, B in ((a, ha, 300), (b, hb, 300), (a, ha, 300), (b, hb, 17), (a, ha, 300), (b, hb, 17), (b, hb, 300)):
+    static(r, h, B)
+""")
+    assert [g["envs"] for g in got] == [300, 300, 300, 17, 300, 17, 300]
+    assert all(g["wrong"] == 0 and g["groups"] == g["envs"] * g["tiles"] for g in got)

@@ -88,3 +88,25 @@ def test_static_entry_point_rejects_what_it_cannot_do():
         with pytest.raises(bps.BpsError) as e:
             bps.bps_render_static(r.handle, np.full(4100, h, np.int32), big_vp, big_d)
         assert e.value.status == -1 and "static scratch" in str(e.value)
+
+
+@pytest.mark.parametrize("first", [0, 1])
+def test_static_entry_point_of_renderers_one_after_the_other(first):
+    """A renderer that is made when another one is gone, for a scene whose frames are cut differently: its first
+    plan is its own (tests/test_launch_plans.py checks the items themselves)."""
+    import torch
+    import paper_2103_07013_amd as bps
+    B = 300
+    scenes = [synth.make_multiroom_scene(T, seed=40 + T % 7) for T in (10_000, 100_000)]
+    for s in (scenes[first], scenes[1 - first], scenes[first]):
+        vp = torch.from_numpy(synth.make_cameras(s, B, seed=8)[0]).cuda()
+        with bps.Renderer(max_batch=B) as r:
+            ids = np.full(B, r.load_scene(s.vertices, s.indices), np.int32)
+            d1 = torch.full((B, 64, 64), -1.0, dtype=torch.float32, device="cuda")
+            i1 = torch.full((B, 64, 64), -2, dtype=torch.int32, device="cuda")
+            bps.bps_render_static(r.handle, ids, vp, d1, out_tri_id=i1)
+            torch.cuda.synchronize()
+            d0, i0 = torch.empty_like(d1), torch.empty_like(i1)
+            bps.bps_render(r.handle, ids, vp, d0, out_tri_id=i0)
+            torch.cuda.synchronize()
+            assert torch.equal(i0, i1) and torch.equal(d0, d1)
