@@ -166,15 +166,19 @@ bps_status bps_render(bps_renderer *r, const bps_scene *scene_ids, const float *
 /* bps_render for callers that cannot allocate: code under HIP graph capture, tight serving loops,
  * harnesses that forbid hipMalloc.  It calls no hipMalloc / hipFree / hipHostMalloc and copies nothing
  * from host memory: the work items travel as kernel arguments, and the launch plan (work items, work
- * items in launch order, cost words) lives in a file-scope __device__ array of the library, 576 KiB on every GPU the
- * library runs on, held until the process ends.  Same frames as bps_render, bit for bit.
+ * items in launch order, cost words) lives in a file-scope __device__ array of the library, 1152 KiB on every GPU the
+ * library runs on (half of it for calls captured into graphs), held until the process ends.  Same frames as bps_render, bit for bit.
  * Limits: depth renderers without supersampling, forced splits or diagnostics; view_proj must be
  * DEVICE memory; B x (64x64-pixel tiles per frame) <= 16384 work-groups (e.g. 16384 environments at
  * 64x64, 4096 at 128x128), otherwise BPS_ERR_INVALID_ARG / BPS_ERR_UNSUPPORTED and nothing is enqueued.
  * Small batches are cut into smaller windows as in bps_render.  scene_ids is host memory as in bps_render.
  * Every call on a GPU, from any renderer and stream, uses that GPU's one array: calls on one stream
  * are ordered and safe; calls that overlap on one GPU (different streams or renderers) race.  Nothing
- * in the array needs clearing: each call overwrites what it reads. */
+ * in the array needs clearing: a call finds its own plan there or overwrites it.
+ * A call on a stream that is being captured is recorded whole (work items included) and takes the array's other half,
+ * so that replays and calls made at once do not disturb each other; replays of different graphs must not overlap.
+ * The scenes of a captured call have to be complete (bps_scene_ready) before it, and stay loaded as long as the graph
+ * is replayed: replays are not requests that bps_unload_scene waits for. */
 bps_status bps_render_static(bps_renderer *r, const bps_scene *scene_ids, const float *view_proj, uint32_t B,
                              float *out_depth, uint32_t *out_tri_id, void *stream);
 

@@ -28,10 +28,11 @@ constexpr size_t kMaxProfiled = 4096;   // profiled requests remembered between 
 thread_local std::string g_create_error = "";
 
 // ---- scratch of bps_render_static, the entry point that allocates nothing ------------------------
-// Work items as staged, work items in launch order, and one cost word per item.
+// Work items as staged, work items in launch order, and one cost word per item; once for calls that run at once and
+// once for calls that are being captured into a graph, whose replays would overwrite what the former rely on.
 constexpr uint32_t kStaticMaxItems = bps::kMaxPlannedItems;
 constexpr size_t kStaticScratchBytes = (size_t)kStaticMaxItems * (2 * sizeof(bps::WorkItem) + sizeof(uint32_t));
-static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
+static __device__ __align__(256) unsigned char scratch[2 * kStaticScratchBytes];
 // In host code the array's name is only a stand-in: its address on each device is looked up once
 // (bps_create, with that device current) and used from then on.
 constexpr int kMaxDevices = 64;
@@ -40,7 +41,7 @@ void* g_scratch_ptr[kMaxDevices] = {};
 // Launch plans are numbered through the whole process: a number is one plan of one renderer for good, also after
 // that renderer is gone and another one lives at its address.
 std::atomic<uint64_t> g_plans{0};
-// the plan whose work items the array on each device holds (0 = none that is whole)
+// the plan whose work items the first half of the array on each device holds (0 = none that is whole)
 uint64_t g_scratch_plan[kMaxDevices] = {};
 
 // Device memory of one scene: a single allocation holding every array, so that loading is one
@@ -1080,21 +1081,29 @@ bps_status bps_render_static(bps_renderer* r, const bps_scene* scene_ids, const 
     cut.S = 1;                          // (no merge buffer here)
     make_plan(r, scene_ids, B, cut);    // (host containers only; they keep their capacity between calls)
     n_items = r->plan_items.size();     // (small batches are cut finer, never past the number the device holds at once)
-    // a ring slot is taken for its completion event only: scene retirement tracks requests through them
-    RingSlot& slot = r->ring[r->ring_next];
-    r->ring_next = (r->ring_next + 1) % kRing;
-    if (slot.pending) {
-        BPS_HIP(r, hipEventSynchronize(slot.done));
-        slot.pending = false;
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    const bool capturing = hipStreamIsCapturing(stream, &capture) == hipSuccess && capture == hipStreamCaptureStatusActive;
+    (void)hipGetLastError();
+    // A ring slot is taken for its completion event only: scene retirement tracks requests through them.  A captured
+    // call is no request (its replays are the caller's, and so is keeping the scenes loaded for them).
+    RingSlot* slot = nullptr;
+    if (!capturing) {
+        slot = &r->ring[r->ring_next];
+        r->ring_next = (r->ring_next + 1) % kRing;
+        if (slot->pending) {
+            BPS_HIP(r, hipEventSynchronize(slot->done));
+            slot->pending = false;
+        }
     }
-    // layout of the static array: items as planned, items in launch order, cost words
-    bps::WorkItem* d_items = reinterpret_cast<bps::WorkItem*>(r->static_scratch);
+    // layout of each half of the static array: items as planned, items in launch order, cost words
+    bps::WorkItem* d_items = reinterpret_cast<bps::WorkItem*>(r->static_scratch + (capturing ? kStaticScratchBytes : 0));
     bps::WorkItem* d_ordered = d_items + kStaticMaxItems;
     uint32_t* d_cost = reinterpret_cast<uint32_t*>(d_ordered + kStaticMaxItems);
-    {   // the items reach the device as kernel arguments, unless the array still holds this very plan
+    {   // the items reach the device as kernel arguments, unless the array still holds this very plan (every replay
+        // of a graph brings its own: what the second half holds depends on the order of replays)
         std::lock_guard<std::mutex> g(g_scratch_mu);
-        if (g_scratch_plan[r->device] != r->plan_version) {
-            g_scratch_plan[r->device] = 0;      // until all of it is on its way
+        if (capturing || g_scratch_plan[r->device] != r->plan_version) {
+            if (!capturing) g_scratch_plan[r->device] = 0;      // until all of it is on its way
             bps::PackedItems packed;
             for (size_t first = 0; first < n_items; first += bps::kPackedItemsPerLaunch) {
                 const uint32_t count = (uint32_t)std::min<size_t>(bps::kPackedItemsPerLaunch, n_items - first);
@@ -1105,7 +1114,7 @@ bps_status bps_render_static(bps_renderer* r, const bps_scene* scene_ids, const 
                 bps::launch_unpack_items(stream, packed, (uint32_t)first, count, d_items);
                 BPS_HIP(r, hipGetLastError());
             }
-            g_scratch_plan[r->device] = r->plan_version;
+            if (!capturing) g_scratch_plan[r->device] = r->plan_version;
         }
     }
     const bps::FrameParams fp = frame_params(r, cut);
@@ -1117,9 +1126,11 @@ bps_status bps_render_static(bps_renderer* r, const bps_scene* scene_ids, const 
     bps::launch_raster(r->threads, dim3((unsigned)n_items), r->lds, stream, r->d_scenes, planned ? d_ordered : d_items, view_proj,
                        fp, r->fixed_layout, nullptr, out_depth, out_tri_id, nullptr);
     BPS_HIP(r, hipGetLastError());
-    BPS_HIP(r, hipEventRecord(slot.done, stream));
-    slot.pending = true;
-    slot.seq = seq;
+    if (slot) {
+        BPS_HIP(r, hipEventRecord(slot->done, stream));
+        slot->pending = true;
+        slot->seq = seq;
+    }
     r->last_splits = 1;
     r->last_groups = (uint64_t)n_items;
     return BPS_OK;

@@ -34,6 +34,19 @@ def static(r, h, B, offset=0):
 """
 
 
+CAPTURE = """
+def capture(r, h, B):
+    fake.fake_capture(1)
+    static(r, h, B)
+    fake.fake_capture(0)
+
+def replay():
+    fake.fake_clear_log()
+    fake.fake_replay()
+    print(fake.fake_log().decode(), end="")
+"""
+
+
 @pytest.fixture(scope="module")
 def fake(tmp_path_factory):
     so = str(tmp_path_factory.mktemp("fake") / "fake_hip.so")
@@ -74,4 +87,26 @@ for r, h, B in ((a, ha, 300), (b, hb, 300), (a, ha, 300), (b, hb, 17), (a, ha, 3
     static(r, h, B)
 """)
     assert [g["envs"] for g in got] == [300, 300, 300, 17, 300, 17, 300]
+    assert all(g["wrong"] == 0 and g["groups"] == g["envs"] * g["tiles"] for g in got)
+
+
+def test_static_plans_of_captured_calls(fake):
+    """A captured call writes nothing when it is made and everything on each replay."""
+    got = _launches(fake, CAPTURE + """
+r = bps.bps_create(max_batch=300)
+hs, hl = load(r, small), load(r, large)
+static(r, hs, 300)
+capture(r, hl, 300)
+static(r, hl, 300)      # the captured plan, which nothing has unpacked yet
+replay()
+static(r, hl, 17)       # another plan
+replay()
+static(r, hl, 17)       # the same again: the replay in between has left it alone
+capture(r, hl, 17)      # a plan that the eager calls' array holds already
+static(r, hs, 300)
+replay()
+static(r, hs, 300)
+""")
+    assert [g["envs"] for g in got] == [300, 300, 300, 17, 300, 17, 300, 17, 300]
+    assert [g["tiles"] for g in got[:3]] == [1, 2, 2] and got[4]["tiles"] == 2 and got[6]["tiles"] == 1
     assert all(g["wrong"] == 0 and g["groups"] == g["envs"] * g["tiles"] for g in got)

@@ -110,3 +110,44 @@ def test_static_entry_point_of_renderers_one_after_the_other(first):
             bps.bps_render(r.handle, ids, vp, d0, out_tri_id=i0)
             torch.cuda.synchronize()
             assert torch.equal(i0, i1) and torch.equal(d0, d1)
+
+
+@pytest.mark.parametrize("B", [5, 300, 700])
+def test_static_entry_point_captured_into_a_graph(B):
+    """One batch cut into small windows, one into halves, one with planning kernels.  Every replay reads the matrices
+    as they are then; calls made at once, with the captured plan and with another one, and synchronizations lie between."""
+    import torch
+    import paper_2103_07013_amd as bps
+    s = synth.make_multiroom_scene(100_000, seed=43)
+    poses = [torch.from_numpy(synth.make_cameras(s, B, seed=50 + k)[0]).cuda() for k in range(4)]
+    with bps.Renderer(max_batch=B) as r:
+        ids = np.full(B, r.load_scene(s.vertices, s.indices), np.int32)
+        ref = []
+        for p in poses:
+            d, _, t = r.render(ids, p, want_tri_id=True)
+            ref.append((d.clone(), t.clone()))
+        torch.cuda.synchronize()
+        vp = poses[0].clone()
+        d1 = torch.empty((B, 64, 64), dtype=torch.float32, device="cuda")
+        i1 = torch.empty((B, 64, 64), dtype=torch.int32, device="cuda")
+        d2, i2 = torch.empty_like(d1), torch.empty_like(i1)
+
+        def at_once(n, p):
+            bps.bps_render_static(r.handle, ids[:n], poses[p][:n], d2[:n], out_tri_id=i2[:n])
+            torch.cuda.synchronize()
+            assert torch.equal(d2[:n], ref[p][0][:n]) and torch.equal(i2[:n], ref[p][1][:n])
+
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            bps.bps_render_static(r.handle, ids, vp, d1, out_tri_id=i1)
+        at_once(B, 1)
+        for k, p in enumerate((0, 1, 2, 3, 2)):
+            vp.copy_(poses[p])
+            d1.fill_(-1.0)
+            i1.fill_(-2)
+            graph.replay()
+            if k % 2:
+                at_once(B, 3)                 # the plan of the graph
+                at_once(max(1, B // 3), 2)    # and another one
+            torch.cuda.synchronize()
+            assert torch.equal(d1, ref[p][0]) and torch.equal(i1, ref[p][1]), f"replay {k}"
