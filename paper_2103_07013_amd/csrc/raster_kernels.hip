@@ -1042,8 +1042,9 @@ __global__ __launch_bounds__(NT, 4) void k_raster(const SceneDev* __restrict__ s
         draw_place();
         uint32_t pop = __builtin_amdgcn_readfirstlane(drawn);      // place of the record in flight
         auto read_record = [&]() -> u64 {
-            const uint32_t at = min(pop, (uint32_t)list_cap - 1u);      // (past the end: any record, it is not looked at)
-            return list[(by_depth && !FRAME) ? (uint32_t)perm[at] : at];
+            // past the end: any record of the list, it is not looked at (the order has no entries there to follow)
+            if (by_depth && !FRAME) return list[perm[min(pop, n_list - 1u)]];
+            return list[min(pop, (uint32_t)list_cap - 1u)];
         };
         u64 record = read_record();
         float nx_ = 0, ny_ = 0, nz_ = 0;

@@ -68,3 +68,29 @@ def test_windows_colour_and_supersampling():
             assert bps.bps_query(r.handle, h, 5) == 3 * 64
             torch.cuda.synchronize()
             assert torch.equal(d[:3], d3) and torch.equal(c[:3], c3)
+
+
+@pytest.mark.parametrize("threads,diagnostics", [(256, 0), (384, 0), (1024, 0), (512, 1), (256, 2), (1024, 4)])
+@pytest.mark.parametrize("H,W", [(64, 64), (72, 104)])
+def test_windows_of_other_group_sizes_and_with_diagnostics(threads, diagnostics, H, W):
+    """The instances with a layout chosen at run time take survivors by way of their order: batches cut into small
+    windows and whole ones, lists with and without an order (more than 64 survivors), several rounds."""
+    import torch
+    import oracle
+    import paper_2103_07013_amd as bps
+    v, idx, M = _scene_and_cameras("rooms", 60, W / H)
+    ref = oracle.render_scene(v, idx, M, H, W)
+    with bps.Renderer(max_batch=1400, height=H, width=W, threads=threads) as r:
+        h = r.load_scene(v, idx)
+        bps.bps_set_diagnostics(r.handle, diagnostics)
+        whole = ((H + 63) // 64) * ((W + 63) // 64)
+        for B in (1, 9, 60, 1400):      # 8 x 60 windows of 72x104 fit 2.1 groups per compute unit
+            d, _, t = r.render(np.full(B, h, np.int32), np.resize(M, (B, 4, 4)), want_tri_id=True)
+            groups = bps.bps_query(r.handle, h, 5)
+            assert groups == B * whole if B == 1400 else groups > B * whole
+            torch.cuda.synchronize()
+            t, d = t.cpu().numpy().view(np.uint32), d.cpu().numpy()
+            for at in range(0, B, 60):
+                n = min(60, B - at)
+                assert np.array_equal(t[at:at + n], ref["tri_id"][:n]), f"B={B}"
+                assert np.array_equal(d[at:at + n], ref["depth"][:n]), f"B={B}"
