@@ -251,8 +251,9 @@ __device__ __forceinline__ void emit(const WaveLds& L, int& small_count, bool va
 // registers they filled 30 of them through the whole kernel, and what that pushed out to memory came back one wait
 // at a time in this very test.
 __device__ __forceinline__ void fill_planes(float4* planes, const float* __restrict__ view_proj, const Window& win, int k) {
-    const float4* rows = reinterpret_cast<const float4*>(view_proj);
-    const float4 r3 = rows[3], r = rows[k >= 4 ? 2 : k >> 1];
+    typedef float row_t __attribute__((ext_vector_type(4), aligned(4)));      // callers' matrices are aligned to floats only
+    const BPS_GLOBAL row_t* rows = (const BPS_GLOBAL row_t*)view_proj;
+    const row_t r3 = rows[3], r = rows[k >= 4 ? 2 : k >> 1];
     // (row_r - a row_3) for the low side, (a row_3 - row_r) for the high side; near = row_2, far = row_3 - row_2
     const float a = k == 0 ? win.aL : k == 1 ? win.aR : k == 2 ? win.aT : k == 3 ? win.aB : k == 4 ? 0.0f : 1.0f;
     const float sg = (k == 1 || k == 3 || k == 5) ? -1.0f : 1.0f, aa = fabsf(a);

@@ -357,3 +357,35 @@ def test_stale_scene_handles_are_refused_after_their_slot_is_reused(room):
         ref = oracle.render_scene(s.vertices, s.indices, w.view_proj[:4], 64, 64)
         assert np.array_equal(tid.cpu().numpy().view(np.uint32), ref["tri_id"])
         assert np.array_equal(depth.cpu().numpy(), ref["depth"])
+
+
+@pytest.mark.parametrize("B", [3, 530])
+@pytest.mark.parametrize("offset", [1, 2, 3])
+def test_matrices_aligned_to_floats_only(offset, B):
+    """Device matrices that start `offset` floats past a 16-byte boundary, with and without planning kernels (more
+    than 512 work-groups), and host matrices of an RGB-D batch, which are staged behind B scene ids."""
+    import torch
+    import paper_2103_07013_amd as bps
+    s = synth.make_multiroom_scene(30_000, seed=23)
+    M = synth.make_cameras(s, B, seed=9)[0]
+    at = torch.zeros(B * 16 + 4, device="cuda")
+    vp = at[offset:offset + B * 16].view(B, 4, 4)
+    vp.copy_(torch.from_numpy(M))
+    aligned = torch.from_numpy(M).cuda()
+    assert vp.data_ptr() % 16 == 4 * offset and aligned.data_ptr() % 16 == 0
+    with bps.Renderer(max_batch=B, flags=bps.FLAG_NO_DISPATCH_ORDER if offset == 2 else 0) as r:
+        ids = np.full(B, r.load_scene(s.vertices, s.indices), np.int32)
+        d0, _, t0 = r.render(ids, aligned, want_tri_id=True)
+        d1, _, t1 = r.render(ids, vp, want_tri_id=True)
+        d2, t2 = torch.empty_like(d0), torch.empty_like(t0)
+        bps.bps_render_static(r.handle, ids, vp, d2, t2)
+        torch.cuda.synchronize()
+        assert torch.equal(t0, t1) and torch.equal(d0, d1) and torch.equal(t0, t2) and torch.equal(d0, d2)
+    n = max(1, B - offset)
+    with bps.Renderer(max_batch=n, mode=bps.MODE_RGBD) as r:
+        ids = np.full(n, r.load_scene(s.vertices, s.indices, s.colors), np.int32)
+        c0, rgb0, u0 = r.render(ids, aligned[:n], want_tri_id=True)
+        c1, rgb1, u1 = r.render(ids, M[:n], want_tri_id=True)
+        torch.cuda.synchronize()
+        assert torch.equal(u0, u1) and torch.equal(c0, c1) and torch.equal(rgb0, rgb1)
+        assert torch.equal(u0, t0[:n]) and torch.equal(c0, d0[:n])
