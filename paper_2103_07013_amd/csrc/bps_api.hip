@@ -169,6 +169,7 @@ bps_status fail(bps_renderer* r, bps_status code, const char* fmt, ...) {
 // A scene handle is its table slot (low 12 bits) and the slot's generation at load time above it.
 constexpr int kSlotBits = 12;
 static_assert((1 << kSlotBits) == kMaxScenes, "a handle holds the table slot in its low bits");
+static_assert(kSlotBits <= (int)bps::kPackedSceneBits, "and so does a packed work item");
 bps_scene make_handle(const bps_renderer* r, int slot) { return (bps_scene)((uint32_t)slot | (r->gens[slot] << kSlotBits)); }
 // Table slot of a live handle, -1 for anything else (never loaded, retired, or retired and the slot reused).
 int slot_of(const bps_renderer* r, bps_scene h) {
@@ -250,7 +251,8 @@ Cut choose_cut(const bps_renderer* r, uint32_t B, uint32_t min_clusters, uint32_
         const double room_per_cu_max = 4.6;
         while (c.w > 8 || c.h > 8) {
             const double per_window = (double)max_clusters / c.windows();
-            const double room = r->num_cu * std::min(2.0 + per_window / 2048.0, room_per_cu_max);
+            // (never more groups than can be planned, which is also what the array of bps_render_static holds)
+            const double room = std::min(r->num_cu * std::min(2.0 + per_window / 2048.0, room_per_cu_max), (double)bps::kMaxPlannedItems);
             Cut f = c;
             if (f.w >= f.h) {
                 f.nx = parts(r->rw, std::max(8, (f.w + 1) / 2));
@@ -259,7 +261,7 @@ Cut choose_cut(const bps_renderer* r, uint32_t B, uint32_t min_clusters, uint32_
                 f.ny = parts(r->rh, std::max(8, (f.h + 1) / 2));
                 f.h = parts(r->rh, f.ny);
             }
-            if (f.windows() == c.windows() || f.windows() > 64 || (double)B * f.windows() > room) break;
+            if (f.windows() == c.windows() || f.windows() > (int)bps::kMaxWindows || (double)B * f.windows() > room) break;
             c = f;
         }
         return c;
@@ -1080,7 +1082,7 @@ bps_status bps_render_static(bps_renderer* r, const bps_scene* scene_ids, const 
     Cut cut = choose_cut(r, B, 1u, max_clusters);
     cut.S = 1;                          // (no merge buffer here)
     make_plan(r, scene_ids, B, cut);    // (host containers only; they keep their capacity between calls)
-    n_items = r->plan_items.size();     // (small batches are cut finer, never past the number the device holds at once)
+    n_items = r->plan_items.size();     // (small batches are cut finer, never into more than kMaxPlannedItems)
     hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
     const bool capturing = hipStreamIsCapturing(stream, &capture) == hipSuccess && capture == hipStreamCaptureStatusActive;
     (void)hipGetLastError();
@@ -1109,7 +1111,7 @@ bps_status bps_render_static(bps_renderer* r, const bps_scene* scene_ids, const 
                 const uint32_t count = (uint32_t)std::min<size_t>(bps::kPackedItemsPerLaunch, n_items - first);
                 for (uint32_t k = 0; k < count; ++k) {
                     const bps::WorkItem& it = r->plan_items[first + k];
-                    packed.word[k] = it.env | (it.scene << bps::kPackedEnvBits) | (it.tile << (bps::kPackedEnvBits + kSlotBits));
+                    packed.word[k] = it.env | (it.scene << bps::kPackedEnvBits) | (it.tile << (bps::kPackedEnvBits + bps::kPackedSceneBits));
                 }
                 bps::launch_unpack_items(stream, packed, (uint32_t)first, count, d_items);
                 BPS_HIP(r, hipGetLastError());

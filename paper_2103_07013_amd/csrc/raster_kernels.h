@@ -121,6 +121,8 @@ hipError_t prepare_raster(int threads, size_t lds, bool fixed_layout);
 // kPackedItemsPerLaunch items per launch, each packed as env (14 bits: at most kMaxPlannedItems items) |
 // scene (12 bits) | tile (6 bits); one work-group per environment and tile, i.e. split_of = 1 << 16.
 constexpr uint32_t kPackedEnvBits = 14, kPackedSceneBits = 12;
+constexpr uint32_t kMaxWindows = 64;      // windows a frame is cut into at most
+static_assert(kMaxWindows <= 1u << (32 - kPackedEnvBits - kPackedSceneBits), "a window's number fits its bits");
 static_assert(kMaxPlannedItems <= 1u << kPackedEnvBits, "every environment of a request has an item");
 constexpr uint32_t kPackedItemsPerLaunch = 960;
 struct PackedItems {

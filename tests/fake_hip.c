@@ -117,11 +117,13 @@ void fake_replay(void) {
     for (int k = 0; k < g_n_graph; ++k) run(g_graph[k].f, g_graph[k].grid, g_graph[k].block, g_graph[k].args, 0, NULL);
 }
 
+static int g_units = 256;
+void fake_compute_units(int n) { g_units = n; }
 hipError_t hipGetDeviceCount(int* n) { *n = 1; return hipSuccess; }
 hipError_t hipGetDevicePropertiesR0600(hipDeviceProp_tR0600* p, int device) {
     (void)device;
     memset(p, 0, sizeof(*p));
-    p->multiProcessorCount = 256;
+    p->multiProcessorCount = g_units;
     p->sharedMemPerBlock = 163840;
     return hipSuccess;
 }

@@ -110,3 +110,16 @@ static(r, hs, 300)
     assert [g["envs"] for g in got] == [300, 300, 300, 17, 300, 17, 300, 17, 300]
     assert [g["tiles"] for g in got[:3]] == [1, 2, 2] and got[4]["tiles"] == 2 and got[6]["tiles"] == 1
     assert all(g["wrong"] == 0 and g["groups"] == g["envs"] * g["tiles"] for g in got)
+
+
+@pytest.mark.parametrize("B", [256, 257, 300, 2000])
+def test_static_plan_stays_within_its_array_on_any_device(fake, B):
+    """A device so large that the rule for small batches would like more groups than the array has items (16384)."""
+    got = _launches(fake, f"""
+fake.fake_compute_units(8192)
+r = bps.bps_create(max_batch={B})
+static(r, load(r, large), {B})
+static(r, load(r, small), {B})
+""")
+    assert all(g["wrong"] == 0 and g["envs"] == B and g["groups"] == B * g["tiles"] and 16384 // 4 < g["groups"] <= 16384 for g in got)
+    assert len(got) == 2 and all(1 < g["tiles"] <= 64 for g in got)
