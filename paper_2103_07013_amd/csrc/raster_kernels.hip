@@ -251,9 +251,10 @@ __device__ __forceinline__ void emit(const WaveLds& L, int& small_count, bool va
 // registers they filled 30 of them through the whole kernel, and what that pushed out to memory came back one wait
 // at a time in this very test.
 __device__ __forceinline__ void fill_planes(float4* planes, const float* __restrict__ view_proj, const Window& win, int k) {
-    typedef float row_t __attribute__((ext_vector_type(4), aligned(4)));      // callers' matrices are aligned to floats only
-    const BPS_GLOBAL row_t* rows = (const BPS_GLOBAL row_t*)view_proj;
-    const row_t r3 = rows[3], r = rows[k >= 4 ? 2 : k >> 1];
+    // (read as single floats: callers' matrices are aligned to no more; row 3 is what the kernel holds anyway)
+    const float* row = view_proj + 4 * (k >= 4 ? 2 : k >> 1);
+    const float4 r3 = make_float4(view_proj[12], view_proj[13], view_proj[14], view_proj[15]);
+    const float4 r = make_float4(row[0], row[1], row[2], row[3]);
     // (row_r - a row_3) for the low side, (a row_3 - row_r) for the high side; near = row_2, far = row_3 - row_2
     const float a = k == 0 ? win.aL : k == 1 ? win.aR : k == 2 ? win.aT : k == 3 ? win.aB : k == 4 ? 0.0f : 1.0f;
     const float sg = (k == 1 || k == 3 || k == 5) ? -1.0f : 1.0f, aa = fabsf(a);
