@@ -49,7 +49,9 @@ def test_windows_match_oracle(kind, H, W):
             assert np.array_equal(depth.cpu().numpy(), ref["depth"][:B])
             assert torch.equal(depth, d2) and torch.equal(tid, t2)
     whole = ((H + 63) // 64) * ((W + 63) // 64)
-    assert groups[0] == (H // 8) * (W // 8) if max(H, W) <= 64 and H == W else groups[0] >= whole
+    # one frame is cut as finely as 64 windows allow (the numbers themselves: test_launch_plans.py)
+    eighths = (H // 8) * (W // 8)
+    assert groups[0] == eighths if eighths <= 64 and max(H, W) <= 64 else whole < groups[0] <= 64
     assert all(g % B == 0 and B * whole <= g <= 64 * B for g, B in zip(groups, Bs))
 
 

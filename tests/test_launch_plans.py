@@ -123,3 +123,45 @@ static(r, load(r, small), {B})
 """)
     assert all(g["wrong"] == 0 and g["envs"] == B and g["groups"] == B * g["tiles"] and 16384 // 4 < g["groups"] <= 16384 for g in got)
     assert len(got) == 2 and all(1 < g["tiles"] <= 64 for g in got)
+
+
+# the numbers of windows that halving along the longer side passes through, down to 8x8 pixels and up to 64 windows
+HALVINGS = {(64, 64): [1, 2, 4, 8, 16, 32, 64], (128, 128): [4, 8, 16, 32, 64], (72, 104): [4, 8, 16, 32, 64],
+            (8, 128): [2, 4, 8, 16], (8, 8): [1], (40, 24): [1, 2, 4, 8, 12, 15], (120, 56): [2, 4, 8, 16, 32, 60]}
+
+
+@pytest.mark.parametrize("H,W", list(HALVINGS))
+def test_windows_per_frame(fake, H, W):
+    """Frames are halved as long as the groups fit 2 + clusters per window / 2048 per compute unit, at most 4.6."""
+    import paper_2103_07013_amd as bps
+    import synth
+    scenes = [synth.make_multiroom_scene(10_000, seed=1), synth.make_multiroom_scene(100_000, seed=2)]
+    clusters = [len(bps.bps_pack_clusters(s.vertices, s.indices)[0]) for s in scenes]
+    Bs = (1, 2, 9, 17, 60, 70, 128, 256, 300, 319, 330, 587, 589, 2048)
+    got = _launches(fake, f"""
+r = bps.bps_create(max_batch=2048, height={H}, width={W})
+hs = load(r, small), load(r, large)
+for B in {Bs}:
+    for h in hs:
+        static(r, h, B)
+""")
+    for k, B in enumerate(Bs):
+        for C, g in zip(clusters, got[2 * k:2 * k + 2]):
+            want = HALVINGS[H, W][0]
+            for finer in HALVINGS[H, W][1:]:
+                if B * finer > 256 * min(2 + C / want / 2048, 4.6):
+                    break
+                want = finer
+            assert g["tiles"] == want and g["wrong"] == 0 and g["groups"] == B * want, (B, C)
+
+
+def test_windows_of_large_scenes(fake):
+    """From 5300 clusters per window on the limit is 4.6 groups per compute unit: 588 frames are halved, 589 are not."""
+    got = _launches(fake, """
+r = bps.bps_create(max_batch=1024)
+h = load(r, synth.make_multiroom_scene(600_000, seed=3))
+assert bps.bps_query(r, h, 0) > 5400
+for B in (588, 589, 1024):
+    static(r, h, B)
+""")
+    assert [g["tiles"] for g in got] == [2, 1, 1] and all(g["wrong"] == 0 for g in got)
