@@ -85,9 +85,9 @@ __device__ __forceinline__ Setup make_setup(uint32_t xy0, uint32_t xy1, uint32_t
 }
 
 // Correctly rounded 1 / w from the hardware approximation and one correction step: equal to the IEEE
-// quotient whenever the result is a normal number (compared for all 2^32 arguments on gfx950).  Zeros,
-// denormals, infinities and arguments whose reciprocal is not normal come out as something that is
-// not normal either.  3 instructions instead of the 11 of a division.
+// quotient whenever the result is a normal number (compared once for all 2^32 arguments on gfx950; a test draws
+// a frame for every mantissa of w).  Zeros, denormals, infinities and arguments whose reciprocal is not normal
+// come out as something that is not normal either.  3 instructions instead of the 11 of a division.
 __device__ __forceinline__ float recip_normal(float w) {
     const float r = __builtin_amdgcn_rcpf(w);
     return fmaf(fmaf(-w, r, 1.0f), r, r);

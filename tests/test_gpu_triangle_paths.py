@@ -83,3 +83,32 @@ def test_clipped_triangles(grid, H, W, B):
     M[3:, 0, 3] = rng.uniform(-0.4, 0.4, max(B - 3, 0))
     t = _check(v, idx, M, H, W)
     assert (t != NOHIT).mean() > 0.3
+
+
+def test_reciprocals_of_every_mantissa():
+    """1/w in three instructions: one triangle of constant clip w per environment, w running through all 2^23 mantissas
+    at one exponent and through every 251st of them at the others the short form takes.  A reciprocal off by its last
+    bit changes some depth of the 8x8 frame for 99 % of them."""
+    import torch
+    import oracle
+    import paper_2103_07013_amd as bps
+    v = np.array([[-0.9, -0.95, 0.2], [0.95, -0.7, 0.4], [-0.1, 0.9, 0.9]], np.float32)
+    idx = np.array([[0, 1, 2]], np.uint32)
+    one = 0x3F800000
+    words = [np.arange(one, one + (1 << 23), dtype=np.uint32)]
+    words += [np.arange(one + (e << 23), one + ((e + 1) << 23), 251, dtype=np.uint32) for e in (-60, -59, -31, -1, 1, 30, 58, 59)]
+    words = np.concatenate(words)
+    B = 1 << 16
+    M = np.zeros((B, 4, 4), np.float32)
+    with bps.Renderer(max_batch=B, height=8, width=8) as r:
+        ids = np.full(B, r.load_scene(v, idx), np.int32)
+        for at in range(0, len(words), B):
+            w = np.resize(words[at:at + B], B).view(np.float32)
+            M[:, 0, 0] = M[:, 1, 1] = M[:, 2, 2] = M[:, 3, 3] = w
+            ref = oracle.render_scene(v, idx, M, 8, 8)
+            depth, _, tid = r.render(ids, M, want_tri_id=True)
+            torch.cuda.synchronize()
+            assert np.array_equal(tid.cpu().numpy().view(np.uint32), ref["tri_id"])
+            assert (ref["tri_id"] == 0).sum() == 26 * B
+            bad = (depth.cpu().numpy() != ref["depth"]).any((1, 2))
+            assert not bad.any(), f"{int(bad.sum())} of {B}, first w = {w[np.argmax(bad)]!r}"
