@@ -245,9 +245,11 @@ Cut choose_cut(const bps_renderer* r, uint32_t B, uint32_t min_clusters, uint32_
         // is two groups per compute unit (all of them resident at once), and more the larger a window's part of
         // the scene is, because large scenes hold the costliest groups: up to 2 + clusters per window / 2048
         // groups per compute unit (at most 4.6) were worth it, on scenes of 10 k to 1 M triangles.  Measured
-        // against undivided windows (1 M triangles, 64x64, us per request): B = 100: 271 -> 108, 300: 276 ->
-        // 176, 600: 282 -> 260, past the rule 768: 307 -> 320; 200 k: B = 8: 81 -> 41, 128: 109 -> 79,
-        // 256: 111 -> 106, past the rule 512: 129 -> 154.
+        // against undivided windows (64x64, us per request), 1 M triangles: B = 100: 215 -> 89, 300: 237 -> 169,
+        // 500: 255 -> 197, 588: 242 -> 220; 200 k triangles: B = 8: 81 -> 33, 128: 96 -> 68, 256: 100 -> 87,
+        // 300: 117 -> 107.  Past the rule halves would take, 1 M: 600: 242 -> 223, 640: 243 -> 235, 700: 246 ->
+        // 252, 768: 257 -> 274; 200 k: 512: 120 -> 146.  So 4.6 is on the safe side: the two are level at about
+        // 5.3 groups per compute unit, and batches between them are drawn whole for up to 8 % more.
         const double room_per_cu_max = 4.6;
         while (c.w > 8 || c.h > 8) {
             const double per_window = (double)max_clusters / c.windows();
