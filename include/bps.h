@@ -224,8 +224,8 @@ bps_status bps_read_diagnostics(bps_renderer *r, uint64_t *out, uint32_t capacit
 /* Facts about a loaded scene and the launch plan, for benchmarks and tests.
  * what: 0 = clusters in the scene, 1 = triangles, 2 = vertices, 3 = device bytes held,
  *       4 = splits used by the last request, 5 = work-groups of the last request,
- *       6 = work-group size, 7 = LDS bytes per work-group, 8 = device blocks allocated for scenes so
- *       far, 9 = retired scene blocks waiting for reuse. */
+ *       6 = work-group size, 7 = LDS bytes per work-group of the next request, 8 = device blocks
+ *       allocated for scenes so far, 9 = retired scene blocks waiting for reuse. */
 bps_status bps_query(bps_renderer *r, bps_scene scene, int32_t what, uint64_t *value);
 
 /* Text of the last error on this renderer (owned by the renderer; never NULL).

@@ -1219,7 +1219,8 @@ bps_status bps_query(bps_renderer* r, bps_scene scene, int32_t what, uint64_t* v
     case 5: *value = r->last_groups; return BPS_OK;
     case 6: *value = (uint64_t)r->threads; return BPS_OK;
     case 7:
-        *value = r->fixed_layout && r->threads == 512 && !(r->cfg.flags & (BPS_FLAG_NO_CLUSTER_CULL | BPS_FLAG_NO_OCCLUSION_CULL))
+        *value = r->fixed_layout && r->threads == 512 && !r->want_stats &&
+                         !(r->cfg.flags & (BPS_FLAG_NO_CLUSTER_CULL | BPS_FLAG_NO_OCCLUSION_CULL))
                      ? (uint64_t)bps::lds_bytes(64, 64, 512, (int)bps::kListCap64)
                      : (uint64_t)r->lds;
         return BPS_OK;

@@ -165,3 +165,19 @@ for B in (588, 589, 1024):
     static(r, h, B)
 """)
     assert [g["tiles"] for g in got] == [2, 1, 1] and all(g["wrong"] == 0 for g in got)
+
+
+@pytest.mark.parametrize("H,W", [(64, 64), (72, 104), (8, 8)])
+def test_reported_lds_is_what_launches_ask_for(fake, H, W):
+    p = _launches(fake, f"""
+for kw in (dict(), dict(threads=256), dict(threads=1024), dict(splits=2), dict(flags=bps.FLAG_NO_CLUSTER_CULL), dict(flags=bps.FLAG_NO_OCCLUSION_CULL)):
+    for diagnostics in (0, 1):
+        r = bps.bps_create(max_batch=4, height={H}, width={W}, **kw)
+        h = load(r, small)
+        bps.bps_set_diagnostics(r, diagnostics)
+        ids = np.full(4, h, np.int32)
+        fake.fake_clear_log()
+        assert lib.bps_render(r, ids.ctypes.data, pool.ctypes.data, 4, out.ctypes.data, None, None, None) == 0
+        print([l for l in fake.fake_log().decode().splitlines() if l.startswith("k_raster")][0], "reported=%d" % bps.bps_query(r, h, 7))
+""")
+    assert len(p) == 12 and all(g["lds"] == g["reported"] for g in p), p
