@@ -9,6 +9,7 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <memory>
 #include <mutex>
 #include <new>
 #include <string>
@@ -508,11 +509,56 @@ struct TextureArg {
     uint32_t w = 0, h = 0;
 };
 
+uint32_t largest_index(const uint32_t* indices, size_t n) {
+    uint32_t m[8] = {};
+    size_t i = 0;
+    for (; i + 8 <= n; i += 8)
+        for (int k = 0; k < 8; ++k) m[k] = std::max(m[k], indices[i + k]);
+    for (; i < n; ++i) m[0] = std::max(m[0], indices[i]);
+    return *std::max_element(m, m + 8);
+}
+
+// Smallest and largest coordinates; false if one is not finite.  Four vertices at a time, on integers that order like
+// the floats, so that the compiler can use vector instructions.
+bool vertex_bounds(const float* v, uint32_t V, float (&lo)[3], float (&hi)[3]) {
+    int32_t mn[12], mx[12];
+    std::fill(mn, mn + 12, INT32_MAX);
+    std::fill(mx, mx + 12, INT32_MIN);
+    auto ordered = [](int32_t b) { return b ^ ((b >> 31) & INT32_MAX); };      // its own inverse
+    auto see = [&](const float* p, int n) {
+        int32_t b[12];
+        std::memcpy(b, p, (size_t)n * 4);
+        for (int k = 0; k < n; ++k) {
+            const int32_t o = ordered(b[k]);
+            mn[k] = o < mn[k] ? o : mn[k];
+            mx[k] = o > mx[k] ? o : mx[k];
+        }
+    };
+    size_t i = 0;
+    const size_t n = 3 * (size_t)V;
+    for (; i + 12 <= n; i += 12) see(v + i, 12);
+    for (; i < n; i += 3) see(v + i, 3);
+    bool finite = true;
+    for (int a = 0; a < 3; ++a) {
+        int32_t l = mn[a], h = mx[a];
+        for (int k = a + 3; k < 12; k += 3) {
+            l = std::min(l, mn[k]);
+            h = std::max(h, mx[k]);
+        }
+        l = ordered(l);
+        h = ordered(h);
+        std::memcpy(&lo[a], &l, 4);
+        std::memcpy(&hi[a], &h, 4);
+        finite = finite && std::isfinite(lo[a]) && std::isfinite(hi[a]);      // infinities and NaNs lie at the ends
+    }
+    return finite;
+}
+
 // Shared by the synchronous and asynchronous entry points: validate, cluster, lay every array out
 // in one pinned image, copy it into one device block on `stream`, update the scene table on the
-// same stream and record the scene's ready event.
+// same stream and record the scene's ready event.  waits: the caller waits for the upload.
 bps_status load_scene_on(bps_renderer* r, const float* vertices, uint32_t V, const uint32_t* indices, uint32_t T,
-                         const uint8_t* colors, const TextureArg& tex, hipStream_t stream, bps_scene* out_handle) {
+                         const uint8_t* colors, const TextureArg& tex, hipStream_t stream, bool waits, bps_scene* out_handle) {
     if (!vertices || !indices || !out_handle) return fail(r, BPS_ERR_INVALID_ARG, "bps_load_scene: null argument");
     const bool textured = tex.uvs != nullptr || tex.texels != nullptr;
     if (textured) {
@@ -521,28 +567,33 @@ bps_status load_scene_on(bps_renderer* r, const float* vertices, uint32_t V, con
             return fail(r, BPS_ERR_INVALID_ARG, "bps_load_scene: texture sides must be powers of two up to 4096 (got %ux%u)", tex.w, tex.h);
     }
     if (V == 0 || T == 0) return fail(r, BPS_ERR_INVALID_ARG, "bps_load_scene: empty mesh (V=%u, T=%u)", V, T);
-    for (size_t i = 0; i < 3 * (size_t)T; ++i)
-        if (indices[i] >= V)
-            return fail(r, BPS_ERR_INVALID_ARG, "bps_load_scene: index %u of triangle %zu is >= V=%u", indices[i], i / 3, V);
-    for (size_t i = 0; i < 3 * (size_t)V; ++i)
-        if (!std::isfinite(vertices[i]))
-            return fail(r, BPS_ERR_INVALID_ARG, "bps_load_scene: vertex %zu has a non-finite coordinate", i / 3);
+    if (largest_index(indices, 3 * (size_t)T) >= V)
+        for (size_t i = 0; i < 3 * (size_t)T; ++i)
+            if (indices[i] >= V)
+                return fail(r, BPS_ERR_INVALID_ARG, "bps_load_scene: index %u of triangle %zu is >= V=%u", indices[i], i / 3, V);
+    float lo[3], hi[3];
+    if (!vertex_bounds(vertices, V, lo, hi))
+        for (size_t i = 0; i < 3 * (size_t)V; ++i)
+            if (!std::isfinite(vertices[i]))
+                return fail(r, BPS_ERR_INVALID_ARG, "bps_load_scene: vertex %zu has a non-finite coordinate", i / 3);
     BPS_HIP(r, hipSetDevice(r->device));
     // the long host-side steps (clustering, filling the pinned image) run without the lock
-    bps::ClusterSet cs;
+    std::unique_ptr<bps::SceneClusters> clusters;
     try {
-        cs = bps::build_clusters(vertices, V, indices, T);
-    } catch (const std::bad_alloc&) {
+        clusters.reset(new bps::SceneClusters(vertices, V, indices, T, lo, hi, bps::chunk_triangles(T, waits)));
+    } catch (const std::exception&) {      // (allocations are all that throws in there)
         return fail(r, BPS_ERR_OOM, "bps_load_scene: out of host memory while clustering");
     }
+    const uint32_t n_clusters = clusters->count();
     // (the raster kernel's survivor records keep 23 bits for the cluster)
-    if (cs.count == 0 || cs.count >= (1u << 23)) return fail(r, BPS_ERR_INVALID_ARG, "bps_load_scene: unsupported cluster count %u", cs.count);
+    if (n_clusters == 0 || n_clusters >= (1u << 23)) return fail(r, BPS_ERR_INVALID_ARG, "bps_load_scene: unsupported cluster count %u", n_clusters);
 
     // ---- layout of the block (every array 256-byte aligned), scene-table record last
-    const uint32_t c_stride = (cs.count + 63u) & ~63u, nblocks = c_stride / 64u;
+    const uint32_t c_stride = (n_clusters + 63u) & ~63u, nblocks = c_stride / 64u;
     size_t off = 0;
     auto place = [&](size_t bytes) { size_t o = off; off = (off + bytes + 255) & ~(size_t)255; return o; };
-    const size_t o_cverts = place(cs.verts.size() * 4), o_ctris = place(cs.tris.size() * 4), o_ids = place(cs.tri_id.size() * 4);
+    const size_t o_cverts = place((size_t)n_clusters * 192 * 4), o_ctris = place((size_t)n_clusters * 128 * 4),
+                 o_ids = place((size_t)n_clusters * 128 * 4);
     const size_t o_verts = place((size_t)V * 12), o_idx = place((size_t)T * 12), o_col = colors ? place((size_t)V * 3) : 0;
     const size_t o_cb = place((size_t)6 * c_stride * 4), o_bb = place((size_t)6 * nblocks * 4);
     // texture: uv per vertex, then every mip level as RGBA8 texels, level after level
@@ -583,9 +634,10 @@ bps_status load_scene_on(bps_renderer* r, const float* vertices, uint32_t V, con
         if (e != hipSuccess) { (void)hipHostFree(stg.ptr); return fail(r, BPS_ERR_HIP, "bps_load_scene: %s", hipGetErrorString(e)); }
     }
     unsigned char* img = (unsigned char*)stg.ptr;
-    std::memcpy(img + o_cverts, cs.verts.data(), cs.verts.size() * 4);
-    std::memcpy(img + o_ctris, cs.tris.data(), cs.tris.size() * 4);
-    std::memcpy(img + o_ids, cs.tri_id.data(), cs.tri_id.size() * 4);
+    float* cb = (float*)(img + o_cb);
+    std::memset(cb, 0, (size_t)6 * c_stride * 4);
+    clusters->write((float*)(img + o_cverts), (uint32_t*)(img + o_ctris), (uint32_t*)(img + o_ids), cb, c_stride);
+    clusters.reset();
     std::memcpy(img + o_verts, vertices, (size_t)V * 12);
     std::memcpy(img + o_idx, indices, (size_t)T * 12);
     if (colors) std::memcpy(img + o_col, colors, (size_t)V * 3);
@@ -620,16 +672,12 @@ bps_status load_scene_on(bps_renderer* r, const float* vertices, uint32_t V, con
         }
     }
     {   // bounds as six planes so that 64 lanes read 64 consecutive clusters (or blocks of 64 clusters)
-        float* cb = (float*)(img + o_cb);
         float* bb = (float*)(img + o_bb);
-        std::memset(cb, 0, (size_t)6 * c_stride * 4);
-        for (uint32_t c = 0; c < cs.count; ++c)
-            for (int k = 0; k < 6; ++k) cb[(size_t)k * c_stride + c] = cs.bounds[(size_t)c * 6 + k];
-        for (uint32_t b = 0; b < nblocks; ++b)
-            for (int k = 0; k < 6; ++k) {
-                float v = cs.bounds[(size_t)b * 64 * 6 + k];
-                for (uint32_t c = b * 64; c < std::min(cs.count, b * 64 + 64); ++c)
-                    v = k < 3 ? std::min(v, cs.bounds[(size_t)c * 6 + k]) : std::max(v, cs.bounds[(size_t)c * 6 + k]);
+        for (int k = 0; k < 6; ++k)
+            for (uint32_t b = 0; b < nblocks; ++b) {
+                const float* plane = cb + (size_t)k * c_stride;
+                float v = plane[b * 64];
+                for (uint32_t c = b * 64; c < std::min(n_clusters, b * 64 + 64); ++c) v = k < 3 ? std::min(v, plane[c]) : std::max(v, plane[c]);
                 bb[(size_t)k * nblocks + b] = v;
             }
     }
@@ -659,14 +707,17 @@ bps_status load_scene_on(bps_renderer* r, const float* vertices, uint32_t V, con
         r->arena_pool[best] = r->arena_pool.back();
         r->arena_pool.pop_back();
     } else {
-        hipError_t e = hipMalloc(&arena.ptr, dev_bytes);
+        // (sizes a sixteenth of a power of two apart, so that scenes of about one size can follow each other in a block)
+        size_t step = 4096;
+        while (32 * step <= dev_bytes) step *= 2;
+        arena.bytes = (dev_bytes + step - 1) / step * step;
+        hipError_t e = hipMalloc(&arena.ptr, arena.bytes);
         if (e != hipSuccess) {
             r->staging.push_back(stg);
             (void)hipEventRecord(stg.done, stream);
-            return fail(r, e == hipErrorOutOfMemory ? BPS_ERR_OOM : BPS_ERR_HIP, "bps_load_scene: hipMalloc(%zu): %s", dev_bytes,
+            return fail(r, e == hipErrorOutOfMemory ? BPS_ERR_OOM : BPS_ERR_HIP, "bps_load_scene: hipMalloc(%zu): %s", arena.bytes,
                         hipGetErrorString(e));
         }
-        arena.bytes = dev_bytes;
         ++r->arena_allocs;
     }
     unsigned char* d = (unsigned char*)arena.ptr;
@@ -688,7 +739,7 @@ bps_status load_scene_on(bps_renderer* r, const float* vertices, uint32_t V, con
     hs.dev.tri_rec = shaded ? (const float*)(d + o_trirec) : nullptr;
     hs.dev.cbounds = (const float*)(d + o_cb);
     hs.dev.bbounds = (const float*)(d + o_bb);
-    hs.dev.n_clusters = cs.count;
+    hs.dev.n_clusters = n_clusters;
     hs.dev.n_tris = T;
     hs.dev.n_verts = V;
     hs.dev.c_stride = c_stride;
@@ -727,7 +778,7 @@ bps_status load_scene_on(bps_renderer* r, const float* vertices, uint32_t V, con
 bps_status bps_load_scene(bps_renderer* r, const float* vertices, uint32_t V, const uint32_t* indices, uint32_t T,
                           const uint8_t* colors, bps_scene* out_handle) {
     if (!r) return BPS_ERR_INVALID_ARG;
-    bps_status st = load_scene_on(r, vertices, V, indices, T, colors, TextureArg{}, r->load_stream, out_handle);
+    bps_status st = load_scene_on(r, vertices, V, indices, T, colors, TextureArg{}, r->load_stream, true, out_handle);
     if (st != BPS_OK) return st;
     BPS_HIP(r, hipStreamSynchronize(r->load_stream));
     std::lock_guard<std::mutex> lock(r->mu);
@@ -742,7 +793,7 @@ bps_status bps_load_scene(bps_renderer* r, const float* vertices, uint32_t V, co
 bps_status bps_load_scene_async(bps_renderer* r, const float* vertices, uint32_t V, const uint32_t* indices, uint32_t T,
                                 const uint8_t* colors, void* copy_stream, bps_scene* out_handle) {
     if (!r) return BPS_ERR_INVALID_ARG;
-    return load_scene_on(r, vertices, V, indices, T, colors, TextureArg{}, (hipStream_t)copy_stream, out_handle);
+    return load_scene_on(r, vertices, V, indices, T, colors, TextureArg{}, (hipStream_t)copy_stream, false, out_handle);
 }
 
 bps_status bps_load_scene_textured(bps_renderer* r, const float* vertices, uint32_t V, const uint32_t* indices, uint32_t T,
@@ -756,7 +807,7 @@ bps_status bps_load_scene_textured(bps_renderer* r, const float* vertices, uint3
     tex.w = tex_w;
     tex.h = tex_h;
     hipStream_t stream = copy_stream ? (hipStream_t)copy_stream : r->load_stream;
-    bps_status st = load_scene_on(r, vertices, V, indices, T, nullptr, tex, stream, out_handle);
+    bps_status st = load_scene_on(r, vertices, V, indices, T, nullptr, tex, stream, copy_stream == nullptr, out_handle);
     if (st != BPS_OK || copy_stream) return st;
     BPS_HIP(r, hipStreamSynchronize(r->load_stream));
     std::lock_guard<std::mutex> lock(r->mu);

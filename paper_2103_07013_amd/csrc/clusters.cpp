@@ -3,10 +3,19 @@
 // most 64 distinct vertices and 128 triangles.
 #include "clusters.h"
 
+#include <sched.h>
+
 #include <algorithm>
+#include <atomic>
 #include <cmath>
+#include <condition_variable>
 #include <cstring>
+#include <exception>
+#include <functional>
+#include <memory>
+#include <mutex>
 #include <numeric>
+#include <thread>
 
 namespace bps {
 namespace {
@@ -315,6 +324,506 @@ ClusterSet build_clusters(const float* vertices, uint32_t V, const uint32_t* ind
     }
     order_for_blocks(out);
     return out;
+}
+
+
+// ---- clusters of a scene that is being loaded ---------------------------------------------------------------------
+
+namespace {
+
+// The threads of one load.  run() hands out tasks 0 .. n - 1 to them and to the caller and returns when all are done.
+class Team {
+public:
+    explicit Team(unsigned threads) {
+        try {
+            for (unsigned k = 1; k < threads; ++k) workers_.emplace_back([this] { work(); });
+        } catch (const std::exception&) {      // no more threads to be had: the ones there are will do
+        }
+    }
+    ~Team() {
+        {
+            std::lock_guard<std::mutex> g(mu_);
+            quit_ = true;
+        }
+        wake_.notify_all();
+        for (std::thread& t : workers_) t.join();
+    }
+    void run(size_t n, const std::function<void(size_t)>& task) {
+        {
+            std::lock_guard<std::mutex> g(mu_);
+            task_ = &task;
+            n_ = n;
+            next_ = 0;
+            failed_ = nullptr;
+            ++round_;
+        }
+        if (n > 1) wake_.notify_all();
+        take();
+        std::unique_lock<std::mutex> g(mu_);
+        idle_.wait(g, [this] { return busy_ == 0; });
+        task_ = nullptr;                       // (a thread that wakes up late finds nothing)
+        if (failed_) std::rethrow_exception(failed_);
+    }
+
+private:
+    void take() {
+        for (;;) {
+            const size_t k = next_.fetch_add(1);
+            if (k >= n_) return;
+            try {
+                (*task_)(k);
+            } catch (...) {
+                std::lock_guard<std::mutex> g(mu_);
+                if (!failed_) failed_ = std::current_exception();
+            }
+        }
+    }
+    void work() {
+        uint64_t seen = 0;
+        std::unique_lock<std::mutex> g(mu_);
+        for (;;) {
+            wake_.wait(g, [&] { return quit_ || (task_ && round_ != seen); });
+            if (quit_) return;
+            seen = round_;
+            ++busy_;
+            g.unlock();
+            take();
+            g.lock();
+            if (--busy_ == 0) idle_.notify_one();
+        }
+    }
+    std::vector<std::thread> workers_;
+    std::mutex mu_;
+    std::condition_variable wake_, idle_;
+    const std::function<void(size_t)>* task_ = nullptr;
+    size_t n_ = 0;
+    std::atomic<size_t> next_{0};
+    unsigned busy_ = 0;
+    uint64_t round_ = 0;
+    bool quit_ = false;
+    std::exception_ptr failed_;
+};
+
+unsigned usable_cpus() {
+    cpu_set_t set;
+    CPU_ZERO(&set);
+    if (sched_getaffinity(0, sizeof(set), &set) != 0) return 1;
+    return (unsigned)std::max(1, CPU_COUNT(&set));
+}
+
+// A triangle on its way into a chunk: centroid in units of the mesh's longest side, from its smallest corner.
+struct Item {
+    float c[3];
+    uint32_t tri;
+};
+struct Range {
+    size_t first, last;
+};
+
+// Slabs with about the same number of triangles each: count[s] of n triangles lie on step s along an axis; slab[s] is the
+// slab that the step's middle triangle falls into.
+constexpr uint32_t kSteps = 2048;
+void cut(const uint32_t* count, size_t n, uint32_t parts, uint32_t* slab) {
+    size_t before = 0;
+    for (uint32_t s = 0; s < kSteps; ++s) {
+        slab[s] = (uint32_t)std::min<size_t>(parts - 1, (before + count[s] / 2) * parts / n);
+        before += count[s];
+    }
+}
+// Cuts in[r] into `parts` slabs along the longest side of its centroids' box and puts them into out[r] one after the other.
+std::vector<Range> slabs(const Item* in, Item* out, Range r, uint32_t parts) {
+    float lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY};
+    for (size_t i = r.first; i < r.last; ++i)
+        for (int a = 0; a < 3; ++a) {
+            lo[a] = std::min(lo[a], in[i].c[a]);
+            hi[a] = std::max(hi[a], in[i].c[a]);
+        }
+    int axis = 0;
+    for (int a = 1; a < 3; ++a)
+        if (hi[a] - lo[a] > hi[axis] - lo[axis]) axis = a;
+    const float base = lo[axis], scale = ((float)kSteps - 0.5f) / std::max(hi[axis] - lo[axis], 1e-30f);
+    auto step = [&](const Item& it) { return std::min((uint32_t)((it.c[axis] - base) * scale), kSteps - 1); };
+    std::vector<uint32_t> count(kSteps, 0), slab(kSteps);
+    for (size_t i = r.first; i < r.last; ++i) ++count[step(in[i])];
+    cut(count.data(), r.last - r.first, parts, slab.data());
+    std::vector<size_t> at(parts, 0);
+    for (uint32_t k = 0; k < kSteps; ++k) at[slab[k]] += count[k];
+    std::vector<Range> made;
+    size_t first = r.first;
+    for (uint32_t p = 0; p < parts; ++p) {
+        const size_t size = at[p];
+        at[p] = first;
+        if (size) made.push_back({first, first + size});
+        first += size;
+    }
+    for (size_t i = r.first; i < r.last; ++i) out[at[slab[step(in[i])]]++] = in[i];
+    return made;
+}
+
+// A chunk's vertices by number of first use.
+class VertexNumbers {
+public:
+    VertexNumbers() : slot_(4096, {0xFFFFFFFFu, 0u}) {}
+    uint32_t of(uint32_t vertex) {
+        size_t k = place(vertex);
+        if (slot_[k].first == vertex) return slot_[k].second;
+        if (2 * numbered.size() >= slot_.size()) {
+            slot_.assign(4 * slot_.size(), {0xFFFFFFFFu, 0u});
+            for (uint32_t n = 0; n < (uint32_t)numbered.size(); ++n) slot_[place(numbered[n])] = {numbered[n], n};
+            k = place(vertex);
+        }
+        slot_[k] = {vertex, (uint32_t)numbered.size()};
+        numbered.push_back(vertex);
+        return slot_[k].second;
+    }
+    std::vector<uint32_t> numbered;
+
+private:
+    size_t place(uint32_t vertex) const {      // where it is, or would be (no vertex is 0xFFFFFFFF: it would not be < V)
+        size_t k = (size_t)(((uint64_t)vertex * 0x9E3779B97F4A7C15ull) >> 32) & (slot_.size() - 1);
+        while (slot_[k].first != vertex && slot_[k].first != 0xFFFFFFFFu) k = (k + 1) & (slot_.size() - 1);
+        return k;
+    }
+    std::vector<std::pair<uint32_t, uint32_t>> slot_;
+};
+
+// The triangles left of a chunk, in groups of 64 neighbours along a Morton curve, for the nearest of them.
+class Neighbourhood {
+public:
+    Neighbourhood(const Item* item, uint32_t n, const float (&lo)[3], float scale) : item_(item) {
+        std::vector<uint32_t> code(n);
+        for (uint32_t t = 0; t < n; ++t) {
+            code[t] = 0;
+            for (int a = 0; a < 3; ++a)
+                code[t] |= spread10((uint32_t)std::min(1023.0f, std::max(0.0f, (item[t].c[a] - lo[a]) * scale))) << a;
+        }
+        tris_ = sorted_by_code(code);
+        group_.resize(n);
+        const uint32_t groups = (n + 63) / 64;
+        left_.assign(groups, 64);
+        left_.back() = n - 64 * (groups - 1);
+        for (auto& b : box_) b.resize(groups);
+        for (uint32_t g = 0; g < groups; ++g) {
+            float l[3] = {INFINITY, INFINITY, INFINITY}, h[3] = {-INFINITY, -INFINITY, -INFINITY};
+            for (uint32_t k = 64 * g; k < std::min(n, 64 * g + 64); ++k) {
+                group_[tris_[k]] = g;
+                for (int a = 0; a < 3; ++a) {
+                    l[a] = std::min(l[a], item[tris_[k]].c[a]);
+                    h[a] = std::max(h[a], item[tris_[k]].c[a]);
+                }
+            }
+            for (int a = 0; a < 3; ++a) {
+                box_[a][g] = l[a];
+                box_[3 + a][g] = h[a];
+            }
+        }
+        far_.resize(groups);
+    }
+    void take(uint32_t t) { --left_[group_[t]]; }
+    // From now on next() looks around c.
+    void look_from(const float (&c)[3]) {
+        std::copy(c, c + 3, from_);
+        asked_ = 0;
+    }
+    // The triangle nearest to that place in the maximum norm that is not taken; 0xFFFFFFFF if there is none.  Groups are
+    // opened one after the other, the nearest first, until none that is left can hold a nearer triangle.  Loose triangles
+    // would have most groups opened for every cluster: a cluster that asks again and again takes them from the groups
+    // that are open, and so does one that has opened six.
+    uint32_t next(const std::vector<uint8_t>& taken) {
+        if (asked_++ == 0) {
+            opened_ = 0;
+            seen_.clear();
+            for (size_t g = 0; g < far_.size(); ++g) {
+                const float x = std::max(box_[0][g] - from_[0], from_[0] - box_[3][g]), y = std::max(box_[1][g] - from_[1], from_[1] - box_[4][g]),
+                            z = std::max(box_[2][g] - from_[2], from_[2] - box_[5][g]);
+                far_[g] = left_[g] ? std::max(std::max(x, y), std::max(z, 0.0f)) : INFINITY;
+            }
+            closest_ = (size_t)(std::min_element(far_.begin(), far_.end()) - far_.begin());
+        }
+        for (;;) {
+            Place best{INFINITY, 0xFFFFFFFFu};
+            for (size_t k = 0; k < seen_.size();) {
+                if (taken[seen_[k].second]) {
+                    seen_[k] = seen_.back();
+                    seen_.pop_back();
+                } else {
+                    best = std::min(best, seen_[k++]);
+                }
+            }
+            const float others = far_[closest_];
+            if (others == INFINITY || best.first < others || ((asked_ > 2 || opened_ >= 6) && best.first != INFINITY)) return best.second;
+            ++opened_;
+            for (uint32_t k = 64 * (uint32_t)closest_; k < std::min<size_t>(tris_.size(), 64 * closest_ + 64); ++k) {
+                const uint32_t t = tris_[k];
+                if (taken[t]) continue;
+                float d = 0.0f;
+                for (int a = 0; a < 3; ++a) d = std::max(d, std::fabs(item_[t].c[a] - from_[a]));
+                seen_.push_back({d, t});
+            }
+            far_[closest_] = INFINITY;
+            closest_ = (size_t)(std::min_element(far_.begin(), far_.end()) - far_.begin());
+        }
+    }
+
+private:
+    typedef std::pair<float, uint32_t> Place;
+    const Item* item_;
+    std::vector<uint32_t> tris_, group_, left_;
+    std::vector<float> box_[6], far_;
+    float from_[3];
+    uint32_t asked_ = 0, opened_ = 0;
+    size_t closest_ = 0;
+    std::vector<Place> seen_;
+};
+
+ClusterSet grow_chunk(const float* vertices, const uint32_t* indices, const Item* item, uint32_t n) {
+    ClusterSet out;
+    // ---- a mesh of its own: vertices numbered by first use, the triangles at each of them
+    std::vector<uint32_t> ix(3 * (size_t)n), vertex;
+    {
+        VertexNumbers numbers;
+        for (uint32_t t = 0; t < n; ++t)
+            for (int k = 0; k < 3; ++k) ix[3 * (size_t)t + k] = numbers.of(indices[3 * (size_t)item[t].tri + k]);
+        vertex = std::move(numbers.numbered);
+    }
+    const uint32_t V = (uint32_t)vertex.size();
+    std::vector<uint32_t> vstart(V + 1, 0), vtris(3 * (size_t)n);
+    for (uint32_t i : ix) ++vstart[i + 1];
+    for (uint32_t v = 0; v < V; ++v) vstart[v + 1] += vstart[v];
+    {
+        std::vector<uint32_t> fill(vstart.begin(), vstart.end() - 1);
+        for (uint32_t t = 0; t < n; ++t)
+            for (int k = 0; k < 3; ++k) vtris[fill[ix[3 * (size_t)t + k]]++] = t;
+    }
+    // ---- along the diagonal of the chunk's box
+    float lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY};
+    for (uint32_t t = 0; t < n; ++t)
+        for (int a = 0; a < 3; ++a) {
+            lo[a] = std::min(lo[a], item[t].c[a]);
+            hi[a] = std::max(hi[a], item[t].c[a]);
+        }
+    const float side = std::max({hi[0] - lo[0], hi[1] - lo[1], hi[2] - lo[2], 1e-30f});
+    std::vector<uint32_t> in_order;
+    {
+        std::vector<uint32_t> code(n);
+        const float scale = 1073741823.0f / (3.0f * side);
+        for (uint32_t t = 0; t < n; ++t) {
+            const float along = (item[t].c[0] - lo[0]) + (item[t].c[1] - lo[1]) + (item[t].c[2] - lo[2]);
+            code[t] = (uint32_t)std::min(1073741760.0f, along * scale);      // (the largest float below 2^30)
+        }
+        in_order = sorted_by_code(code);
+    }
+    Neighbourhood near(item, n, lo, 1023.0f / side);
+
+    std::vector<uint32_t> vfirst(vstart.begin(), vstart.end() - 1);   // first entry of a vertex's list that may be free
+    std::vector<uint32_t> stamp(V, 0xFFFFFFFFu);     // cluster that last used the vertex
+    std::vector<uint8_t> local(V, 0), taken(n, 0);
+    std::vector<uint32_t> listed(n, 0xFFFFFFFFu), place(n);           // cluster whose candidates hold the triangle, its number there
+    Candidates cand;
+    const size_t expect = n / 85 + 2;
+    out.verts.reserve(expect * 192);
+    out.tris.reserve(expect * 128);
+    out.tri_id.reserve(expect * 128);
+    uint32_t head = 0;
+    for (;;) {
+        while (head < n && taken[in_order[head]]) ++head;
+        if (head >= n) break;
+        const uint32_t c = out.count++, seed = in_order[head];
+        const size_t vbase = out.verts.size(), tbase = out.tris.size();
+        out.verts.resize(vbase + 192, 0.0f);
+        out.tris.resize(tbase + 128, 0u);
+        out.tri_id.resize(tbase + 128, 0xFFFFFFFFu);
+        uint32_t nv = 0, nt = 0;
+        float bl[3] = {INFINITY, INFINITY, INFINITY}, bh[3] = {-INFINITY, -INFINITY, -INFINITY};
+        const float at[3] = {item[seed].c[0], item[seed].c[1], item[seed].c[2]};
+        cand.clear();
+        near.look_from(at);
+        auto fresh_of = [&](uint32_t t) {
+            const uint32_t* i = &ix[3 * (size_t)t];
+            uint32_t d = stamp[i[0]] != c ? 1u : 0u;
+            if (i[1] != i[0] && stamp[i[1]] != c) ++d;
+            if (i[2] != i[0] && i[2] != i[1] && stamp[i[2]] != c) ++d;
+            return d;
+        };
+        auto distance = [&](uint32_t t) {
+            float d = 0.0f;
+            for (int a = 0; a < 3; ++a) d = std::max(d, std::fabs(item[t].c[a] - at[a]));
+            return d;
+        };
+        auto add = [&](uint32_t t) {
+            taken[t] = 1;
+            near.take(t);
+            uint32_t li[3];
+            for (int k = 0; k < 3; ++k) {
+                const uint32_t v = ix[3 * (size_t)t + k];
+                if (stamp[v] != c) {
+                    stamp[v] = c;
+                    local[v] = (uint8_t)nv;
+                    for (int a = 0; a < 3; ++a) {
+                        const float f = vertices[3 * (size_t)vertex[v] + a];
+                        out.verts[vbase + 64 * a + nv] = f;
+                        bl[a] = std::min(bl[a], f);
+                        bh[a] = std::max(bh[a], f);
+                    }
+                    ++nv;
+                    // (vertices of enormous valence: see build_clusters)
+                    uint32_t& from = vfirst[v];
+                    const uint32_t end = vstart[v + 1];
+                    while (from < end && taken[vtris[from]]) ++from;
+                    const bool walk = end - from <= 4 * kMaxCandidates;
+                    for (uint32_t q = from; q < end && (walk || cand.live < kMaxCandidates); ++q) {
+                        const uint32_t o = vtris[q];
+                        if (taken[o] || (q > from && vtris[q - 1] == o)) continue;
+                        if (listed[o] == c) {
+                            if (walk) cand.move(place[o], cand.fresh[place[o]] - 1u);
+                        } else if (cand.live < kMaxCandidates) {
+                            listed[o] = c;
+                            place[o] = cand.list(o, fresh_of(o), distance(o));
+                        }
+                    }
+                    if (!walk)
+                        for (uint32_t q = 0; q < (uint32_t)cand.tri.size(); ++q)
+                            if (!taken[cand.tri[q]]) cand.move(q, fresh_of(cand.tri[q]));
+                }
+                li[k] = local[v];
+            }
+            out.tris[tbase + nt] = li[0] | (li[1] << 8) | (li[2] << 16);
+            out.tri_id[tbase + nt] = item[t].tri;
+            ++nt;
+        };
+        add(seed);
+        while (nt < kClusterTris) {
+            const uint32_t cheapest = cand.cheapest();
+            const bool connected = cheapest != Candidates::kNone;
+            const uint32_t best = connected ? cand.tri[cheapest] : near.next(taken);
+            if (best == 0xFFFFFFFFu || nv + (connected ? cand.fresh[cheapest] : fresh_of(best)) > kClusterVerts) break;
+            add(best);
+            if (connected) cand.drop(cheapest);
+        }
+        for (uint32_t l = nv; l < kClusterVerts; ++l)
+            for (int a = 0; a < 3; ++a) out.verts[vbase + 64 * a + l] = out.verts[vbase + 64 * a];
+        out.tris[tbase] |= nt << 24;
+        out.bounds.insert(out.bounds.end(), bl, bl + 3);
+        out.bounds.insert(out.bounds.end(), bh, bh + 3);
+    }
+    return out;
+}
+
+}  // namespace
+
+struct SceneClusters::Impl {
+    std::vector<ClusterSet> chunks;
+    Team team;
+    explicit Impl(unsigned threads) : team(threads) {}
+};
+
+SceneClusters::SceneClusters(const float* vertices, uint32_t V, const uint32_t* indices, uint32_t T, const float (&lo)[3],
+                             const float (&hi)[3], uint32_t chunk_tris)
+    : impl_(nullptr) {
+    (void)V;
+    const uint32_t n_chunks = T / chunk_tris + (T % chunk_tris ? 1 : 0);
+    // (a chunk of less than 1024 triangles is done before a second thread has started)
+    std::unique_ptr<Impl> impl(new Impl(T < 2048 ? 1u : std::min({kMostThreads, usable_cpus(), std::max(n_chunks, T / 65536u)})));
+    Team& team = impl->team;
+    // halves, so that no difference of finite numbers overflows
+    float longest = 1e-30f;
+    int axis = 0;
+    for (int x = 0; x < 3; ++x)
+        if (0.5f * hi[x] - 0.5f * lo[x] > longest) {
+            longest = 0.5f * hi[x] - 0.5f * lo[x];
+            axis = x;
+        }
+    const float unit = 1.0f / longest;
+    std::unique_ptr<Item[]> a(new Item[T]), b(n_chunks > 1 ? new Item[T] : nullptr);
+    constexpr size_t kBatch = 8192;
+    const size_t batches = ((size_t)T + kBatch - 1) / kBatch;
+    auto step = [&](const Item& it) { return std::min((uint32_t)(it.c[axis] * ((float)kSteps - 0.5f)), kSteps - 1); };
+    std::vector<uint32_t> counts(n_chunks > 1 ? batches * kSteps : 0, 0);      // by batch: triangles on each step
+    team.run(batches, [&](size_t k) {
+        for (size_t t = k * kBatch; t < std::min<size_t>(T, (k + 1) * kBatch); ++t) {
+            Item& it = a[t];
+            it.tri = (uint32_t)t;
+            for (int x = 0; x < 3; ++x) {
+                float c = 0.0f;
+                for (int j = 0; j < 3; ++j) c += (0.5f * vertices[3 * (size_t)indices[3 * t + j] + x] - 0.5f * lo[x]) * unit;
+                it.c[x] = c * (1.0f / 3.0f);
+            }
+            if (n_chunks > 1) ++counts[k * kSteps + step(it)];
+        }
+    });
+    // ---- slabs along the longest side, each cut into slabs again: near-cubes of about the same number of triangles
+    std::vector<Range> ranges{{0, T}};
+    const Item* items = a.get();
+    if (n_chunks > 1) {
+        const uint32_t first_cut = n_chunks <= 3 ? n_chunks : (uint32_t)std::ceil(std::sqrt((double)n_chunks));
+        std::vector<uint32_t> all(kSteps, 0), slab(kSteps);
+        for (size_t k = 0; k < batches; ++k)
+            for (uint32_t s = 0; s < kSteps; ++s) all[s] += counts[k * kSteps + s];
+        cut(all.data(), T, first_cut, slab.data());
+        std::vector<size_t> at(batches * first_cut, 0);      // where a batch's triangles of a slab go
+        for (size_t k = 0; k < batches; ++k)
+            for (uint32_t s = 0; s < kSteps; ++s) at[k * first_cut + slab[s]] += counts[k * kSteps + s];
+        ranges.clear();
+        size_t first = 0;
+        for (uint32_t p = 0; p < first_cut; ++p) {
+            const size_t from = first;
+            for (size_t k = 0; k < batches; ++k) {
+                const size_t n = at[k * first_cut + p];
+                at[k * first_cut + p] = first;
+                first += n;
+            }
+            if (first > from) ranges.push_back({from, first});
+        }
+        team.run(batches, [&](size_t k) {
+            for (size_t t = k * kBatch; t < std::min<size_t>(T, (k + 1) * kBatch); ++t) b[at[k * first_cut + slab[step(a[t])]]++] = a[t];
+        });
+        items = b.get();
+        if (n_chunks > 3) {
+            std::vector<std::vector<Range>> parts(ranges.size());
+            team.run(ranges.size(), [&](size_t k) {
+                const size_t n = ranges[k].last - ranges[k].first;
+                parts[k] = slabs(b.get(), a.get(), ranges[k], (uint32_t)std::max<size_t>(1, (n + chunk_tris / 2) / chunk_tris));
+            });
+            ranges.clear();
+            for (const auto& p : parts) ranges.insert(ranges.end(), p.begin(), p.end());
+            items = a.get();
+        }
+    }
+    impl->chunks.resize(ranges.size());
+    team.run(ranges.size(), [&](size_t k) {
+        impl->chunks[k] = grow_chunk(vertices, indices, items + ranges[k].first, (uint32_t)(ranges[k].last - ranges[k].first));
+    });
+    // ---- blocks of 64 clusters that are close in space
+    std::vector<float> centre;
+    std::vector<uint64_t> number;
+    for (size_t k = 0; k < impl->chunks.size(); ++k)
+        for (uint32_t c = 0; c < impl->chunks[k].count; ++c) {
+            const float* box = &impl->chunks[k].bounds[6 * (size_t)c];
+            for (int x = 0; x < 3; ++x) centre.push_back(0.5f * box[x] + 0.5f * box[3 + x]);
+            number.push_back((uint64_t)k << 32 | c);
+        }
+    std::vector<uint32_t> order(number.size());
+    std::iota(order.begin(), order.end(), 0u);
+    split_blocks(order, 0, order.size(), centre);
+    order_.resize(order.size());
+    for (size_t k = 0; k < order.size(); ++k) order_[k] = number[order[k]];
+    impl_ = impl.release();
+}
+
+SceneClusters::~SceneClusters() { delete impl_; }
+
+void SceneClusters::write(float* verts, uint32_t* tris, uint32_t* tri_id, float* bounds, size_t stride) {
+    constexpr size_t kBatch = 256;
+    impl_->team.run((order_.size() + kBatch - 1) / kBatch, [&](size_t k) {
+        for (size_t c = k * kBatch; c < std::min(order_.size(), (k + 1) * kBatch); ++c) {
+            const ClusterSet& from = impl_->chunks[order_[c] >> 32];
+            const size_t s = (uint32_t)order_[c];
+            std::memcpy(verts + c * 192, &from.verts[s * 192], 192 * sizeof(float));
+            std::memcpy(tris + c * 128, &from.tris[s * 128], 128 * sizeof(uint32_t));
+            std::memcpy(tri_id + c * 128, &from.tri_id[s * 128], 128 * sizeof(uint32_t));
+            for (int x = 0; x < 6; ++x) bounds[(size_t)x * stride + c] = from.bounds[s * 6 + x];
+        }
+    });
 }
 
 }  // namespace bps

@@ -1,0 +1,87 @@
+"""The clusters a scene is loaded as: every triangle in exactly one of them, within the limits, whatever the mesh and the
+number of chunks it is cut into.  clusters.cpp is compiled by itself: no GPU is needed."""
+import ctypes
+import os
+import subprocess
+
+import numpy as np
+import pytest
+
+import synth
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+SHIM = """
+#include "clusters.h"
+extern "C" unsigned pack(const float* v, unsigned V, const unsigned* i, unsigned T, const float* lo, const float* hi, unsigned chunk,
+                         unsigned room, float* verts, unsigned* tris, unsigned* ids, float* bounds) {
+    const float l[3] = {lo[0], lo[1], lo[2]}, h[3] = {hi[0], hi[1], hi[2]};
+    bps::SceneClusters c(v, V, i, T, l, h, chunk);
+    if (c.count() <= room) c.write(verts, tris, ids, bounds, room);
+    return c.count();
+}
+extern "C" unsigned chunk(unsigned T, int waits) { return bps::chunk_triangles(T, waits != 0); }
+"""
+
+
+@pytest.fixture(scope="module")
+def lib(tmp_path_factory):
+    d = tmp_path_factory.mktemp("clusters")
+    (d / "shim.cpp").write_text(SHIM)
+    csrc = os.path.join(ROOT, "paper_2103_07013_amd", "csrc")
+    subprocess.run(["g++", "-O2", "-std=c++17", "-pthread", "-shared", "-fPIC", "-I" + csrc, str(d / "shim.cpp"),
+                    os.path.join(csrc, "clusters.cpp"), "-o", str(d / "shim.so")], check=True)
+    return ctypes.CDLL(str(d / "shim.so"))
+
+
+def _pack(lib, v, t, chunk):
+    T, room = len(t), len(t) // 21 + 64 + 2 * (len(t) // chunk)      # a cluster that is full holds 21 triangles or more
+    verts, tris = np.zeros((room, 3, 64), np.float32), np.zeros((room, 128), np.uint32)
+    ids, bounds = np.zeros((room, 128), np.uint32), np.zeros((6, room), np.float32)
+    lo, hi = v.min(0).copy(), v.max(0).copy()
+    p = [a.ctypes.data_as(ctypes.c_void_p) for a in (v, t, lo, hi, verts, tris, ids, bounds)]
+    C = lib.pack(p[0], len(v), p[1], T, p[2], p[3], chunk, room, *p[4:])
+    assert 0 < C <= room
+    return verts[:C], tris[:C], ids[:C], bounds[:, :C]
+
+
+def _mesh(kind):
+    rng = np.random.default_rng(11)
+    if kind == "scan":
+        s = synth.make_multiroom_scene(20_000, seed=5, jitter=0.3)
+        return s.vertices, s.indices
+    if kind == "soup":              # nothing connected; degenerate and repeated triangles
+        t = np.arange(9000).reshape(-1, 3)
+        t[::9, 1] = t[::9, 0]
+        return rng.normal(size=(9000, 3)), np.concatenate([t, t[::7]])
+    if kind == "fan":               # one vertex in every triangle
+        return rng.normal(size=(6002, 3)), np.stack([np.zeros(6000, int), np.arange(1, 6001), np.arange(2, 6002)], 1)
+    if kind == "point":             # no extent at all
+        return np.full((500, 3), 7.0), rng.integers(0, 500, size=(3000, 3))
+    if kind == "plane":             # no extent along two axes, and everything on two steps of the third
+        return np.stack([rng.integers(0, 2, 2000), np.zeros(2000), np.zeros(2000)], 1), rng.integers(0, 2000, size=(4000, 3))
+    if kind == "huge":              # differences of coordinates overflow
+        return rng.choice([-3.4e38, 3.4e38, 0.0, 1.0], size=(2000, 3)), rng.integers(0, 2000, size=(4000, 3))
+    return np.eye(3), np.array([[0, 1, 2]])
+
+
+@pytest.mark.parametrize("chunk", [100, 1500, 1 << 20])      # many chunks (two levels of cuts), a few, one
+@pytest.mark.parametrize("kind", ["scan", "soup", "fan", "point", "plane", "huge", "one"])
+def test_every_triangle_is_in_one_cluster(lib, kind, chunk):
+    v, t = (np.ascontiguousarray(a, d) for a, d in zip(_mesh(kind), (np.float32, np.uint32)))
+    verts, tris, ids, bounds = _pack(lib, v, t, chunk)
+    n = tris[:, 0] >> 24
+    used = np.arange(128)[None, :] < n[:, None]
+    assert (n >= 1).all() and (n <= 128).all() and (ids[~used] == 0xFFFFFFFF).all() and (tris[~used] == 0).all()
+    assert np.array_equal(np.sort(ids[used]), np.arange(len(t)))
+    c = np.nonzero(used)[0]
+    for k in range(3):
+        corner = verts[c, :, (tris[used] >> (8 * k)) & (0xFF if k < 2 else 0x3F)]      # (the top byte of word 0 is the count)
+        assert np.array_equal(corner, v[t[ids[used], k]])
+    assert np.array_equal(bounds[:3], verts.min(2).T) and np.array_equal(bounds[3:], verts.max(2).T)
+    again = _pack(lib, v, t, chunk)      # whichever thread takes which chunk
+    assert all(np.array_equal(a, b) for a, b in zip(again, (verts, tris, ids, bounds)))
+
+
+def test_chunks_are_neither_empty_nor_too_many(lib):
+    for T in [1, 2, 4999, 5000, 20_000, 32_767, 32_768, 100_000, 200_000, 1_000_000, 0xFFFFFFFF]:
+        assert lib.chunk(T, 1) == 65536 and 5000 <= lib.chunk(T, 0) <= 16384
