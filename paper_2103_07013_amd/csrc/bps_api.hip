@@ -131,6 +131,8 @@ struct bps_renderer {
     int plan_splits = 0;
     int plan_windows = 0;
     bool fixed_layout = false;        // the raster kernel's instances with a constant LDS layout fit this device
+    bool wide_layout = false;         // and so does the one with 1024 threads, and nothing else was asked for
+    bool last_wide = false;           // the last request ran on that one
     uint64_t plan_version = 0;        // number of the current plan (0 = none yet); ring slots remember which one they hold
     std::vector<bps::WorkItem> plan_items;
     std::vector<bps_scene> call_slots;    // table slots of the current request's scene handles (keeps its capacity)
@@ -227,15 +229,17 @@ bool slot_busy(const bps_renderer* r, int slot) {
 bool fp_cull_enabled(const bps_renderer* r) { return !(r->cfg.flags & BPS_FLAG_NO_CLUSTER_CULL); }
 
 // How one request is cut into work-groups: nx x ny windows of w x h pixels per frame, and S interleaved
-// shares of the scene's clusters per window.
+// shares of the scene's clusters per window; wide: groups of 1024 threads instead of the usual size.
 struct Cut {
     int w, h, nx, ny, S;
+    bool wide;
     int windows() const { return nx * ny; }
 };
 
-Cut choose_cut(const bps_renderer* r, uint32_t B, uint32_t min_clusters, uint32_t max_clusters) {
+// coarser: the cut may be made coarser for the sake of wide groups (bps_render; how bps_render_static cuts is fixed).
+Cut choose_cut(const bps_renderer* r, uint32_t B, uint32_t min_clusters, uint32_t max_clusters, bool coarser) {
     auto parts = [](int n, int size) { return (n + size - 1) / size; };
-    Cut c{r->tile_w, r->tile_h, parts(r->rw, r->tile_w), parts(r->rh, r->tile_h), 1};
+    Cut c{r->tile_w, r->tile_h, parts(r->rw, r->tile_w), parts(r->rh, r->tile_h), 1, false};
     if (r->cfg.splits > 0) {
         c.S = r->cfg.splits;
         return c;
@@ -252,21 +256,42 @@ Cut choose_cut(const bps_renderer* r, uint32_t B, uint32_t min_clusters, uint32_
         // 252, 768: 257 -> 274; 200 k: 512: 120 -> 146.  So 4.6 is on the safe side: the two are level at about
         // 5.3 groups per compute unit, and batches between them are drawn whole for up to 8 % more.
         const double room_per_cu_max = 4.6;
-        while (c.w > 8 || c.h > 8) {
-            const double per_window = (double)max_clusters / c.windows();
-            // (never more groups than can be planned, which is also what the array of bps_render_static holds)
-            const double room = std::min(r->num_cu * std::min(2.0 + per_window / 2048.0, room_per_cu_max), (double)bps::kMaxPlannedItems);
-            Cut f = c;
-            if (f.w >= f.h) {
-                f.nx = parts(r->rw, std::max(8, (f.w + 1) / 2));
-                f.w = parts(r->rw, f.nx);
-            } else {
-                f.ny = parts(r->rh, std::max(8, (f.h + 1) / 2));
-                f.h = parts(r->rh, f.ny);
+        auto halve = [&](Cut c, bool one_per_cu) {
+            while (c.w > 8 || c.h > 8) {
+                const double per_window = (double)max_clusters / c.windows();
+                // (never more groups than can be planned, which is also what the array of bps_render_static holds)
+                const double per_cu = one_per_cu ? 1.0 : std::min(2.0 + per_window / 2048.0, room_per_cu_max);
+                const double room = std::min(r->num_cu * per_cu, (double)bps::kMaxPlannedItems);
+                Cut f = c;
+                if (f.w >= f.h) {
+                    f.nx = parts(r->rw, std::max(8, (f.w + 1) / 2));
+                    f.w = parts(r->rw, f.nx);
+                } else {
+                    f.ny = parts(r->rh, std::max(8, (f.h + 1) / 2));
+                    f.h = parts(r->rh, f.ny);
+                }
+                if (f.windows() == c.windows() || f.windows() > (int)bps::kMaxWindows || (double)B * f.windows() > room) break;
+                c = f;
             }
-            if (f.windows() == c.windows() || f.windows() > (int)bps::kMaxWindows || (double)B * f.windows() > room) break;
-            c = f;
+            return c;
+        };
+        const Cut fine = halve(c, false);
+        if (!r->wide_layout || (r->cfg.flags & BPS_FLAG_NO_OCCLUSION_CULL) || r->want_stats) return fine;
+        // A compute unit holds two groups of eight wavefronts, or one of sixteen.  Where no unit has a second group to
+        // hold, the sixteen halve the time between its barriers: 1 environment of 100 k triangles 25.2 -> 22.5 us per
+        // request, of 1 M 44.9 -> 40.8.  And where the time goes into clusters rather than pixels (a cluster or more to
+        // four pixels of the frame), sixteen wavefronts on one window are better than eight on each of its halves,
+        // which repeat what lies on the cut and see fewer occluders: 1 M triangles, 64x64, 8 environments 49.5 -> 43.8,
+        // 16: 58.3 -> 49.4, 32: 68.3 -> 54.0; 128x128, 32: 84.3 -> 67.9; 100 k, 64x64, 8: 28.5 -> 25.7, 24: 43.3 ->
+        // 38.1.  Below that they are worse (100 k at 128x128, 32 environments 71 -> 78), and so are frames of fewer than
+        // eight windows (1 M, 100 environments of 2 windows 87 -> 105).
+        if (coarser && 4u * (uint64_t)max_clusters >= (uint64_t)r->rw * r->rh) {
+            Cut one = halve(c, true);
+            one.wide = true;
+            if (one.windows() >= 8) return one;
         }
+        c = fine;
+        c.wide = (uint64_t)B * c.windows() <= (uint64_t)r->num_cu;
         return c;
     }
     // without culling every window would stream the whole scene, and scenes whose blocks cannot be ordered
@@ -442,7 +467,8 @@ bps_status bps_create(const bps_config* cfg, bps_renderer** out) {
 #endif
         r->lds = bps::lds_bytes(r->tile_h, r->tile_w, r->threads, r->list_cap);
         r->fixed_layout = bps::lds_bytes(64, 64, 512, (int)bps::kListCap64) <= r->max_lds;
-        BPS_HIP(r, bps::prepare_raster(r->threads, r->lds, r->fixed_layout));
+        r->wide_layout = r->fixed_layout && r->threads == 512 && bps::lds_bytes(64, 64, 1024, (int)bps::kListCap64) <= r->max_lds;
+        BPS_HIP(r, bps::prepare_raster(r->threads, r->lds, r->fixed_layout, r->wide_layout));
         BPS_HIP(r, hipMalloc((void**)&r->d_scenes, sizeof(bps::SceneDev) * kMaxScenes));
         BPS_HIP(r, hipMemset(r->d_scenes, 0, sizeof(bps::SceneDev) * kMaxScenes));
         for (RingSlot& s : r->ring) {
@@ -929,7 +955,7 @@ bps_status bps_render(bps_renderer* r, const bps_scene* scene_ids, const float* 
         out_depth = r->ss_depth;
         out_rgb = r->ss_rgb;
     }
-    const Cut cut = choose_cut(r, B, min_clusters, max_clusters);
+    const Cut cut = choose_cut(r, B, min_clusters, max_clusters, true);
     const int S = cut.S;
     make_plan(r, scene_ids, B, cut);
     const size_t n_items = r->plan_items.size();
@@ -1056,7 +1082,7 @@ bps_status bps_render(bps_renderer* r, const bps_scene* scene_ids, const float* 
         r->ev_used += 2;
     }
     bps::launch_raster(r->threads, dim3((unsigned)n_items), r->lds, stream, r->d_scenes, planned ? d_ordered : d_items, d_vp, fp,
-                       r->fixed_layout, r->gvis, out_depth, out_tri_id, d_stats);
+                       r->fixed_layout, cut.wide, r->gvis, out_depth, out_tri_id, d_stats);
     BPS_HIP(r, hipGetLastError());
     if (ev_stop) BPS_HIP(r, hipEventRecord(ev_stop, stream));
     if (S > 1) {
@@ -1082,6 +1108,7 @@ bps_status bps_render(bps_renderer* r, const bps_scene* scene_ids, const float* 
     }
     r->last_splits = (uint64_t)S;
     r->last_groups = (uint64_t)n_items;
+    r->last_wide = cut.wide;
     return BPS_OK;
 }
 
@@ -1132,7 +1159,7 @@ bps_status bps_render_static(bps_renderer* r, const bps_scene* scene_ids, const 
             }
         }
     }
-    Cut cut = choose_cut(r, B, 1u, max_clusters);
+    Cut cut = choose_cut(r, B, 1u, max_clusters, false);
     cut.S = 1;                          // (no merge buffer here)
     make_plan(r, scene_ids, B, cut);    // (host containers only; they keep their capacity between calls)
     n_items = r->plan_items.size();     // (small batches are cut finer, never into more than kMaxPlannedItems)
@@ -1179,7 +1206,7 @@ bps_status bps_render_static(bps_renderer* r, const bps_scene* scene_ids, const 
         BPS_HIP(r, hipGetLastError());
     }
     bps::launch_raster(r->threads, dim3((unsigned)n_items), r->lds, stream, r->d_scenes, planned ? d_ordered : d_items, view_proj,
-                       fp, r->fixed_layout, nullptr, out_depth, out_tri_id, nullptr);
+                       fp, r->fixed_layout, cut.wide, nullptr, out_depth, out_tri_id, nullptr);
     BPS_HIP(r, hipGetLastError());
     if (slot) {
         BPS_HIP(r, hipEventRecord(slot->done, stream));
@@ -1188,6 +1215,7 @@ bps_status bps_render_static(bps_renderer* r, const bps_scene* scene_ids, const 
     }
     r->last_splits = 1;
     r->last_groups = (uint64_t)n_items;
+    r->last_wide = cut.wide;
     return BPS_OK;
 }
 
@@ -1272,7 +1300,7 @@ bps_status bps_query(bps_renderer* r, bps_scene scene, int32_t what, uint64_t* v
     case 7:
         *value = r->fixed_layout && r->threads == 512 && !r->want_stats &&
                          !(r->cfg.flags & (BPS_FLAG_NO_CLUSTER_CULL | BPS_FLAG_NO_OCCLUSION_CULL))
-                     ? (uint64_t)bps::lds_bytes(64, 64, 512, (int)bps::kListCap64)
+                     ? (uint64_t)bps::lds_bytes(64, 64, r->last_wide ? 1024 : 512, (int)bps::kListCap64)
                      : (uint64_t)r->lds;
         return BPS_OK;
     case 8: *value = r->arena_allocs; return BPS_OK;

@@ -94,7 +94,8 @@ __host__ __device__ inline size_t lds_bytes(int tile_h, int tile_w, int threads,
 // DIAG = true is the instance launched while diagnostics are on; it alone keeps counters and timers.
 // CULL = FrameParams::cull of the launch (0 none, 1 frustum, 2 frustum + occlusion).
 // FRAME = 64 or 128: the frame is square of that size and drawn as 64x64 windows; 1 = any frame and window,
-// with the LDS layout of those two (a 64x64 key buffer and kListCap64 survivors, whatever the window's size);
+// with the LDS layout of those two (a 64x64 key buffer and kListCap64 survivors, whatever the window's size), also with
+// 1024 threads for launches that put one group on a compute unit (choose_cut);
 // 0 = any frame, window, layout.
 template <int NT, bool DIAG, int CULL, int FRAME>
 __global__ void k_raster(const SceneDev* __restrict__ scenes, const WorkItem* __restrict__ items,
@@ -109,14 +110,14 @@ __global__ void k_fill_keys(unsigned long long* __restrict__ gvis, size_t n);
 __global__ void k_zero_words(unsigned long long* __restrict__ p, size_t n);
 
 void launch_raster(int threads, dim3 grid, size_t lds, hipStream_t stream, const SceneDev* scenes, const WorkItem* items,
-                   const float* view_proj, const FrameParams& fp, bool fixed_layout, unsigned long long* gvis,
+                   const float* view_proj, const FrameParams& fp, bool fixed_layout, bool wide, unsigned long long* gvis,
                    float* out_depth, uint32_t* out_id, unsigned long long* stats);
 // Fills ordered[n_items] with the items in launch order, costliest first; cost is scratch, one word
 // per item.
 constexpr uint32_t kMaxPlannedItems = 16384;
 void launch_plan(hipStream_t stream, const SceneDev* scenes, const WorkItem* items, const float* view_proj,
                  const FrameParams& fp, uint32_t n_items, uint32_t* cost, WorkItem* ordered);
-hipError_t prepare_raster(int threads, size_t lds, bool fixed_layout);
+hipError_t prepare_raster(int threads, size_t lds, bool fixed_layout, bool wide_layout);
 // Work items handed over as kernel arguments (no host-to-device copy, no staging memory): up to
 // kPackedItemsPerLaunch items per launch, each packed as env (14 bits: at most kMaxPlannedItems items) |
 // scene (12 bits) | tile (6 bits); one work-group per environment and tile, i.e. split_of = 1 << 16.

@@ -1513,7 +1513,7 @@ const void* raster_entry(int threads) {
 }
 }  // namespace
 
-hipError_t prepare_raster(int threads, size_t lds, bool fixed_layout) {
+hipError_t prepare_raster(int threads, size_t lds, bool fixed_layout, bool wide_layout) {
     const void* entries[6] = {raster_entry<false, 0>(threads), raster_entry<false, 1>(threads), raster_entry<false, 2>(threads),
                               raster_entry<true, 0>(threads),  raster_entry<true, 1>(threads),  raster_entry<true, 2>(threads)};
     for (const void* f : entries) {
@@ -1528,16 +1528,23 @@ hipError_t prepare_raster(int threads, size_t lds, bool fixed_layout) {
         hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes(64, 64, 512, (int)kListCap64));
         if (e != hipSuccess) return e;
     }
-    return hipSuccess;
+    if (!wide_layout) return hipSuccess;
+    return hipFuncSetAttribute(reinterpret_cast<const void*>(&k_raster<1024, false, 2, 1>), hipFuncAttributeMaxDynamicSharedMemorySize,
+                               (int)lds_bytes(64, 64, 1024, (int)kListCap64));
 }
 
 void launch_raster(int threads, dim3 grid, size_t lds, hipStream_t stream, const SceneDev* scenes, const WorkItem* items,
-                   const float* view_proj, const FrameParams& fp, bool fixed_layout, unsigned long long* gvis,
+                   const float* view_proj, const FrameParams& fp, bool fixed_layout, bool wide, unsigned long long* gvis,
                    float* out_depth, uint32_t* out_id, unsigned long long* stats) {
     // The default configuration runs on instances whose LDS layout is a compile-time constant: one each for
     // 64x64 and 128x128 frames drawn as 64x64 windows, and one for every other frame and window size.
     if (threads == 512 && !stats && fp.cull == 2 && fixed_layout) {
         const size_t lds64 = lds_bytes(64, 64, 512, (int)kListCap64);
+        if (wide) {
+            hipLaunchKernelGGL((k_raster<1024, false, 2, 1>), grid, dim3(1024), lds_bytes(64, 64, 1024, (int)kListCap64), stream, scenes,
+                               items, view_proj, fp, gvis, out_depth, out_id, stats);
+            return;
+        }
         const bool full = fp.tile_w == 64 && fp.tile_h == 64;
 #define BPS_LAUNCH_FIXED(FRAME)                                                                                        \
     hipLaunchKernelGGL((k_raster<512, false, 2, FRAME>), grid, dim3(512), lds64, stream, scenes, items, view_proj, fp, gvis, \
