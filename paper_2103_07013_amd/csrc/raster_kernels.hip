@@ -142,36 +142,48 @@ __device__ __forceinline__ void raster_large(uint32_t xy0, uint32_t xy1, uint32_
 // a box of 12x12), edge functions stepped from tile to tile, and the short division.  Coarse meshes and larger frames
 // are bound by this: 512 environments of 30 k triangles 131 -> 113 us per request, 1000 at 128x128 of 100 k 628 -> 543,
 // 192 textured at 128x128 243 -> 222, 61 at 72x104 65.5 -> 61.5; 1024 of 500 k triangles 236.8 -> 236.1.
+// One triangle per lane of `big` is set up, at the cost of setting up one; the wavefront then draws one after the other,
+// handing round what the loop over its tiles needs (11 words instead of 8, and no products of its own): 1000 at 128x128
+// of 100 k triangles 550 -> 531 us, 512 of 30 k 115 -> 110, 192 textured at 128x128 223 -> 219, 4096 at 128x128 of 500 k
+// 2227 -> 2200.
 __device__ __forceinline__ void raster_large_packed(uint32_t xy0, uint32_t xy1, uint32_t xy2, float iw0, float iw1, float iw2,
-                                                    uint32_t id, uint32_t box, int lane, u64* vis, const Window& win, uint32_t* tally) {
+                                                    uint32_t id, uint32_t box, u64 big, int lane, u64* vis, const Window& win, uint32_t* tally) {
     const PackedSetup s = make_packed_setup(xy0, xy1, xy2, iw0, iw1, iw2);
-    if (s.A2 == 0) return;
-    const int i_lo = (int)(box & 0xFFu), j_lo = (int)((box >> 8) & 0xFFu), nx = (int)((box >> 16) & 0xFFu), ny = (int)(box >> 24);
+    int first0, first1, unused;      // edge functions at the box's first pixel
+    packed_edges(s, pack_xy((int)((box & 0xFFu) << 8) + 128, (int)(((box >> 8) & 0xFFu) << 8) + 128), first0, first1, unused);
+    const int inside = s.t0 | (s.t1 << 1) | (s.t2 << 2);
     const int li = lane & 7, lj = lane >> 3;
-    // (lanes beyond the box may overflow 16 bits here; they take no part in any tile)
-    int E0, E1, unused;
-    packed_edges(s, pack_xy(((i_lo + li) << 8) + 128, ((j_lo + lj) << 8) + 128), E0, E1, unused);
-    const int right0 = -(unpack_y(s.e0) << 11), right1 = -(unpack_y(s.e1) << 11);
-    const int down0 = unpack_x(s.e0) << 11, down1 = unpack_x(s.e1) << 11;
-    const float a2f = (float)s.A2;
-    int row = __mul24(j_lo + lj - win.y0, win.pitch) + (i_lo + li - win.x0);
-    for (int y = 0; y < ny; y += 8) {
-        const bool in_rows = lj < ny - y;
-        int F0 = E0, F1 = E1, at = row;
-        for (int x = 0; x < nx; x += 8) {
-            ++tally[kTLargeSteps];
-            const int F2 = s.A2 - F0 - F1;
-            if (in_rows & (li < nx - x) & (F0 >= s.t0) & (F1 >= s.t1) & (F2 >= s.t2)) {
-                const float num = fmaf((float)F2, s.iw2, fmaf((float)F1, s.iw1, (float)F0 * s.iw0));
-                atomicMin(&vis[at], ((u64)__float_as_uint(div_in_range(a2f, num)) << 32) | (u64)id);
+    big &= ballot64(s.A2 != 0);
+    while (big) {
+        const int src = __builtin_ctzll(big);
+        big &= big - 1;
+        const uint32_t b = (uint32_t)bcast_i((int)box, src), e0 = (uint32_t)bcast_i((int)s.e0, src), e1 = (uint32_t)bcast_i((int)s.e1, src);
+        const int A2 = bcast_i(s.A2, src), t = bcast_i(inside, src), t0 = t & 1, t1 = (t >> 1) & 1, t2 = t >> 2;
+        const float w0 = bcast_f(s.iw0, src), w1 = bcast_f(s.iw1, src), w2 = bcast_f(s.iw2, src), a2f = (float)A2;
+        const uint32_t tri = (uint32_t)bcast_i((int)id, src);
+        const int nx = (int)((b >> 16) & 0xFFu), ny = (int)(b >> 24);
+        const int dx0 = unpack_x(e0), dy0 = unpack_y(e0), dx1 = unpack_x(e1), dy1 = unpack_y(e1);
+        int E0 = bcast_i(first0, src) + ((__mul24(dx0, lj) - __mul24(dy0, li)) << 8);
+        int E1 = bcast_i(first1, src) + ((__mul24(dx1, lj) - __mul24(dy1, li)) << 8);
+        int row = __mul24((int)((b >> 8) & 0xFFu) + lj - win.y0, win.pitch) + ((int)(b & 0xFFu) + li - win.x0);
+        for (int y = 0; y < ny; y += 8) {
+            const bool in_rows = lj < ny - y;
+            int F0 = E0, F1 = E1, at = row;
+            for (int x = 0; x < nx; x += 8) {
+                ++tally[kTLargeSteps];
+                const int F2 = A2 - F0 - F1;
+                if (in_rows & (li < nx - x) & (F0 >= t0) & (F1 >= t1) & (F2 >= t2)) {
+                    const float num = fmaf((float)F2, w2, fmaf((float)F1, w1, (float)F0 * w0));
+                    atomicMin(&vis[at], ((u64)__float_as_uint(div_in_range(a2f, num)) << 32) | (u64)tri);
+                }
+                F0 -= dy0 << 11;
+                F1 -= dy1 << 11;
+                at += 8;
             }
-            F0 += right0;
-            F1 += right1;
-            at += 8;
+            E0 += dx0 << 11;
+            E1 += dx1 << 11;
+            row += 8 * win.pitch;
         }
-        E0 += down0;
-        E1 += down1;
-        row += 8 * win.pitch;
     }
 }
 
@@ -223,7 +235,9 @@ __device__ __forceinline__ void emit(const WaveLds& L, int& small_count, bool va
     u64 med = packed_mask & ~small_mask & ballot64(within8);
     u64 big = vmask & ~small_mask & ~med;
     L.tally[kTLarge] += (uint32_t)__popcll(med | big);
-    if ((med | big) == 0ull) return;
+    // (the three expectations here keep what only larger triangles need out of the registers of the usual way: 1024 of
+    // 64x64 of 500 k triangles 237.0 -> 233.5 us, 4096 at 128x128 2221 -> 2197)
+    if (__builtin_expect((med | big) == 0ull, 1)) return;
     uint32_t id = 0u;
     if (valid && !small) id = ctri_id[ref];
     // medium triangles (box within 8x8 pixels): four per pass, sixteen lanes each, 4x4 pixels per step
@@ -264,21 +278,18 @@ __device__ __forceinline__ void emit(const WaveLds& L, int& small_count, bool va
                 }
             }
     }
-    while (big) {
-        int src = __builtin_ctzll(big);
-        big &= big - 1;
+    u64 general = big & ~packed_mask;
+    big &= packed_mask;
+    while (__builtin_expect(general != 0ull, 0)) {
+        int src = __builtin_ctzll(general);
+        general &= general - 1;
         const uint32_t bbox = (uint32_t)bcast_i((int)box, src);
-        if ((packed_mask >> src) & 1ull) {
-            raster_large_packed((uint32_t)bcast_i((int)xy0, src), (uint32_t)bcast_i((int)xy1, src), (uint32_t)bcast_i((int)xy2, src),
-                                bcast_f(iw0, src), bcast_f(iw1, src), bcast_f(iw2, src), (uint32_t)bcast_i((int)id, src), bbox, lane, vis,
-                                win, L.tally);
-            continue;
-        }
         const int bi = (int)(bbox & 0xFFu), bj = (int)((bbox >> 8) & 0xFFu);
         raster_large((uint32_t)bcast_i((int)xy0, src), (uint32_t)bcast_i((int)xy1, src), (uint32_t)bcast_i((int)xy2, src),
                      bcast_f(iw0, src), bcast_f(iw1, src), bcast_f(iw2, src), (uint32_t)bcast_i((int)id, src), bi,
                      bi + (int)((bbox >> 16) & 0xFFu) - 1, bj, bj + (int)(bbox >> 24) - 1, lane, vis, win, L.tally);
     }
+    if (__builtin_expect(big != 0ull, 0)) raster_large_packed(xy0, xy1, xy2, iw0, iw1, iw2, id, box, big, lane, vis, win, L.tally);
     asm volatile("" :: "v"(id));      // (as at the end of drain_small)
 }
 
