@@ -758,7 +758,8 @@ __device__ __forceinline__ void draw_clipped(const WaveLds& L, uint32_t ref, int
 // 274 -> 251 us; 4096 at 128x128 (1 M triangles): 2.70 -> 2.54 ms.  Of what remains a wavefront waits 40 % of its
 // time, most of it on LDS round trips: clusters come off the list ahead of their use, no load is left in flight that
 // only one path uses, and the planes of the box tests sit in LDS instead of registers (no vector register spilled in
-// the 64x64 instance, one in the 128x128 and the any-window one): 78.8 M instructions, 238 us; 2.27 ms.
+// the 64x64 instance, one in the 128x128 and the any-window one): 78.8 M instructions, 238 us; 2.27 ms.  With clusters of
+// smaller boxes and raster_large_packed: 238 -> 229 us; 2.29 -> 2.17 ms.
 template <int NT, bool DIAG, int CULL, int FRAME>
 __global__ __launch_bounds__(NT, 4) void k_raster(const SceneDev* __restrict__ scenes, const WorkItem* __restrict__ items,
                                                const float* __restrict__ view_proj, FrameParams fp,
