@@ -544,40 +544,18 @@ uint32_t largest_index(const uint32_t* indices, size_t n) {
     return *std::max_element(m, m + 8);
 }
 
-// Smallest and largest coordinates; false if one is not finite.  Four vertices at a time, on integers that order like
-// the floats, so that the compiler can use vector instructions.
-bool vertex_bounds(const float* v, uint32_t V, float (&lo)[3], float (&hi)[3]) {
-    int32_t mn[12], mx[12];
-    std::fill(mn, mn + 12, INT32_MAX);
-    std::fill(mx, mx + 12, INT32_MIN);
-    auto ordered = [](int32_t b) { return b ^ ((b >> 31) & INT32_MAX); };      // its own inverse
-    auto see = [&](const float* p, int n) {
-        int32_t b[12];
-        std::memcpy(b, p, (size_t)n * 4);
-        for (int k = 0; k < n; ++k) {
-            const int32_t o = ordered(b[k]);
-            mn[k] = o < mn[k] ? o : mn[k];
-            mx[k] = o > mx[k] ? o : mx[k];
-        }
-    };
+// (an infinity or a NaN has all bits of the exponent; integers, eight at a time, for vector instructions)
+bool all_finite(const float* v, size_t n) {
+    uint32_t m[8] = {};
     size_t i = 0;
-    const size_t n = 3 * (size_t)V;
-    for (; i + 12 <= n; i += 12) see(v + i, 12);
-    for (; i < n; i += 3) see(v + i, 3);
-    bool finite = true;
-    for (int a = 0; a < 3; ++a) {
-        int32_t l = mn[a], h = mx[a];
-        for (int k = a + 3; k < 12; k += 3) {
-            l = std::min(l, mn[k]);
-            h = std::max(h, mx[k]);
-        }
-        l = ordered(l);
-        h = ordered(h);
-        std::memcpy(&lo[a], &l, 4);
-        std::memcpy(&hi[a], &h, 4);
-        finite = finite && std::isfinite(lo[a]) && std::isfinite(hi[a]);      // infinities and NaNs lie at the ends
-    }
-    return finite;
+    auto see = [&](const float* p, int n) {
+        uint32_t b[8];
+        std::memcpy(b, p, (size_t)n * 4);
+        for (int k = 0; k < n; ++k) m[k] = std::max(m[k], b[k] & 0x7FFFFFFFu);
+    };
+    for (; i + 8 <= n; i += 8) see(v + i, 8);
+    for (; i < n; ++i) see(v + i, 1);
+    return *std::max_element(m, m + 8) < 0x7F800000u;
 }
 
 // Shared by the synchronous and asynchronous entry points: validate, cluster, lay every array out
@@ -597,8 +575,7 @@ bps_status load_scene_on(bps_renderer* r, const float* vertices, uint32_t V, con
         for (size_t i = 0; i < 3 * (size_t)T; ++i)
             if (indices[i] >= V)
                 return fail(r, BPS_ERR_INVALID_ARG, "bps_load_scene: index %u of triangle %zu is >= V=%u", indices[i], i / 3, V);
-    float lo[3], hi[3];
-    if (!vertex_bounds(vertices, V, lo, hi))
+    if (!all_finite(vertices, 3 * (size_t)V))
         for (size_t i = 0; i < 3 * (size_t)V; ++i)
             if (!std::isfinite(vertices[i]))
                 return fail(r, BPS_ERR_INVALID_ARG, "bps_load_scene: vertex %zu has a non-finite coordinate", i / 3);
@@ -606,7 +583,7 @@ bps_status load_scene_on(bps_renderer* r, const float* vertices, uint32_t V, con
     // the long host-side steps (clustering, filling the pinned image) run without the lock
     std::unique_ptr<bps::SceneClusters> clusters;
     try {
-        clusters.reset(new bps::SceneClusters(vertices, V, indices, T, lo, hi, bps::chunk_triangles(T, waits)));
+        clusters.reset(new bps::SceneClusters(vertices, indices, T, bps::chunk_triangles(T, waits)));
     } catch (const std::exception&) {      // (allocations are all that throws in there)
         return fail(r, BPS_ERR_OOM, "bps_load_scene: out of host memory while clustering");
     }

@@ -411,7 +411,9 @@ unsigned usable_cpus() {
     return (unsigned)std::max(1, CPU_COUNT(&set));
 }
 
-// A triangle on its way into a chunk: centroid in units of the mesh's longest side, from its smallest corner.
+// A triangle on its way into a chunk: centroid relative to a place among the triangles, times 3/64 (so that neither sums nor
+// differences of finite numbers overflow).  The place is a median, so that a few triangles far away, which a box would have to
+// hold, cost the others none of their precision.
 struct Item {
     float c[3];
     uint32_t tri;
@@ -430,21 +432,35 @@ void cut(const uint32_t* count, size_t n, uint32_t parts, uint32_t* slab) {
         before += count[s];
     }
 }
+struct Box {
+    float lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY};
+    void add(const float (&c)[3]) {
+        for (int a = 0; a < 3; ++a) {
+            lo[a] = std::min(lo[a], c[a]);
+            hi[a] = std::max(hi[a], c[a]);
+        }
+    }
+    int longest() const {
+        int axis = 0;
+        for (int a = 1; a < 3; ++a)
+            if (hi[a] - lo[a] > hi[axis] - lo[axis]) axis = a;
+        return axis;
+    }
+};
+// Steps of equal length along the longest side of a box.
+struct Steps {
+    explicit Steps(const Box& box) : axis(box.longest()), base(box.lo[axis]), scale(((float)kSteps - 0.5f) / std::max(box.hi[axis] - base, 1e-30f)) {}
+    uint32_t of(const Item& it) const { return std::min((uint32_t)((it.c[axis] - base) * scale), kSteps - 1); }
+    int axis;
+    float base, scale;
+};
 // Cuts in[r] into `parts` slabs along the longest side of its centroids' box and puts them into out[r] one after the other.
 std::vector<Range> slabs(const Item* in, Item* out, Range r, uint32_t parts) {
-    float lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY};
-    for (size_t i = r.first; i < r.last; ++i)
-        for (int a = 0; a < 3; ++a) {
-            lo[a] = std::min(lo[a], in[i].c[a]);
-            hi[a] = std::max(hi[a], in[i].c[a]);
-        }
-    int axis = 0;
-    for (int a = 1; a < 3; ++a)
-        if (hi[a] - lo[a] > hi[axis] - lo[axis]) axis = a;
-    const float base = lo[axis], scale = ((float)kSteps - 0.5f) / std::max(hi[axis] - lo[axis], 1e-30f);
-    auto step = [&](const Item& it) { return std::min((uint32_t)((it.c[axis] - base) * scale), kSteps - 1); };
+    Box box;
+    for (size_t i = r.first; i < r.last; ++i) box.add(in[i].c);
+    const Steps steps(box);
     std::vector<uint32_t> count(kSteps, 0), slab(kSteps);
-    for (size_t i = r.first; i < r.last; ++i) ++count[step(in[i])];
+    for (size_t i = r.first; i < r.last; ++i) ++count[steps.of(in[i])];
     cut(count.data(), r.last - r.first, parts, slab.data());
     std::vector<size_t> at(parts, 0);
     for (uint32_t k = 0; k < kSteps; ++k) at[slab[k]] += count[k];
@@ -456,8 +472,27 @@ std::vector<Range> slabs(const Item* in, Item* out, Range r, uint32_t parts) {
         if (size) made.push_back({first, first + size});
         first += size;
     }
-    for (size_t i = r.first; i < r.last; ++i) out[at[slab[step(in[i])]]++] = in[i];
+    for (size_t i = r.first; i < r.last; ++i) out[at[slab[steps.of(in[i])]]++] = in[i];
     return made;
+}
+// Halves a range at the median along its longest side until no part has more than `most` triangles.  For what steps of equal
+// length do not separate: most triangles on one of them, because a few lie far away or because all have one place.
+void halve(Item* items, Range r, size_t most, bool whole, std::vector<Range>& made) {
+    if (r.last - r.first <= most) {
+        // (a median may leave its two sides in any order; chunks are grown from triangles in the order of their numbers)
+        if (!whole) std::sort(items + r.first, items + r.last, [](const Item& x, const Item& y) { return x.tri < y.tri; });
+        made.push_back(r);
+        return;
+    }
+    Box box;
+    for (size_t i = r.first; i < r.last; ++i) box.add(items[i].c);
+    const int axis = box.longest();
+    const size_t mid = r.first + (r.last - r.first) / 2;
+    std::nth_element(items + r.first, items + mid, items + r.last, [axis](const Item& x, const Item& y) {
+        return x.c[axis] < y.c[axis] || (x.c[axis] == y.c[axis] && x.tri < y.tri);
+    });
+    halve(items, {r.first, mid}, most, false, made);
+    halve(items, {mid, r.last}, most, false, made);
 }
 
 // A chunk's vertices by number of first use.
@@ -717,44 +752,48 @@ struct SceneClusters::Impl {
     explicit Impl(unsigned threads) : team(threads) {}
 };
 
-SceneClusters::SceneClusters(const float* vertices, uint32_t V, const uint32_t* indices, uint32_t T, const float (&lo)[3],
-                             const float (&hi)[3], uint32_t chunk_tris)
-    : impl_(nullptr) {
-    (void)V;
+SceneClusters::SceneClusters(const float* vertices, const uint32_t* indices, uint32_t T, uint32_t chunk_tris) : impl_(nullptr) {
     const uint32_t n_chunks = T / chunk_tris + (T % chunk_tris ? 1 : 0);
     // (a chunk of less than 1024 triangles is done before a second thread has started)
     std::unique_ptr<Impl> impl(new Impl(T < 2048 ? 1u : std::min({kMostThreads, usable_cpus(), std::max(n_chunks, T / 65536u)})));
     Team& team = impl->team;
-    // halves, so that no difference of finite numbers overflows
-    float longest = 1e-30f;
-    int axis = 0;
-    for (int x = 0; x < 3; ++x)
-        if (0.5f * hi[x] - 0.5f * lo[x] > longest) {
-            longest = 0.5f * hi[x] - 0.5f * lo[x];
-            axis = x;
-        }
-    const float unit = 1.0f / longest;
+    float origin[3];
+    for (int x = 0; x < 3; ++x) {
+        constexpr size_t kSamples = 63;
+        float sample[kSamples];
+        for (size_t k = 0; k < kSamples; ++k) sample[k] = vertices[3 * (size_t)indices[3 * (k * T / kSamples)] + x];
+        std::nth_element(sample, sample + kSamples / 2, sample + kSamples);
+        origin[x] = sample[kSamples / 2] * (1.0f / 64.0f);
+    }
     std::unique_ptr<Item[]> a(new Item[T]), b(n_chunks > 1 ? new Item[T] : nullptr);
     constexpr size_t kBatch = 8192;
     const size_t batches = ((size_t)T + kBatch - 1) / kBatch;
-    auto step = [&](const Item& it) { return std::min((uint32_t)(it.c[axis] * ((float)kSteps - 0.5f)), kSteps - 1); };
-    std::vector<uint32_t> counts(n_chunks > 1 ? batches * kSteps : 0, 0);      // by batch: triangles on each step
+    std::vector<Box> boxes(batches);
     team.run(batches, [&](size_t k) {
         for (size_t t = k * kBatch; t < std::min<size_t>(T, (k + 1) * kBatch); ++t) {
             Item& it = a[t];
             it.tri = (uint32_t)t;
             for (int x = 0; x < 3; ++x) {
                 float c = 0.0f;
-                for (int j = 0; j < 3; ++j) c += (0.5f * vertices[3 * (size_t)indices[3 * t + j] + x] - 0.5f * lo[x]) * unit;
-                it.c[x] = c * (1.0f / 3.0f);
+                for (int j = 0; j < 3; ++j) c += vertices[3 * (size_t)indices[3 * t + j] + x] * (1.0f / 64.0f) - origin[x];
+                it.c[x] = c;
             }
-            if (n_chunks > 1) ++counts[k * kSteps + step(it)];
+            boxes[k].add(it.c);
         }
     });
     // ---- slabs along the longest side, each cut into slabs again: near-cubes of about the same number of triangles
     std::vector<Range> ranges{{0, T}};
-    const Item* items = a.get();
+    Item* items = a.get();
     if (n_chunks > 1) {
+        for (size_t k = 1; k < batches; ++k) {
+            boxes[0].add(boxes[k].lo);
+            boxes[0].add(boxes[k].hi);
+        }
+        const Steps steps(boxes[0]);
+        std::vector<uint32_t> counts(batches * kSteps, 0);      // by batch: triangles on each step
+        team.run(batches, [&](size_t k) {
+            for (size_t t = k * kBatch; t < std::min<size_t>(T, (k + 1) * kBatch); ++t) ++counts[k * kSteps + steps.of(a[t])];
+        });
         const uint32_t first_cut = n_chunks <= 3 ? n_chunks : (uint32_t)std::ceil(std::sqrt((double)n_chunks));
         std::vector<uint32_t> all(kSteps, 0), slab(kSteps);
         for (size_t k = 0; k < batches; ++k)
@@ -775,19 +814,18 @@ SceneClusters::SceneClusters(const float* vertices, uint32_t V, const uint32_t* 
             if (first > from) ranges.push_back({from, first});
         }
         team.run(batches, [&](size_t k) {
-            for (size_t t = k * kBatch; t < std::min<size_t>(T, (k + 1) * kBatch); ++t) b[at[k * first_cut + slab[step(a[t])]]++] = a[t];
+            for (size_t t = k * kBatch; t < std::min<size_t>(T, (k + 1) * kBatch); ++t) b[at[k * first_cut + slab[steps.of(a[t])]]++] = a[t];
         });
-        items = b.get();
-        if (n_chunks > 3) {
-            std::vector<std::vector<Range>> parts(ranges.size());
-            team.run(ranges.size(), [&](size_t k) {
-                const size_t n = ranges[k].last - ranges[k].first;
-                parts[k] = slabs(b.get(), a.get(), ranges[k], (uint32_t)std::max<size_t>(1, (n + chunk_tris / 2) / chunk_tris));
-            });
-            ranges.clear();
-            for (const auto& p : parts) ranges.insert(ranges.end(), p.begin(), p.end());
-            items = a.get();
-        }
+        items = n_chunks > 3 ? a.get() : b.get();
+        std::vector<std::vector<Range>> parts(ranges.size());
+        team.run(ranges.size(), [&](size_t k) {
+            std::vector<Range> made{ranges[k]};
+            const size_t n = ranges[k].last - ranges[k].first;
+            if (n_chunks > 3) made = slabs(b.get(), a.get(), ranges[k], (uint32_t)std::max<size_t>(1, (n + chunk_tris / 2) / chunk_tris));
+            for (Range r : made) halve(items, r, 2 * (size_t)chunk_tris, true, parts[k]);
+        });
+        ranges.clear();
+        for (const auto& p : parts) ranges.insert(ranges.end(), p.begin(), p.end());
     }
     impl->chunks.resize(ranges.size());
     team.run(ranges.size(), [&](size_t k) {

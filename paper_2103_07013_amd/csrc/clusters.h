@@ -52,9 +52,8 @@ inline uint32_t chunk_triangles(uint32_t T, bool caller_waits) {
 
 class SceneClusters {
 public:
-    // lo, hi: smallest and largest coordinates; all of them finite.
-    SceneClusters(const float* vertices, uint32_t V, const uint32_t* indices, uint32_t T, const float (&lo)[3],
-                  const float (&hi)[3], uint32_t chunk_tris);
+    // Every coordinate finite, every index that of a vertex.
+    SceneClusters(const float* vertices, const uint32_t* indices, uint32_t T, uint32_t chunk_tris);
     ~SceneClusters();
     uint32_t count() const { return (uint32_t)order_.size(); }
     // Copies the clusters out, in the order the renderer wants; arrays as in ClusterSet, bounds in six planes of

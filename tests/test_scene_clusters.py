@@ -12,10 +12,9 @@ import synth
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 SHIM = """
 #include "clusters.h"
-extern "C" unsigned pack(const float* v, unsigned V, const unsigned* i, unsigned T, const float* lo, const float* hi, unsigned chunk,
-                         unsigned room, float* verts, unsigned* tris, unsigned* ids, float* bounds) {
-    const float l[3] = {lo[0], lo[1], lo[2]}, h[3] = {hi[0], hi[1], hi[2]};
-    bps::SceneClusters c(v, V, i, T, l, h, chunk);
+extern "C" unsigned pack(const float* v, const unsigned* i, unsigned T, unsigned chunk, unsigned room, float* verts, unsigned* tris,
+                         unsigned* ids, float* bounds) {
+    bps::SceneClusters c(v, i, T, chunk);
     if (c.count() <= room) c.write(verts, tris, ids, bounds, room);
     return c.count();
 }
@@ -37,9 +36,8 @@ def _pack(lib, v, t, chunk):
     T, room = len(t), len(t) // 21 + 64 + 2 * (len(t) // chunk)      # a cluster that is full holds 21 triangles or more
     verts, tris = np.zeros((room, 3, 64), np.float32), np.zeros((room, 128), np.uint32)
     ids, bounds = np.zeros((room, 128), np.uint32), np.zeros((6, room), np.float32)
-    lo, hi = v.min(0).copy(), v.max(0).copy()
-    p = [a.ctypes.data_as(ctypes.c_void_p) for a in (v, t, lo, hi, verts, tris, ids, bounds)]
-    C = lib.pack(p[0], len(v), p[1], T, p[2], p[3], chunk, room, *p[4:])
+    p = [a.ctypes.data_as(ctypes.c_void_p) for a in (v, t, verts, tris, ids, bounds)]
+    C = lib.pack(p[0], p[1], T, chunk, room, *p[2:])
     assert 0 < C <= room
     return verts[:C], tris[:C], ids[:C], bounds[:, :C]
 
@@ -80,6 +78,33 @@ def test_every_triangle_is_in_one_cluster(lib, kind, chunk):
     assert np.array_equal(bounds[:3], verts.min(2).T) and np.array_equal(bounds[3:], verts.max(2).T)
     again = _pack(lib, v, t, chunk)      # whichever thread takes which chunk
     assert all(np.array_equal(a, b) for a, b in zip(again, (verts, tris, ids, bounds)))
+
+
+def _faces(bounds):
+    """Sum of the faces of all boxes, as the renderer's tests see them."""
+    d = bounds[3:].astype(np.float64) - bounds[:3]
+    return (d[0] * d[1] + d[1] * d[2] + d[2] * d[0]).sum()
+
+
+@pytest.mark.parametrize("far", [-1e30, -1e8, 1e8, 1e30])
+def test_a_vertex_that_no_triangle_uses_changes_nothing(lib, far):
+    v, t = (np.ascontiguousarray(a, d) for a, d in zip(_mesh("scan"), (np.float32, np.uint32)))
+    for chunk in (1500, 1 << 20):
+        a, b = _pack(lib, v, t, chunk), _pack(lib, np.concatenate([v, np.full((1, 3), far, np.float32)]), t, chunk)
+        assert all(np.array_equal(x, y) for x, y in zip(a, b))
+
+
+@pytest.mark.parametrize("far", [-1e8, 1e8])
+@pytest.mark.parametrize("at", [0, -1])
+def test_a_triangle_far_away_leaves_the_others_their_chunks(lib, far, at):
+    """Whether it is the first or the last of them.  The clusters are as small as without it, but for its own."""
+    v, t = (np.ascontiguousarray(a, d) for a, d in zip(_mesh("scan"), (np.float32, np.uint32)))
+    clean = _pack(lib, v, t, 1500)
+    more = np.array([[far, 0, 0], [far, 1e3, 0], [far, 0, 1e3]], np.float32)
+    t2 = np.insert(t, 0 if at == 0 else len(t), np.arange(len(v), len(v) + 3, dtype=np.uint32), axis=0)
+    _, _, ids, bounds = _pack(lib, np.concatenate([v, more]), t2, 1500)
+    rest = bounds[:, ~(ids == (0 if at == 0 else len(t))).any(1)]
+    assert _faces(rest) < 1.1 * _faces(clean[3]) and rest.shape[1] < 1.1 * clean[3].shape[1]
 
 
 def test_chunks_are_neither_empty_nor_too_many(lib):
