@@ -3,6 +3,7 @@ number of chunks it is cut into.  clusters.cpp is compiled by itself: no GPU is 
 import ctypes
 import os
 import subprocess
+import time
 
 import numpy as np
 import pytest
@@ -105,6 +106,25 @@ def test_a_triangle_far_away_leaves_the_others_their_chunks(lib, far, at):
     _, _, ids, bounds = _pack(lib, np.concatenate([v, more]), t2, 1500)
     rest = bounds[:, ~(ids == (0 if at == 0 else len(t))).any(1)]
     assert _faces(rest) < 1.1 * _faces(clean[3]) and rest.shape[1] < 1.1 * clean[3].shape[1]
+
+
+@pytest.mark.parametrize("place", ["spread", "one"])
+def test_loose_triangles_take_time_in_proportion(lib, place):
+    """No two connected, in one chunk: four times as many take about four times as long (where every cluster looks at
+    all groups of the chunk, nine times or more; seven lies between)."""
+    def best(n):
+        rng = np.random.default_rng(5)
+        c = rng.uniform(-5, 5, (n if place == "spread" else 1, 1, 3))
+        v = np.ascontiguousarray(np.resize(c + rng.normal(0, 0.03, (len(c), 3, 3)), (3 * n, 3)), np.float32)
+        t = np.arange(3 * n, dtype=np.uint32).reshape(-1, 3)
+        p = [a.ctypes.data_as(ctypes.c_void_p) for a in (v, t)]
+        times = []
+        for _ in range(2):
+            t0 = time.perf_counter()
+            lib.pack(*p, n, 1 << 20, 0, None, None, None, None)
+            times.append(time.perf_counter() - t0)
+        return min(times)
+    assert best(360_000) < 7 * best(90_000)
 
 
 def test_chunks_are_neither_empty_nor_too_many(lib):
