@@ -793,16 +793,19 @@ SceneClusters::SceneClusters(const float* vertices, const uint32_t* indices, uin
     const size_t batches = ((size_t)T + kBatch - 1) / kBatch;
     std::vector<Box> boxes(batches);
     team.run(batches, [&](size_t k) {
+        Box box;      // (in registers: neighbouring batches' boxes share cache lines)
         for (size_t t = k * kBatch; t < std::min<size_t>(T, (k + 1) * kBatch); ++t) {
-            Item& it = a[t];
+            Item it;
             it.tri = (uint32_t)t;
             for (int x = 0; x < 3; ++x) {
                 float c = 0.0f;
                 for (int j = 0; j < 3; ++j) c += vertices[3 * (size_t)indices[3 * t + j] + x] * (1.0f / 64.0f) - origin[x];
                 it.c[x] = c;
             }
-            boxes[k].add(it.c);
+            box.add(it.c);
+            a[t] = it;
         }
+        boxes[k] = box;
     });
     // ---- slabs along the longest side, each cut into slabs again: near-cubes of about the same number of triangles
     std::vector<Range> ranges{{0, T}};
