@@ -128,8 +128,8 @@ bps_status bps_load_scene_textured(bps_renderer *r, const float *vertices, uint3
                                    uint32_t T, const float *uvs, const uint8_t *texels, uint32_t tex_w,
                                    uint32_t tex_h, void *copy_stream, bps_scene *out_handle);
 
-/* Host-only helper (no GPU needed): re-pack a mesh into the clusters bps_load_scene works with (same
- * limits and arrays; scenes are packed in parallel chunks, which choose other seeds) and copy the
+/* Host-only helper (no GPU needed): re-pack a mesh exactly as bps_load_scene does (a load on a stream
+ * of the caller's cuts large meshes finer, into other clusters of the same triangles) and copy the
  * cluster arrays out, for tests and tools.  On entry *count is the capacity of the output
  * arrays in clusters (ignored when all three are NULL); on return it is the cluster count.
  *   verts_out [count][3][64] float32   x, y, z planes; unused lanes repeat the first vertex

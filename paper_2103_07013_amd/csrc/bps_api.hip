@@ -842,19 +842,16 @@ bps_status bps_pack_clusters(const float* vertices, uint32_t V, const uint32_t* 
     if (!vertices || !indices || !count || V == 0 || T == 0) return BPS_ERR_INVALID_ARG;
     for (size_t i = 0; i < 3 * (size_t)T; ++i)
         if (indices[i] >= V) return BPS_ERR_INVALID_ARG;
-    bps::ClusterSet cs;
     try {
-        cs = bps::build_clusters(vertices, V, indices, T);
-    } catch (const std::bad_alloc&) {
+        bps::SceneClusters cs(vertices, indices, T, bps::chunk_triangles(T, true));
+        const uint32_t room = *count;
+        *count = cs.count();
+        if (!verts_out && !tris_out && !ids_out) return BPS_OK;
+        if (room < cs.count()) return BPS_ERR_INVALID_ARG;
+        cs.write(verts_out, tris_out, ids_out, nullptr, 0);
+    } catch (const std::exception&) {      // (allocations are all that throws in there)
         return BPS_ERR_OOM;
     }
-    const uint32_t room = *count;
-    *count = cs.count;
-    if (!verts_out && !tris_out && !ids_out) return BPS_OK;
-    if (room < cs.count) return BPS_ERR_INVALID_ARG;
-    if (verts_out) std::memcpy(verts_out, cs.verts.data(), cs.verts.size() * sizeof(float));
-    if (tris_out) std::memcpy(tris_out, cs.tris.data(), cs.tris.size() * sizeof(uint32_t));
-    if (ids_out) std::memcpy(ids_out, cs.tri_id.data(), cs.tri_id.size() * sizeof(uint32_t));
     return BPS_OK;
 }
 

@@ -15,38 +15,22 @@ namespace bps {
 constexpr uint32_t kClusterVerts = 64;
 constexpr uint32_t kClusterTris = 128;
 
-struct ClusterSet {
-    uint32_t count = 0;
-    // per cluster: x[64], y[64], z[64]; unused lanes repeat the cluster's first vertex
-    std::vector<float> verts;
-    // per cluster: 128 words, local indices i0 | i1 << 8 | i2 << 16; unused slots are 0 (a
-    // degenerate triangle); bits 24..31 of word 0 hold the number of used slots
-    std::vector<uint32_t> tris;
-    // per cluster: 128 words, row of the triangle in the caller's index array (0xFFFFFFFF unused)
-    std::vector<uint32_t> tri_id;
-    // per cluster: axis-aligned bounds, min xyz then max xyz
-    std::vector<float> bounds;
-};
-
-// vertices [V][3], indices [T][3]; every index must already be < V.
-ClusterSet build_clusters(const float* vertices, uint32_t V, const uint32_t* indices, uint32_t T);
-
-// The clusters of a scene that is being loaded.  The mesh is cut into chunks, which are turned into clusters side by
-// side on up to kMostThreads threads, by the rule of build_clusters with two differences: a cluster's seed is the
-// triangle that comes first along the diagonal of its chunk, and where nothing connected is left the triangle nearest to
-// the seed stands in.  Both make the clusters' boxes smaller; chunks cost a few clusters along their borders.
-//   500 k triangles   build_clusters   5370 clusters, faces of their boxes 1.85 times the mesh's area   29.5 ms
-//                     chunks of 65536  5350, 1.57                                                        9.8 ms
-//                     chunks of 16384  5410, 1.66                                                        6.2 ms
-//   100 k             build_clusters   1136, 2.21                                                        5.5 ms
-//                     chunks of 8192   1149, 1.82
+// The clusters of a scene.  The mesh is cut into chunks, which are turned into clusters side by side on up to kMostThreads
+// threads: a cluster's seed is the triangle that comes first along the diagonal of its chunk, and where nothing connected
+// is left the triangle nearest to the seed stands in.  Chunks cost a few clusters along their borders.  Against the whole
+// mesh by one thread, seeds and stand-ins along a Morton curve ("whole"; clusters, faces of their boxes over the mesh's
+// area, time):
+//   500 k triangles   whole 5370, 1.85, 29.5 ms   chunks of 65536 5350, 1.57, 9.8 ms   of 16384 5410, 1.66, 6.2 ms
+//   100 k             whole 1136, 2.21, 5.5 ms    chunks of 8192  1149, 1.82
 // Frames: 1024 of 64x64 242 -> 234 us, 256 of 64x64 (200 k triangles) 97 -> 93, 1024 RGB-D (1 M triangles) 404 -> 391.
+// What chunks cost more than that are meshes whose neighbours lie anywhere (a fan of 200 k triangles with its rim's
+// vertices at random: whole 3340 clusters in 920 ms, chunks 5054 in 149 ms or 5828 in 69).
 constexpr uint32_t kMostThreads = 12;
 // Triangles per chunk: when the caller waits for the scene anyway, and when it is only to be on its way soon (a share
-// of the mesh for every thread, but chunks no smaller than the clusters of build_clusters are matched by).  Small meshes
-// come in two or three chunks either way: in one, which one thread works through, they took longer than with
-// build_clusters, and more chunks than that cost clusters.
-//   40 k triangles   build_clusters 5.3 ms, one chunk 8.3, three 4.3 (faces of the boxes 4920, 3967, 3993)
+// of the mesh for every thread, but no chunks that would cost more clusters than "whole").  Small meshes come in two or
+// three chunks either way: in one, which one thread works through, they took longer than "whole", and more chunks than
+// that cost clusters.
+//   40 k triangles   whole 5.3 ms, one chunk 8.3, three 4.3 (faces of the boxes 4920, 3967, 3993)
 //   10 k             2.2, 3.0, two 1.8 (4879, 3702, 3677)
 //   4 k              0.8, 1.0, two 0.7 (804, 631, 680); below 2048 a second thread would start too late
 inline uint32_t chunk_triangles(uint32_t T, bool caller_waits) {
@@ -59,12 +43,17 @@ inline uint32_t chunk_triangles(uint32_t T, bool caller_waits) {
 
 class SceneClusters {
 public:
-    // Every coordinate finite, every index that of a vertex.
+    // vertices [V][3], indices [T][3]; every index has to be that of a vertex.
     SceneClusters(const float* vertices, const uint32_t* indices, uint32_t T, uint32_t chunk_tris);
     ~SceneClusters();
     uint32_t count() const { return (uint32_t)order_.size(); }
-    // Copies the clusters out, in the order the renderer wants; arrays as in ClusterSet, bounds in six planes of
-    // `stride` values.
+    // Copies the clusters out, in the order the renderer wants:
+    //   verts   [count][3][64]  x, y, z planes; unused lanes repeat the cluster's first vertex
+    //   tris    [count][128]    local indices i0 | i1 << 8 | i2 << 16, 0 in unused slots; how many are used in bits 24..31
+    //                           of a cluster's first word
+    //   tri_id  [count][128]    row of the triangle in the caller's index array, 0xFFFFFFFF in unused slots
+    //   bounds  [6][stride]     axis-aligned, min xyz then max xyz
+    // Null arrays are left out.
     void write(float* verts, uint32_t* tris, uint32_t* tri_id, float* bounds, size_t stride);
 
 private:

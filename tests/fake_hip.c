@@ -18,6 +18,8 @@ static int g_n_vars;
 static char g_log[1 << 20];
 static size_t g_log_at;
 
+static const void* g_scenes;      /* the scene table of the last k_raster */
+const void* fake_scenes(void) { return g_scenes; }
 const char* fake_log(void) { return g_log; }
 void fake_clear_log(void) { g_log[g_log_at = 0] = 0; }
 
@@ -73,6 +75,7 @@ static hipError_t run(const void* f, dim3 grid, dim3 block, void** args, size_t 
     } else if (strstr(name, "k_raster")) {           /* (scenes, items, view_proj, ...) */
         /* shared: work-groups whose item names no share of the scene, or one drawn by another group already */
         const item* items = ARG(const item*, 1);
+        g_scenes = ARG(const void*, 0);
         uint32_t envs = 0, tiles = 0, wrong = 0;
         uint8_t* seen = (uint8_t*)calloc(1, 65536u * 64u);
         for (uint32_t k = 0; k < grid.x; ++k) {
