@@ -73,6 +73,7 @@ struct Staging {      // pinned host image of a scene being copied
     void* ptr = nullptr;
     size_t bytes = 0;
     hipEvent_t done = nullptr;
+    bool taken = false;           // by a load that is still on the host
 };
 
 struct RingSlot {
@@ -154,7 +155,11 @@ bps_status fail(bps_renderer* r, bps_status code, const char* fmt, ...) {
     va_end(ap);
     if (r) {
         std::lock_guard<std::mutex> g(r->err_mu);
-        r->error = buf;
+        try {
+            r->error = buf;
+        } catch (const std::bad_alloc&) {
+            r->error.clear();
+        }
     } else {
         g_create_error = buf;
     }
@@ -203,6 +208,11 @@ void collect(bps_renderer* r) {
         if (s.pending && hipEventQuery(s.done) == hipSuccess) s.pending = false;
     (void)hipGetLastError();
     note_completions(r);
+    try {
+        r->arena_pool.reserve(r->arena_pool.size() + r->retired.size());
+    } catch (const std::bad_alloc&) {
+        return;      // another time
+    }
     for (size_t i = 0; i < r->retired.size();) {
         Retired& x = r->retired[i];
         if (x.upload && hipEventQuery(x.upload) == hipSuccess) {
@@ -506,8 +516,8 @@ void bps_destroy(bps_renderer* r) {
     }
     for (Arena& x : r->arena_pool) (void)hipFree(x.ptr);
     for (Staging& x : r->staging) {
-        (void)hipHostFree(x.ptr);
-        (void)hipEventDestroy(x.done);
+        if (x.ptr) (void)hipHostFree(x.ptr);
+        if (x.done) (void)hipEventDestroy(x.done);
     }
     if (r->load_stream) (void)hipStreamDestroy(r->load_stream);
     if (r->plan_stream) (void)hipStreamDestroy(r->plan_stream);
@@ -619,22 +629,45 @@ bps_status load_scene_on(bps_renderer* r, const float* vertices, uint32_t V, con
     const size_t img_bytes = off;
 
     // ---- pinned image: reuse one whose copy has finished, else allocate
-    Staging stg;
     std::unique_lock<std::mutex> lock(r->mu);
-    for (size_t i = 0; i < r->staging.size(); ++i)
-        if (r->staging[i].bytes >= img_bytes && hipEventQuery(r->staging[i].done) == hipSuccess) {
-            stg = r->staging[i];
-            r->staging[i] = r->staging.back();
-            r->staging.pop_back();
+    size_t image = r->staging.size();      // its place in the list, which only grows
+    for (size_t i = 0; i < r->staging.size(); ++i) {
+        const Staging& s = r->staging[i];
+        if (s.taken) continue;
+        if (!s.ptr) {
+            image = i;      // a place whose allocation failed
+        } else if (s.bytes >= img_bytes && hipEventQuery(s.done) == hipSuccess) {
+            image = i;
             break;
         }
+    }
     (void)hipGetLastError();
+    if (image == r->staging.size()) {
+        try {
+            r->staging.emplace_back();
+        } catch (const std::bad_alloc&) {
+            return fail(r, BPS_ERR_OOM, "bps_load_scene: out of host memory");
+        }
+    }
+    r->staging[image].taken = true;
+    Staging stg = r->staging[image];
     lock.unlock();
+    auto give_back = [&] {      // (holding the lock)
+        stg.taken = false;
+        if (stg.done) (void)hipEventRecord(stg.done, stream);
+        r->staging[image] = stg;
+    };
     if (!stg.ptr) {
-        BPS_HIP(r, hipHostMalloc(&stg.ptr, img_bytes, hipHostMallocDefault));
+        hipError_t e = stg.done ? hipSuccess : hipEventCreateWithFlags(&stg.done, hipEventDisableTiming);
+        if (e == hipSuccess) e = hipHostMalloc(&stg.ptr, img_bytes, hipHostMallocDefault);
+        if (e != hipSuccess) {
+            (void)hipGetLastError();
+            stg.ptr = nullptr;
+            lock.lock();
+            give_back();
+            return fail(r, e == hipErrorOutOfMemory ? BPS_ERR_OOM : BPS_ERR_HIP, "bps_load_scene: hipHostMalloc(%zu): %s", img_bytes, hipGetErrorString(e));
+        }
         stg.bytes = img_bytes;
-        hipError_t e = hipEventCreateWithFlags(&stg.done, hipEventDisableTiming);
-        if (e != hipSuccess) { (void)hipHostFree(stg.ptr); return fail(r, BPS_ERR_HIP, "bps_load_scene: %s", hipGetErrorString(e)); }
     }
     unsigned char* img = (unsigned char*)stg.ptr;
     float* cb = (float*)(img + o_cb);
@@ -693,13 +726,18 @@ bps_status load_scene_on(bps_renderer* r, const float* vertices, uint32_t V, con
         if (!r->scenes[i].live && !slot_busy(r, (int)i)) { slot = (int)i; break; }
     if (slot < 0) {
         if ((int)r->scenes.size() >= kMaxScenes) {
-            r->staging.push_back(stg);
-            (void)hipEventRecord(stg.done, stream);
+            give_back();
             return fail(r, BPS_ERR_OOM, "bps_load_scene: scene table full (%d)", kMaxScenes);
         }
         slot = (int)r->scenes.size();
-        r->scenes.emplace_back();
-        r->gens.push_back(0u);
+    }
+    try {      // (room for whatever is added from here on, so that nothing below throws)
+        r->scenes.resize(std::max(r->scenes.size(), (size_t)slot + 1));
+        r->gens.resize(r->scenes.size(), 0u);
+        r->arena_pool.reserve(r->arena_pool.size() + 1);
+    } catch (const std::bad_alloc&) {
+        give_back();
+        return fail(r, BPS_ERR_OOM, "bps_load_scene: out of host memory");
     }
     Arena arena;
     int best = -1;
@@ -716,8 +754,7 @@ bps_status load_scene_on(bps_renderer* r, const float* vertices, uint32_t V, con
         arena.bytes = (dev_bytes + step - 1) / step * step;
         hipError_t e = hipMalloc(&arena.ptr, arena.bytes);
         if (e != hipSuccess) {
-            r->staging.push_back(stg);
-            (void)hipEventRecord(stg.done, stream);
+            give_back();
             return fail(r, e == hipErrorOutOfMemory ? BPS_ERR_OOM : BPS_ERR_HIP, "bps_load_scene: hipMalloc(%zu): %s", arena.bytes,
                         hipGetErrorString(e));
         }
@@ -751,8 +788,7 @@ bps_status load_scene_on(bps_renderer* r, const float* vertices, uint32_t V, con
 
     auto undo = [&](hipError_t e, const char* what) {
         r->arena_pool.push_back(arena);
-        r->staging.push_back(stg);
-        (void)hipEventRecord(stg.done, stream);
+        give_back();
         return fail(r, BPS_ERR_HIP, "bps_load_scene: %s: %s", what, hipGetErrorString(e));
     };
     hipError_t e = hipMemcpyAsync(d, img, copy_bytes, hipMemcpyHostToDevice, stream);
@@ -767,8 +803,7 @@ bps_status load_scene_on(bps_renderer* r, const float* vertices, uint32_t V, con
     e = hipEventCreateWithFlags(&hs.ready, hipEventDisableTiming);
     if (e != hipSuccess) return undo(e, "event");
     (void)hipEventRecord(hs.ready, stream);
-    (void)hipEventRecord(stg.done, stream);
-    r->staging.push_back(stg);
+    give_back();
     hs.live = true;
     r->scenes[slot] = hs;
     r->plan_ids.clear();

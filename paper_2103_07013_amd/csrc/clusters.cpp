@@ -15,6 +15,7 @@
 #include <mutex>
 #include <numeric>
 #include <thread>
+#include <type_traits>
 
 namespace bps {
 namespace {
@@ -164,10 +165,13 @@ public:
         wake_.notify_all();
         for (std::thread& t : workers_) t.join();
     }
-    void run(size_t n, const std::function<void(size_t)>& task) {
+    // (the task is only referred to: run() itself allocates nothing and throws what a task throws)
+    template <class Task>
+    void run(size_t n, Task&& task) {
+        const Call call{[](void* t, size_t k) { (*static_cast<std::remove_reference_t<Task>*>(t))(k); }, &task};
         {
             std::lock_guard<std::mutex> g(mu_);
-            task_ = &task;
+            task_ = &call;
             n_ = n;
             next_ = 0;
             failed_ = nullptr;
@@ -182,12 +186,16 @@ public:
     }
 
 private:
+    struct Call {
+        void (*of)(void*, size_t);
+        void* task;
+    };
     void take() {
         for (;;) {
             const size_t k = next_.fetch_add(1);
             if (k >= n_) return;
             try {
-                (*task_)(k);
+                task_->of(task_->task, k);
             } catch (...) {
                 std::lock_guard<std::mutex> g(mu_);
                 if (!failed_) failed_ = std::current_exception();
@@ -211,7 +219,7 @@ private:
     std::vector<std::thread> workers_;
     std::mutex mu_;
     std::condition_variable wake_, idle_;
-    const std::function<void(size_t)>* task_ = nullptr;
+    const Call* task_ = nullptr;
     size_t n_ = 0;
     std::atomic<size_t> next_{0};
     unsigned busy_ = 0;

@@ -142,10 +142,26 @@ hipError_t hipGetSymbolAddress(void** p, const void* symbol) {
     return hipErrorInvalidSymbol;
 }
 
-hipError_t hipMalloc(void** p, size_t n) { return posix_memalign(p, 256, n ? n : 1) ? hipErrorOutOfMemory : hipSuccess; }
-hipError_t hipFree(void* p) { free(p); return hipSuccess; }
-hipError_t hipHostMalloc(void** p, size_t n, unsigned flags) { (void)flags; return hipMalloc(p, n); }
-hipError_t hipHostFree(void* p) { return hipFree(p); }
+/* device blocks and pinned ones: how many were allocated, how many of them live, and the largest that there is room for */
+static struct { unsigned long allocated, live; size_t largest; } g_memory[2] = {{0, 0, (size_t)-1}, {0, 0, (size_t)-1}};
+unsigned long fake_allocated(int pinned) { return g_memory[pinned].allocated; }
+unsigned long fake_live(int pinned) { return g_memory[pinned].live; }
+void fake_largest(int pinned, size_t n) { g_memory[pinned].largest = n; }
+static hipError_t allocate(int pinned, void** p, size_t n) {
+    if (n > g_memory[pinned].largest || posix_memalign(p, 256, n ? n : 1)) return hipErrorOutOfMemory;
+    ++g_memory[pinned].allocated;
+    ++g_memory[pinned].live;
+    return hipSuccess;
+}
+static hipError_t release(int pinned, void* p) {
+    if (p) --g_memory[pinned].live;
+    free(p);
+    return hipSuccess;
+}
+hipError_t hipMalloc(void** p, size_t n) { return allocate(0, p, n); }
+hipError_t hipFree(void* p) { return release(0, p); }
+hipError_t hipHostMalloc(void** p, size_t n, unsigned flags) { (void)flags; return allocate(1, p, n); }
+hipError_t hipHostFree(void* p) { return release(1, p); }
 hipError_t hipMemcpy(void* d, const void* s, size_t n, hipMemcpyKind k) { (void)k; memcpy(d, s, n); return hipSuccess; }
 hipError_t hipMemcpyAsync(void* d, const void* s, size_t n, hipMemcpyKind k, hipStream_t q) { (void)q; return hipMemcpy(d, s, n, k); }
 hipError_t hipMemset(void* d, int v, size_t n) { memset(d, v, n); return hipSuccess; }
