@@ -753,6 +753,11 @@ bps_status load_scene_on(bps_renderer* r, const float* vertices, uint32_t V, con
         while (32 * step <= dev_bytes) step *= 2;
         arena.bytes = (dev_bytes + step - 1) / step * step;
         hipError_t e = hipMalloc(&arena.ptr, arena.bytes);
+        if (e == hipErrorOutOfMemory) {      // no room for that: there may be for the scene alone
+            (void)hipGetLastError();
+            arena.bytes = dev_bytes;
+            e = hipMalloc(&arena.ptr, arena.bytes);
+        }
         if (e != hipSuccess) {
             give_back();
             return fail(r, e == hipErrorOutOfMemory ? BPS_ERR_OOM : BPS_ERR_HIP, "bps_load_scene: hipMalloc(%zu): %s", arena.bytes,

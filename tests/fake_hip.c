@@ -142,13 +142,16 @@ hipError_t hipGetSymbolAddress(void** p, const void* symbol) {
     return hipErrorInvalidSymbol;
 }
 
-/* device blocks and pinned ones: how many were allocated, how many of them live, and the largest that there is room for */
-static struct { unsigned long allocated, live; size_t largest; } g_memory[2] = {{0, 0, (size_t)-1}, {0, 0, (size_t)-1}};
+/* device blocks and pinned ones: how many were allocated, how many of them live, the last one's size, and the
+ * largest that there is room for */
+static struct { unsigned long allocated, live; size_t largest, last; } g_memory[2] = {{0, 0, (size_t)-1, 0}, {0, 0, (size_t)-1, 0}};
 unsigned long fake_allocated(int pinned) { return g_memory[pinned].allocated; }
 unsigned long fake_live(int pinned) { return g_memory[pinned].live; }
+unsigned long fake_last_size(int pinned) { return g_memory[pinned].last; }
 void fake_largest(int pinned, size_t n) { g_memory[pinned].largest = n; }
 static hipError_t allocate(int pinned, void** p, size_t n) {
     if (n > g_memory[pinned].largest || posix_memalign(p, 256, n ? n : 1)) return hipErrorOutOfMemory;
+    g_memory[pinned].last = n;
     ++g_memory[pinned].allocated;
     ++g_memory[pinned].live;
     return hipSuccess;

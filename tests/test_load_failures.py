@@ -92,3 +92,26 @@ load(r, small)
 assert fake.fake_live(1) == 1 and bps.bps_query(r, 0, 8) == 2
 print("done")
 """)
+
+
+def test_a_device_block_is_as_large_as_the_scene_where_there_is_no_more(fake):  # noqa: F811
+    """Blocks come in coarse sizes, which must not refuse a scene that fits."""
+    _run(fake, """
+r = bps.bps_create(max_batch=1)
+scenes = [synth.make_room_scene(T) for T in (300, 3000, 10_000)] + [small, large]
+for s in scenes:
+    load(r, s)
+    coarse = fake.fake_last_size(0)
+    fake.fake_largest(0, ctypes.c_size_t(coarse - 1))
+    load(r, s)
+    exact = fake.fake_last_size(0)
+    assert coarse - max(4096, coarse // 16) <= exact < coarse, (exact, coarse)
+    fake.fake_largest(0, ctypes.c_size_t(exact - 1))
+    try:
+        load(r, s)
+        raise SystemExit("loaded")
+    except bps.BpsError as e:
+        assert e.status == -3, e
+    fake.fake_largest(0, ctypes.c_size_t(1 << 40))
+print("done")
+""")
