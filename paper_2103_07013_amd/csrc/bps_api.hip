@@ -56,7 +56,6 @@ struct HostScene {
     bool live = false;
     bps::SceneDev dev{};
     Arena arena;
-    uint64_t bytes = 0;
     bool has_colors = false;
     hipEvent_t ready = nullptr;   // copy finished (asynchronous loads); null once known complete
     uint64_t last_use = 0;        // sequence number of the last request that referenced the scene
@@ -768,7 +767,6 @@ bps_status load_scene_on(bps_renderer* r, const float* vertices, uint32_t V, con
     unsigned char* d = (unsigned char*)arena.ptr;
     HostScene hs;
     hs.arena = arena;
-    hs.bytes = dev_bytes;
     hs.has_colors = colors != nullptr || textured;
     hs.dev.cverts = (const float*)(d + o_cverts);
     hs.dev.ctris = (const uint32_t*)(d + o_ctris);
@@ -1304,7 +1302,7 @@ bps_status bps_query(bps_renderer* r, bps_scene scene, int32_t what, uint64_t* v
         const int slot = slot_of(r, scene);
         if (slot < 0) return fail(r, BPS_ERR_BAD_HANDLE, "bps_query: scene %d is not loaded", scene);
         const HostScene& s = r->scenes[slot];
-        *value = what == 0 ? s.dev.n_clusters : what == 1 ? s.dev.n_tris : what == 2 ? s.dev.n_verts : s.bytes;
+        *value = what == 0 ? s.dev.n_clusters : what == 1 ? s.dev.n_tris : what == 2 ? s.dev.n_verts : s.arena.bytes;
         return BPS_OK;
     }
     switch (what) {

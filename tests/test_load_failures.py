@@ -100,11 +100,12 @@ def test_a_device_block_is_as_large_as_the_scene_where_there_is_no_more(fake):  
 r = bps.bps_create(max_batch=1)
 scenes = [synth.make_room_scene(T) for T in (300, 3000, 10_000)] + [small, large]
 for s in scenes:
-    load(r, s)
+    h = load(r, s)
     coarse = fake.fake_last_size(0)
     fake.fake_largest(0, ctypes.c_size_t(coarse - 1))
-    load(r, s)
+    g = load(r, s)
     exact = fake.fake_last_size(0)
+    assert bps.bps_query(r, h, 3) == coarse and bps.bps_query(r, g, 3) == exact      # what they hold
     assert coarse - max(4096, coarse // 16) <= exact < coarse, (exact, coarse)
     fake.fake_largest(0, ctypes.c_size_t(exact - 1))
     try:
