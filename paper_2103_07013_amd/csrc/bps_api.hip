@@ -567,6 +567,14 @@ bool all_finite(const float* v, size_t n) {
     return *std::max_element(m, m + 8) < 0x7F800000u;
 }
 
+// Blocks and pinned images come in sizes a sixteenth of a power of two apart, so that scenes of about one size can follow
+// each other in them, and so that there are only so many.
+size_t coarse_size(size_t bytes) {
+    size_t step = 4096;
+    while (32 * step <= bytes) step *= 2;
+    return (bytes + step - 1) / step * step;
+}
+
 // Shared by the synchronous and asynchronous entry points: validate, cluster, lay every array out
 // in one pinned image, copy it into one device block on `stream`, update the scene table on the
 // same stream and record the scene's ready event.  waits: the caller waits for the upload.
@@ -632,13 +640,9 @@ bps_status load_scene_on(bps_renderer* r, const float* vertices, uint32_t V, con
     size_t image = r->staging.size();      // its place in the list, which only grows
     for (size_t i = 0; i < r->staging.size(); ++i) {
         const Staging& s = r->staging[i];
-        if (s.taken) continue;
-        if (!s.ptr) {
-            image = i;      // a place whose allocation failed
-        } else if (s.bytes >= img_bytes && hipEventQuery(s.done) == hipSuccess) {
-            image = i;
-            break;
-        }
+        if (s.taken || (s.ptr && (s.bytes < img_bytes || hipEventQuery(s.done) != hipSuccess))) continue;
+        // the smallest that is free and large enough; failing that a place whose allocation failed
+        if (image == r->staging.size() || !r->staging[image].ptr || (s.ptr && s.bytes < r->staging[image].bytes)) image = i;
     }
     (void)hipGetLastError();
     if (image == r->staging.size()) {
@@ -658,15 +662,21 @@ bps_status load_scene_on(bps_renderer* r, const float* vertices, uint32_t V, con
     };
     if (!stg.ptr) {
         hipError_t e = stg.done ? hipSuccess : hipEventCreateWithFlags(&stg.done, hipEventDisableTiming);
-        if (e == hipSuccess) e = hipHostMalloc(&stg.ptr, img_bytes, hipHostMallocDefault);
+        stg.bytes = coarse_size(img_bytes);
+        if (e == hipSuccess) e = hipHostMalloc(&stg.ptr, stg.bytes, hipHostMallocDefault);
+        if (e == hipErrorOutOfMemory) {
+            (void)hipGetLastError();
+            stg.bytes = img_bytes;
+            e = hipHostMalloc(&stg.ptr, stg.bytes, hipHostMallocDefault);
+        }
         if (e != hipSuccess) {
             (void)hipGetLastError();
             stg.ptr = nullptr;
+            stg.bytes = 0;
             lock.lock();
             give_back();
             return fail(r, e == hipErrorOutOfMemory ? BPS_ERR_OOM : BPS_ERR_HIP, "bps_load_scene: hipHostMalloc(%zu): %s", img_bytes, hipGetErrorString(e));
         }
-        stg.bytes = img_bytes;
     }
     unsigned char* img = (unsigned char*)stg.ptr;
     float* cb = (float*)(img + o_cb);
@@ -747,10 +757,7 @@ bps_status load_scene_on(bps_renderer* r, const float* vertices, uint32_t V, con
         r->arena_pool[best] = r->arena_pool.back();
         r->arena_pool.pop_back();
     } else {
-        // (sizes a sixteenth of a power of two apart, so that scenes of about one size can follow each other in a block)
-        size_t step = 4096;
-        while (32 * step <= dev_bytes) step *= 2;
-        arena.bytes = (dev_bytes + step - 1) / step * step;
+        arena.bytes = coarse_size(dev_bytes);
         hipError_t e = hipMalloc(&arena.ptr, arena.bytes);
         if (e == hipErrorOutOfMemory) {      // no room for that: there may be for the scene alone
             (void)hipGetLastError();

@@ -181,10 +181,13 @@ hipError_t hipStreamCreateWithFlags(hipStream_t* s, unsigned flags) { (void)flag
 hipError_t hipStreamDestroy(hipStream_t s) { free(s); return hipSuccess; }
 hipError_t hipStreamSynchronize(hipStream_t s) { (void)s; return hipSuccess; }
 hipError_t hipStreamWaitEvent(hipStream_t s, hipEvent_t e, unsigned flags) { (void)s; (void)e; (void)flags; return hipSuccess; }
-hipError_t hipEventCreateWithFlags(hipEvent_t* e, unsigned flags) { (void)flags; *e = (hipEvent_t)malloc(8); return hipSuccess; }
+/* events recorded while the device is held are not reached until it goes on */
+static long g_held, g_holds;
+void fake_hold(int on) { g_held = on ? ++g_holds : 0; }
+hipError_t hipEventCreateWithFlags(hipEvent_t* e, unsigned flags) { (void)flags; *e = (hipEvent_t)calloc(1, sizeof(long)); return hipSuccess; }
 hipError_t hipEventCreate(hipEvent_t* e) { return hipEventCreateWithFlags(e, 0); }
 hipError_t hipEventDestroy(hipEvent_t e) { free(e); return hipSuccess; }
-hipError_t hipEventRecord(hipEvent_t e, hipStream_t s) { (void)e; (void)s; return hipSuccess; }
-hipError_t hipEventQuery(hipEvent_t e) { (void)e; return hipSuccess; }
+hipError_t hipEventRecord(hipEvent_t e, hipStream_t s) { (void)s; *(long*)e = g_held; return hipSuccess; }
+hipError_t hipEventQuery(hipEvent_t e) { return g_held && *(long*)e == g_held ? hipErrorNotReady : hipSuccess; }
 hipError_t hipEventSynchronize(hipEvent_t e) { (void)e; return hipSuccess; }
 hipError_t hipEventElapsedTime(float* ms, hipEvent_t a, hipEvent_t b) { (void)a; (void)b; *ms = 0.0f; return hipSuccess; }
