@@ -172,7 +172,8 @@ bps_status bps_render(bps_renderer *r, const bps_scene *scene_ids, const float *
  * Limits: depth renderers without supersampling, forced splits or diagnostics; view_proj must be
  * DEVICE memory; B x (64x64-pixel tiles per frame) <= 16384 work-groups (e.g. 16384 environments at
  * 64x64, 4096 at 128x128), otherwise BPS_ERR_INVALID_ARG / BPS_ERR_UNSUPPORTED and nothing is enqueued.
- * Small batches are cut into smaller windows as in bps_render.  scene_ids is host memory as in bps_render.
+ * Small batches are cut into smaller windows, as in bps_render but for scenes of many clusters, which that cuts
+ * coarser (a renderer keeps a launch plan for each).  scene_ids is host memory as in bps_render.
  * Every call on a GPU, from any renderer and stream, uses that GPU's one array: calls on one stream
  * are ordered and safe; calls that overlap on one GPU (different streams or renderers) race.  Nothing
  * in the array needs clearing: a call finds its own plan there or overwrites it.

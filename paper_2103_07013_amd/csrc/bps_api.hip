@@ -86,6 +86,14 @@ struct RingSlot {
     uint64_t items_version = 0;      // plan whose work items the device buffer holds (0 = none)
 };
 
+struct Plan {         // valid while the scene ids, the split count and the window size repeat
+    std::vector<bps_scene> ids;      // none: no plan
+    int splits = 0;
+    int windows = 0;
+    uint64_t version = 0;            // its number (0 = none yet); ring slots remember which one they hold
+    std::vector<bps::WorkItem> items;
+};
+
 }  // namespace
 
 struct bps_renderer {
@@ -126,15 +134,13 @@ struct bps_renderer {
     size_t ev_used = 0;
     bool profiling = false;
     uint32_t profile_every = 1, profile_count = 0;   // every n-th request is timed
-    // cached plan: valid while the scene ids, the split count and the window size repeat
-    std::vector<bps_scene> plan_ids;
-    int plan_splits = 0;
-    int plan_windows = 0;
+    // the two plans used last (bps_render and bps_render_static may cut the same batch differently, and a caller may use
+    // both in turn); `plan` is the present one
+    Plan plans[2];
+    Plan* plan = &plans[0];
     bool fixed_layout = false;        // the raster kernel's instances with a constant LDS layout fit this device
     bool wide_layout = false;         // and so does the one with 1024 threads, and nothing else was asked for
     bool last_wide = false;           // the last request ran on that one
-    uint64_t plan_version = 0;        // number of the current plan (0 = none yet); ring slots remember which one they hold
-    std::vector<bps::WorkItem> plan_items;
     std::vector<bps_scene> call_slots;    // table slots of the current request's scene handles (keeps its capacity)
     uint64_t last_splits = 0, last_groups = 0;
     unsigned char* static_scratch = nullptr;   // this device's copy of the static scratch array (bps_render_static)
@@ -235,6 +241,10 @@ bool slot_busy(const bps_renderer* r, int slot) {
     return false;
 }
 
+void forget_plans(bps_renderer* r) {
+    for (Plan& p : r->plans) p.ids.clear();
+}
+
 bool fp_cull_enabled(const bps_renderer* r) { return !(r->cfg.flags & BPS_FLAG_NO_CLUSTER_CULL); }
 
 // How one request is cut into work-groups: nx x ny windows of w x h pixels per frame, and S interleaved
@@ -245,7 +255,8 @@ struct Cut {
     int windows() const { return nx * ny; }
 };
 
-// coarser: the cut may be made coarser for the sake of wide groups (bps_render; how bps_render_static cuts is fixed).
+// coarser: the cut may be made coarser for the sake of wide groups (bps_render; bps_render_static keeps to one rule for
+// scenes of any kind).
 Cut choose_cut(const bps_renderer* r, uint32_t B, uint32_t min_clusters, uint32_t max_clusters, bool coarser) {
     auto parts = [](int n, int size) { return (n + size - 1) / size; };
     Cut c{r->tile_w, r->tile_h, parts(r->rw, r->tile_w), parts(r->rh, r->tile_h), 1, false};
@@ -318,40 +329,44 @@ Cut choose_cut(const bps_renderer* r, uint32_t B, uint32_t min_clusters, uint32_
 // scene.  Cached while the scene ids and the cut repeat.
 void make_plan(bps_renderer* r, const bps_scene* scene_ids, uint32_t B, const Cut& cut) {
     const int S = cut.S, windows = cut.windows();
-    bool replan = r->plan_splits != S || r->plan_windows != windows || r->plan_ids.size() != B ||
-                  std::memcmp(r->plan_ids.data(), scene_ids, B * sizeof(bps_scene)) != 0;
-    if (replan) {
-        std::vector<uint32_t> order(B);
-        for (uint32_t b = 0; b < B; ++b) order[b] = b;
-        std::stable_sort(order.begin(), order.end(), [&](uint32_t a, uint32_t b) { return scene_ids[a] < scene_ids[b]; });
-        std::vector<bps::WorkItem> sorted;
-        sorted.reserve((size_t)B * S * windows);
-        for (uint32_t k = 0; k < B; ++k) {
-            uint32_t b = order[k];
-            for (int tile = 0; tile < windows; ++tile)
-                for (int s = 0; s < S; ++s) {
-                    bps::WorkItem it;
-                    it.env = b;
-                    it.scene = (uint32_t)scene_ids[b];
-                    it.split_of = ((uint32_t)S << 16) | (uint32_t)s;
-                    it.tile = (uint32_t)tile;
-                    sorted.push_back(it);
-                }
-        }
-        const size_t n = sorted.size();
-        r->plan_items.resize(n);
-        // block i runs on die i % 8: give die x the x-th contiguous chunk of the sorted list
-        size_t start = 0;
-        for (int x = 0; x < kXcds; ++x) {
-            size_t cnt = n / kXcds + ((size_t)x < n % kXcds ? 1 : 0);
-            for (size_t k = 0; k < cnt; ++k) r->plan_items[x + k * kXcds] = sorted[start + k];
-            start += cnt;
-        }
-        r->plan_ids.assign(scene_ids, scene_ids + B);
-        r->plan_splits = S;
-        r->plan_windows = windows;
-        r->plan_version = ++g_plans;
+    auto is_it = [&](const Plan& p) {
+        return p.splits == S && p.windows == windows && p.ids.size() == B && std::memcmp(p.ids.data(), scene_ids, B * sizeof(bps_scene)) == 0;
+    };
+    if (is_it(*r->plan)) return;
+    r->plan = r->plan == &r->plans[0] ? &r->plans[1] : &r->plans[0];
+    Plan& plan = *r->plan;
+    if (is_it(plan)) return;
+    plan.ids.clear();
+    std::vector<uint32_t> order(B);
+    for (uint32_t b = 0; b < B; ++b) order[b] = b;
+    std::stable_sort(order.begin(), order.end(), [&](uint32_t a, uint32_t b) { return scene_ids[a] < scene_ids[b]; });
+    std::vector<bps::WorkItem> sorted;
+    sorted.reserve((size_t)B * S * windows);
+    for (uint32_t k = 0; k < B; ++k) {
+        uint32_t b = order[k];
+        for (int tile = 0; tile < windows; ++tile)
+            for (int s = 0; s < S; ++s) {
+                bps::WorkItem it;
+                it.env = b;
+                it.scene = (uint32_t)scene_ids[b];
+                it.split_of = ((uint32_t)S << 16) | (uint32_t)s;
+                it.tile = (uint32_t)tile;
+                sorted.push_back(it);
+            }
     }
+    const size_t n = sorted.size();
+    plan.items.resize(n);
+    // block i runs on die i % 8: give die x the x-th contiguous chunk of the sorted list
+    size_t start = 0;
+    for (int x = 0; x < kXcds; ++x) {
+        size_t cnt = n / kXcds + ((size_t)x < n % kXcds ? 1 : 0);
+        for (size_t k = 0; k < cnt; ++k) plan.items[x + k * kXcds] = sorted[start + k];
+        start += cnt;
+    }
+    plan.ids.assign(scene_ids, scene_ids + B);
+    plan.splits = S;
+    plan.windows = windows;
+    plan.version = ++g_plans;
 }
 
 bps::FrameParams frame_params(const bps_renderer* r, const Cut& cut) {
@@ -816,7 +831,7 @@ bps_status load_scene_on(bps_renderer* r, const float* vertices, uint32_t V, con
     give_back();
     hs.live = true;
     r->scenes[slot] = hs;
-    r->plan_ids.clear();
+    forget_plans(r);
     *out_handle = make_handle(r, slot);
     return BPS_OK;
 }
@@ -917,7 +932,7 @@ bps_status bps_unload_scene(bps_renderer* r, bps_scene scene) {
     r->retired.push_back(x);
     hs = HostScene{};
     r->gens[slot] = (r->gens[slot] + 1u) & ((1u << (31 - kSlotBits)) - 1u);      // handles to the old scene stop matching
-    r->plan_ids.clear();
+    forget_plans(r);
     collect(r);
     return BPS_OK;
 }
@@ -977,7 +992,7 @@ bps_status bps_render(bps_renderer* r, const bps_scene* scene_ids, const float* 
     const Cut cut = choose_cut(r, B, min_clusters, max_clusters, true);
     const int S = cut.S;
     make_plan(r, scene_ids, B, cut);
-    const size_t n_items = r->plan_items.size();
+    const size_t n_items = r->plan->items.size();
 
     // ---- stage the request (work items + matrices unless they already live on the device)
     hipPointerAttribute_t attr;
@@ -1013,8 +1028,8 @@ bps_status bps_render(bps_renderer* r, const bps_scene* scene_ids, const float* 
     // The work items only change with the scene ids: each slot keeps the copy it has until then, so
     // a depth request whose matrices are on the device stages nothing at all.
     size_t copy_from = items_bytes, copy_to = items_bytes;
-    if (slot.items_version != r->plan_version) {
-        std::memcpy(slot.host, r->plan_items.data(), items_bytes);
+    if (slot.items_version != r->plan->version) {
+        std::memcpy(slot.host, r->plan->items.data(), items_bytes);
         copy_from = 0;
     }
     if (rgbd) {
@@ -1038,7 +1053,7 @@ bps_status bps_render(bps_renderer* r, const bps_scene* scene_ids, const float* 
         for (hipEvent_t e : uploads_pending) BPS_HIP(r, hipStreamWaitEvent(pstream, e, 0));
     if (copy_to > copy_from)
         BPS_HIP(r, hipMemcpyAsync(payload + copy_from, slot.host + copy_from, copy_to - copy_from, hipMemcpyHostToDevice, pstream));
-    slot.items_version = r->plan_version;
+    slot.items_version = r->plan->version;
     const bps::WorkItem* d_items = reinterpret_cast<const bps::WorkItem*>(payload);
     const uint32_t* d_env_scene = reinterpret_cast<const uint32_t*>(payload + items_bytes);
     const float* d_vp = vp_on_device ? view_proj : reinterpret_cast<const float*>(payload + items_bytes + ids_bytes);
@@ -1181,7 +1196,7 @@ bps_status bps_render_static(bps_renderer* r, const bps_scene* scene_ids, const 
     Cut cut = choose_cut(r, B, 1u, max_clusters, false);
     cut.S = 1;                          // (no merge buffer here)
     make_plan(r, scene_ids, B, cut);    // (host containers only; they keep their capacity between calls)
-    n_items = r->plan_items.size();     // (small batches are cut finer, never into more than kMaxPlannedItems)
+    n_items = r->plan->items.size();     // (small batches are cut finer, never into more than kMaxPlannedItems)
     hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
     const bool capturing = hipStreamIsCapturing(stream, &capture) == hipSuccess && capture == hipStreamCaptureStatusActive;
     (void)hipGetLastError();
@@ -1203,19 +1218,19 @@ bps_status bps_render_static(bps_renderer* r, const bps_scene* scene_ids, const 
     {   // the items reach the device as kernel arguments, unless the array still holds this very plan (every replay
         // of a graph brings its own: what the second half holds depends on the order of replays)
         std::lock_guard<std::mutex> g(g_scratch_mu);
-        if (capturing || g_scratch_plan[r->device] != r->plan_version) {
+        if (capturing || g_scratch_plan[r->device] != r->plan->version) {
             if (!capturing) g_scratch_plan[r->device] = 0;      // until all of it is on its way
             bps::PackedItems packed;
             for (size_t first = 0; first < n_items; first += bps::kPackedItemsPerLaunch) {
                 const uint32_t count = (uint32_t)std::min<size_t>(bps::kPackedItemsPerLaunch, n_items - first);
                 for (uint32_t k = 0; k < count; ++k) {
-                    const bps::WorkItem& it = r->plan_items[first + k];
+                    const bps::WorkItem& it = r->plan->items[first + k];
                     packed.word[k] = it.env | (it.scene << bps::kPackedEnvBits) | (it.tile << (bps::kPackedEnvBits + bps::kPackedSceneBits));
                 }
                 bps::launch_unpack_items(stream, packed, (uint32_t)first, count, d_items);
                 BPS_HIP(r, hipGetLastError());
             }
-            if (!capturing) g_scratch_plan[r->device] = r->plan_version;
+            if (!capturing) g_scratch_plan[r->device] = r->plan->version;
         }
     }
     const bps::FrameParams fp = frame_params(r, cut);

@@ -166,7 +166,9 @@ hipError_t hipFree(void* p) { return release(0, p); }
 hipError_t hipHostMalloc(void** p, size_t n, unsigned flags) { (void)flags; return allocate(1, p, n); }
 hipError_t hipHostFree(void* p) { return release(1, p); }
 hipError_t hipMemcpy(void* d, const void* s, size_t n, hipMemcpyKind k) { (void)k; memcpy(d, s, n); return hipSuccess; }
-hipError_t hipMemcpyAsync(void* d, const void* s, size_t n, hipMemcpyKind k, hipStream_t q) { (void)q; return hipMemcpy(d, s, n, k); }
+static unsigned long g_copied;
+unsigned long fake_copied(void) { return g_copied; }
+hipError_t hipMemcpyAsync(void* d, const void* s, size_t n, hipMemcpyKind k, hipStream_t q) { (void)q; g_copied += n; return hipMemcpy(d, s, n, k); }
 hipError_t hipMemset(void* d, int v, size_t n) { memset(d, v, n); return hipSuccess; }
 /* memory is on the device where the test says so */
 static uintptr_t g_device_lo, g_device_hi;

@@ -112,6 +112,28 @@ static(r, hs, 300)
     assert all(g["wrong"] == 0 and g["groups"] == g["envs"] * g["tiles"] for g in got)
 
 
+@pytest.mark.parametrize("B", [17, 300])      # cut differently by the two entry points, and alike
+def test_two_entry_points_in_turn_keep_their_plans(fake, B):
+    got = _launches(fake, f"""
+r = bps.bps_create(max_batch={B})
+h = load(r, large)
+ids = np.full({B}, h, np.int32)
+for k in range(8):
+    if k == 4:
+        copied = fake.fake_copied()
+    fake.fake_clear_log()
+    assert lib.bps_render(r, ids.ctypes.data, pool.ctypes.data, {B}, out.ctypes.data, None, None, None) == 0
+    print(fake.fake_log().decode(), end="")
+    static(r, h, {B})
+    if k >= 4:
+        assert "k_unpack_items" not in fake.fake_log().decode()
+assert fake.fake_copied() == copied
+""")
+    assert len(got) == 16 and all(g["wrong"] == 0 and g["envs"] == B for g in got)
+    assert (got[0]["tiles"] == got[1]["tiles"]) == (B == 300)
+    assert got[2:] == 7 * got[:2]
+
+
 @pytest.mark.parametrize("B", [256, 257, 300, 2000])
 def test_static_plan_stays_within_its_array_on_any_device(fake, B):
     """A device so large that the rule for small batches would like more groups than the array has items (16384)."""
