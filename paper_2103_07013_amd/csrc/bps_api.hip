@@ -139,7 +139,7 @@ struct bps_renderer {
     Plan plans[2];
     Plan* plan = &plans[0];
     bool fixed_layout = false;        // the raster kernel's instances with a constant LDS layout fit this device
-    bool wide_layout = false;         // and so does the one with 1024 threads, and nothing else was asked for
+    bool wide_layout = false;         // and so does the one with 1024 threads, and no group size was asked for
     bool last_wide = false;           // the last request ran on that one
     std::vector<bps_scene> call_slots;    // table slots of the current request's scene handles (keeps its capacity)
     uint64_t last_splits = 0, last_groups = 0;
@@ -491,7 +491,7 @@ bps_status bps_create(const bps_config* cfg, bps_renderer** out) {
 #endif
         r->lds = bps::lds_bytes(r->tile_h, r->tile_w, r->threads, r->list_cap);
         r->fixed_layout = bps::lds_bytes(64, 64, 512, (int)bps::kListCap64) <= r->max_lds;
-        r->wide_layout = r->fixed_layout && r->threads == 512 && bps::lds_bytes(64, 64, 1024, (int)bps::kListCap64) <= r->max_lds;
+        r->wide_layout = r->fixed_layout && !cfg->threads && r->threads == 512 && bps::lds_bytes(64, 64, 1024, (int)bps::kListCap64) <= r->max_lds;
         BPS_HIP(r, bps::prepare_raster(r->threads, r->lds, r->fixed_layout, r->wide_layout));
         BPS_HIP(r, hipMalloc((void**)&r->d_scenes, sizeof(bps::SceneDev) * kMaxScenes));
         BPS_HIP(r, hipMemset(r->d_scenes, 0, sizeof(bps::SceneDev) * kMaxScenes));

@@ -53,7 +53,7 @@ hipError_t __hipPopCallConfiguration(dim3* grid, dim3* block, size_t* shared, hi
 #define ARG(type, k) (*(type*)args[k])
 
 static hipError_t run(const void* f, dim3 grid, dim3 block, void** args, size_t shared, hipStream_t stream) {
-    (void)block; (void)stream;
+    (void)stream;
     const char* name = "?";
     for (int k = 0; k < g_n_kernels; ++k)
         if (g_kernels[k].host == f) name = g_kernels[k].name;
@@ -84,7 +84,7 @@ static hipError_t run(const void* f, dim3 grid, dim3 block, void** args, size_t 
             if (items[k].split_of != 1u << 16 || items[k].env > 0xFFFFu || items[k].tile > 63u || seen[64u * items[k].env + items[k].tile]++) ++wrong;
         }
         free(seen);
-        n = snprintf(out, room, "k_raster groups=%u envs=%u tiles=%u wrong=%u lds=%zu\n", grid.x, envs, tiles, wrong, shared);
+        n = snprintf(out, room, "k_raster groups=%u envs=%u tiles=%u wrong=%u threads=%u lds=%zu\n", grid.x, envs, tiles, wrong, block.x, shared);
     } else {
         n = snprintf(out, room, "%s\n", name);
     }

@@ -189,6 +189,21 @@ for B in (588, 589, 1024):
     assert [g["tiles"] for g in got] == [2, 1, 1] and all(g["wrong"] == 0 for g in got)
 
 
+@pytest.mark.parametrize("threads", [0, 256, 384, 512, 1024])
+def test_groups_have_the_size_that_was_asked_for(fake, threads):
+    """Where none was, launches of one group per compute unit run 1024 threads and others 512."""
+    got = _launches(fake, f"""
+r = bps.bps_create(max_batch=300, threads={threads})
+h = load(r, small)
+for B in (1, 300):
+    static(r, h, B)
+    fake.fake_clear_log()
+    assert lib.bps_render(r, np.full(B, h, np.int32).ctypes.data, pool.ctypes.data, B, out.ctypes.data, None, None, None) == 0
+    print(fake.fake_log().decode(), end="")
+""")
+    assert [g["threads"] for g in got] == ([threads] * 4 if threads else [1024, 1024, 512, 512])
+
+
 @pytest.mark.parametrize("H,W", [(64, 64), (72, 104), (8, 8)])
 def test_reported_lds_is_what_launches_ask_for(fake, H, W):
     p = _launches(fake, f"""
