@@ -198,7 +198,8 @@ h = load(r, small)
 for B in (1, 300):
     static(r, h, B)
     fake.fake_clear_log()
-    assert lib.bps_render(r, np.full(B, h, np.int32).ctypes.data, pool.ctypes.data, B, out.ctypes.data, None, None, None) == 0
+    ids = np.full(B, h, np.int32)
+    assert lib.bps_render(r, ids.ctypes.data, pool.ctypes.data, B, out.ctypes.data, None, None, None) == 0
     print(fake.fake_log().decode(), end="")
 """)
     assert [g["threads"] for g in got] == ([threads] * 4 if threads else [1024, 1024, 512, 512])
