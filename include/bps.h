@@ -226,8 +226,8 @@ bps_status bps_read_diagnostics(bps_renderer *r, uint64_t *out, uint32_t capacit
 /* Facts about a loaded scene and the launch plan, for benchmarks and tests.
  * what: 0 = clusters in the scene, 1 = triangles, 2 = vertices, 3 = device bytes held,
  *       4 = splits used by the last request, 5 = work-groups of the last request,
- *       6 = work-group size (requests that put at most one group on a compute unit may run 1024
- *       threads instead of the default), 7 = LDS bytes per work-group of a request like the last one, 8 = device blocks
+ *       6 = work-group size of the last request (1024 threads instead of the default where that puts at
+ *       most one group on a compute unit), 7 = LDS bytes per work-group of a request like the last one, 8 = device blocks
  *       allocated for scenes so far, 9 = retired scene blocks waiting for reuse. */
 bps_status bps_query(bps_renderer *r, bps_scene scene, int32_t what, uint64_t *value);
 

@@ -108,6 +108,7 @@ struct bps_renderer {
     int list_cap = 2048;
     int round_target = 2048, first_round = 192;
     size_t lds = 0;
+    size_t wide_lds = 0;              // the same with 1024 threads (diagnostics of requests on wide groups)
     size_t max_lds = 0;
     std::string error = "";
     std::mutex err_mu;                // guards `error` alone (failures are also reported from outside `mu`)
@@ -296,7 +297,7 @@ Cut choose_cut(const bps_renderer* r, uint32_t B, uint32_t min_clusters, uint32_
             return c;
         };
         const Cut fine = halve(c, false);
-        if (!r->wide_layout || (r->cfg.flags & BPS_FLAG_NO_OCCLUSION_CULL) || r->want_stats) return fine;
+        if (!r->wide_layout || (r->cfg.flags & BPS_FLAG_NO_OCCLUSION_CULL)) return fine;
         // A compute unit holds two groups of eight wavefronts, or one of sixteen.  Where no unit has a second group to
         // hold, the sixteen halve the time between its barriers: 1 environment of 100 k triangles 25.2 -> 22.5 us per
         // request, of 1 M 44.9 -> 40.8.  And where the time goes into clusters rather than pixels (a cluster or more to
@@ -491,8 +492,10 @@ bps_status bps_create(const bps_config* cfg, bps_renderer** out) {
 #endif
         r->lds = bps::lds_bytes(r->tile_h, r->tile_w, r->threads, r->list_cap);
         r->fixed_layout = bps::lds_bytes(64, 64, 512, (int)bps::kListCap64) <= r->max_lds;
-        r->wide_layout = r->fixed_layout && !cfg->threads && r->threads == 512 && bps::lds_bytes(64, 64, 1024, (int)bps::kListCap64) <= r->max_lds;
-        BPS_HIP(r, bps::prepare_raster(r->threads, r->lds, r->fixed_layout, r->wide_layout));
+        r->wide_lds = bps::lds_bytes(r->tile_h, r->tile_w, 1024, r->list_cap);
+        r->wide_layout = r->fixed_layout && !cfg->threads && r->threads == 512 &&
+                         std::max(r->wide_lds, bps::lds_bytes(64, 64, 1024, (int)bps::kListCap64)) <= r->max_lds;
+        BPS_HIP(r, bps::prepare_raster(r->threads, r->lds, r->fixed_layout, r->wide_layout ? r->wide_lds : 0));
         BPS_HIP(r, hipMalloc((void**)&r->d_scenes, sizeof(bps::SceneDev) * kMaxScenes));
         BPS_HIP(r, hipMemset(r->d_scenes, 0, sizeof(bps::SceneDev) * kMaxScenes));
         for (RingSlot& s : r->ring) {
@@ -1115,8 +1118,8 @@ bps_status bps_render(bps_renderer* r, const bps_scene* scene_ids, const float* 
         ev_stop = r->ev[r->ev_used + 1];
         r->ev_used += 2;
     }
-    bps::launch_raster(r->threads, dim3((unsigned)n_items), r->lds, stream, r->d_scenes, planned ? d_ordered : d_items, d_vp, fp,
-                       r->fixed_layout, cut.wide, r->gvis, out_depth, out_tri_id, d_stats);
+    bps::launch_raster(r->threads, dim3((unsigned)n_items), cut.wide ? r->wide_lds : r->lds, stream, r->d_scenes,
+                       planned ? d_ordered : d_items, d_vp, fp, r->fixed_layout, cut.wide, r->gvis, out_depth, out_tri_id, d_stats);
     BPS_HIP(r, hipGetLastError());
     if (ev_stop) BPS_HIP(r, hipEventRecord(ev_stop, stream));
     if (S > 1) {
@@ -1330,12 +1333,12 @@ bps_status bps_query(bps_renderer* r, bps_scene scene, int32_t what, uint64_t* v
     switch (what) {
     case 4: *value = r->last_splits; return BPS_OK;
     case 5: *value = r->last_groups; return BPS_OK;
-    case 6: *value = (uint64_t)r->threads; return BPS_OK;
+    case 6: *value = r->last_wide ? 1024u : (uint64_t)r->threads; return BPS_OK;
     case 7:
         *value = r->fixed_layout && r->threads == 512 && !r->want_stats &&
                          !(r->cfg.flags & (BPS_FLAG_NO_CLUSTER_CULL | BPS_FLAG_NO_OCCLUSION_CULL))
                      ? (uint64_t)bps::lds_bytes(64, 64, r->last_wide ? 1024 : 512, (int)bps::kListCap64)
-                     : (uint64_t)r->lds;
+                     : (uint64_t)(r->last_wide ? r->wide_lds : r->lds);
         return BPS_OK;
     case 8: *value = r->arena_allocs; return BPS_OK;
     case 9: *value = (uint64_t)r->arena_pool.size() + (uint64_t)r->retired.size(); return BPS_OK;

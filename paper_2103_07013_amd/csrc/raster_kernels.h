@@ -117,7 +117,8 @@ void launch_raster(int threads, dim3 grid, size_t lds, hipStream_t stream, const
 constexpr uint32_t kMaxPlannedItems = 16384;
 void launch_plan(hipStream_t stream, const SceneDev* scenes, const WorkItem* items, const float* view_proj,
                  const FrameParams& fp, uint32_t n_items, uint32_t* cost, WorkItem* ordered);
-hipError_t prepare_raster(int threads, size_t lds, bool fixed_layout, bool wide_layout);
+// wide_lds: what launches of the 1024-thread instances with a layout chosen at run time ask for; 0 = there are none.
+hipError_t prepare_raster(int threads, size_t lds, bool fixed_layout, size_t wide_lds);
 // Work items handed over as kernel arguments (no host-to-device copy, no staging memory): up to
 // kPackedItemsPerLaunch items per launch, each packed as env (14 bits: at most kMaxPlannedItems items) |
 // scene (12 bits) | tile (6 bits); one work-group per environment and tile, i.e. split_of = 1 << 16.

@@ -1569,7 +1569,7 @@ const void* raster_entry(int threads) {
 }
 }  // namespace
 
-hipError_t prepare_raster(int threads, size_t lds, bool fixed_layout, bool wide_layout) {
+hipError_t prepare_raster(int threads, size_t lds, bool fixed_layout, size_t wide_lds) {
     const void* entries[6] = {raster_entry<false, 0>(threads), raster_entry<false, 1>(threads), raster_entry<false, 2>(threads),
                               raster_entry<true, 0>(threads),  raster_entry<true, 1>(threads),  raster_entry<true, 2>(threads)};
     for (const void* f : entries) {
@@ -1584,7 +1584,9 @@ hipError_t prepare_raster(int threads, size_t lds, bool fixed_layout, bool wide_
         hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes(64, 64, 512, (int)kListCap64));
         if (e != hipSuccess) return e;
     }
-    if (!wide_layout) return hipSuccess;
+    if (!wide_lds) return hipSuccess;
+    hipError_t e = hipFuncSetAttribute(raster_entry<true, 2>(1024), hipFuncAttributeMaxDynamicSharedMemorySize, (int)wide_lds);
+    if (e != hipSuccess) return e;
     return hipFuncSetAttribute(reinterpret_cast<const void*>(&k_raster<1024, false, 2, 1>), hipFuncAttributeMaxDynamicSharedMemorySize,
                                (int)lds_bytes(64, 64, 1024, (int)kListCap64));
 }
@@ -1625,7 +1627,8 @@ void launch_raster(int threads, dim3 grid, size_t lds, hipStream_t stream, const
         if (stats) BPS_LAUNCH2(NT, true);                                                                              \
         else BPS_LAUNCH2(NT, false);                                                                                   \
     } while (0)
-    if (threads == 256) BPS_LAUNCH(256);
+    if (wide) BPS_LAUNCH(1024);      // (diagnostics of what the instance above draws otherwise)
+    else if (threads == 256) BPS_LAUNCH(256);
     else if (threads == 384) BPS_LAUNCH(384);
     else if (threads == 512) BPS_LAUNCH(512);
     else BPS_LAUNCH(1024);

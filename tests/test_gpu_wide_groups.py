@@ -37,3 +37,30 @@ def test_wide_groups_match_oracle(H, W, T):
             assert np.array_equal(depth.cpu().numpy(), ref["depth"][:B]), f"B={B}"
             assert torch.equal(depth, d2) and torch.equal(tid, t2), f"B={B}"
     assert len(set(wide_lds)) == 1 and wide_lds[0] > 82_000
+
+
+@pytest.mark.parametrize("diagnostics", [1, 2, 4])
+@pytest.mark.parametrize("H,W", [(64, 64), (72, 104)])
+def test_wide_groups_with_diagnostics(H, W, diagnostics):
+    """The records come from groups of the number and size that draw the request otherwise, and from the same frames."""
+    import torch
+    import oracle
+    import paper_2103_07013_amd as bps
+    s = synth.make_multiroom_scene(100_000, seed=41, jitter=0.3)
+    M = synth.make_cameras(s, 17, seed=6, aspect=W / H)[0]
+    ref = oracle.render_scene(s.vertices, s.indices, M, H, W)
+    with bps.Renderer(max_batch=17, height=H, width=W) as r:
+        h = r.load_scene(s.vertices, s.indices)
+        for B in (1, 9, 17):
+            ran = []
+            for on in (0, diagnostics):
+                bps.bps_set_diagnostics(r.handle, on)
+                d, _, t = r.render(np.full(B, h, np.int32), M[:B], want_tri_id=True)
+                torch.cuda.synchronize()
+                ran.append((bps.bps_query(r.handle, h, 5), bps.bps_query(r.handle, h, 6)))
+                assert np.array_equal(t.cpu().numpy().view(np.uint32), ref["tri_id"][:B]), (B, on)
+                assert np.array_equal(d.cpu().numpy(), ref["depth"][:B]), (B, on)
+            assert ran[0] == ran[1]
+            words = bps.bps_read_diagnostics(r.handle).reshape(-1, 16)
+            assert len(words) == ran[0][0] and words[:, 2].sum() > 0
+            bps.bps_set_diagnostics(r.handle, 0)

@@ -206,6 +206,28 @@ for B in (1, 300):
 
 
 @pytest.mark.parametrize("H,W", [(64, 64), (72, 104), (8, 8)])
+def test_diagnostics_describe_the_request_as_it_is_drawn(fake, H, W):
+    got = _launches(fake, f"""
+r = bps.bps_create(max_batch=300, height={H}, width={W})
+hs = load(r, small), load(r, large)
+for B in (1, 9, 17, 40, 300):
+    for h in hs:
+        for diagnostics in (0, 1, 4):
+            bps.bps_set_diagnostics(r, diagnostics)
+            ids = np.full(B, h, np.int32)
+            fake.fake_clear_log()
+            assert lib.bps_render(r, ids.ctypes.data, pool.ctypes.data, B, out.ctypes.data, None, None, None) == 0
+            print([l for l in fake.fake_log().decode().splitlines() if l.startswith("k_raster")][0],
+                  "said=%d reported=%d" % (bps.bps_query(r, h, 6), bps.bps_query(r, h, 7)))
+""")
+    assert len(got) == 30 and {g["threads"] for g in got} == {512, 1024}
+    for k in range(0, 30, 3):
+        for g in got[k:k + 3]:
+            assert g["wrong"] == 0 and g["said"] == g["threads"] and g["reported"] == g["lds"]
+            assert all(g[x] == got[k][x] for x in ("groups", "tiles", "threads"))
+
+
+@pytest.mark.parametrize("H,W", [(64, 64), (72, 104), (8, 8)])
 def test_reported_lds_is_what_launches_ask_for(fake, H, W):
     p = _launches(fake, f"""
 for kw in (dict(), dict(threads=256), dict(threads=1024), dict(splits=2), dict(flags=bps.FLAG_NO_CLUSTER_CULL), dict(flags=bps.FLAG_NO_OCCLUSION_CULL)):
