@@ -27,17 +27,18 @@ constexpr uint32_t kClusterTris = 128;
 // vertices at random: whole 3340 clusters in 920 ms, chunks 5054 in 149 ms or 5828 in 69).
 constexpr uint32_t kMostThreads = 12;
 // Triangles per chunk: when the caller waits for the scene anyway, and when it is only to be on its way soon (a share
-// of the mesh for every thread, but no chunks that would cost more clusters than "whole").  Small meshes come in two or
-// three chunks either way: in one, which one thread works through, they took longer than "whole", and more chunks than
-// that cost clusters.
-//   40 k triangles   whole 5.3 ms, one chunk 8.3, three 4.3 (faces of the boxes 4920, 3967, 3993)
-//   10 k             2.2, 3.0, two 1.8 (4879, 3702, 3677)
-//   4 k              0.8, 1.0, two 0.7 (804, 631, 680); below 2048 a second thread would start too late
+// of the mesh for every thread, but no chunks that would cost more clusters than "whole").  Small meshes come in two
+// halves either way: in one, which one thread works through, they took longer than "whole", and in three their boxes are
+// larger (a load that is waited for, its copy included, on a 16-core host; faces of the boxes; request of 78 environments):
+//   40 k triangles       whole 2.6 ms, one chunk 4.0, halves 2.2, thirds 1.6 (6453, 5168, 5164, 5198)
+//   10 k                 whole 0.78, one chunk 1.02, halves 0.69 (6787, 5832, 5265)
+//   20 k, a single room  (845, 668, 688, thirds 690)   one chunk 47.2 us, halves 47.7, thirds 48.8
+// Below 6144 a second thread saves less than its start costs (4 k: whole 0.24 ms, one chunk 0.29, halves 0.32).
 inline uint32_t chunk_triangles(uint32_t T, bool caller_waits) {
-    if (T < 2048u) return 2048u;
-    const uint32_t few = T / (T < 16384u ? 2u : 3u) + 1u;
-    if (caller_waits) return T < 65536u ? few : 65536u;
-    if (T < 4u * 8192u) return std::min(few, std::max(5000u, T / 4u + 1u));
+    if (T < 6144u) return 6144u;
+    const uint32_t half = T / 2u + 1u;
+    if (caller_waits) return T < 65536u ? half : 65536u;
+    if (T < 4u * 8192u) return std::min(half, std::max(5000u, T / 4u + 1u));
     return std::min(std::max(8192u, T / kMostThreads + 1u), 16384u);
 }
 

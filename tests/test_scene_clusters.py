@@ -128,10 +128,10 @@ def test_loose_triangles_take_time_in_proportion(lib, place):
 
 
 def test_chunks_are_neither_empty_nor_too_many(lib):
-    """From 2048 triangles on there is work for a second thread, whether the caller waits for the scene or not."""
-    for T in [1, 2, 2047, 2048, 4999, 5000, 9_999, 20_000, 32_767, 32_768, 65_535, 65_537, 100_000, 200_000, 1_000_000, 0xFFFFFFFF]:
+    """From 6144 triangles on there is work for a second thread, whether the caller waits for the scene or not."""
+    for T in [1, 2, 4999, 6143, 6144, 9_999, 20_000, 32_767, 32_768, 65_535, 65_537, 100_000, 200_000, 1_000_000, 0xFFFFFFFF]:
         for waits, most in ((1, 65536), (0, 16384)):
             chunk = lib.chunk(T, waits) & 0xFFFFFFFF
-            assert 1025 <= chunk <= most
+            assert 3073 <= chunk <= most
             n = -(-T // chunk)
-            assert n == 1 if T < 2048 else 2 <= n <= max(12, T // most + 1)
+            assert n == 1 if T < 6144 else 2 <= n <= max(12, T // most + 1)
