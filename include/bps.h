@@ -94,7 +94,9 @@ void bps_destroy(bps_renderer *r);
  *   colors    uint8   [V][3]  per-vertex RGB or NULL (required for RGB-D rendering)
  * The mesh is validated (every index < V, every coordinate finite), re-packed on the host into
  * clusters of <= 64 vertices / <= 128 triangles, and copied to the device; the caller may free
- * its arrays on return.  Synchronous.  *out_handle receives the scene id. */
+ * its arrays on return.  Synchronous.  *out_handle receives the scene id.
+ * Meshes of more than 6143 triangles are re-packed on several threads: the calling one and, for the time of the
+ * call, up to eleven more, in all no more than there are CPUs in the calling thread's affinity mask. */
 bps_status bps_load_scene(bps_renderer *r, const float *vertices, uint32_t V, const uint32_t *indices, uint32_t T,
                           const uint8_t *colors, bps_scene *out_handle);
 

@@ -138,7 +138,7 @@ __device__ __forceinline__ void raster_large(uint32_t xy0, uint32_t xy1, uint32_
 }
 
 // The same on packed coordinates (for triangles that the small and medium paths could take but for their size): tiles
-// of 8x8 pixels from the box's first one on, which are fewer than those of a fixed grid (4 instead of 5.8 on average for
+// of 8x8 pixels from the box's first one on, which are fewer than those of a fixed grid (4 instead of 5.6 on average for
 // a box of 12x12), edge functions stepped from tile to tile, and the short division.  Coarse meshes and larger frames
 // are bound by this: 512 environments of 30 k triangles 131 -> 113 us per request, 1000 at 128x128 of 100 k 628 -> 543,
 // 192 textured at 128x128 243 -> 222, 61 at 72x104 65.5 -> 61.5; 1024 of 500 k triangles 236.8 -> 236.1.
@@ -757,8 +757,8 @@ __device__ __forceinline__ void draw_clipped(const WaveLds& L, uint32_t ref, int
 // 1024 environments of 500 k triangles at 64x64: 104.0 M -> 82.5 M vector instructions per launch, request
 // 274 -> 251 us; 4096 at 128x128 (1 M triangles): 2.70 -> 2.54 ms.  Of what remains a wavefront waits 40 % of its
 // time, most of it on LDS round trips: clusters come off the list ahead of their use, no load is left in flight that
-// only one path uses, and the planes of the box tests sit in LDS instead of registers (no vector register spilled in
-// the 64x64 instance, one in the 128x128 and the any-window one): 78.8 M instructions, 238 us; 2.27 ms.  With clusters of
+// only one path uses, and the planes of the box tests sit in LDS instead of registers (no vector register is spilled
+// in the instances that draw by default, and 81 to 90 scalar ones): 78.8 M instructions, 238 us; 2.27 ms.  With clusters of
 // smaller boxes and raster_large_packed: 238 -> 229 us; 2.29 -> 2.17 ms.
 template <int NT, bool DIAG, int CULL, int FRAME>
 __global__ __launch_bounds__(NT, 4) void k_raster(const SceneDev* __restrict__ scenes, const WorkItem* __restrict__ items,

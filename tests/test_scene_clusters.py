@@ -3,6 +3,7 @@ number of chunks it is cut into.  clusters.cpp is compiled by itself: no GPU is 
 import ctypes
 import os
 import subprocess
+import threading
 import time
 
 import numpy as np
@@ -125,6 +126,29 @@ def test_loose_triangles_take_time_in_proportion(lib, place):
             times.append(time.perf_counter() - t0)
         return min(times)
     assert best(360_000) < 7 * best(90_000)
+
+
+@pytest.mark.parametrize("cpus", [1, 2])
+def test_no_more_threads_than_cpus_the_caller_may_use(lib, cpus):
+    """A loader keeps its scenes' packing to some CPUs by its own affinity mask."""
+    mine = sorted(os.sched_getaffinity(0))
+    if len(mine) < 4:
+        pytest.skip("too few CPUs to tell")
+    v, t = (np.ascontiguousarray(a, d) for a, d in zip(_mesh("scan"), (np.float32, np.uint32)))
+    t = np.ascontiguousarray(np.resize(t, (600_000, 3)))
+    p = [a.ctypes.data_as(ctypes.c_void_p) for a in (v, t)]
+
+    def most(mask):
+        def load():
+            os.sched_setaffinity(0, mask)      # (of this thread alone)
+            lib.pack(*p, len(t), 16384, 0, None, None, None, None)
+        before, th, seen = len(os.listdir("/proc/self/task")), threading.Thread(target=load), 0
+        th.start()
+        while th.is_alive():
+            seen = max(seen, len(os.listdir("/proc/self/task")))
+        th.join()
+        return seen - before
+    assert most(mine[:cpus]) <= cpus and 2 < most(mine) <= 12
 
 
 def test_chunks_are_neither_empty_nor_too_many(lib):
