@@ -167,7 +167,11 @@ bps_status fail(bps_renderer* r, bps_status code, const char* fmt, ...) {
             r->error.clear();
         }
     } else {
-        g_create_error = buf;
+        try {
+            g_create_error = buf;
+        } catch (const std::bad_alloc&) {
+            g_create_error.clear();
+        }
     }
     return code;
 }
@@ -179,6 +183,17 @@ bps_status fail(bps_renderer* r, bps_status code, const char* fmt, ...) {
             return fail((r), e_ == hipErrorOutOfMemory ? BPS_ERR_OOM : BPS_ERR_HIP, "%s: %s", \
                         #call, hipGetErrorString(e_));                                        \
     } while (0)
+
+// The C interface lets no exception through: lists that cannot grow are all that throws in there, before anything is enqueued
+// that depends on them.
+template <class Call>
+bps_status guarded(bps_renderer* r, const char* what, Call&& call) {
+    try {
+        return call();
+    } catch (const std::bad_alloc&) {
+        return fail(r, BPS_ERR_OOM, "%s: out of host memory", what);
+    }
+}
 
 // A scene handle is its table slot (low 12 bits) and the slot's generation at load time above it.
 constexpr int kSlotBits = 12;
@@ -918,8 +933,9 @@ bps_status bps_pack_clusters(const float* vertices, uint32_t V, const uint32_t* 
     return BPS_OK;
 }
 
-bps_status bps_unload_scene(bps_renderer* r, bps_scene scene) {
-    if (!r) return BPS_ERR_INVALID_ARG;
+namespace {
+
+bps_status unload(bps_renderer* r, bps_scene scene) {
     std::lock_guard<std::mutex> lock(r->mu);
     const int slot = slot_of(r, scene);
     if (slot < 0) return fail(r, BPS_ERR_BAD_HANDLE, "bps_unload_scene: scene %d is not loaded", scene);
@@ -940,10 +956,8 @@ bps_status bps_unload_scene(bps_renderer* r, bps_scene scene) {
     return BPS_OK;
 }
 
-bps_status bps_render(bps_renderer* r, const bps_scene* scene_ids, const float* view_proj, uint32_t B, float* out_depth,
-                      uint8_t* out_rgb, uint32_t* out_tri_id, void* stream_) {
-    if (!r) return BPS_ERR_INVALID_ARG;
-    if (B == 0) return BPS_OK;
+bps_status render(bps_renderer* r, const bps_scene* scene_ids, const float* view_proj, uint32_t B, float* out_depth,
+                  uint8_t* out_rgb, uint32_t* out_tri_id, void* stream_) {
     std::lock_guard<std::mutex> lock(r->mu);
     if (!scene_ids || !view_proj || !out_depth) return fail(r, BPS_ERR_INVALID_ARG, "bps_render: null argument");
     if (B > (uint32_t)r->cfg.max_batch)
@@ -953,6 +967,7 @@ bps_status bps_render(bps_renderer* r, const bps_scene* scene_ids, const float* 
     hipStream_t stream = (hipStream_t)stream_;
     uint32_t min_clusters = 0xFFFFFFFFu, max_clusters = 0u;
     r->call_slots.resize(B);
+    if (r->profiling) r->ev.reserve(r->ev_used + 2);
     for (uint32_t b = 0; b < B; ++b) {
         const int s = slot_of(r, scene_ids[b]);
         if (s < 0) return fail(r, BPS_ERR_BAD_HANDLE, "bps_render: scene_ids[%u]=%d is not a loaded scene", b, scene_ids[b]);
@@ -1149,10 +1164,8 @@ bps_status bps_render(bps_renderer* r, const bps_scene* scene_ids, const float* 
     return BPS_OK;
 }
 
-bps_status bps_render_static(bps_renderer* r, const bps_scene* scene_ids, const float* view_proj, uint32_t B,
-                             float* out_depth, uint32_t* out_tri_id, void* stream_) {
-    if (!r) return BPS_ERR_INVALID_ARG;
-    if (B == 0) return BPS_OK;
+bps_status render_static(bps_renderer* r, const bps_scene* scene_ids, const float* view_proj, uint32_t B,
+                         float* out_depth, uint32_t* out_tri_id, void* stream_) {
     std::lock_guard<std::mutex> lock(r->mu);
     if (!scene_ids || !view_proj || !out_depth) return fail(r, BPS_ERR_INVALID_ARG, "bps_render_static: null argument");
     if (B > (uint32_t)r->cfg.max_batch)
@@ -1254,6 +1267,27 @@ bps_status bps_render_static(bps_renderer* r, const bps_scene* scene_ids, const 
     r->last_groups = (uint64_t)n_items;
     r->last_wide = cut.wide;
     return BPS_OK;
+}
+
+}  // namespace
+
+bps_status bps_unload_scene(bps_renderer* r, bps_scene scene) {
+    if (!r) return BPS_ERR_INVALID_ARG;
+    return guarded(r, "bps_unload_scene", [&] { return unload(r, scene); });
+}
+
+bps_status bps_render(bps_renderer* r, const bps_scene* scene_ids, const float* view_proj, uint32_t B, float* out_depth,
+                      uint8_t* out_rgb, uint32_t* out_tri_id, void* stream) {
+    if (!r) return BPS_ERR_INVALID_ARG;
+    if (B == 0) return BPS_OK;
+    return guarded(r, "bps_render", [&] { return render(r, scene_ids, view_proj, B, out_depth, out_rgb, out_tri_id, stream); });
+}
+
+bps_status bps_render_static(bps_renderer* r, const bps_scene* scene_ids, const float* view_proj, uint32_t B,
+                             float* out_depth, uint32_t* out_tri_id, void* stream) {
+    if (!r) return BPS_ERR_INVALID_ARG;
+    if (B == 0) return BPS_OK;
+    return guarded(r, "bps_render_static", [&] { return render_static(r, scene_ids, view_proj, B, out_depth, out_tri_id, stream); });
 }
 
 bps_status bps_set_profiling(bps_renderer* r, int32_t enable) {

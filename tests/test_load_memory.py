@@ -1,6 +1,6 @@
 """What memory scene loads take from one another, without a GPU (fake_hip.c)."""
 from test_launch_plans import fake  # noqa: F401  (a fixture)
-from test_load_failures import _run
+from test_out_of_memory import _run
 
 
 def test_scenes_of_about_one_size_follow_each_other(fake):  # noqa: F811

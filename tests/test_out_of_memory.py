@@ -1,5 +1,5 @@
-"""Scene loads that find no memory, without a GPU (fake_hip.c): they end as an error, whichever allocation it was that failed,
-and leave nothing behind."""
+"""Scene loads, requests and retirements that find no memory, without a GPU (fake_hip.c): they end as an error, whichever
+allocation it was that failed, and leave nothing behind."""
 import subprocess
 import sys
 
@@ -30,6 +30,14 @@ def _run(fake, code, *args):  # noqa: F811
     assert p.returncode == 0 and p.stdout.endswith("done\n"), p.stdout + p.stderr
 
 
+def _run_failing(fake, failing_new, code):  # noqa: F811
+    """With `new` as the library of that operator, loaded before libbps.so (which the prelude loads)."""
+    code = PRELUDE.replace("import paper_2103_07013_amd", "new = ctypes.CDLL(sys.argv[2], mode=ctypes.RTLD_GLOBAL)\nnew.fail_left.restype = ctypes.c_long\n"
+                           "import paper_2103_07013_amd", 1) + code
+    p = subprocess.run([sys.executable, "-c", code, fake, failing_new], cwd=ROOT, capture_output=True, text=True, timeout=300)
+    assert p.returncode == 0 and p.stdout.endswith("done\n"), p.stdout + p.stderr
+
+
 @pytest.fixture(scope="module")
 def failing_new(tmp_path_factory):
     d = tmp_path_factory.mktemp("new")
@@ -38,11 +46,9 @@ def failing_new(tmp_path_factory):
     return str(d / "new.so")
 
 
-@pytest.mark.parametrize("T,step", [(600, 1), (5000, 7)])      # one thread, and two
+@pytest.mark.parametrize("T,step", [(600, 1), (8000, 3)])      # one thread, and two
 def test_any_allocation_of_a_load_may_fail(fake, failing_new, T, step):  # noqa: F811
-    # (loaded before libbps.so, which the prelude loads)
-    code = PRELUDE.replace("import paper_2103_07013_amd", "new = ctypes.CDLL(sys.argv[2], mode=ctypes.RTLD_GLOBAL)\nnew.fail_left.restype = ctypes.c_long\n"
-                           "import paper_2103_07013_amd", 1) + f"""
+    _run_failing(fake, failing_new, f"""
 s = synth.make_room_scene({T})
 v, t = np.ascontiguousarray(s.vertices, np.float32), np.ascontiguousarray(s.indices, np.uint32)
 r = bps.bps_create(max_batch=1)
@@ -63,15 +69,43 @@ while True:
     if left >= 0:      # there was none left to fail
         break
     n += {step}
-assert st == 0 and failures > 20 and n > 20 * {step}, (failures, n)
+assert st == 0 and failures > 20, (failures, n)
 assert fake.fake_live(1) == 1 and fake.fake_allocated(1) == 1, "one pinned image served all of them"
 assert bps.bps_query(r, 0, 8) == 1, "and so did one device block"
 bps.bps_destroy(r)
 assert fake.fake_live(0) == fake.fake_live(1) == 0
 print("done")
-"""
-    p = subprocess.run([sys.executable, "-c", code, fake, failing_new], cwd=ROOT, capture_output=True, text=True, timeout=300)
-    assert p.returncode == 0 and p.stdout.endswith("done\n"), p.stdout + p.stderr
+""")
+
+
+def test_any_allocation_of_a_request_or_a_retirement_may_fail(fake, failing_new):  # noqa: F811
+    """Each call is made again until it succeeds, with another allocation failing every time; what is drawn then is right."""
+    _run_failing(fake, failing_new, """
+r = bps.bps_create(max_batch=300)
+def until_it_succeeds(call):
+    for n in range(100):
+        new.fail_after(ctypes.c_long(n))
+        st = call()
+        new.fail_after(ctypes.c_long(-1))
+        assert st in (0, -3), st
+        if st == 0:
+            return n
+    raise SystemExit("never")
+failures = 0
+bps.bps_set_profiling(r, 1)
+for B in (300, 17, 300, 5):
+    h = load(r, small if B == 17 else large)
+    ids = np.full(B, h, np.int32)
+    for k in range(2):
+        fake.fake_clear_log()
+        failures += until_it_succeeds(lambda: lib.bps_render(r, ids.ctypes.data, pool.ctypes.data, B, out.ctypes.data, None, None, None))
+        failures += until_it_succeeds(lambda: lib.bps_render_static(r, ids.ctypes.data, pool.ctypes.data, B, out.ctypes.data, None, None))
+        drawn = [l for l in fake.fake_log().decode().splitlines() if l.startswith("k_raster")]
+        assert len(drawn) == 2 and all(f" envs={B} " in l and " wrong=0 " in l for l in drawn), drawn
+    failures += until_it_succeeds(lambda: lib.bps_unload_scene(r, h))
+assert failures > 20, failures
+print("done")
+""")
 
 
 def test_no_room_for_the_pinned_image_or_the_device_block(fake):  # noqa: F811
