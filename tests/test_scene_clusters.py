@@ -120,10 +120,10 @@ def test_loose_triangles_take_time_in_proportion(lib, place):
         t = np.arange(3 * n, dtype=np.uint32).reshape(-1, 3)
         p = [a.ctypes.data_as(ctypes.c_void_p) for a in (v, t)]
         times = []
-        for _ in range(2):
-            t0 = time.perf_counter()
+        for _ in range(3):
+            t0 = time.thread_time()      # (the chunk is grown by the calling thread; others' load does not count)
             lib.pack(*p, n, 1 << 20, 0, None, None, None, None)
-            times.append(time.perf_counter() - t0)
+            times.append(time.thread_time() - t0)
         return min(times)
     assert best(360_000) < 7 * best(90_000)
 
