@@ -391,6 +391,10 @@ bps::FrameParams frame_params(const bps_renderer* r, const Cut& cut) {
     fp.W = r->rw;
     fp.tile_w = cut.w;
     fp.tile_h = cut.h;
+    fp.tiles_x = cut.nx;
+    fp.tiles_x_recip = (65536u + (uint32_t)cut.nx - 1u) / (uint32_t)cut.nx;
+    fp.two_per_w = 2.0f / (float)fp.W;
+    fp.two_per_h = 2.0f / (float)fp.H;
     fp.sx = 128.0f * (float)fp.W;
     fp.sy = 128.0f * (float)fp.H;
     fp.xmax = 2.0f * fp.sx + 64.0f;

@@ -48,6 +48,9 @@ struct WorkItem {
 struct FrameParams {
     int32_t H, W;
     int32_t tile_w, tile_h; // a work-group owns one tile of the frame (the whole frame when it fits)
+    int32_t tiles_x;        // tiles side by side
+    uint32_t tiles_x_recip; // 65536 / tiles_x rounded up: tile / tiles_x = tile * recip >> 16 for the kMaxWindows tiles there can be
+    float two_per_w, two_per_h;   // 2 / W, 2 / H
     float sx, sy;          // 128*W, 128*H
     float xmax, ymax;      // 2*sx + 64, 2*sy + 64
     float background;
@@ -85,10 +88,10 @@ constexpr int kHizTiles = 64;          // 8x8-pixel tiles of a window of at most
 constexpr int kDepthBins = 128;        // bins of the per-round depth sort of surviving clusters
 
 // visibility buffer, per-wave blocks, survivor list (8 B record + two 2 B sort words per cluster),
-// block order, depth histogram and its prefix, depth tiles, the window's planes, eight counters, clip ring
+// block order, depth histogram, depth tiles, the window's planes, eight counters, clip ring
 __host__ __device__ inline size_t lds_bytes(int tile_h, int tile_w, int threads, int list_cap) {
     return (size_t)((tile_h * tile_w + 1) & ~1) * 8 + (size_t)(threads / 64) * kWaveLdsBytes + (size_t)list_cap * 12 + kOrderCap * 2 +
-           2 * kDepthBins * 4 + kHizTiles * 4 + 12 * 16 + 32 + (size_t)clip_ring_entries(threads) * 4;
+           kDepthBins * 4 + kHizTiles * 4 + 8 * 48 + 32 + (size_t)clip_ring_entries(threads) * 4;
 }
 
 // DIAG = true is the instance launched while diagnostics are on; it alone keeps counters and timers.
@@ -126,6 +129,7 @@ constexpr uint32_t kPackedEnvBits = 14, kPackedSceneBits = 12;
 constexpr uint32_t kMaxWindows = 64;      // windows a frame is cut into at most
 static_assert(kMaxWindows <= 1u << (32 - kPackedEnvBits - kPackedSceneBits), "a window's number fits its bits");
 static_assert(kMaxPlannedItems <= 1u << kPackedEnvBits, "every environment of a request has an item");
+static_assert(kMaxWindows * kMaxWindows <= 65536u, "exact division by a multiplication (FrameParams::tiles_x_recip)");
 constexpr uint32_t kPackedItemsPerLaunch = 960;
 struct PackedItems {
     uint32_t word[kPackedItemsPerLaunch];
