@@ -882,7 +882,11 @@ __global__ __launch_bounds__(NT, 4) void k_raster(const SceneDev* __restrict__ s
     ring.mask = clip_ring_entries(NT) - 1u;
 
     const WorkItem item = items[blockIdx.x];     // the host or the planner has put the items in launch order
-    const SceneDev sc = scenes[item.scene];
+    // (field by field: the record is loaded sixteen registers at a time, and whatever of it were still needed later would be
+    // spilled, and come back, with all the rest)
+    SceneDev sc = scenes[item.scene];
+    asm volatile("" : "+s"(sc.cverts), "+s"(sc.ctris), "+s"(sc.ctri_id), "+s"(sc.cbounds), "+s"(sc.bbounds), "+s"(sc.n_clusters), "+s"(sc.c_stride),
+                 "+s"(sc.b_stride));
     float M[16];
 #pragma unroll
     for (int k = 0; k < 16; ++k) M[k] = view_proj[(size_t)item.env * 16 + k];
