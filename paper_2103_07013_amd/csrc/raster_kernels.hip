@@ -80,14 +80,17 @@ __device__ __forceinline__ void drain_small(const WaveLds& L, int n, int lane, u
     asm volatile("" :: "v"(id));
 }
 
+// The lane's bit of a mask as a condition (no instruction: conditions are masks).
+__device__ __forceinline__ bool in_mask(u64 mask) { return __builtin_amdgcn_inverse_ballot_w64(mask); }
+
 // Append small triangles to the wave's queue; whenever it reaches 64 entries, drain them.
-__device__ __forceinline__ void push_small(const WaveLds& L, int& count, bool want, uint32_t xy0, uint32_t xy1,
+__device__ __forceinline__ void push_small(const WaveLds& L, int& count, uint32_t xy0, uint32_t xy1,
                                            uint32_t xy2, float iw0, float iw1, float iw2, uint32_t ref, uint32_t box,
                                            int lane, u64* vis, const Window& win,
                                            const BPS_GLOBAL uint32_t* ctri_id, u64 mask) {
-    // mask = the lanes that want (handed in: callers build it from ballots of single comparisons,
+    // mask = the lanes that want (callers build it from ballots of single comparisons,
     // which cost one compare each, instead of a ballot of the combined condition)
-    if (mask == 0) return;
+    if (__builtin_expect(mask == 0, 0)) return;
     int n = __popcll(mask);
     L.tally[kTSmall] += (uint32_t)n;
     ++L.tally[kTPushes];
@@ -99,18 +102,18 @@ __device__ __forceinline__ void push_small(const WaveLds& L, int& count, bool wa
         L.smallq[5 * 64 + pos] = __float_as_uint(iw2);
         L.smallq[6 * 64 + pos] = ref; L.smallq[7 * 64 + pos] = box;
     };
-    if (count + n < 64) {
-        if (want) put();
+    if (__builtin_expect(count + n < 64, 1)) {
+        if (in_mask(mask)) put();
         count += n;
         return;
     }
-    const bool first = want && pos < 64, later = want && !first;
-    if (first) put();
+    const u64 first = mask & ballot64(pos < 64);
+    if (in_mask(first)) put();
     wave_lds_sync();
     drain_small(L, 64, lane, vis, win, ctri_id);
     wave_lds_sync();
     pos -= 64;
-    if (later) put();
+    if (in_mask(mask & ~first)) put();
     count += n - 64;
 }
 
@@ -208,12 +211,12 @@ __device__ __forceinline__ bool centre_box(uint32_t xy0, uint32_t xy1, uint32_t 
 // ref = cluster * 128 + slot addresses the triangle's original id in ctri_id; small triangles
 // carry it through the queue, only large ones look the id up here.
 template <int FRAME>
-__device__ __forceinline__ void emit(const WaveLds& L, int& small_count, bool valid, short2v lo, short2v ext, uint32_t wide,
+__device__ __forceinline__ void emit(const WaveLds& L, int& small_count, short2v lo, short2v ext, uint32_t wide,
                                      bool tame,
                                      uint32_t xy0, uint32_t xy1, uint32_t xy2, float iw0, float iw1, float iw2,
                                      uint32_t ref, const BPS_GLOBAL uint32_t* ctri_id, int lane, u64* vis,
                                      const Window& win, u64 vmask) {
-    // vmask = the lanes with valid set
+    // vmask = the lanes that have one
     // first pixel and size per axis as four bytes: i | j << 8 | nx << 16 | ny << 24
     const uint32_t first = as_u32(lo + (short)64), size = as_u32(ext + (short)1);
     const uint32_t box = __builtin_amdgcn_perm(size, first, 0x06040200u);
@@ -227,8 +230,7 @@ __device__ __forceinline__ void emit(const WaveLds& L, int& small_count, bool va
     ++L.tally[kTEmits];
     const u64 packed_mask = !tame ? 0ull : vmask & narrow_mask;
     const u64 small_mask = packed_mask & few_mask;
-    const bool small = valid && few && (FRAME == 64 || (wide & 0x80008000u) == 0u) && tame;
-    push_small(L, small_count, small, xy0, xy1, xy2, iw0, iw1, iw2, ref, box, lane, vis, win, ctri_id, small_mask);
+    push_small(L, small_count, xy0, xy1, xy2, iw0, iw1, iw2, ref, box, lane, vis, win, ctri_id, small_mask);
     u64 med = packed_mask & ~small_mask & ballot64(within8);
     u64 big = vmask & ~small_mask & ~med;
     L.tally[kTLarge] += (uint32_t)__popcll(med | big);
@@ -236,7 +238,7 @@ __device__ __forceinline__ void emit(const WaveLds& L, int& small_count, bool va
     // 64x64 of 500 k triangles 237.0 -> 233.5 us, 4096 at 128x128 2221 -> 2197)
     if (__builtin_expect((med | big) == 0ull, 1)) return;
     uint32_t id = 0u;
-    if (valid && !small) id = ctri_id[ref];
+    if (in_mask(med | big)) id = ctri_id[ref];
     // medium triangles (box within 8x8 pixels): four per pass, sixteen lanes each, 4x4 pixels per step
     while (med) {
         ++L.tally[kTMedPasses];
@@ -485,13 +487,13 @@ struct ClipRing {
 };
 
 // tail_seen: the ring's tail right after this wavefront's reservation
-__device__ __forceinline__ void push_clip(const ClipRing& R, bool want, uint32_t ref, u64 mask, int lane, uint32_t& tail_seen) {
+__device__ __forceinline__ void push_clip(const ClipRing& R, uint32_t ref, u64 mask, int lane, uint32_t& tail_seen) {
     if (mask == 0) return;
     const uint32_t count = (uint32_t)__popcll(mask);
     uint32_t pos = 0;
     if (lane == 0) pos = atomicAdd(R.tail, count);
     pos = __builtin_amdgcn_readfirstlane(pos);
-    if (want) R.slot[(pos + rank_below(mask)) & R.mask] = ref;
+    if (in_mask(mask)) R.slot[(pos + rank_below(mask)) & R.mask] = ref;
     tail_seen = pos + count;
 }
 
@@ -806,7 +808,7 @@ __device__ __forceinline__ void draw_clipped(const WaveLds& L, uint32_t ref, int
                     cl.w2 = next.y;
                 }
             }
-            emit<FRAME>(L, small_count, has, lo, ext, wide, tame, cl.p0, b, d, cl.w0, wb, wd, cl.ref, ctri_id, lane, vis, win, ballot64(has));
+            emit<FRAME>(L, small_count, lo, ext, wide, tame, cl.p0, b, d, cl.w0, wb, wd, cl.ref, ctri_id, lane, vis, win, ballot64(has));
         }
         have = left;
     } while (__builtin_expect(ballot64(have) != 0ull, 0));
@@ -1313,31 +1315,25 @@ __global__ __launch_bounds__(NT, 4) void k_raster(const SceneDev* __restrict__ s
                 uint32_t t = (slot == 0 ? t0 : t1) & full_tri_mask;
                 const uint32_t i0 = t & 0xFFu, i1 = (t >> 8) & 0xFFu, i2 = t >> 16;
                 float2 a = L.stage[i0], b = L.stage[i1], d = L.stage[i2];
-                bool fast = true;
-                u64 fast_mask = ~0ull;      // masks are combined on the scalar unit
                 short2v lo, ext;
                 uint32_t wide;
                 const bool has = centre_box(__float_as_uint(a.x), __float_as_uint(b.x), __float_as_uint(d.x), win, lo, ext, wide);
-                const u64 has_mask = ballot64(has);
-                if (!all_inside) {
+                u64 drawable = ballot64(has);      // masks are combined on the scalar unit
+                if (__builtin_expect(!all_inside, 0)) {
                     uint32_t oa = L.stage_oc[i0], ob = L.stage_oc[i1], od = L.stage_oc[i2];
                     uint32_t o_or = oa | ob | od, o_and = oa & ob & od;
-                    const bool sound = (o_or & kInvalid) == 0, apart = (o_and & 0x3Fu) == 0, crossing = (o_or & 0x3Fu) != 0;
-                    const bool behind = (o_or & kNoProject) != 0;
-                    const bool live = sound && apart;
-                    const u64 live_mask = ballot64(sound) & ballot64(apart), crossing_mask = ballot64(crossing);
-                    fast = live && !crossing;
-                    fast_mask = live_mask & ~crossing_mask;
+                    const u64 live = ballot64((o_or & kInvalid) == 0) & ballot64((o_and & 0x3Fu) == 0);
+                    const u64 crossing = ballot64((o_or & 0x3Fu) != 0), behind = ballot64((o_or & kNoProject) != 0);
                     // A straddler whose three vertices all project (w > 0) cannot reach a pixel centre
                     // outside the box of its projected vertices: only the others need the clipper.
-                    const bool straddle = live && crossing && (has || behind);
-                    const u64 straddle_mask = live_mask & crossing_mask & (has_mask | ballot64(behind));
-                    st_straddle += (uint32_t)__popcll(straddle_mask);
-                    push_clip(ring, straddle, (c << 7) | (uint32_t)(slot * 64 + lane), straddle_mask, lane, clip_tail_seen);
+                    const u64 straddling = live & crossing & (drawable | behind);
+                    drawable &= live & ~crossing;
+                    st_straddle += (uint32_t)__popcll(straddling);
+                    push_clip(ring, (c << 7) | (uint32_t)(slot * 64 + lane), straddling, lane, clip_tail_seen);
                 }
-                emit<FRAME>(L, small_count, fast && has, lo, ext, wide, tame, __float_as_uint(a.x), __float_as_uint(b.x),
+                emit<FRAME>(L, small_count, lo, ext, wide, tame, __float_as_uint(a.x), __float_as_uint(b.x),
                      __float_as_uint(d.x), a.y, b.y, d.y, c * 128u + (uint32_t)(slot * 64 + lane), g_ctri_id, lane, vis,
-                     win, fast_mask & has_mask);
+                     win, drawable);
             }
         }
         TICK(5);
