@@ -143,7 +143,10 @@ __device__ __forceinline__ void raster_large(uint32_t xy0, uint32_t xy1, uint32_
 // One triangle per lane of `big` is set up, at the cost of setting up one; the wavefront then draws one after the other,
 // handing round what the loop over its tiles needs (11 words instead of 8, and no products of its own): 1000 at 128x128
 // of 100 k triangles 550 -> 531 us, 512 of 30 k 115 -> 110, 192 textured at 128x128 223 -> 219, 4096 at 128x128 of 500 k
-// 2227 -> 2200.
+// 2227 -> 2200.  What bounds a tile is the chain of its instructions, scalar ones and waits between the units among
+// them: here and for medium triangles one comparison of a sign bit decides instead of five combined by the scalar unit,
+// and which 4x4 pixels of the medium ones are entered is known once per pass.  192 textured at 128x128 218 -> 209 us, 61
+// at 72x104 56.9 -> 54.7, 4096 at 128x128 1994 -> 1963, 512 106.0 -> 104.5.
 __device__ __forceinline__ void raster_large_packed(uint32_t xy0, uint32_t xy1, uint32_t xy2, float iw0, float iw1, float iw2,
                                                     uint32_t id, uint32_t box, u64 big, int lane, u64* vis, const Window& win, uint32_t* tally) {
     const PackedSetup s = make_packed_setup(xy0, xy1, xy2, iw0, iw1, iw2);
@@ -155,32 +158,41 @@ __device__ __forceinline__ void raster_large_packed(uint32_t xy0, uint32_t xy1, 
     while (big) {
         const int src = __builtin_ctzll(big);
         big &= big - 1;
-        const uint32_t b = (uint32_t)bcast_i((int)box, src), e0 = (uint32_t)bcast_i((int)s.e0, src), e1 = (uint32_t)bcast_i((int)s.e1, src);
-        const int A2 = bcast_i(s.A2, src), t = bcast_i(inside, src), t0 = t & 1, t1 = (t >> 1) & 1, t2 = t >> 2;
-        const float w0 = bcast_f(s.iw0, src), w1 = bcast_f(s.iw1, src), w2 = bcast_f(s.iw2, src), a2f = (float)A2;
+        const uint32_t b = (uint32_t)bcast_i((int)box, src);
+        // (in vector registers from here on: the scalar unit would wait for each of them)
+        uint32_t e0 = (uint32_t)bcast_i((int)s.e0, src), e1 = (uint32_t)bcast_i((int)s.e1, src), at0 = b;
+        int A2 = bcast_i(s.A2, src), t = bcast_i(inside, src);
+        const float w0 = bcast_f(s.iw0, src), w1 = bcast_f(s.iw1, src), w2 = bcast_f(s.iw2, src);
         const uint32_t tri = (uint32_t)bcast_i((int)id, src);
-        const int nx = (int)((b >> 16) & 0xFFu), ny = (int)(b >> 24);
+        asm volatile("" : "+v"(e0), "+v"(e1), "+v"(A2), "+v"(t), "+v"(at0));
+        const float a2f = (float)A2;
         const int dx0 = unpack_x(e0), dy0 = unpack_y(e0), dx1 = unpack_x(e1), dy1 = unpack_y(e1);
+        // sign bits tell what is inside: of an edge (E0 >= t0, E1 >= t1, and E2 >= t2 with E2 = A2 - E0 - E1), of the box
         int E0 = bcast_i(first0, src) + ((__mul24(dx0, lj) - __mul24(dy0, li)) << 8);
         int E1 = bcast_i(first1, src) + ((__mul24(dx1, lj) - __mul24(dy1, li)) << 8);
-        int row = __mul24((int)((b >> 8) & 0xFFu) + lj - win.y0, win.pitch) + ((int)(b & 0xFFu) + li - win.x0);
+        const int t0 = t & 1, t1 = (t >> 1) & 1, most = A2 - (t >> 2);
+        const int nx = (int)((b >> 16) & 0xFFu), ny = (int)(b >> 24);
+        int row = __mul24((int)((at0 >> 8) & 0xFFu) + lj - win.y0, win.pitch) + ((int)(at0 & 0xFFu) + li - win.x0);
+        const int right0 = dy0 << 11, right1 = dy1 << 11, down0 = dx0 << 11, down1 = dx1 << 11;
+        int in_rows = lj - ny;
         for (int y = 0; y < ny; y += 8) {
-            const bool in_rows = lj < ny - y;
-            int F0 = E0, F1 = E1, at = row;
+            int F0 = E0, F1 = E1, at = row, in_columns = li - nx;
             for (int x = 0; x < nx; x += 8) {
                 ++tally[kTLargeSteps];
-                const int F2 = A2 - F0 - F1;
-                if (in_rows & (li < nx - x) & (F0 >= t0) & (F1 >= t1) & (F2 >= t2)) {
-                    const float num = fmaf((float)F2, w2, fmaf((float)F1, w1, (float)F0 * w0));
+                const int outside = (F0 - t0) | (F1 - t1) | (most - F0 - F1);
+                if ((~outside & in_rows & in_columns) < 0) {
+                    const float num = fmaf((float)(A2 - F0 - F1), w2, fmaf((float)F1, w1, (float)F0 * w0));
                     atomicMin(&vis[at], ((u64)__float_as_uint(div_in_range(a2f, num)) << 32) | (u64)tri);
                 }
-                F0 -= dy0 << 11;
-                F1 -= dy1 << 11;
+                F0 -= right0;
+                F1 -= right1;
                 at += 8;
+                in_columns += 8;
             }
-            E0 += dx0 << 11;
-            E1 += dx1 << 11;
+            E0 += down0;
+            E1 += down1;
             row += 8 * win.pitch;
+            in_rows += 8;
         }
     }
 }
@@ -259,23 +271,29 @@ __device__ __forceinline__ void emit(const WaveLds& L, int& small_count, short2v
         const PackedSetup st = make_packed_setup(mxy0, mxy1, mxy2, miw0, miw1, miw2);
         const float a2f = (float)st.A2;
         const int mi = (int)(mbox & 0xFFu), mj = (int)((mbox >> 8) & 0xFFu);
-        const int mnx = (int)((mbox >> 16) & 0xFFu), mny = (int)(mbox >> 24);
+        const int mnx = on && st.A2 != 0 ? (int)((mbox >> 16) & 0xFFu) : 0, mny = (int)(mbox >> 24);
         const int li = lane & 3, lj = (lane >> 2) & 3;
-#pragma unroll
-        for (int by = 0; by < 2; ++by)
-#pragma unroll
-            for (int bx = 0; bx < 2; ++bx) {
-                const int di = bx * 4 + li, dj = by * 4 + lj;
-                const bool act = on && di < mnx && dj < mny;
-                if (ballot64(act) == 0) continue;
-                int E0, E1, E2;
-                packed_edges(st, pack_xy(((mi + di) << 8) + 128, ((mj + dj) << 8) + 128), E0, E1, E2);
-                if (act & (st.A2 != 0) & (E0 >= st.t0) & (E1 >= st.t1) & (E2 >= st.t2)) {
-                    const float num = fmaf((float)E2, st.iw2, fmaf((float)E1, st.iw1, (float)E0 * st.iw0));
-                    const u64 key = ((u64)__float_as_uint(div_in_range(a2f, num)) << 32) | (u64)mid;
-                    atomicMin(&vis[__mul24(mj + dj - win.y0, win.pitch) + (mi + di - win.x0)], key);
-                }
+        // 4x4 pixels at the corner of the box, to the right of them, below, and beside; sign bits as in raster_large_packed
+        const u64 wider = ballot64(mnx > 4), taller = ballot64(mnx != 0 && mny > 4);
+        int E0, E1, E2;
+        packed_edges(st, pack_xy(((mi + li) << 8) + 128, ((mj + lj) << 8) + 128), E0, E1, E2);
+        const int most = st.A2 - st.t2, right0 = unpack_y(st.e0) << 10, right1 = unpack_y(st.e1) << 10;
+        const int at = __mul24(mj + lj - win.y0, win.pitch) + (mi + li - win.x0);
+        auto tile = [&](int F0, int F1, int in_columns, int in_rows, int where) {
+            const int outside = (F0 - st.t0) | (F1 - st.t1) | (most - F0 - F1);
+            if ((~outside & in_rows & in_columns) < 0) {
+                const float num = fmaf((float)(st.A2 - F0 - F1), st.iw2, fmaf((float)F1, st.iw1, (float)F0 * st.iw0));
+                atomicMin(&vis[where], ((u64)__float_as_uint(div_in_range(a2f, num)) << 32) | (u64)mid);
             }
+        };
+        tile(E0, E1, li - mnx, lj - mny, at);
+        if (wider != 0ull) tile(E0 - right0, E1 - right1, li + 4 - mnx, lj - mny, at + 4);
+        if (taller != 0ull) {
+            E0 += unpack_x(st.e0) << 10;
+            E1 += unpack_x(st.e1) << 10;
+            tile(E0, E1, li - mnx, lj + 4 - mny, at + 4 * win.pitch);
+            if (wider != 0ull) tile(E0 - right0, E1 - right1, li + 4 - mnx, lj + 4 - mny, at + 4 * win.pitch + 4);
+        }
     }
     u64 general = big & ~packed_mask;
     big &= packed_mask;
