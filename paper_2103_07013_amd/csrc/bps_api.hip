@@ -1,5 +1,6 @@
 // Host side of the C ABI declared in include/bps.h: renderer object, scene table, request
 // staging and launch planning.  All rendering arithmetic is in raster_kernels.hip.
+#include <dlfcn.h>
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -100,6 +101,7 @@ struct bps_renderer {
     bps_config cfg{};
     int device = 0;
     int num_cu = 0;
+    bool events_in_launches = false;  // a request's event is the end of its last kernel rather than a packet behind it
     int threads = 512;
     int ss = 1, rw = 64, rh = 64;     // supersampling factor and rendered frame size
     float* ss_depth = nullptr;        // [max_batch][rh][rw] when supersampling
@@ -460,6 +462,11 @@ bps_status bps_create(const bps_config* cfg, bps_renderer** out) {
         hipDeviceProp_t prop;
         BPS_HIP(r, hipGetDeviceProperties(&prop, r->device));
         r->num_cu = prop.multiProcessorCount;
+        // A library put in front of the runtime may have the plain launch and not the extended one: what it shows of a
+        // launch and of an event then belongs together only if both are its own.
+        Dl_info plain{}, extended{};
+        r->events_in_launches = dladdr(reinterpret_cast<const void*>(&hipLaunchKernel), &plain) != 0 &&
+                                dladdr(reinterpret_cast<const void*>(&hipExtLaunchKernel), &extended) != 0 && plain.dli_fbase == extended.dli_fbase;
         int lds_optin = 0;
         if (hipDeviceGetAttribute(&lds_optin, hipDeviceAttributeSharedMemPerBlockOptin, r->device) != hipSuccess) lds_optin = 0;
         (void)hipGetLastError();
@@ -1137,9 +1144,12 @@ bps_status render(bps_renderer* r, const bps_scene* scene_ids, const float* view
         ev_stop = r->ev[r->ev_used + 1];
         r->ev_used += 2;
     }
-    bps::launch_raster(r->threads, dim3((unsigned)n_items), cut.wide ? r->wide_lds : r->lds, stream, r->d_scenes,
-                       planned ? d_ordered : d_items, d_vp, fp, r->fixed_layout, cut.wide, r->gvis, out_depth, out_tri_id, d_stats);
-    BPS_HIP(r, hipGetLastError());
+    // the request ends with its last kernel
+    const bool raster_last = r->events_in_launches && S <= 1 && !rgbd && r->ss <= 1 && !ev_stop;
+    const bool shade_last = r->events_in_launches && rgbd && r->ss <= 1, downsample_last = r->events_in_launches && r->ss > 1;
+    BPS_HIP(r, bps::launch_raster(raster_last ? slot.done : nullptr, r->threads, dim3((unsigned)n_items), cut.wide ? r->wide_lds : r->lds, stream,
+                                  r->d_scenes, planned ? d_ordered : d_items, d_vp, fp, r->fixed_layout, cut.wide, r->gvis, out_depth,
+                                  out_tri_id, d_stats));
     if (ev_stop) BPS_HIP(r, hipEventRecord(ev_stop, stream));
     if (S > 1) {
         size_t n = (size_t)B * HW;
@@ -1148,14 +1158,12 @@ bps_status render(bps_renderer* r, const bps_scene* scene_ids, const float* view
         BPS_HIP(r, hipGetLastError());
     }
     if (rgbd) {
-        bps::launch_shade(stream, r->d_scenes, d_env_scene, d_vp, fp, B, out_tri_id, out_rgb);
-        BPS_HIP(r, hipGetLastError());
+        BPS_HIP(r, bps::launch_shade(shade_last ? slot.done : nullptr, stream, r->d_scenes, d_env_scene, d_vp, fp, B, out_tri_id, out_rgb));
     }
     if (r->ss > 1) {
-        bps::launch_downsample(stream, out_depth, out_rgb, B, H, W, final_depth, final_rgb);
-        BPS_HIP(r, hipGetLastError());
+        BPS_HIP(r, bps::launch_downsample(downsample_last ? slot.done : nullptr, stream, out_depth, out_rgb, B, H, W, final_depth, final_rgb));
     }
-    BPS_HIP(r, hipEventRecord(slot.done, stream));
+    if (!raster_last && !shade_last && !downsample_last) BPS_HIP(r, hipEventRecord(slot.done, stream));
     slot.pending = true;
     slot.seq = seq;
     if (uses_shared) {
@@ -1259,11 +1267,10 @@ bps_status render_static(bps_renderer* r, const bps_scene* scene_ids, const floa
         bps::launch_plan(stream, r->d_scenes, d_items, view_proj, fp, (uint32_t)n_items, d_cost, d_ordered);
         BPS_HIP(r, hipGetLastError());
     }
-    bps::launch_raster(r->threads, dim3((unsigned)n_items), r->lds, stream, r->d_scenes, planned ? d_ordered : d_items, view_proj,
-                       fp, r->fixed_layout, cut.wide, nullptr, out_depth, out_tri_id, nullptr);
-    BPS_HIP(r, hipGetLastError());
+    BPS_HIP(r, bps::launch_raster(slot && r->events_in_launches ? slot->done : nullptr, r->threads, dim3((unsigned)n_items), r->lds, stream, r->d_scenes,
+                                  planned ? d_ordered : d_items, view_proj, fp, r->fixed_layout, cut.wide, nullptr, out_depth, out_tri_id, nullptr));
     if (slot) {
-        BPS_HIP(r, hipEventRecord(slot->done, stream));
+        if (!r->events_in_launches) BPS_HIP(r, hipEventRecord(slot->done, stream));
         slot->pending = true;
         slot->seq = seq;
     }

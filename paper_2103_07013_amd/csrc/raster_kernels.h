@@ -17,6 +17,7 @@
 // All float arithmetic follows one fixed IEEE sequence (explicit fmaf, no contraction, exact
 // division) so that coverage and ids are reproducible bit for bit.
 #pragma once
+#include <hip/hip_ext.h>
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -112,7 +113,23 @@ __global__ void k_resolve(unsigned long long* __restrict__ gvis, size_t n, float
 __global__ void k_fill_keys(unsigned long long* __restrict__ gvis, size_t n);
 __global__ void k_zero_words(unsigned long long* __restrict__ p, size_t n);
 
-void launch_raster(int threads, dim3 grid, size_t lds, hipStream_t stream, const SceneDev* scenes, const WorkItem* items,
+// Launches a kernel; `done`, if given, is an event that is reached when the kernel has finished.  The event is the end
+// of the kernel's own packet: recorded behind it, it takes a packet of its own, which costs a request 3 us (one environment
+// 22.1 -> 19.1 us, 16 in a small room 24.5 -> 21.7, 61 at 72x104 54.6 -> 51.7, 512 104.6 -> 101.6).
+template <class T>
+struct same { using type = T; };      // (no deduction from the arguments)
+template <class... P>
+hipError_t launch_kernel(hipEvent_t done, void (*kernel)(P...), dim3 grid, dim3 block, size_t lds, hipStream_t stream,
+                         typename same<P>::type... args) {
+    if (done) {
+        void* list[] = {&args...};
+        return hipExtLaunchKernel(reinterpret_cast<const void*>(kernel), grid, block, list, lds, stream, nullptr, done, 0);
+    }
+    hipLaunchKernelGGL(kernel, grid, block, lds, stream, args...);
+    return hipGetLastError();
+}
+
+hipError_t launch_raster(hipEvent_t done, int threads, dim3 grid, size_t lds, hipStream_t stream, const SceneDev* scenes, const WorkItem* items,
                    const float* view_proj, const FrameParams& fp, bool fixed_layout, bool wide, unsigned long long* gvis,
                    float* out_depth, uint32_t* out_id, unsigned long long* stats);
 // Fills ordered[n_items] with the items in launch order, costliest first; cost is scratch, one word
@@ -135,11 +152,11 @@ struct PackedItems {
     uint32_t word[kPackedItemsPerLaunch];
 };
 void launch_unpack_items(hipStream_t stream, const PackedItems& packed, uint32_t first, uint32_t count, WorkItem* items);
-void launch_downsample(hipStream_t stream, const float* depth, const uint8_t* rgb, uint32_t B, int H, int W,
+hipError_t launch_downsample(hipEvent_t done, hipStream_t stream, const float* depth, const uint8_t* rgb, uint32_t B, int H, int W,
                        float* out_depth, uint8_t* out_rgb);
 // Fills sc.tri_rec from the scene's original arrays (once per scene, on the stream that uploads it).
 void launch_build_shade_records(hipStream_t stream, const SceneDev& sc, float* tri_rec);
-void launch_shade(hipStream_t stream, const SceneDev* scenes, const uint32_t* env_scene, const float* view_proj,
+hipError_t launch_shade(hipEvent_t done, hipStream_t stream, const SceneDev* scenes, const uint32_t* env_scene, const float* view_proj,
                   const FrameParams& fp, uint32_t B, const uint32_t* tri_id, uint8_t* out_rgb);
 
 }  // namespace bps

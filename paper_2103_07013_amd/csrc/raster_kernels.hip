@@ -1701,7 +1701,7 @@ hipError_t prepare_raster(int threads, size_t lds, bool fixed_layout, size_t wid
                                (int)lds_bytes(64, 64, 1024, (int)kListCap64));
 }
 
-void launch_raster(int threads, dim3 grid, size_t lds, hipStream_t stream, const SceneDev* scenes, const WorkItem* items,
+hipError_t launch_raster(hipEvent_t done, int threads, dim3 grid, size_t lds, hipStream_t stream, const SceneDev* scenes, const WorkItem* items,
                    const float* view_proj, const FrameParams& fp, bool fixed_layout, bool wide, unsigned long long* gvis,
                    float* out_depth, uint32_t* out_id, unsigned long long* stats) {
     // The default configuration runs on instances whose LDS layout is a compile-time constant: one each for
@@ -1709,23 +1709,21 @@ void launch_raster(int threads, dim3 grid, size_t lds, hipStream_t stream, const
     if (threads == 512 && !stats && fp.cull == 2 && fixed_layout) {
         const size_t lds64 = lds_bytes(64, 64, 512, (int)kListCap64);
         if (wide) {
-            hipLaunchKernelGGL((k_raster<1024, false, 2, 1>), grid, dim3(1024), lds_bytes(64, 64, 1024, (int)kListCap64), stream, scenes,
-                               items, view_proj, fp, gvis, out_depth, out_id, stats);
-            return;
+            return launch_kernel(done, &k_raster<1024, false, 2, 1>, grid, dim3(1024), lds_bytes(64, 64, 1024, (int)kListCap64), stream, scenes,
+                                 items, view_proj, fp, gvis, out_depth, out_id, stats);
         }
         const bool full = fp.tile_w == 64 && fp.tile_h == 64;
 #define BPS_LAUNCH_FIXED(FRAME)                                                                                        \
-    hipLaunchKernelGGL((k_raster<512, false, 2, FRAME>), grid, dim3(512), lds64, stream, scenes, items, view_proj, fp, gvis, \
-                       out_depth, out_id, stats)
+    return launch_kernel(done, &k_raster<512, false, 2, FRAME>, grid, dim3(512), lds64, stream, scenes, items, view_proj, fp, gvis, \
+                         out_depth, out_id, stats)
         if (full && fp.W == 64 && fp.H == 64) BPS_LAUNCH_FIXED(64);
         else if (full && fp.W == 128 && fp.H == 128) BPS_LAUNCH_FIXED(128);
         else BPS_LAUNCH_FIXED(1);
 #undef BPS_LAUNCH_FIXED
-        return;
     }
 #define BPS_LAUNCH3(NT, DIAG, CULL)                                                                                    \
-    hipLaunchKernelGGL((k_raster<NT, DIAG, CULL, 0>), grid, dim3(NT), lds, stream, scenes, items, view_proj, fp, gvis,          \
-                       out_depth, out_id, stats)
+    return launch_kernel(done, &k_raster<NT, DIAG, CULL, 0>, grid, dim3(NT), lds, stream, scenes, items, view_proj, fp, gvis,   \
+                         out_depth, out_id, stats)
 #define BPS_LAUNCH2(NT, DIAG)                                                                                          \
     do {                                                                                                               \
         if (fp.cull == 0) BPS_LAUNCH3(NT, DIAG, 0);                                                                    \

@@ -566,11 +566,10 @@ __global__ __launch_bounds__(256) void k_downsample(const float* __restrict__ de
                                             (int)rgb[3 * (s + W + 1) + c] + 2) >> 2);
 }
 
-void launch_downsample(hipStream_t stream, const float* depth, const uint8_t* rgb, uint32_t B, int H, int W,
+hipError_t launch_downsample(hipEvent_t done, hipStream_t stream, const float* depth, const uint8_t* rgb, uint32_t B, int H, int W,
                        float* out_depth, uint8_t* out_rgb) {
     size_t n = (size_t)B * (H / 2) * (W / 2);
-    hipLaunchKernelGGL(k_downsample, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, stream, depth, rgb, B, H, W, out_depth,
-                       out_rgb);
+    return launch_kernel(done, &k_downsample, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, stream, depth, rgb, B, H, W, out_depth, out_rgb);
 }
 
 // One thread per triangle: gather its three positions and colours (or texture coordinates) from the
@@ -603,12 +602,12 @@ void launch_build_shade_records(hipStream_t stream, const SceneDev& sc, float* t
     hipLaunchKernelGGL(k_build_shade_records, dim3((sc.n_tris + 255u) / 256u), dim3(256), 0, stream, sc, tri_rec);
 }
 
-void launch_shade(hipStream_t stream, const SceneDev* scenes, const uint32_t* env_scene, const float* view_proj,
+hipError_t launch_shade(hipEvent_t done, hipStream_t stream, const SceneDev* scenes, const uint32_t* env_scene, const float* view_proj,
                   const FrameParams& fp, uint32_t B, const uint32_t* tri_id, uint8_t* out_rgb) {
     const uint32_t tiles_x = (uint32_t)fp.W / 8u, tiles = tiles_x * ((uint32_t)fp.H / 8u), per_frame = (tiles + 3u) / 4u;
     const int dword_stores = (reinterpret_cast<uintptr_t>(out_rgb) & 3u) == 0u ? 1 : 0;      // frames are multiples of 4 bytes
-    hipLaunchKernelGGL(k_shade, dim3(B * per_frame), dim3(256), 0, stream, scenes, env_scene, view_proj, fp, B, per_frame,
-                       make_divider(per_frame), make_divider(tiles_x), tri_id, out_rgb, dword_stores);
+    return launch_kernel(done, &k_shade, dim3(B * per_frame), dim3(256), 0, stream, scenes, env_scene, view_proj, fp, B, per_frame,
+                         make_divider(per_frame), make_divider(tiles_x), tri_id, out_rgb, dword_stores);
 }
 
 }  // namespace bps
