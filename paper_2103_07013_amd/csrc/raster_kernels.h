@@ -66,7 +66,13 @@ struct FrameParams {
 
 constexpr unsigned long long kEmptyKey = ~0ull;
 constexpr int kOrigin = 16384;         // packed screen coordinates are stored relative to pixel 64
-constexpr int kSmallMax = 12;          // pixel centres a "small" triangle may touch (one lane rasterises it)
+// Pixel centres a "small" triangle may touch (one lane rasterises it; larger ones share a wavefront, four or one at a time).
+// A drain of the queue takes as many steps as its largest triangle has centres, so the line lies where such steps cost what a
+// pass over larger triangles costs: 12 in frames of 64x64 (us per request against 8 / 10 / 16: 1024 of 500 k triangles 198.5
+// against 202.9 / 200.0 / 201.2), 20 in windows of 128x128 frames and of other sizes, where more pixels fall on a triangle
+// (against 12: 61 at 72x104 55.6 -> 53.3, 192 textured at 128x128 205.7 -> 202.2, 4096 at 128x128 1923 -> 1919, 256 of two
+// windows each 77.2 -> 76.8; 24 in the latter: one environment in 64 windows 17.1 -> 18.6).
+constexpr int small_max(int frame) { return frame == 1 || frame == 128 ? 20 : 12; }
 constexpr uint32_t kInvalid = 0x40u;   // outcode bit: vertex unusable, drop its triangles
 constexpr uint32_t kNoProject = 0x80u; // outcode bit: vertex has no finite screen position (w <= 0 or overflow)
 

@@ -26,7 +26,8 @@ enum { kTSmall = 0, kTLarge = 1, kTDrains = 2, kTDrainIters = 3, kTDrainDepth = 
        kTPushes = 8, kTClipDrains = 9, kTClipPasses = 10, kTFanIters = 11, kTPopPasses = 12, kTSlots = 13, kTClusters = 14,
        kTPhaseAPasses = 15, kTCount = 16 };
 
-// One lane per queued small triangle: at most kSmallMax pixel centres each.
+// One lane per queued small triangle: at most small_max(FRAME) pixel centres each.
+template <int FRAME>
 __device__ __forceinline__ void drain_small(const WaveLds& L, int n, int lane, u64* vis, const Window& win,
                                             const BPS_GLOBAL uint32_t* ctri_id) {
     bool have = lane < n;
@@ -56,7 +57,7 @@ __device__ __forceinline__ void drain_small(const WaveLds& L, int n, int lane, u
     const int at_wrap = win.pitch - nx + 1;
     const float a2f = (float)s.A2;
     ++L.tally[kTDrains];
-    for (int k = 0; k < kSmallMax; ++k) {
+    for (int k = 0; k < small_max(FRAME); ++k) {
         const bool act = k < cnt;
         if (ballot64(act) == 0) break;
         ++L.tally[kTDrainIters];
@@ -84,6 +85,7 @@ __device__ __forceinline__ void drain_small(const WaveLds& L, int n, int lane, u
 __device__ __forceinline__ bool in_mask(u64 mask) { return __builtin_amdgcn_inverse_ballot_w64(mask); }
 
 // Append small triangles to the wave's queue; whenever it reaches 64 entries, drain them.
+template <int FRAME>
 __device__ __forceinline__ void push_small(const WaveLds& L, int& count, uint32_t xy0, uint32_t xy1,
                                            uint32_t xy2, float iw0, float iw1, float iw2, uint32_t ref, uint32_t box,
                                            int lane, u64* vis, const Window& win,
@@ -110,7 +112,7 @@ __device__ __forceinline__ void push_small(const WaveLds& L, int& count, uint32_
     const u64 first = mask & ballot64(pos < 64);
     if (in_mask(first)) put();
     wave_lds_sync();
-    drain_small(L, 64, lane, vis, win, ctri_id);
+    drain_small<FRAME>(L, 64, lane, vis, win, ctri_id);
     wave_lds_sync();
     pos -= 64;
     if (in_mask(mask & ~first)) put();
@@ -232,7 +234,7 @@ __device__ __forceinline__ void emit(const WaveLds& L, int& small_count, short2v
     // first pixel and size per axis as four bytes: i | j << 8 | nx << 16 | ny << 24
     const uint32_t first = as_u32(lo + (short)64), size = as_u32(ext + (short)1);
     const uint32_t box = __builtin_amdgcn_perm(size, first, 0x06040200u);
-    const bool few = __mul24((int)(size & 0xFFFFu), (int)(size >> 16)) <= kSmallMax;
+    const bool few = __mul24((int)(size & 0xFFFFu), (int)(size >> 16)) <= small_max(FRAME);
     const bool within8 = (as_u32(ext) & 0xFFF8FFF8u) == 0u;
     // The small and medium paths compute on packed 16-bit differences and divide in a narrowed exponent
     // range: triangles with a vertex outside that range, or wider than 16 bits hold, are drawn as large ones.
@@ -242,7 +244,7 @@ __device__ __forceinline__ void emit(const WaveLds& L, int& small_count, short2v
     ++L.tally[kTEmits];
     const u64 packed_mask = !tame ? 0ull : vmask & narrow_mask;
     const u64 small_mask = packed_mask & few_mask;
-    push_small(L, small_count, xy0, xy1, xy2, iw0, iw1, iw2, ref, box, lane, vis, win, ctri_id, small_mask);
+    push_small<FRAME>(L, small_count, xy0, xy1, xy2, iw0, iw1, iw2, ref, box, lane, vis, win, ctri_id, small_mask);
     u64 med = packed_mask & ~small_mask & ballot64(within8);
     u64 big = vmask & ~small_mask & ~med;
     L.tally[kTLarge] += (uint32_t)__popcll(med | big);
@@ -845,7 +847,9 @@ __device__ __forceinline__ void draw_clipped(const WaveLds& L, uint32_t ref, int
 // time, most of it on LDS round trips: clusters come off the list ahead of their use, no load is left in flight that
 // only one path uses, and the planes of the box tests sit in LDS instead of registers (no vector register is spilled
 // in the instances that draw by default, and 81 to 90 scalar ones): 78.8 M instructions, 238 us; 2.27 ms.  With clusters of
-// smaller boxes and raster_large_packed: 238 -> 229 us; 2.29 -> 2.17 ms.
+// smaller boxes and raster_large_packed: 238 -> 229 us; 2.29 -> 2.17 ms.  With the matrix cores, a draw loop without waits
+// between the vector and the scalar unit, and one comparison per step: 75.4 M vector instructions (65 % of the issue slots
+// over a launch), 228 -> 199 us; 2.18 -> 1.91 ms.
 template <int NT, bool DIAG, int CULL, int FRAME>
 __global__ __launch_bounds__(NT, 4) void k_raster(const SceneDev* __restrict__ scenes, const WorkItem* __restrict__ items,
                                                const float* __restrict__ view_proj, FrameParams fp,
@@ -1357,7 +1361,7 @@ __global__ __launch_bounds__(NT, 4) void k_raster(const SceneDev* __restrict__ s
         TICK(5);
         if ((occlusion || last_round) && small_count > 0) {
             wave_lds_sync();
-            drain_small(L, small_count, lane, vis, win, g_ctri_id);
+            drain_small<FRAME>(L, small_count, lane, vis, win, g_ctri_id);
             wave_lds_sync();
             small_count = 0;
         }
