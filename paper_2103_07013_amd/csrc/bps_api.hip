@@ -1027,6 +1027,9 @@ bps_status render(bps_renderer* r, const bps_scene* scene_ids, const float* view
     hipPointerAttribute_t attr;
     bool vp_on_device = false;
     if (hipPointerGetAttributes(&attr, view_proj) == hipSuccess) vp_on_device = attr.type == hipMemoryTypeDevice || attr.type == hipMemoryTypeManaged;
+    // (what is recorded into a graph has its event recorded by itself, as a kernel there has none)
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    const bool in_launch = r->events_in_launches && hipStreamIsCapturing(stream, &capture) == hipSuccess && capture == hipStreamCaptureStatusNone;
     (void)hipGetLastError();
     const size_t items_bytes = n_items * sizeof(bps::WorkItem);
     const size_t vp_bytes = (size_t)B * 16 * sizeof(float);
@@ -1145,8 +1148,8 @@ bps_status render(bps_renderer* r, const bps_scene* scene_ids, const float* view
         r->ev_used += 2;
     }
     // the request ends with its last kernel
-    const bool raster_last = r->events_in_launches && S <= 1 && !rgbd && r->ss <= 1 && !ev_stop;
-    const bool shade_last = r->events_in_launches && rgbd && r->ss <= 1, downsample_last = r->events_in_launches && r->ss > 1;
+    const bool raster_last = in_launch && S <= 1 && !rgbd && r->ss <= 1 && !ev_stop;
+    const bool shade_last = in_launch && rgbd && r->ss <= 1, downsample_last = in_launch && r->ss > 1;
     BPS_HIP(r, bps::launch_raster(raster_last ? slot.done : nullptr, r->threads, dim3((unsigned)n_items), cut.wide ? r->wide_lds : r->lds, stream,
                                   r->d_scenes, planned ? d_ordered : d_items, d_vp, fp, r->fixed_layout, cut.wide, r->gvis, out_depth,
                                   out_tri_id, d_stats));
