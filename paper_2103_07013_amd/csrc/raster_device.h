@@ -165,6 +165,7 @@ __device__ __forceinline__ void packed_edges(const PackedSetup& s, uint32_t p, i
 struct Window {
     int x0, y0, w, h;
     int pitch;                // pixels from one row of the key buffer to the next
+    int corner;               // y0 * pitch + x0: pixel (i, j) of the frame is j * pitch + i - corner there
     float aL, aR, aT, aB;
 };
 

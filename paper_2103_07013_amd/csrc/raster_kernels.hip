@@ -53,7 +53,7 @@ __device__ __forceinline__ void drain_small(const WaveLds& L, int n, int lane, u
     const int dy0 = unpack_y(s.e0), dy1 = unpack_y(s.e1);
     const int right0 = -(dy0 << 8), right1 = -(dy1 << 8);
     const int wrap0 = (unpack_x(s.e0) + __mul24(nx - 1, dy0)) << 8, wrap1 = (unpack_x(s.e1) + __mul24(nx - 1, dy1)) << 8;
-    int at = __mul24(j_lo - win.y0, win.pitch) + (i_lo - win.x0), col = 0;
+    int at = __mul24(j_lo, win.pitch) + i_lo - win.corner, col = 0;
     const int at_wrap = win.pitch - nx + 1;
     const float a2f = (float)s.A2;
     ++L.tally[kTDrains];
@@ -174,7 +174,7 @@ __device__ __forceinline__ void raster_large_packed(uint32_t xy0, uint32_t xy1, 
         int E1 = bcast_i(first1, src) + ((__mul24(dx1, lj) - __mul24(dy1, li)) << 8);
         const int t0 = t & 1, t1 = (t >> 1) & 1, most = A2 - (t >> 2);
         const int nx = (int)((b >> 16) & 0xFFu), ny = (int)(b >> 24);
-        int row = __mul24((int)((at0 >> 8) & 0xFFu) + lj - win.y0, win.pitch) + ((int)(at0 & 0xFFu) + li - win.x0);
+        int row = __mul24((int)((at0 >> 8) & 0xFFu) + lj, win.pitch) + ((int)(at0 & 0xFFu) + li) - win.corner;
         const int right0 = dy0 << 11, right1 = dy1 << 11, down0 = dx0 << 11, down1 = dx1 << 11;
         int in_rows = lj - ny;
         for (int y = 0; y < ny; y += 8) {
@@ -262,7 +262,8 @@ __device__ __forceinline__ void emit(const WaveLds& L, int& small_count, short2v
             src[k] = med ? __builtin_ctzll(med) : -1;
             med &= med - 1;     // 0 & anything stays 0
         }
-        const int g = lane >> 4;
+        int g = lane >> 4;
+        asm volatile("" : "+v"(g));      // (the three conditions on it would each be kept, and spilled, over the kernel)
         const int from = g == 0 ? src[0] : g == 1 ? src[1] : g == 2 ? src[2] : src[3];
         const bool on = from >= 0;
         const int f = on ? from : 0;
@@ -280,7 +281,7 @@ __device__ __forceinline__ void emit(const WaveLds& L, int& small_count, short2v
         int E0, E1, E2;
         packed_edges(st, pack_xy(((mi + li) << 8) + 128, ((mj + lj) << 8) + 128), E0, E1, E2);
         const int most = st.A2 - st.t2, right0 = unpack_y(st.e0) << 10, right1 = unpack_y(st.e1) << 10;
-        const int at = __mul24(mj + lj - win.y0, win.pitch) + (mi + li - win.x0);
+        const int at = __mul24(mj + lj, win.pitch) + (mi + li) - win.corner;
         auto tile = [&](int F0, int F1, int in_columns, int in_rows, int where) {
             const int outside = (F0 - st.t0) | (F1 - st.t1) | (most - F0 - F1);
             if ((~outside & in_rows & in_columns) < 0) {
@@ -554,12 +555,10 @@ __device__ __forceinline__ int pop_clip(const ClipRing& R, uint32_t at_least, in
     return (int)n;
 }
 
-// A straddling triangle per lane, clipped and projected: corners 0 .. cnt - 1, of which the first five are in
-// registers; of a lane that needed the general clipper the first three are, and all of them in its ring.
+// A straddling triangle per lane, clipped and projected: corners 0 .. cnt - 1.
 struct Clipped {
     uint32_t ref;                            // cluster * 128 + slot
     int cnt;                                 // 0: nothing to draw
-    int first;                               // where the polygon starts in the lane's ring
     uint32_t p0, p1, p2, p3, p4;             // packed positions
     float w0, w1, w2, w3, w4;                // 1/w
 };
@@ -575,24 +574,6 @@ struct LanePlane {
     }
 };
 
-// Polygons of the general clipper: sixteen corners each, in rings that take the place of the staged vertices (the clipper
-// runs between clusters).  A plane's pass reads the corners behind and writes the ones ahead: it overtakes itself only if
-// more than 16 - n of its n corners are entered from outside, at most n / 2 can be, and n is at most 10 before the last plane.
-constexpr int kClipRings = 3;
-static_assert(kClipRings * kMaxPoly * 16 <= 64 * 12 && kWaveLdsBytes % 16 == 0, "the rings fit where the staged vertices are");
-struct PolyRing {
-    float4m* at;
-    __device__ __forceinline__ Clip4 get(int q) const {
-        const float4m v = at[q & (kMaxPoly - 1)];
-        return Clip4{v.x, v.y, v.z, v.w};
-    }
-    __device__ __forceinline__ void put(int q, const Clip4& v) const { at[q & (kMaxPoly - 1)] = float4m{v.x, v.y, v.z, v.w}; }
-    __device__ __forceinline__ void put_projected(int q, uint32_t xy, float iw) const {
-        *reinterpret_cast<float2*>(at + (q & (kMaxPoly - 1))) = make_float2(__uint_as_float(xy), iw);
-    }
-    __device__ __forceinline__ float2 projected(int q) const { return *reinterpret_cast<const float2*>(at + (q & (kMaxPoly - 1))); }
-};
-
 __device__ __forceinline__ Clip4 pick(bool first, const Clip4& p, const Clip4& q) {
     return Clip4{first ? p.x : q.x, first ? p.y : q.y, first ? p.z : q.z, first ? p.w : q.w};
 }
@@ -602,15 +583,14 @@ __device__ __forceinline__ Clip4 along(const Clip4& a, const Clip4& b, float t) 
 
 // One lane per queued straddling triangle: clip and project.  Triangles that cross one plane (nine in ten) or two
 // are clipped in registers; three and more, and numbers outside the range of the short divisions, by the general
-// clipper, which few wavefronts enter.  The general clipper alone kept its polygons in private memory (a trip to L2
-// per corner) and met every crossing and every corner in a branch of its own: 10 % of the kernel's vector
-// instructions, and the longest wait at the end of a round.  61 frames of 72x104: 71.5 -> 67.5 us per request, 256 of
-// 64x64: 108.5 -> 104.5, 4096 of 128x128: 2410 -> 2365; 1024 of 64x64 unchanged.
-// have: the lane has a triangle.  The general clipper takes kClipRings of them at a time: `general` tells which these are,
-// and `left` which lanes have to come back.
-__device__ __forceinline__ void clip_triangles(const WaveLds& L, uint32_t ref, bool have, const SceneDev& sc, const ClipRows& R,
-                                               const FrameParams& fp, int lane, Clipped& out, PolyRing& ring, bool& general, bool& left) {
-    uint32_t* const tally = L.tally;
+// clipper (clip_general), which few wavefronts of a finely tessellated scene enter.  The general clipper alone kept its
+// polygons in private memory (a trip to L2 per corner) and met every crossing and every corner in a branch of its own: 10 %
+// of the kernel's vector instructions, and the longest wait at the end of a round.  61 frames of 72x104: 71.5 -> 67.5 us per
+// request, 256 of 64x64: 108.5 -> 104.5, 4096 of 128x128: 2410 -> 2365; 1024 of 64x64 unchanged.
+// general: 0, or 64 and the planes that the lane's triangle crosses (bit k: the k-th of the rule's order), if that takes the
+// general clipper.
+__device__ __forceinline__ void clip_triangles(uint32_t* tally, uint32_t ref, bool have, const SceneDev& sc, const ClipRows& R,
+                                               const FrameParams& fp, Clipped& out, uint32_t& general) {
     if (!have) ref = 0u;
     out.ref = ref;
     const uint32_t c = ref >> 7;
@@ -636,8 +616,10 @@ __device__ __forceinline__ void clip_triangles(const WaveLds& L, uint32_t ref, b
                            outside([](const Clip4& q) { return !(q.y >= -q.w); }), outside([](const Clip4& q) { return !(q.y <= q.w); })};
     bool one = false, two = false, more = false;      // lanes with at least that many planes
     bool f[6], g[6];                                  // the lane's first and second plane
+    general = 64u;
 #pragma unroll
     for (int k = 0; k < 6; ++k) {
+        general |= cross[k] ? 1u << k : 0u;
         f[k] = cross[k] & !one;
         g[k] = cross[k] & one & !two;
         more = more | (cross[k] & two);
@@ -724,114 +706,145 @@ __device__ __forceinline__ void clip_triangles(const WaveLds& L, uint32_t ref, b
         fits = fits & (turns <= 2);
         out.cnt = at;
     }
-    general = have & !fits;
-    left = false;
     if (!fits) out.cnt = 0;
-    out.first = 0;
-    const u64 general_mask = ballot64(general);
-    if (__builtin_expect(general_mask == 0ull, 1)) return;
-    // ---- the general clipper
-    const uint32_t slot = rank_below(general_mask);
-    left = general & (slot >= (uint32_t)kClipRings);
-    general = general & (slot < (uint32_t)kClipRings);
-    ring.at = reinterpret_cast<float4m*>(L.stage) + kMaxPoly * (general ? (int)slot : 0);
-    ++tally[kTClipPasses];
-    if (general) {
-        const uint32_t oc_or = outcode(tri[0]) | outcode(tri[1]) | outcode(tri[2]);
-        // The lane's own planes, in the rule's order near, far, left, right, top, bottom (bit p: p-th plane of the order).
-        // A plane is applied as c.x x + c.y y + c.z z + c.w w with coefficients 0 and +-1, which rounds exactly like the
-        // written-out w + x, w - x, ..., z, w - z (products with 0 and +-1 and sums with 0 are exact).
-        uint32_t todo = ((oc_or >> 4) & 3u) | ((oc_or & 15u) << 2);
-        ring.put(0, tri[0]);
-        ring.put(1, tri[1]);
-        ring.put(2, tri[2]);
-        int cnt = 3, from = 0;
-        while (todo != 0u && cnt >= 3) {
-            const int p = __builtin_ctz(todo);
-            todo &= todo - 1u;
-            const int k = p < 2 ? p + 4 : p - 2;                         // plane number: 4 5 0 1 2 3
-            const float cx = k == 0 ? 1.0f : k == 1 ? -1.0f : 0.0f, cy = k == 2 ? 1.0f : k == 3 ? -1.0f : 0.0f;
-            const float cz = k == 4 ? 1.0f : k == 5 ? -1.0f : 0.0f, cw = k == 4 ? 0.0f : 1.0f;
-            auto dist = [&](const Clip4& q) { return fmaf(cx, q.x, fmaf(cy, q.y, fmaf(cz, q.z, cw * q.w))); };
-            int m = 0;
-            const int to = from + cnt;
-            Clip4 prev = ring.get(to - 1), ahead = ring.get(from);      // fetch one corner ahead of its use
-            float dprev = dist(prev);
-            for (int q = 0; q < cnt; ++q) {
-                const Clip4 v = ahead;
-                ahead = ring.get(from + q + 1);
-                const float dv = dist(v);
-                const bool cin = dv >= 0.0f, pin = dprev >= 0.0f;
-                if (cin != pin && m < kMaxPoly) {
-                    // always from the inside vertex to the outside one
-                    const float da = cin ? dv : dprev, db = cin ? dprev : dv;
-                    ring.put(to + m, along(pick(cin, v, prev), pick(cin, prev, v), da / (da - db)));
-                    ++m;
-                }
-                if (cin && m < kMaxPoly) {
-                    ring.put(to + m, v);
-                    ++m;
-                }
-                prev = v;
-                dprev = dv;
-            }
-            cnt = m;
-            from = to;
-        }
-        bool ok = cnt >= 3;
-        for (int q = 0; ok && q < cnt; ++q) {
-            bool unused;
-            uint32_t xy;
-            float iw;
-            ok = project(ring.get(from + q), fp, xy, iw, unused);
-            ring.put_projected(from + q, xy, iw);
-        }
-        out.cnt = ok ? cnt : 0;
-        out.first = from;
-        const float2 a = ring.projected(from), b = ring.projected(from + 1), d = ring.projected(from + 2);
-        out.p0 = __float_as_uint(a.x); out.p1 = __float_as_uint(b.x); out.p2 = __float_as_uint(d.x);
-        out.w0 = a.y; out.w1 = b.y; out.w2 = d.y;
-    }
+    general = have & !fits ? general : 0u;
 }
 
-// Clips up to 64 queued triangles and hands the pieces (0, k, k + 1) of their polygons to emit().
+// The general clipper: the first 64 / wide of the triangles in `waiting` (a bit per lane that holds one, with `ref` and
+// `general` of clip_triangles), `wide` lanes each: 16, which is as many corners as the rule keeps of a polygon, or 8, and what
+// turns out to have more is put into `again`.  A lane holds a corner and the one before it; at a plane it puts out the
+// crossing between the two, then the corner, and its place among what the row puts out is a count of bits, so that a plane
+// takes one trip through LDS (x and y, then z and w, where the staged vertices are between clusters) however many corners
+// there are.  Lane j of a row then holds the piece (0, j, j + 1) of the polygon: returns whether there is one.
+// What bounds it is the chain of steps of one wavefront where few triangles come here, and vector issue where many do, so
+// polygons stay out of private memory (where all 64 triangles of a clipper's run fit) and out of one lane's loop over its
+// corners (of which LDS holds three at a time: several planes crossed by most triangles cost up to 4 times the request).
+// Us per request, private memory / three at a time / rows of 16 only / this: 16 environments in a room of 500 triangles
+// 34.9 / 37.4 / 27.6 / 25.4, 200 of them at 24x24 40.1 / 45.7 / 31.1 / 29.1; among 2000 triangles as large as the room
+// 1024 environments 2268 / 2582 / 2029 / 1926 and one 67.1 / 277 / 98.5 / 67.6; one among 20000 of them 230 / - / - / 252.
+__device__ __forceinline__ bool clip_general(const WaveLds& L, int wide, u64& waiting, u64& again, uint32_t ref, uint32_t general,
+                                             const SceneDev& sc, const ClipRows& R, const FrameParams& fp, int lane, uint32_t& of,
+                                             uint32_t& p0, uint32_t& p1, uint32_t& p2, float& w0, float& w1, float& w2) {
+    static_assert(kMaxPoly == 16, "a corner per lane of the widest row");
+    asm volatile("" : "+v"(lane));      // (what follows from it is worked out here and not kept, and spilled, over the kernel)
+    const int j = lane & (wide - 1), row = lane - j;
+    const uint32_t row_mask = (1u << wide) - 1u;
+    const uint32_t rank = rank_below(waiting) * (uint32_t)wide;      // the lane's own triangle: the row that takes it
+    const u64 taken = waiting & ballot64(rank < 64u);
+    wave_lds_sync();
+    if (in_mask(taken)) L.stage[rank] = make_float2(__uint_as_float(ref), __uint_as_float(general));
+    wave_lds_sync();
+    const bool on = row < __popcll(waiting) * wide;
+    waiting &= ~taken;
+    const float2 mine = L.stage[row];
+    of = on ? __float_as_uint(mine.x) : 0u;
+    uint32_t todo = on ? __float_as_uint(mine.y) & 63u : 0u;
+    int n = on ? 3 : 0;
+    const uint32_t t = gptr(sc.ctris)[of] & 0x00FFFFFFu, vi = (t >> (8 * min(j, 2))) & 0xFFu;
+    const BPS_GLOBAL float* cv = gptr(sc.cverts) + (size_t)(of >> 7) * 192;
+    Clip4 v = to_clip(R, cv[vi], cv[64 + vi], cv[128 + vi]), u;
+    {
+        const int before = row + (j == 0 ? 2 : j - 1);
+        u = Clip4{__shfl(v.x, before, 64), __shfl(v.y, before, 64), __shfl(v.z, before, 64), __shfl(v.w, before, 64)};
+    }
+    u64 large = 0ull;      // rows whose polygon has become too large for them
+    for (;;) {
+        const u64 open = ballot64(todo != 0u) & ballot64(n >= 3);
+        if (open == 0ull) break;
+        ++L.tally[kTClipPasses];
+        const uint32_t p = (uint32_t)__builtin_ctz(todo | 64u);      // near, far, left, right, top, bottom
+        auto dist = [&](float x, float y, float z, float w) -> float {      // z, w - z, w + x, w - x, w + y or w - y
+            const float s = p < 2u ? z : p < 4u ? x : y;
+            return (p == 0u ? 0.0f : w) + ((p & 1u) ? -s : s);
+        };
+        const float dv = dist(v.x, v.y, v.z, v.w), du = dist(u.x, u.y, u.z, u.w);
+        const bool in = dv >= 0.0f;
+        const u64 inside = ballot64(in), there = open & ballot64(j < n);
+        const u64 keeps = there & inside, turns = there & (inside ^ ballot64(du >= 0.0f));
+        // (a crossing is taken from the inside corner to the outside one; u - v is v - u but for its sign)
+        const float da = in ? dv : du, part = da / (da - (in ? du : dv)), towards = in ? part : -part;
+        const Clip4 x = {fmaf(towards, u.x - v.x, in ? v.x : u.x), fmaf(towards, u.y - v.y, in ? v.y : u.y), fmaf(towards, u.z - v.z, in ? v.z : u.z),
+                         fmaf(towards, u.w - v.w, in ? v.w : u.w)};
+        const uint32_t row_keeps = (uint32_t)(keeps >> row) & row_mask, row_turns = (uint32_t)(turns >> row) & row_mask;
+        const uint32_t below = (1u << j) - 1u;
+        const int at = __popc(row_keeps & below) + __popc(row_turns & below);
+        int m = __popc(row_keeps) + __popc(row_turns);
+        const int at_v = at + (in_mask(turns) ? 1 : 0);
+        const bool put_x = in_mask(turns) & (at < wide), put_v = in_mask(keeps) & (at_v < wide);
+        if (wide < kMaxPoly) {
+            const u64 more = open & ballot64(m > wide);
+            large |= more;
+            m = in_mask(more) ? 0 : m;
+        }
+        m = min(m, kMaxPoly);
+        const int before = row + (j == 0 ? max(m - 1, 0) : j - 1);
+        float2* const out = L.stage + row;
+        wave_lds_sync();
+        if (put_x) out[at] = make_float2(x.x, x.y);
+        if (put_v) out[at_v] = make_float2(v.x, v.y);
+        wave_lds_sync();
+        const float2 v_xy = L.stage[lane], u_xy = L.stage[before];
+        wave_lds_sync();
+        if (put_x) out[at] = make_float2(x.z, x.w);
+        if (put_v) out[at_v] = make_float2(v.z, v.w);
+        wave_lds_sync();
+        const float2 v_zw = L.stage[lane], u_zw = L.stage[before];
+        if (in_mask(open)) {
+            v = Clip4{v_xy.x, v_xy.y, v_zw.x, v_zw.y};
+            u = Clip4{u_xy.x, u_xy.y, u_zw.x, u_zw.y};
+            n = m;
+            todo &= todo - 1u;
+        }
+    }
+    bool unused;
+    const bool ok = project(v, fp, p1, w1, unused);
+    const u64 dropped = ballot64(j < n) & ~ballot64(ok);      // one corner without a place drops the triangle
+    wave_lds_sync();
+    L.stage[lane] = make_float2(__uint_as_float(p1), w1);
+    wave_lds_sync();
+    const float2 first = L.stage[row], next = L.stage[row + min(j + 1, wide - 1)];
+    p0 = __float_as_uint(first.x); w0 = first.y;
+    p2 = __float_as_uint(next.x); w2 = next.y;
+    again |= taken & ballot64(((large >> (rank & 63u)) & 1ull) != 0ull);
+    return ((uint32_t)(dropped >> row) & row_mask) == 0u && j >= 1 && j + 1 < n;
+}
+
+// Clips up to 64 queued triangles and hands the pieces (0, k, k + 1) of their polygons to emit(): the k-th ones of all that
+// were clipped in registers together, then all the pieces of eight of the others at a time.
 template <int FRAME>
 __device__ __forceinline__ void draw_clipped(const WaveLds& L, uint32_t ref, int n, int& small_count, const SceneDev& sc,
                                              const ClipRows& R, const FrameParams& fp, const Window& win, int lane, u64* vis) {
     const BPS_GLOBAL uint32_t* ctri_id = gptr(sc.ctri_id);
-    bool have = lane < n && ref != kClipEmpty;
-    do {
-        Clipped cl;
-        PolyRing ring;
-        bool general, left;
-        clip_triangles(L, ref, have, sc, R, fp, lane, cl, ring, general, left);
-        const u64 general_mask = ballot64(general);
+    Clipped cl;
+    uint32_t general;
+    clip_triangles(L.tally, ref, lane < n && ref != kClipEmpty, sc, R, fp, cl, general);
+    u64 waiting = ballot64(general != 0u), again = 0ull;
+    int wide = 8;
 #pragma unroll 1
-        for (int k = 0;; ++k) {
-            const bool live = k + 2 < cl.cnt;
-            if (ballot64(live) == 0ull) break;
-            ++L.tally[kTFanIters];
-            const uint32_t b = cl.p1, d = cl.p2;
-            const float wb = cl.w1, wd = cl.w2;
-            short2v lo, ext;
-            uint32_t wide;
-            const bool has = live && centre_box(cl.p0, b, d, win, lo, ext, wide);
-            bool tame = true;
+    for (int k = 0;; ++k) {
+        bool live = k + 2 < cl.cnt, tame = true;
+        uint32_t of = cl.ref, a = cl.p0, b = cl.p1, d = cl.p2;
+        float wa = cl.w0, wb = cl.w1, wd = cl.w2;
+        if (__builtin_expect(ballot64(live) != 0ull, 1)) {
             // the next piece's corners
             cl.p1 = cl.p2; cl.p2 = cl.p3; cl.p3 = cl.p4;
             cl.w1 = cl.w2; cl.w2 = cl.w3; cl.w3 = cl.w4;
-            if (__builtin_expect(general_mask != 0ull, 0)) {
-                tame = ballot64(has && !(iw_in_range(cl.w0) && iw_in_range(wb) && iw_in_range(wd))) == 0ull;
-                if (general) {
-                    const float2 next = ring.projected(cl.first + k + 3);
-                    cl.p2 = __float_as_uint(next.x);
-                    cl.w2 = next.y;
-                }
+        } else {
+            if (__builtin_expect((waiting | again) == 0ull, 1)) break;
+            if (waiting == 0ull) {
+                waiting = again;
+                again = 0ull;
+                wide = kMaxPoly;
             }
-            emit<FRAME>(L, small_count, lo, ext, wide, tame, cl.p0, b, d, cl.w0, wb, wd, cl.ref, ctri_id, lane, vis, win, ballot64(has));
+            live = clip_general(L, wide, waiting, again, cl.ref, general, sc, R, fp, lane, of, a, b, d, wa, wb, wd);
+            tame = ballot64(live && !(iw_in_range(wa) && iw_in_range(wb) && iw_in_range(wd))) == 0ull;
         }
-        have = left;
-    } while (__builtin_expect(ballot64(have) != 0ull, 0));
+        ++L.tally[kTFanIters];
+        short2v lo, ext;
+        uint32_t wide;
+        const bool has = live && centre_box(a, b, d, win, lo, ext, wide);
+        emit<FRAME>(L, small_count, lo, ext, wide, tame, a, b, d, wa, wb, wd, of, ctri_id, lane, vis, win, ballot64(has));
+    }
 }
 
 }  // namespace
@@ -938,6 +951,7 @@ __global__ __launch_bounds__(NT, 4) void k_raster(const SceneDev* __restrict__ s
         place_window(win, item.tile, fp);
         if (FRAME == 0) win.pitch = win.w;
     }
+    win.corner = __mul24(win.y0, win.pitch) + win.x0;
     const int nslots = win.h * win.pitch;      // (columns beyond the window's width are never looked at)
     int small_count = 0;
     uint32_t clip_tail_seen = 0u, clip_head_seen = 0u;    // this wavefront's last view of the clip ring
