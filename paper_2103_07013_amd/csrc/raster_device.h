@@ -166,6 +166,7 @@ struct Window {
     int x0, y0, w, h;
     int pitch;                // pixels from one row of the key buffer to the next
     int corner;               // y0 * pitch + x0: pixel (i, j) of the frame is j * pitch + i - corner there
+    int small_max;            // pixel centres of the largest triangle that one lane rasterises
     float aL, aR, aT, aB;
 };
 

@@ -11,7 +11,7 @@
 //   triangle phase two triangles per lane: outcode reject, bounding box vs pixel centres
 //   compaction     survivors are appended to LDS queues with ballot + prefix count so
 //                  that the expensive steps run on full wavefronts:
-//                    small queue  (per wavefront) triangles touching <= 12 pixel centres, one lane per triangle
+//                    small queue  (per wavefront) triangles touching few pixel centres (small_max), one lane per triangle
 //                    clip ring    (per work-group) triangles straddling a frustum plane, one lane per triangle
 //                  large triangles are rasterised by the whole wavefront, 8x8 pixels at a time.
 // All float arithmetic follows one fixed IEEE sequence (explicit fmaf, no contraction, exact
@@ -62,16 +62,19 @@ struct FrameParams {
     int32_t first_round;   // the same for an environment's first round (kept short when occlusion culling is on)
     int32_t phase_timers;  // diagnostics: 1 also time the kernel's phases (slows it down), 2 / 3 path tallies
     int32_t bilinear;      // colour pass: sample textures with bilinear filtering instead of the nearest texel
+    int32_t small_max = 0; // (set by launch_raster, for the instances that count: see small_max below)
 };
 
 constexpr unsigned long long kEmptyKey = ~0ull;
 constexpr int kOrigin = 16384;         // packed screen coordinates are stored relative to pixel 64
 // Pixel centres a "small" triangle may touch (one lane rasterises it; larger ones share a wavefront, four or one at a time).
 // A drain of the queue takes as many steps as its largest triangle has centres, so the line lies where such steps cost what a
-// pass over larger triangles costs: 12 in frames of 64x64 (us per request against 8 / 10 / 16: 1024 of 500 k triangles 198.5
-// against 202.9 / 200.0 / 201.2), 20 in windows of 128x128 frames and of other sizes, where more pixels fall on a triangle
-// (against 12: 61 at 72x104 55.6 -> 53.3, 192 textured at 128x128 205.7 -> 202.2, 4096 at 128x128 1923 -> 1919, 256 of two
-// windows each 77.2 -> 76.8; 24 in the latter: one environment in 64 windows 17.1 -> 18.6).
+// pass over larger triangles costs.  That depends on the mesh too; the number is one per instance, so that the loop over
+// the steps is unrolled.  Frames of 64x64 drawn whole: 12 (us per request with 8 / 10 / 12 / 16: 1024 of 500 k triangles
+// 202.9 / 200.0 / 198.5 / 201.2; with 12 / 16: of 100 k 162.8 / 161.2, of 20 k 179 / 172, of 500 179 / 169).  Every other
+// window, also those of frames of 64x64 that are cut: 20 (with 12 / 20: 61 at 72x104 55.6 / 53.3, 4096 at 128x128 1923 / 1919,
+// 512 at 128x128 of 100 k 284 / 274, 200 at 64x64 of 20 k 70.7 / 67.7, 512 at 128x128 of 500 263 / 273, 16 at 64x64 of 100 k
+// 21.9 / 22.4; one environment in 64 windows with 20 / 24 17.1 / 18.6).
 constexpr int small_max(int frame) { return frame == 1 || frame == 128 ? 20 : 12; }
 constexpr uint32_t kInvalid = 0x40u;   // outcode bit: vertex unusable, drop its triangles
 constexpr uint32_t kNoProject = 0x80u; // outcode bit: vertex has no finite screen position (w <= 0 or overflow)

@@ -26,8 +26,7 @@ enum { kTSmall = 0, kTLarge = 1, kTDrains = 2, kTDrainIters = 3, kTDrainDepth = 
        kTPushes = 8, kTClipDrains = 9, kTClipPasses = 10, kTFanIters = 11, kTPopPasses = 12, kTSlots = 13, kTClusters = 14,
        kTPhaseAPasses = 15, kTCount = 16 };
 
-// One lane per queued small triangle: at most small_max(FRAME) pixel centres each.
-template <int FRAME>
+// One lane per queued small triangle: at most win.small_max pixel centres each.
 __device__ __forceinline__ void drain_small(const WaveLds& L, int n, int lane, u64* vis, const Window& win,
                                             const BPS_GLOBAL uint32_t* ctri_id) {
     bool have = lane < n;
@@ -57,7 +56,7 @@ __device__ __forceinline__ void drain_small(const WaveLds& L, int n, int lane, u
     const int at_wrap = win.pitch - nx + 1;
     const float a2f = (float)s.A2;
     ++L.tally[kTDrains];
-    for (int k = 0; k < small_max(FRAME); ++k) {
+    for (int k = 0; k < win.small_max; ++k) {
         const bool act = k < cnt;
         if (ballot64(act) == 0) break;
         ++L.tally[kTDrainIters];
@@ -85,7 +84,6 @@ __device__ __forceinline__ void drain_small(const WaveLds& L, int n, int lane, u
 __device__ __forceinline__ bool in_mask(u64 mask) { return __builtin_amdgcn_inverse_ballot_w64(mask); }
 
 // Append small triangles to the wave's queue; whenever it reaches 64 entries, drain them.
-template <int FRAME>
 __device__ __forceinline__ void push_small(const WaveLds& L, int& count, uint32_t xy0, uint32_t xy1,
                                            uint32_t xy2, float iw0, float iw1, float iw2, uint32_t ref, uint32_t box,
                                            int lane, u64* vis, const Window& win,
@@ -112,7 +110,7 @@ __device__ __forceinline__ void push_small(const WaveLds& L, int& count, uint32_
     const u64 first = mask & ballot64(pos < 64);
     if (in_mask(first)) put();
     wave_lds_sync();
-    drain_small<FRAME>(L, 64, lane, vis, win, ctri_id);
+    drain_small(L, 64, lane, vis, win, ctri_id);
     wave_lds_sync();
     pos -= 64;
     if (in_mask(mask & ~first)) put();
@@ -234,7 +232,7 @@ __device__ __forceinline__ void emit(const WaveLds& L, int& small_count, short2v
     // first pixel and size per axis as four bytes: i | j << 8 | nx << 16 | ny << 24
     const uint32_t first = as_u32(lo + (short)64), size = as_u32(ext + (short)1);
     const uint32_t box = __builtin_amdgcn_perm(size, first, 0x06040200u);
-    const bool few = __mul24((int)(size & 0xFFFFu), (int)(size >> 16)) <= small_max(FRAME);
+    const bool few = __mul24((int)(size & 0xFFFFu), (int)(size >> 16)) <= win.small_max;
     const bool within8 = (as_u32(ext) & 0xFFF8FFF8u) == 0u;
     // The small and medium paths compute on packed 16-bit differences and divide in a narrowed exponent
     // range: triangles with a vertex outside that range, or wider than 16 bits hold, are drawn as large ones.
@@ -244,7 +242,7 @@ __device__ __forceinline__ void emit(const WaveLds& L, int& small_count, short2v
     ++L.tally[kTEmits];
     const u64 packed_mask = !tame ? 0ull : vmask & narrow_mask;
     const u64 small_mask = packed_mask & few_mask;
-    push_small<FRAME>(L, small_count, xy0, xy1, xy2, iw0, iw1, iw2, ref, box, lane, vis, win, ctri_id, small_mask);
+    push_small(L, small_count, xy0, xy1, xy2, iw0, iw1, iw2, ref, box, lane, vis, win, ctri_id, small_mask);
     u64 med = packed_mask & ~small_mask & ballot64(within8);
     u64 big = vmask & ~small_mask & ~med;
     L.tally[kTLarge] += (uint32_t)__popcll(med | big);
@@ -937,6 +935,7 @@ __global__ __launch_bounds__(NT, 4) void k_raster(const SceneDev* __restrict__ s
     // this work-group's window of the frame
     Window win;
     win.pitch = 64;
+    win.small_max = DIAG ? fp.small_max : small_max(FRAME);
     if (FRAME == 64) {
         // the instance for 64x64 frames (the paper's main resolution): the window is the frame, and
         // with its origin and size known to the compiler the pixel arithmetic of every loop shrinks
@@ -1375,7 +1374,7 @@ __global__ __launch_bounds__(NT, 4) void k_raster(const SceneDev* __restrict__ s
         TICK(5);
         if ((occlusion || last_round) && small_count > 0) {
             wave_lds_sync();
-            drain_small<FRAME>(L, small_count, lane, vis, win, g_ctri_id);
+            drain_small(L, small_count, lane, vis, win, g_ctri_id);
             wave_lds_sync();
             small_count = 0;
         }
@@ -1720,22 +1719,29 @@ hipError_t prepare_raster(int threads, size_t lds, bool fixed_layout, size_t wid
 }
 
 hipError_t launch_raster(hipEvent_t done, int threads, dim3 grid, size_t lds, hipStream_t stream, const SceneDev* scenes, const WorkItem* items,
-                   const float* view_proj, const FrameParams& fp, bool fixed_layout, bool wide, unsigned long long* gvis,
+                   const float* view_proj, const FrameParams& request, bool fixed_layout, bool wide, unsigned long long* gvis,
                    float* out_depth, uint32_t* out_id, unsigned long long* stats) {
     // The default configuration runs on instances whose LDS layout is a compile-time constant: one each for
     // 64x64 and 128x128 frames drawn as 64x64 windows, and one for every other frame and window size.
-    if (threads == 512 && !stats && fp.cull == 2 && fixed_layout) {
+    int frame = 0;
+    if (threads == 512 && request.cull == 2 && fixed_layout) {
+        const bool full = request.tile_w == 64 && request.tile_h == 64;
+        frame = full && !wide && request.W == 64 && request.H == 64 ? 64 : full && !wide && request.W == 128 && request.H == 128 ? 128 : 1;
+    }
+    // (the instances that count are no such, and count what the one does that draws the request otherwise)
+    FrameParams fp = request;
+    fp.small_max = small_max(frame);
+    if (frame != 0 && !stats) {
         const size_t lds64 = lds_bytes(64, 64, 512, (int)kListCap64);
         if (wide) {
             return launch_kernel(done, &k_raster<1024, false, 2, 1>, grid, dim3(1024), lds_bytes(64, 64, 1024, (int)kListCap64), stream, scenes,
                                  items, view_proj, fp, gvis, out_depth, out_id, stats);
         }
-        const bool full = fp.tile_w == 64 && fp.tile_h == 64;
 #define BPS_LAUNCH_FIXED(FRAME)                                                                                        \
     return launch_kernel(done, &k_raster<512, false, 2, FRAME>, grid, dim3(512), lds64, stream, scenes, items, view_proj, fp, gvis, \
                          out_depth, out_id, stats)
-        if (full && fp.W == 64 && fp.H == 64) BPS_LAUNCH_FIXED(64);
-        else if (full && fp.W == 128 && fp.H == 128) BPS_LAUNCH_FIXED(128);
+        if (frame == 64) BPS_LAUNCH_FIXED(64);
+        else if (frame == 128) BPS_LAUNCH_FIXED(128);
         else BPS_LAUNCH_FIXED(1);
 #undef BPS_LAUNCH_FIXED
     }
