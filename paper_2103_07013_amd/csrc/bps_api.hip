@@ -1,6 +1,5 @@
 // Host side of the C ABI declared in include/bps.h: renderer object, scene table, request
 // staging and launch planning.  All rendering arithmetic is in raster_kernels.hip.
-#include <dlfcn.h>
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -101,7 +100,6 @@ struct bps_renderer {
     bps_config cfg{};
     int device = 0;
     int num_cu = 0;
-    bool events_in_launches = false;  // a request's event is the end of its last kernel rather than a packet behind it
     int threads = 512;
     int ss = 1, rw = 64, rh = 64;     // supersampling factor and rendered frame size
     float* ss_depth = nullptr;        // [max_batch][rh][rw] when supersampling
@@ -462,11 +460,6 @@ bps_status bps_create(const bps_config* cfg, bps_renderer** out) {
         hipDeviceProp_t prop;
         BPS_HIP(r, hipGetDeviceProperties(&prop, r->device));
         r->num_cu = prop.multiProcessorCount;
-        // A library put in front of the runtime may have the plain launch and not the extended one: what it shows of a
-        // launch and of an event then belongs together only if both are its own.
-        Dl_info plain{}, extended{};
-        r->events_in_launches = dladdr(reinterpret_cast<const void*>(&hipLaunchKernel), &plain) != 0 &&
-                                dladdr(reinterpret_cast<const void*>(&hipExtLaunchKernel), &extended) != 0 && plain.dli_fbase == extended.dli_fbase;
         int lds_optin = 0;
         if (hipDeviceGetAttribute(&lds_optin, hipDeviceAttributeSharedMemPerBlockOptin, r->device) != hipSuccess) lds_optin = 0;
         (void)hipGetLastError();
@@ -946,6 +939,18 @@ bps_status bps_pack_clusters(const float* vertices, uint32_t V, const uint32_t* 
 
 namespace {
 
+// Whether calls on a stream are being recorded into a graph.  The event of a request is the end of its last kernel only
+// where that is certain not to be (kNone): a kernel of a graph has no event, so there, and where it cannot be told, the
+// event is recorded by itself.
+enum class Capture { kNone, kActive, kUnknown };
+Capture capture_of(hipStream_t stream) {
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    const hipError_t e = hipStreamIsCapturing(stream, &status);
+    (void)hipGetLastError();
+    if (e != hipSuccess) return Capture::kUnknown;
+    return status == hipStreamCaptureStatusNone ? Capture::kNone : status == hipStreamCaptureStatusActive ? Capture::kActive : Capture::kUnknown;
+}
+
 bps_status unload(bps_renderer* r, bps_scene scene) {
     std::lock_guard<std::mutex> lock(r->mu);
     const int slot = slot_of(r, scene);
@@ -1027,10 +1032,8 @@ bps_status render(bps_renderer* r, const bps_scene* scene_ids, const float* view
     hipPointerAttribute_t attr;
     bool vp_on_device = false;
     if (hipPointerGetAttributes(&attr, view_proj) == hipSuccess) vp_on_device = attr.type == hipMemoryTypeDevice || attr.type == hipMemoryTypeManaged;
-    // (what is recorded into a graph has its event recorded by itself, as a kernel there has none)
-    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-    const bool in_launch = r->events_in_launches && hipStreamIsCapturing(stream, &capture) == hipSuccess && capture == hipStreamCaptureStatusNone;
     (void)hipGetLastError();
+    const bool in_launch = capture_of(stream) == Capture::kNone;
     const size_t items_bytes = n_items * sizeof(bps::WorkItem);
     const size_t vp_bytes = (size_t)B * 16 * sizeof(float);
     const size_t ids_bytes = rgbd ? (size_t)B * sizeof(uint32_t) : 0;
@@ -1228,9 +1231,8 @@ bps_status render_static(bps_renderer* r, const bps_scene* scene_ids, const floa
     cut.S = 1;                          // (no merge buffer here)
     make_plan(r, scene_ids, B, cut);    // (host containers only; they keep their capacity between calls)
     n_items = r->plan->items.size();     // (small batches are cut finer, never into more than kMaxPlannedItems)
-    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-    const bool capturing = hipStreamIsCapturing(stream, &capture) == hipSuccess && capture == hipStreamCaptureStatusActive;
-    (void)hipGetLastError();
+    const Capture capture = capture_of(stream);
+    const bool capturing = capture == Capture::kActive, in_launch = capture == Capture::kNone;
     // A ring slot is taken for its completion event only: scene retirement tracks requests through them.  A captured
     // call is no request (its replays are the caller's, and so is keeping the scenes loaded for them).
     RingSlot* slot = nullptr;
@@ -1270,10 +1272,10 @@ bps_status render_static(bps_renderer* r, const bps_scene* scene_ids, const floa
         bps::launch_plan(stream, r->d_scenes, d_items, view_proj, fp, (uint32_t)n_items, d_cost, d_ordered);
         BPS_HIP(r, hipGetLastError());
     }
-    BPS_HIP(r, bps::launch_raster(slot && r->events_in_launches ? slot->done : nullptr, r->threads, dim3((unsigned)n_items), r->lds, stream, r->d_scenes,
+    BPS_HIP(r, bps::launch_raster(in_launch ? slot->done : nullptr, r->threads, dim3((unsigned)n_items), r->lds, stream, r->d_scenes,
                                   planned ? d_ordered : d_items, view_proj, fp, r->fixed_layout, cut.wide, nullptr, out_depth, out_tri_id, nullptr));
     if (slot) {
-        if (!r->events_in_launches) BPS_HIP(r, hipEventRecord(slot->done, stream));
+        if (!in_launch) BPS_HIP(r, hipEventRecord(slot->done, stream));
         slot->pending = true;
         slot->seq = seq;
     }

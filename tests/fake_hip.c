@@ -22,6 +22,19 @@ static const void* g_scenes;      /* the scene table of the last k_raster */
 const void* fake_scenes(void) { return g_scenes; }
 const char* fake_log(void) { return g_log; }
 void fake_clear_log(void) { g_log[g_log_at = 0] = 0; }
+/* kernels and records of events in the order they were enqueued, a line each; events by their numbers */
+static char g_ops[1 << 16];
+static size_t g_ops_at;
+const char* fake_ops(void) { return g_ops; }
+void fake_clear_ops(void) { g_ops[g_ops_at = 0] = 0; }
+typedef struct { long held; int number; } event;
+static const char* kernel_name(const void* f);
+static void op(const char* what, hipEvent_t e) {
+    const size_t room = sizeof(g_ops) - g_ops_at;
+    const int n = e ? snprintf(g_ops + g_ops_at, room, "%s event=%d\n", what, ((event*)e)->number) : snprintf(g_ops + g_ops_at, room, "%s\n", what);
+    if (n < 0 || (size_t)n >= room) abort();
+    g_ops_at += (size_t)n;
+}
 
 void** __hipRegisterFatBinary(const void* data) { (void)data; static void* handle; return &handle; }
 void __hipUnregisterFatBinary(void** modules) { (void)modules; }
@@ -52,11 +65,14 @@ hipError_t __hipPopCallConfiguration(dim3* grid, dim3* block, size_t* shared, hi
 
 #define ARG(type, k) (*(type*)args[k])
 
+static const char* kernel_name(const void* f) {
+    for (int k = 0; k < g_n_kernels; ++k)
+        if (g_kernels[k].host == f) return g_kernels[k].name;
+    return "?";
+}
 static hipError_t run(const void* f, dim3 grid, dim3 block, void** args, size_t shared, hipStream_t stream) {
     (void)stream;
-    const char* name = "?";
-    for (int k = 0; k < g_n_kernels; ++k)
-        if (g_kernels[k].host == f) name = g_kernels[k].name;
+    const char* name = kernel_name(f);
     char* out = g_log + g_log_at;
     const size_t room = sizeof(g_log) - g_log_at;
     int n;
@@ -96,25 +112,38 @@ static hipError_t run(const void* f, dim3 grid, dim3 block, void** args, size_t 
 /* Capture: launches are kept, with copies of the arguments the logged kernels have, and carried out by fake_replay. */
 typedef struct { const void* f; dim3 grid, block; void* args[4]; } captured;
 static captured g_graph[64];
-static int g_capturing, g_n_graph;
+static int g_capturing, g_n_graph, g_unknown;
+void fake_capture_unknown(int on) { g_unknown = on; }      /* whether a stream is being captured cannot be told */
 void fake_capture(int on) { g_capturing = on; if (on) g_n_graph = 0; }
 hipError_t hipStreamIsCapturing(hipStream_t s, hipStreamCaptureStatus* status) {
     (void)s;
+    if (g_unknown) return hipErrorStreamCaptureImplicit;
     *status = g_capturing ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone;
     return hipSuccess;
 }
-hipError_t hipLaunchKernel(const void* f, dim3 grid, dim3 block, void** args, size_t shared, hipStream_t stream) {
+static hipError_t launch(const void* f, dim3 grid, dim3 block, void** args, size_t shared, hipStream_t stream) {
     if (!g_capturing) return run(f, grid, block, args, shared, stream);
     if (g_n_graph == 64) abort();
     captured* c = &g_graph[g_n_graph++];
     c->f = f; c->grid = grid; c->block = block;
-    const char* name = "";
-    for (int k = 0; k < g_n_kernels; ++k)
-        if (g_kernels[k].host == f) name = g_kernels[k].name;
+    const char* name = kernel_name(f);
     const size_t unpack[4] = {3840, 4, 4, 8}, order[4] = {8, 4, 8, 8}, raster[4] = {8, 8, 8, 0}, none[4] = {0, 0, 0, 0};
     const size_t* size = strstr(name, "k_unpack_items") ? unpack : strstr(name, "k_dispatch_order") ? order : strstr(name, "k_raster") ? raster : none;
     for (int k = 0; k < 4; ++k) c->args[k] = memcpy(malloc(size[k] + 1), size[k] ? args[k] : "", size[k]);
     return hipSuccess;
+}
+hipError_t hipLaunchKernel(const void* f, dim3 grid, dim3 block, void** args, size_t shared, hipStream_t stream) {
+    op(kernel_name(f), NULL);
+    return launch(f, grid, block, args, shared, stream);
+}
+/* an event that is the end of a kernel; a kernel of a graph has none */
+static long g_held, g_holds;
+hipError_t hipExtLaunchKernel(const void* f, dim3 grid, dim3 block, void** args, size_t shared, hipStream_t stream, hipEvent_t start,
+                              hipEvent_t stop, int flags) {
+    if (g_capturing || start || !stop || flags) return hipErrorNotSupported;
+    op(kernel_name(f), stop);
+    ((event*)stop)->held = g_held;
+    return launch(f, grid, block, args, shared, stream);
 }
 void fake_replay(void) {
     for (int k = 0; k < g_n_graph; ++k) run(g_graph[k].f, g_graph[k].grid, g_graph[k].block, g_graph[k].args, 0, NULL);
@@ -184,12 +213,11 @@ hipError_t hipStreamDestroy(hipStream_t s) { free(s); return hipSuccess; }
 hipError_t hipStreamSynchronize(hipStream_t s) { (void)s; return hipSuccess; }
 hipError_t hipStreamWaitEvent(hipStream_t s, hipEvent_t e, unsigned flags) { (void)s; (void)e; (void)flags; return hipSuccess; }
 /* events recorded while the device is held are not reached until it goes on */
-static long g_held, g_holds;
 void fake_hold(int on) { g_held = on ? ++g_holds : 0; }
-hipError_t hipEventCreateWithFlags(hipEvent_t* e, unsigned flags) { (void)flags; *e = (hipEvent_t)calloc(1, sizeof(long)); return hipSuccess; }
+hipError_t hipEventCreateWithFlags(hipEvent_t* e, unsigned flags) { (void)flags; static int n; *e = (hipEvent_t)calloc(1, sizeof(event)); ((event*)*e)->number = ++n; return hipSuccess; }
 hipError_t hipEventCreate(hipEvent_t* e) { return hipEventCreateWithFlags(e, 0); }
 hipError_t hipEventDestroy(hipEvent_t e) { free(e); return hipSuccess; }
-hipError_t hipEventRecord(hipEvent_t e, hipStream_t s) { (void)s; *(long*)e = g_held; return hipSuccess; }
-hipError_t hipEventQuery(hipEvent_t e) { return g_held && *(long*)e == g_held ? hipErrorNotReady : hipSuccess; }
+hipError_t hipEventRecord(hipEvent_t e, hipStream_t s) { (void)s; op("record", e); ((event*)e)->held = g_held; return hipSuccess; }
+hipError_t hipEventQuery(hipEvent_t e) { return g_held && ((event*)e)->held == g_held ? hipErrorNotReady : hipSuccess; }
 hipError_t hipEventSynchronize(hipEvent_t e) { (void)e; return hipSuccess; }
 hipError_t hipEventElapsedTime(float* ms, hipEvent_t a, hipEvent_t b) { (void)a; (void)b; *ms = 0.0f; return hipSuccess; }
