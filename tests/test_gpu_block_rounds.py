@@ -1,5 +1,6 @@
 """How a work-group's rounds begin: fewer blocks of 64 clusters than wavefronts, as many, one more, more than threads
-take at a time; every group size; and the box tests on numbers far from one.  Frames are the oracle's, bit for bit."""
+take at a time (and one more than can be ordered); every group size; and the box tests on numbers far from one.  Frames are
+the oracle's, bit for bit."""
 import numpy as np
 import pytest
 
@@ -58,3 +59,30 @@ def test_boxes_of_extreme_size(scale):
     v, t = patches(600, 7, scale)
     check(v, t, cameras(5, 3, scale), 64, 64)
     check(v, t, cameras(40, 4, scale), 48, 72)
+
+
+def loose(n, seed):
+    """n small triangles apart from each other (21 to a cluster) behind a wall that hides two thirds of them from +z."""
+    rng = np.random.default_rng(seed)
+    v = (rng.uniform(-1, 1, (n, 1, 3)) * [4, 1.5, 4] + rng.normal(size=(n, 3, 3)) * .04).reshape(-1, 3)
+    g = np.stack(np.meshgrid(np.linspace(-4, 1, 8), np.linspace(-2, 2, 8)), -1).reshape(-1, 2)
+    q = (np.arange(7)[:, None] * 8 + np.arange(7)).reshape(-1, 1)
+    quads = np.concatenate([q + [0, 1, 8], q + [1, 9, 8]]) + len(v)
+    wall = np.concatenate([g, np.full((64, 1), 4.5)], 1)
+    return np.concatenate([v, wall]).astype(np.float32), np.concatenate([np.arange(3 * n).reshape(n, 3), quads]).astype(np.uint32)
+
+
+@pytest.mark.parametrize("n,blocks,threads", [(345_000, 257, 256), (500_000, 373, 256), (500_000, 373, 384), (690_000, 514, 512),
+                                              (690_000, 514, 256), (1_375_000, 1024, 512), (1_380_000, 1027, 256)])
+def test_more_blocks_than_threads(n, blocks, threads):
+    """One group on a whole scene (no windows, no shares), from where nearly all blocks are in view and from among them."""
+    import paper_2103_07013_amd as bps
+    v, t = loose(n, n)
+    assert -(-len(bps.bps_pack_clusters(v, t)[0]) // 64) == blocks
+    M = cameras(3, n)
+    for b, z in enumerate((9, 12)):      # from outside, behind the wall
+        P = np.array([[1, 0, 0, 0], [0, -1, 0, 0], [0, 0, -20 / 19.99, -.2 / 19.99], [0, 0, -1, 0]])
+        V = np.eye(4)
+        V[2, 3] = -z
+        M[b] = P @ V
+    check(v, t, M, 64, 64, threads=threads, splits=1)
