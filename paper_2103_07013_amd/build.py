@@ -31,14 +31,19 @@ def build(force: bool = True, verbose: bool = False) -> str:
     """Compile every HIP source into paper_2103_07013_amd/libbps.so."""
     if not force and not stale():
         return LIB
+    return compile_hip([os.path.join(CSRC, f) for f in SOURCES], LIB, verbose)
+
+
+def compile_hip(sources, lib: str, verbose: bool = False) -> str:
+    """Compile HIP sources into one shared library with the flags that the numeric rule needs."""
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
-    cmd = [hipcc, *HIPCC_FLAGS, *[os.path.join(CSRC, f) for f in SOURCES], "-o", LIB]
+    cmd = [hipcc, *HIPCC_FLAGS, *sources, "-o", lib]
     res = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
     if verbose or res.returncode != 0:
         print(res.stdout)
     if res.returncode != 0:
-        raise RuntimeError("hipcc failed building libbps.so:\n" + res.stdout)
-    return LIB
+        raise RuntimeError("hipcc failed building %s:\n" % os.path.basename(lib) + res.stdout)
+    return lib
 
 
 if __name__ == "__main__":
