@@ -858,9 +858,10 @@ __device__ __forceinline__ void draw_clipped(const WaveLds& L, uint32_t ref, int
 // time, most of it on LDS round trips: clusters come off the list ahead of their use, no load is left in flight that
 // only one path uses, and the planes of the box tests sit in LDS instead of registers (no vector register is spilled
 // in the instances that draw by default, and 81 to 90 scalar ones): 78.8 M instructions, 238 us; 2.27 ms.  With clusters of
-// smaller boxes and raster_large_packed: 238 -> 229 us; 2.29 -> 2.17 ms.  With the matrix cores, a draw loop without waits
-// between the vector and the scalar unit, and one comparison per step: 75.4 M vector instructions (65 % of the issue slots
-// over a launch), 228 -> 199 us; 2.18 -> 1.91 ms.
+// smaller boxes and raster_large_packed: 238 -> 229 us; 2.29 -> 2.17 ms.  With transforms on the matrix cores (their share:
+// see ClipRows), a shorter set-up, a draw loop without waits between the vector and the scalar unit, and one comparison per
+// step: 75.7 M vector instructions, matrix ones included (the vector units issue in 80 % of the cycles in which a compute
+// unit is busy, 82 % at 4096), 228 -> 199 us; 2.18 -> 1.90 ms.
 template <int NT, bool DIAG, int CULL, int FRAME>
 __global__ __launch_bounds__(NT, 4) void k_raster(const SceneDev* __restrict__ scenes, const WorkItem* __restrict__ items,
                                                const float* __restrict__ view_proj, FrameParams fp,
@@ -904,6 +905,7 @@ __global__ __launch_bounds__(NT, 4) void k_raster(const SceneDev* __restrict__ s
     uint16_t* slot_in_bin = perm + list_cap;                                                       // [list_cap]
     uint32_t* hist = reinterpret_cast<uint32_t*>(slot_in_bin + list_cap);                          // [kDepthBins]
     uint32_t* hiz = hist + kDepthBins;                                                                // [kHizTiles]
+    static_assert(kWaveLdsBytes % 16 == 0, "planes are read four words at a time (list capacities are multiples of 64)");
     float* planes = reinterpret_cast<float*>(hiz + kHizTiles);                                        // [8][kPlaneRow]
     uint32_t* counters = reinterpret_cast<uint32_t*>(planes + 8 * kPlaneRow);
     uint32_t* list_count = counters;       // survivors appended in this round
@@ -976,12 +978,13 @@ __global__ __launch_bounds__(NT, 4) void k_raster(const SceneDev* __restrict__ s
     const uint32_t* vis_hi = reinterpret_cast<const uint32_t*>(vis) + 1;   // depth word of pixel p is vis_hi[2 p]
 
     // ---- prologue: LDS cleared, and the item's blocks ordered near to far
-    // What bounds it is one wavefront's chain of steps: a group drew its first cluster 12 400 cycles after its start,
-    // which is 40 % of the median group of a small request.  Hence box tests on the matrix cores (1100 -> 600 cycles a
-    // test), three barriers before the first round instead of five and two in the depth sort instead of four, bounds
-    // fetched ahead, no divisions, and a first block per wavefront without a trip to the counters.  Requests: 1
-    // environment 25.9 -> 24.6 us, 16 in a small room 27.1 -> 25.7, 61 at 72x104 58.7 -> 56.8, 512 119.9 -> 117.1, 1024
-    // of 500 k triangles 230.2 -> 224.4, 4096 at 128x128 2220 -> 2180.
+    // What bounds it is one wavefront's chain of steps.  Hence three barriers before the first round instead of five and
+    // two in the depth sort instead of four, prefix sums by lane permutes, bounds fetched ahead, no divisions, a first block
+    // per wavefront without a trip to the counters, and box tests on the matrix cores.  Together, us per request: 1
+    // environment 25.9 -> 24.6, 16 in a small room 27.1 -> 25.7, 61 at 72x104 58.7 -> 56.8, 512 119.9 -> 117.1, 1024 of
+    // 500 k triangles 230.2 -> 224.4, 4096 at 128x128 2220 -> 2180; this part of a group 2.0 -> 1.5 us of 10 (one
+    // environment).  The box tests' own share does not show: as fmaf chains of the same ten terms they take the same
+    // requests (1024: 197 and 199 us against 195 and 199, 4096: 1904 against 1895 and 1906).
     const bool sorted = CULL != 0 && nb_item <= kOrderCap && nb_item > 1;
     // A wavefront's part of the block order is a block per lane, and on with the next NT blocks; the bounds of the
     // first ones arrive while LDS is being cleared.
