@@ -254,17 +254,16 @@ __device__ __forceinline__ void emit(const WaveLds& L, int& small_count, short2v
     // medium triangles (box within 8x8 pixels): four per pass, sixteen lanes each, 4x4 pixels per step
     while (med) {
         ++L.tally[kTMedPasses];
-        int src[4];
+        uint32_t four = 0u;     // the lanes of the next four, a byte each, and 64 where there are no more
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
-            src[k] = med ? __builtin_ctzll(med) : -1;
+            four |= (med ? (uint32_t)__builtin_ctzll(med) : 64u) << (8 * k);
             med &= med - 1;     // 0 & anything stays 0
         }
-        int g = lane >> 4;
-        asm volatile("" : "+v"(g));      // (the three conditions on it would each be kept, and spilled, over the kernel)
-        const int from = g == 0 ? src[0] : g == 1 ? src[1] : g == 2 ? src[2] : src[3];
-        const bool on = from >= 0;
-        const int f = on ? from : 0;
+        int which = lane;
+        asm volatile("" : "+v"(which));      // (what follows from it would be kept, and spilled, over the kernel)
+        const int f = (int)((four >> ((which >> 1) & 24)) & 0xFFu);      // (permutes take it modulo 64)
+        const bool on = f < 64;
         const uint32_t mxy0 = (uint32_t)__shfl((int)xy0, f, 64), mxy1 = (uint32_t)__shfl((int)xy1, f, 64),
                        mxy2 = (uint32_t)__shfl((int)xy2, f, 64);
         const float miw0 = __shfl(iw0, f, 64), miw1 = __shfl(iw1, f, 64), miw2 = __shfl(iw2, f, 64);
@@ -553,6 +552,20 @@ __device__ __forceinline__ int pop_clip(const ClipRing& R, uint32_t at_least, in
     return (int)n;
 }
 
+// A copy of a uniform pointer: a pointer that is loaded with its neighbours is spilled, and comes back, with all of them.
+template <class T>
+__device__ __forceinline__ T* apart(T* p) {
+    T* q;
+    asm volatile("s_mov_b64 %0, %1" : "=s"(q) : "s"(p));
+    return q;
+}
+
+struct ClusterData {      // of the scene: see SceneDev
+    const BPS_GLOBAL float* verts;
+    const BPS_GLOBAL uint32_t* tris;
+    const BPS_GLOBAL uint32_t* tri_id;
+};
+
 // A straddling triangle per lane, clipped and projected: corners 0 .. cnt - 1.
 struct Clipped {
     uint32_t ref;                            // cluster * 128 + slot
@@ -587,13 +600,13 @@ __device__ __forceinline__ Clip4 along(const Clip4& a, const Clip4& b, float t) 
 // request, 256 of 64x64: 108.5 -> 104.5, 4096 of 128x128: 2410 -> 2365; 1024 of 64x64 unchanged.
 // general: 0, or 64 and the planes that the lane's triangle crosses (bit k: the k-th of the rule's order), if that takes the
 // general clipper.
-__device__ __forceinline__ void clip_triangles(uint32_t* tally, uint32_t ref, bool have, const SceneDev& sc, const ClipRows& R,
+__device__ __forceinline__ void clip_triangles(uint32_t* tally, uint32_t ref, bool have, const ClusterData& sc, const ClipRows& R,
                                                const FrameParams& fp, Clipped& out, uint32_t& general) {
     if (!have) ref = 0u;
     out.ref = ref;
     const uint32_t c = ref >> 7;
-    const uint32_t t = gptr(sc.ctris)[ref] & 0x00FFFFFFu;
-    const BPS_GLOBAL float* cv = gptr(sc.cverts) + (size_t)c * 192;
+    const uint32_t t = sc.tris[ref] & 0x00FFFFFFu;
+    const BPS_GLOBAL float* cv = sc.verts + (size_t)c * 192;
     float p[3][3];
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
@@ -721,7 +734,7 @@ __device__ __forceinline__ void clip_triangles(uint32_t* tally, uint32_t ref, bo
 // 34.9 / 37.4 / 27.6 / 25.4, 200 of them at 24x24 40.1 / 45.7 / 31.1 / 29.1; among 2000 triangles as large as the room
 // 1024 environments 2268 / 2582 / 2029 / 1926 and one 67.1 / 277 / 98.5 / 67.6; one among 20000 of them 230 / - / - / 252.
 __device__ __forceinline__ bool clip_general(const WaveLds& L, int wide, u64& waiting, u64& again, uint32_t ref, uint32_t general,
-                                             const SceneDev& sc, const ClipRows& R, const FrameParams& fp, int lane, uint32_t& of,
+                                             const ClusterData& sc, const ClipRows& R, const FrameParams& fp, int lane, uint32_t& of,
                                              uint32_t& p0, uint32_t& p1, uint32_t& p2, float& w0, float& w1, float& w2) {
     static_assert(kMaxPoly == 16, "a corner per lane of the widest row");
     asm volatile("" : "+v"(lane));      // (what follows from it is worked out here and not kept, and spilled, over the kernel)
@@ -738,8 +751,8 @@ __device__ __forceinline__ bool clip_general(const WaveLds& L, int wide, u64& wa
     of = on ? __float_as_uint(mine.x) : 0u;
     uint32_t todo = on ? __float_as_uint(mine.y) & 63u : 0u;
     int n = on ? 3 : 0;
-    const uint32_t t = gptr(sc.ctris)[of] & 0x00FFFFFFu, vi = (t >> (8 * min(j, 2))) & 0xFFu;
-    const BPS_GLOBAL float* cv = gptr(sc.cverts) + (size_t)(of >> 7) * 192;
+    const uint32_t t = sc.tris[of] & 0x00FFFFFFu, vi = (t >> (8 * min(j, 2))) & 0xFFu;
+    const BPS_GLOBAL float* cv = sc.verts + (size_t)(of >> 7) * 192;
     Clip4 v = to_clip(R, cv[vi], cv[64 + vi], cv[128 + vi]), u;
     {
         const int before = row + (j == 0 ? 2 : j - 1);
@@ -810,9 +823,8 @@ __device__ __forceinline__ bool clip_general(const WaveLds& L, int wide, u64& wa
 // Clips up to 64 queued triangles and hands the pieces (0, k, k + 1) of their polygons to emit(): the k-th ones of all that
 // were clipped in registers together, then all the pieces of eight of the others at a time.
 template <int FRAME>
-__device__ __forceinline__ void draw_clipped(const WaveLds& L, uint32_t ref, int n, int& small_count, const SceneDev& sc,
+__device__ __forceinline__ void draw_clipped(const WaveLds& L, uint32_t ref, int n, int& small_count, const ClusterData& sc,
                                              const ClipRows& R, const FrameParams& fp, const Window& win, int lane, u64* vis) {
-    const BPS_GLOBAL uint32_t* ctri_id = gptr(sc.ctri_id);
     Clipped cl;
     uint32_t general;
     clip_triangles(L.tally, ref, lane < n && ref != kClipEmpty, sc, R, fp, cl, general);
@@ -841,7 +853,7 @@ __device__ __forceinline__ void draw_clipped(const WaveLds& L, uint32_t ref, int
         short2v lo, ext;
         uint32_t wide;
         const bool has = live && centre_box(a, b, d, win, lo, ext, wide);
-        emit<FRAME>(L, small_count, lo, ext, wide, tame, a, b, d, wa, wb, wd, of, ctri_id, lane, vis, win, ballot64(has));
+        emit<FRAME>(L, small_count, lo, ext, wide, tame, a, b, d, wa, wb, wd, of, sc.tri_id, lane, vis, win, ballot64(has));
     }
 }
 
@@ -964,9 +976,9 @@ __global__ __launch_bounds__(NT, 4) void k_raster(const SceneDev* __restrict__ s
     uint32_t ticks[8] = {0, 0, 0, 0, 0, 0, 0, 0};
 #define TICK(k) do { if (phase_timers) { unsigned long long t_ = wall_clock64(); ticks[k] += (uint32_t)(t_ - t_prev); t_prev = t_; } } while (0)
     const uint32_t full_tri_mask = 0x00FFFFFFu;
-    const BPS_GLOBAL float* g_cverts = gptr(sc.cverts);
-    const BPS_GLOBAL uint32_t* g_ctris = gptr(sc.ctris);
-    const BPS_GLOBAL uint32_t* g_ctri_id = gptr(sc.ctri_id);
+    const BPS_GLOBAL float* g_cverts = apart(gptr(sc.cverts));
+    const BPS_GLOBAL uint32_t* g_ctris = apart(gptr(sc.ctris));
+    const BPS_GLOBAL uint32_t* g_ctri_id = apart(gptr(sc.ctri_id));
     const BPS_GLOBAL float* g_bounds = gptr(sc.cbounds);
     const uint32_t S = item.split_of >> 16, item_split = item.split_of & 0xFFFFu;
     const uint32_t nblocks_total = (sc.n_clusters + 63u) / 64u;
@@ -1295,7 +1307,7 @@ __global__ __launch_bounds__(NT, 4) void k_raster(const SceneDev* __restrict__ s
                 const int n = pop_clip(ring, streaming ? 64u : 1u, lane, clip_ref, clip_head_seen, clip_tail_seen);
                 if (n != 0) {
                     wave_lds_sync();
-                    draw_clipped<FRAME>(L, clip_ref, n, small_count, sc, R, fq, win, lane, vis);
+                    draw_clipped<FRAME>(L, clip_ref, n, small_count, ClusterData{g_cverts, g_ctris, g_ctri_id}, R, fq, win, lane, vis);
                     continue;
                 }
             }
