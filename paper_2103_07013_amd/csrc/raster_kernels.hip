@@ -732,7 +732,7 @@ __device__ __forceinline__ void clip_triangles(uint32_t* tally, uint32_t ref, bo
 // corners (of which LDS holds three at a time: several planes crossed by most triangles cost up to 4 times the request).
 // Us per request, private memory / three at a time / rows of 16 only / this: 16 environments in a room of 500 triangles
 // 34.9 / 37.4 / 27.6 / 25.4, 200 of them at 24x24 40.1 / 45.7 / 31.1 / 29.1; among 2000 triangles as large as the room
-// 1024 environments 2268 / 2582 / 2029 / 1926 and one 67.1 / 277 / 98.5 / 67.6; one among 20000 of them 230 / - / - / 252.
+// 1024 environments 2270 / 2580 / 2030 / 2000 and one 67 / 277 / 98 / 67; one among 20000 of them 230 / - / - / 248.
 __device__ __forceinline__ bool clip_general(const WaveLds& L, int wide, u64& waiting, u64& again, uint32_t ref, uint32_t general,
                                              const ClusterData& sc, const ClipRows& R, const FrameParams& fp, int lane, uint32_t& of,
                                              uint32_t& p0, uint32_t& p1, uint32_t& p2, float& w0, float& w1, float& w2) {
